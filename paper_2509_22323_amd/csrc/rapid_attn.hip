@@ -5,7 +5,7 @@
 // per layer and per head).  The pruned map is given as a block mask; pruned tiles
 // are never read.
 //
-// Building blocks (a wavefront always owns 32 queries and walks over 64-key tiles):
+// Building blocks of the sparse kernels (a wavefront owns 32 queries and walks over 64-key tiles):
 //   S^T = K Q^T    v_mfma_f32_32x32x16_bf16, A = K tile rows from LDS (128-bit
 //                  reads), B = the wavefront's Q rows held in registers for the
 //                  whole kernel.  Computing the TRANSPOSED score tile puts one
@@ -23,8 +23,10 @@
 //   tiles          global -> LDS directly (global_load_lds_dwordx4), chunk-swizzled,
 //                  several tiles ahead of their use.
 // Kernels:
-//   attn_dense_pp_kernel<D>     dense: 256 queries per workgroup, 8 wavefronts in two groups that
-//                               alternate a softmax phase and an MFMA phase in anti-phase
+//   attn_dense_stream_kernel<D> dense: 256 queries per workgroup (the last, partly filled round of an XCD
+//                               in halves or quarters), on the 16x16x32 stream described there
+//   attn_dense_pp_kernel<D>     dense, small problems: 32 queries per workgroup, the keys split between
+//                               two groups of wavefronts
 //   attn_sparse_sg_kernel<D>    sparse, 128-token mask tiles: one four-wavefront workgroup per plan
 //                               record (a query-block or a piece of its kept list); pieces are
 //                               merged by the last one to finish
@@ -41,6 +43,7 @@
 
 #include <atomic>
 #include <initializer_list>
+#include <type_traits>
 
 #include "rapid_attn.h"
 #include "rapid_internal.h"
@@ -54,6 +57,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
@@ -113,6 +117,7 @@ struct AttnParams {
     int nq;                  // query tiles per (sample, head)
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
+    int whole, cut;          // dense: whole items of an XCD, pieces of each of the others
     int block, nb;           // mask tile edge, N / block (sparse only)
     int sub_shift;           // log2(block / 64)
     float c;                 // scale * log2(e)
@@ -684,6 +689,42 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
     }
 }
 
+// The same copy, one instruction at a time, as buffer loads: rows at or beyond kv_len (and whole
+// tiles there) lie outside the buffer and arrive as zeros, so nothing in the tile loop branches on
+// the tile.  A descriptor covers the valid part of one tile.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+struct TileBuffer {
+    unsigned lo, hi, bytes;
+};
+template <int ROWS>
+__device__ __forceinline__ TileBuffer tile_buffer(const Rows& src, int key0, int kv_len)
+{
+    const char* tile = src.row(key0);                      // a tile never straddles the segments
+    int rows = kv_len - key0;
+    rows = rows < 0 ? 0 : rows;
+    asm("" : "+s"(rows));                                  // two scalar instructions, not one vector clamp
+    rows = rows > ROWS ? ROWS : rows;
+    TileBuffer r;
+    r.lo = (unsigned)(size_t)tile;
+    r.hi = (unsigned)((size_t)tile >> 32) & 0xffffu;
+    r.bytes = (unsigned)rows * src.row_bytes;
+    return r;
+}
+// Byte offset of this lane's chunk from the tile's first row, in copy instruction ld (1 KB of the stage).
+template <int D, bool IS_V>
+__device__ __forceinline__ unsigned copy_offset(unsigned row_bytes, int ld, int lane)
+{
+    typedef Geo<D> G;
+    const int row = ld * G::ROWS_PER_LOAD + lane / G::CPR;
+    const int logical = (lane % G::CPR) ^ (IS_V ? G::swz_v(row) : G::swz_k(row));
+    return (unsigned)row * row_bytes + (unsigned)logical * 16u;
+}
+__device__ __forceinline__ void copy_1k(const TileBuffer& b, unsigned off, unsigned dst)
+{
+    const i32x4 rsrc = {(int)b.lo, (int)b.hi, (int)b.bytes, 0x00020000};
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc));
+}
+
 struct SoftmaxState {
     float m;      // reference of the exponents, in units of scale * log2(e); same in both lane halves
     float l;      // this lane's partial sum of probabilities
@@ -1061,190 +1102,803 @@ __device__ __forceinline__ void phase_barrier()
 }
 
 // ---------------------------------------------------------------------------
-// Dense path: 256 queries per workgroup, 8 wavefronts in two groups of four (one wavefront
-// of each group on every SIMD), 4 LDS stages, tile copies issued 3 tiles ahead.
-//
-// Per tile a wavefront alternates two phases separated by workgroup barriers:
-//   B(j)  softmax of S_j                      -- VALU / transcendental work
-//   A(j)  O^T += V_j^T P_j^T ; S_{j+1} = K_{j+1} Q^T   -- 32 MFMAs, LDS reads
-// Group 1 enters the loop one barrier later than group 0, so between any two barriers one
-// group is in a B phase while the other is in an A phase: the two wavefronts that share a
-// SIMD are held in anti-phase and the matrix pipe of one overlaps the vector work of the
-// other, instead of both running the same phase in lock-step after every barrier.
-// Every barrier is executed by all wavefronts (group 0 makes up its missing one at the end).
-// Copy bookkeeping (slot = interval between two barriers; group 0 runs A(j) in slot 2j+2,
-// group 1 in slot 2j+3): tile j+3 is issued at the start of A(j) into the stage of tile j-1,
-// which both groups have finished (group 1's A(j-1) is slot 2j+1); every wavefront waits for
-// its share of tile j+1 before its first barrier of iteration j, i.e. before barrier 2j+2 at
-// the latest, which precedes the first use of tile j+1 (group 0's A(j)).
+// The tile loop as ONE software-pipelined stream of 16x16x32 MFMAs.  A wavefront owns NQ groups of
+// 16 queries; a step = 32 keys.  Step i issues
+//   items 0 .. NQK-1     S_{i+1}^T = K_{i+1} Q^T     per item: one 128-bit LDS read, NQ MFMAs
+//   items NQK .. NI-1    O^T += V_i^T P_i^T          per item: two LDS transpose reads, NQ MFMAs
+// and between the MFMAs, a few instructions at a time, the softmax arithmetic that needs no MFMA of
+// this half: the second half of step i's probabilities beside the first items, the first half of
+// step i+1's beside the others.  The LDS reads of an item are requested PD items ahead, across the
+// end of a step.
+// What bounds it and why this form.  A full chip runs at its power limit, so energy per product counts as much
+// as cycles: on unit-normal data a loop of 32x32x16 MFMAs sustains 1.67 PFLOP/s, of 16x16x32 ones 1.97; with the
+// LDS reads of 32 queries per wavefront 1.50 and 1.72.  v_dot2 (the row sum of the 32x32 kernels) costs 17-20 cycles
+// next to MFMAs, hence the sum as an MFMA of ones (2-3 % of the call; as vector adds 5 % more than that).
+// Dense B = 1, H = 24, D = 128, against softmax and MFMA phases alternating between two groups of
+// wavefronts: N = 4608 242 -> 218 us (1.20 PFLOP/s), N = 16896 3166 -> 2689 us (1.30); D = 64, B = 2, N = 4480
+// 278 -> 231 us.  At D = 64 the issue port is busy 96 % of the time (the exponentials alone are a third of it).
+// Layouts (lane = 16 g + n):
+//   K, V^T operand   lane holds row n of the 16-row fragment, its 8 elements 8 g .. 8 g + 7 of 32
+//   S^T              register r of tile kt, group q: key 16 kt + 4 g + r, query 16 q + n
+//   P^T operand      the 8 probabilities of a lane and query group, tile 0 then tile 1, as bf16: the
+//                    contraction index 8 g + e stands for key 16 (e / 4) + 4 g + e % 4, and V^T is
+//                    fetched in that order
 // ---------------------------------------------------------------------------
-// The body, for the 256 queries starting at row q0 of (sample, head) bh.  `lds` = 8 tile
-// stages: K stages 0..3, V stages 4..7; tile t lives in stage t % 4.  All LDS traffic of the
-// loop is explicit assembly, so the stages are plain runtime offsets into one array.
-template <int D>
-__device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int bh, int q0)
+template <int D, int NQ_, int PD_, int NBUF_>
+struct Stream {
+    static constexpr int NQ = NQ_;
+    static constexpr int KS = D / 32;          // k-steps of a score
+    static constexpr int DT = D / 16;          // 16-row blocks of O^T
+    static constexpr int NQK = 2 * KS, NPV = DT, NI = NQK + NPV;
+    static constexpr int PD = PD_, NBUF = NBUF_;
+    static constexpr int HALF = 2 * NQ;        // pairs of probabilities in half a step
+    static constexpr int UNITS = NQK * NQ;     // MFMAs in half a step
+    static constexpr int UPM = 4 * HALF / UNITS;    // quarter pairs beside one MFMA: 1 at D = 128, 2 at D = 64
+    static_assert(NQK == NPV && UPM * UNITS == 4 * HALF && (UPM == 1 || UPM == 2), "");
+    static_assert(NBUF > PD && NI % NBUF == 0, "an item keeps its buffer from step to step");
+    static constexpr int reads(int i) { return (i % NI) < NQK ? 1 : 2; }
+    // LDS requests newer than item i's when everything before item `last` has been requested
+    static constexpr int newer(int i, int last)
+    {
+        int s = 0;
+        for (int k = i + 1; k < last; ++k) s += reads(k);
+        return s;
+    }
+    // LDS tile geometry: as Geo, with the chunks of a V row swizzled for 16-row x 32-byte patches
+    static constexpr int RB = D * 2;
+    static __device__ __forceinline__ int swz_k(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+    static __device__ __forceinline__ int swz_v(int row) { return D == 128 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1); }
+};
+
+template <class S, int D>
+struct StreamRegs {
+    unsigned kaddr[S::KS];                     // LDS byte address of this lane's chunk of K row n, per k-step
+    unsigned vaddr[S::DT];                     // of its element of the transpose read, per block of O^T
+    u32x2 lo[S::NBUF], hi[S::NBUF];
+    u32x4 kf[S::NBUF];
+    bf16x8 qf[S::NQ][S::KS];
+    f32x16 acc[S::DT * S::NQ / 4];             // block b, query group q: registers of quarter b * NQ + q
+    f32x4 ls[S::NQ];                           // row sums, the same in all four registers
+    float m[S::NQ];                            // references of the exponents
+    bf16x8 ones;                               // 1.0 everywhere
+    unsigned seen;                             // all packed probabilities since the references last moved, or-ed
+    float x0, x1, e0, e1;                      // pairs under way
+    unsigned kc, kn, vc;                       // offsets of a step outside the unrolled loop
+};
+
+constexpr float REF_UP = 60.f;
+
+// Lane addresses in a K tile at byte address k0 and a V tile at v0.
+template <class S, int D>
+__device__ __forceinline__ void stream_addresses(StreamRegs<S, D>& x, unsigned k0, unsigned v0, int lane)
+{
+    const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < S::KS; ++t) x.kaddr[t] = k0 + n * S::RB + (((4 * t + g) ^ S::swz_k(n)) << 4);
+    // 16 lanes of a group: lane j points at row 4 g + j / 4, columns 4 (j % 4) .. + 3 of the block
+    const int row = 4 * g + (n >> 2);
+#pragma unroll
+    for (int b = 0; b < S::DT; ++b)
+        x.vaddr[b] = v0 + row * S::RB + (((2 * b + ((n & 3) >> 1)) ^ S::swz_v(row)) << 4) + (n & 1) * 8;
+}
+
+// Request item I (I >= NI: item I - NI of the next step); KC, KN, VC: byte offsets of the 32 rows
+// of K_{i+1}, K_{i+2} and V_i from the addresses of the context; KC < 0: they are in x.kc, x.kn, x.vc.
+template <class S, int D, int KC, int KN, int VC, int I>
+__device__ __forceinline__ void stream_request(StreamRegs<S, D>& x)
+{
+    constexpr int J = I % S::NI, slot = J % S::NBUF;
+    if constexpr (KC < 0 && J < S::NQK) {
+        asm volatile("ds_read_b128 %0, %1 offset:%2"
+                     : "=&v"(x.kf[slot]) : "v"(x.kaddr[J / 2] + (I < S::NI ? x.kc : x.kn)), "i"(J % 2 * 16 * S::RB));
+    } else if constexpr (KC < 0) {
+        asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:%3"
+                     : "=&v"(x.lo[slot]), "=&v"(x.hi[slot]) : "v"(x.vaddr[J - S::NQK] + x.vc), "i"(16 * S::RB));
+    } else if constexpr (J < S::NQK) {
+        constexpr int t = J / 2, kt = J % 2;
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(x.kf[slot]) : "v"(x.kaddr[t]), "i"((I < S::NI ? KC : KN) + kt * 16 * S::RB));
+    } else {
+        asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+                     : "=&v"(x.lo[slot]), "=&v"(x.hi[slot])
+                     : "v"(x.vaddr[J - S::NQK]), "i"(VC), "i"(VC + 16 * S::RB));
+    }
+}
+
+// Wait for item I when everything before item LAST has been requested.
+template <class S, int D, int I, int LAST>
+__device__ __forceinline__ void stream_wait(StreamRegs<S, D>& x)
+{
+    constexpr int slot = I % S::NBUF, N = S::newer(I, LAST);
+    static_assert(N + S::reads(I) <= 15, "lgkmcnt is a 4-bit counter");
+    if constexpr (I % S::NI < S::NQK) asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x.kf[slot]) : "i"(N));
+    else asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(x.lo[slot]), "+v"(x.hi[slot]) : "i"(N));
+}
+
+// The requests of a step that does not exist are in flight when the loop ends: they land before
+// their registers serve anything else.
+template <class S, int D>
+__device__ __forceinline__ void stream_drain(StreamRegs<S, D>& x)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)");
+#pragma unroll
+    for (int b = 0; b < S::NBUF; ++b) asm volatile("" : "+v"(x.kf[b]));
+}
+
+// Four 16x16x32 accumulators live in one 16-register vector: the compiler then updates a quarter in
+// place.  (As vectors of their own they move to other registers with every product, and the second
+// set of registers spills.)
+template <int Q>
+__device__ __forceinline__ f32x4 quarter(const f32x16& v)
+{
+    return __builtin_shufflevector(v, v, 4 * Q, 4 * Q + 1, 4 * Q + 2, 4 * Q + 3);
+}
+template <int Q>
+__device__ __forceinline__ void set_quarter(f32x16& v, f32x4 x)
+{
+    v[4 * Q] = x[0]; v[4 * Q + 1] = x[1]; v[4 * Q + 2] = x[2]; v[4 * Q + 3] = x[3];
+}
+template <int Q>
+__device__ __forceinline__ void mfma16(f32x16& acc, bf16x8 a, bf16x8 b, bool zero = false)
+{
+    const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+    set_quarter<Q>(acc, __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, zero ? none : quarter<Q>(acc), 0, 0, 0));
+    asm volatile("" : "+v"(acc));                 // in place
+}
+
+// S^T of one step: tile kt, query group q
+template <class S>
+struct Scores {
+    f32x16 v[(S::NQ + 1) / 2];                 // tile kt, group q, register r: element 4 (kt * NQ + q) + r
+    __device__ __forceinline__ float get(int kt, int q, int r) const { const int i = 4 * (kt * S::NQ + q) + r; return v[i >> 4][i & 15]; }
+    __device__ __forceinline__ void set(int kt, int q, int r, float x) { const int i = 4 * (kt * S::NQ + q) + r; v[i >> 4][i & 15] = x; }
+};
+// P^T of one step: words 0, 1 from tile 0, words 2, 3 from tile 1
+template <class S>
+struct Probs {
+    u32x4 q[S::NQ];
+};
+
+// The accumulators as one value each at this point of the program.
+template <class S, int D>
+__device__ __forceinline__ void stream_pin(StreamRegs<S, D>& x)
+{
+#pragma unroll
+    for (int b = 0; b < S::DT * S::NQ / 4; ++b) asm volatile("" : "+v"(x.acc[b]));
+#pragma unroll
+    for (int q = 0; q < S::NQ; ++q) asm volatile("" : "+v"(x.ls[q]));
+}
+
+// The probabilities exp2(c * s - m) of half HF of a step, spread over its MFMAs.  Pair k = query group
+// k / 2, registers 2 (k % 2) .. + 1 of tile HF, in four parts: EXPONENTS, FIRST and SECOND exponential, PACK.
+enum { EXPONENTS, FIRST, SECOND, PACK };
+template <class S, int D, int HF, int K, int PART>
+__device__ __forceinline__ void soft_part(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    constexpr int q = K / 2, r = 2 * (K % 2);
+    if constexpr (PART == EXPONENTS) {
+        x.x0 = __builtin_fmaf(st.get(HF, q, r), c, -x.m[q]);
+        x.x1 = __builtin_fmaf(st.get(HF, q, r + 1), c, -x.m[q]);
+        asm volatile("" : "+v"(x.x0), "+v"(x.x1));
+    } else if constexpr (PART == FIRST) {
+        x.e0 = __builtin_amdgcn_exp2f(x.x0);
+        asm volatile("" : "+v"(x.e0));
+    } else if constexpr (PART == SECOND) {
+        x.e1 = __builtin_amdgcn_exp2f(x.x1);
+        asm volatile("" : "+v"(x.e1));
+    } else {
+        bf16x2 pr;
+        pr[0] = (__bf16)x.e0;
+        pr[1] = (__bf16)x.e1;
+        unsigned w = __builtin_bit_cast(unsigned, pr);
+        if constexpr (K % 2 == 1) {
+            x.seen = x.seen | p.q[q][2 * HF] | w;
+            asm volatile("" : "+v"(w), "+v"(x.seen));
+        } else asm volatile("" : "+v"(w));
+        p.q[q][2 * HF + K % 2] = w;
+    }
+}
+
+// What goes beside MFMA U of the half.  The parts beside one MFMA do not depend on each other.
+template <class S, int D, int HF, int U>
+__device__ __forceinline__ void soft_unit(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
+{
+    if constexpr (S::UPM == 1) {
+        soft_part<S, D, HF, U / 4, U % 4>(x, st, c, p);
+    } else {
+        constexpr int k = U / 2;
+        if constexpr (U % 2 == 0) {
+            if constexpr (k > 0) soft_part<S, D, HF, k - 1, PACK>(x, st, c, p);
+            soft_part<S, D, HF, k, EXPONENTS>(x, st, c, p);
+        } else {
+            soft_part<S, D, HF, k, FIRST>(x, st, c, p);
+            soft_part<S, D, HF, k, SECOND>(x, st, c, p);
+            if constexpr (k == S::HALF - 1) soft_part<S, D, HF, k, PACK>(x, st, c, p);
+        }
+    }
+}
+
+template <class S, int D, int HF, int U = 0>
+__device__ __forceinline__ void soft_half(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
+{
+    if constexpr (U < S::UNITS) {
+        soft_unit<S, D, HF, U>(x, st, c, p);
+        soft_half<S, D, HF, U + 1>(x, st, c, p);
+    }
+}
+
+// Largest exponent of a query of group q over the step (a finite number: every step has a valid key).
+template <class S>
+__device__ __forceinline__ float step_max(const Scores<S>& st, int q, float c)
+{
+    float mx = st.get(0, q, 0);
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, st.get(kt, q, r));
+    // swaps of rows 1, 3 with rows 0, 2, then of the upper with the lower half: pairwise maxima
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1])) * c;
+}
+
+// Range of the exponents.  The reference m of a query is the maximum of its first step plus REF_UP, so
+// that probabilities of 2 and more mean a later maximum more than 61 above the first.  Such a value
+// has the top bit of its bf16 exponent set, which the or over all packed words shows; only then the
+// references move up to the step's maximum (plus REF_UP), the sums and the accumulators are rescaled
+// and the step's probabilities are made again.  What lies 2^66 below a row's first maximum is lost.
+template <class S, int D>
+__device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
+{
+    unsigned long long out = __builtin_amdgcn_ballot_w64((x.seen & 0x40004000u) != 0u);
+    if (__builtin_expect(out != 0ull, 0)) {
+#pragma unroll
+        for (int q = 0; q < S::NQ; ++q) {
+            const float delta = fmaxf(step_max<S>(st, q, c) + REF_UP - x.m[q], 0.f);
+            const float alpha = __builtin_amdgcn_exp2f(-delta);
+            x.m[q] += delta;
+            x.ls[q] *= alpha;
+#pragma unroll
+            for (int b = 0; b < S::DT; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x.acc[(b * S::NQ + q) >> 2][((b * S::NQ + q) & 3) * 4 + r] *= alpha;
+        }
+        stream_pin<S, D>(x);                      // in place, before anything else is made
+        asm volatile("" : "+s"(out));
+    }
+    if (__builtin_expect(out != 0ull, 0)) {       // (in a block of its own: together they need a second set of accumulators)
+        x.seen = 0u;
+        soft_half<S, D, 0>(x, st, c, p);
+        soft_half<S, D, 1>(x, st, c, p);
+        x.seen = 0u;
+    }
+}
+
+// Keys at or beyond kv_len -> -inf, for a step whose first key is key0.
+template <class S>
+__device__ __forceinline__ void mask_step(Scores<S>& st, int key0, int kv_len, int lane)
+{
+    if (key0 + 32 > kv_len) {
+        const int left = kv_len - key0 - 4 * (lane >> 4);
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int q = 0; q < S::NQ; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float v = st.get(kt, q, r);
+                    st.set(kt, q, r, 16 * kt + r >= left ? -INFINITY : v);
+                }
+    }
+}
+
+// MFMAs of score item J
+template <class S, int D, int J, int Q>
+__device__ __forceinline__ void qk_mfma(StreamRegs<S, D>& x, Scores<S>& sn)
+{
+    constexpr int t = J / 2, kt = J % 2;
+    constexpr int at = kt * S::NQ + Q;
+    mfma16<at & 3>(sn.v[at >> 2], __builtin_bit_cast(bf16x8, x.kf[J % S::NBUF]), x.qf[Q][t], t == 0);
+}
+// MFMAs of output item J (counted from NQK); the row sums ride on the first NQ of them
+template <class S, int D, int J, int Q>
+__device__ __forceinline__ void pv_mfma(StreamRegs<S, D>& x, const Probs<S>& p)
+{
+    constexpr int slot = (J + S::NQK) % S::NBUF;
+    const u32x4 both = __builtin_shufflevector(x.lo[slot], x.hi[slot], 0, 1, 2, 3);
+    const bf16x8 pq = __builtin_bit_cast(bf16x8, p.q[Q]);
+    constexpr int at = J * S::NQ + Q;
+    mfma16<at & 3>(x.acc[at >> 2], __builtin_bit_cast(bf16x8, both), pq);
+    if constexpr (J == Q) x.ls[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.ones, pq, x.ls[Q], 0, 0, 0);
+}
+
+// MFMAs Q .. NQ-1 of item I, each followed by its softmax units.  Item I has arrived; after the first MFMA
+// the wait for item I + 1 (not right before its use: the compiler would pad that).
+template <class S, int D, bool QK, int I, int Q, int LAST, class Soft>
+__device__ __forceinline__ void item_body(StreamRegs<S, D>& x, Scores<S>& sn, const Probs<S>& p, Soft soft)
+{
+    if constexpr (Q < S::NQ) {
+        constexpr int J = QK ? I : I - S::NQK;
+        if constexpr (QK) qk_mfma<S, D, J, Q>(x, sn);
+        else pv_mfma<S, D, J, Q>(x, p);
+        __builtin_amdgcn_sched_barrier(0);
+        soft(std::integral_constant<int, J * S::NQ + Q>());
+        if constexpr (Q == 0 && I + 1 < LAST) stream_wait<S, D, I + 1, LAST>(x);
+        __builtin_amdgcn_sched_barrier(0);
+        item_body<S, D, QK, I, Q + 1, LAST>(x, sn, p, soft);
+    }
+}
+
+// First half of a step: S_{i+1} beside the second half of step i's probabilities.
+template <class S, int D, int KC, int KN, int VC, int I, class Hook>
+__device__ __forceinline__ void step_qk(StreamRegs<S, D>& x, const Scores<S>& sc, Scores<S>& sn, float c, Probs<S>& p, Hook hook)
+{
+    if constexpr (I < S::NQK) {
+        stream_request<S, D, KC, KN, VC, I + S::PD>(x);
+        item_body<S, D, true, I, 0, I + S::PD + 1>(x, sn, p, [&](auto u) {
+            soft_unit<S, D, 1, decltype(u)::value>(x, sc, c, p);
+        });
+        hook(std::integral_constant<int, I>());
+        step_qk<S, D, KC, KN, VC, I + 1>(x, sc, sn, c, p, hook);
+    }
+}
+
+// Second half: O beside the first half of step i+1's probabilities.
+template <class S, int D, int KC, int KN, int VC, int I, class Hook>
+__device__ __forceinline__ void step_pv(StreamRegs<S, D>& x, Scores<S>& sn, float c, const Probs<S>& p, Probs<S>& pn, Hook hook)
+{
+    if constexpr (I < S::NI) {
+        stream_request<S, D, KC, KN, VC, I + S::PD>(x);
+        item_body<S, D, false, I, 0, I + S::PD + 1>(x, sn, p, [&](auto u) {
+            soft_unit<S, D, 0, decltype(u)::value>(x, sn, c, pn);
+        });
+        hook(std::integral_constant<int, I>());
+        step_pv<S, D, KC, KN, VC, I + 1>(x, sn, c, p, pn, hook);
+    }
+}
+
+// The last step has no successor: its PV items alone.
+template <class S, int D, int I, bool REQUEST_ONLY>
+__device__ __forceinline__ void last_pv(StreamRegs<S, D>& x, const Probs<S>& p)
+{
+    if constexpr (REQUEST_ONLY) {
+        if constexpr (I < S::NQK + S::PD) {
+            stream_request<S, D, 0, 0, 0, I>(x);
+            last_pv<S, D, I + 1, true>(x, p);
+        }
+    } else if constexpr (I < S::NI) {
+        if constexpr (I + S::PD < S::NI) stream_request<S, D, 0, 0, 0, I + S::PD>(x);
+        if constexpr (I == S::NQK) stream_wait<S, D, I, (I + S::PD < S::NI ? I + S::PD + 1 : S::NI)>(x);
+        Scores<S> none;
+        item_body<S, D, false, I, 0, (I + S::PD < S::NI ? I + S::PD + 1 : S::NI)>(x, none, p, [](auto) {});
+        last_pv<S, D, I + 1, false>(x, p);
+    }
+}
+
+// The scores of one step on their own: request the first PD items (REQUEST_ONLY), then run them.
+template <class S, int D, int KC, int I, bool REQUEST_ONLY>
+__device__ __forceinline__ void first_qk(StreamRegs<S, D>& x, Scores<S>& sn)
+{
+    if constexpr (REQUEST_ONLY) {
+        if constexpr (I < S::PD && I < S::NQK) {
+            stream_request<S, D, KC, KC, 0, I>(x);
+            first_qk<S, D, KC, I + 1, true>(x, sn);
+        }
+    } else if constexpr (I < S::NQK) {
+        if constexpr (I + S::PD < S::NQK) stream_request<S, D, KC, KC, 0, I + S::PD>(x);
+        if constexpr (I == 0) stream_wait<S, D, 0, (S::PD < S::NQK ? S::PD + 1 : S::NQK)>(x);
+        Probs<S> none;
+        item_body<S, D, true, I, 0, (I + S::PD < S::NQK ? I + S::PD + 1 : S::NQK)>(x, sn, none, [](auto) {});
+        first_qk<S, D, KC, I + 1, false>(x, sn);
+    }
+}
+
+// Byte offset of this lane's chunk from the tile's first row, in copy instruction ld (1 KB of the stage).
+template <class S, int D, bool IS_V>
+__device__ __forceinline__ unsigned stream_copy_offset(unsigned row_bytes, int ld, int lane)
 {
     typedef Geo<D> G;
-    // How far ahead the LDS reads run (TileItems).  At D = 64 four wavefronts share a SIMD on 128
-    // registers each; the depth is the largest at which this kernel keeps everything in registers
-    // (a few values in scratch memory inside the loop cost 4-8 %); the other wavefronts cover the latency.
-    constexpr int PD = D == 64 ? 2 : 6;
-    typedef TileItems<D, PD> TI;
-    constexpr int NW = 8, KS = D / 16, DB = D / 32;
-    constexpr int LPT = 2 * G::LOADS / NW;        // copy instructions per wavefront per tile (K + V), all copying
-    auto k_stage = [&](int t) -> char* { return lds + (t & 3) * G::TILE_BYTES; };
-    auto v_stage = [&](int t) -> char* { return lds + (4 + (t & 3)) * G::TILE_BYTES; };
+    const int row = ld * G::ROWS_PER_LOAD + lane / G::CPR;
+    const int logical = (lane % G::CPR) ^ (IS_V ? S::swz_v(row) : S::swz_k(row));
+    return (unsigned)row * row_bytes + (unsigned)logical * 16u;
+}
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int group = wave >> 2;
-    const int n = lane & 31;                      // query within the wavefront / MFMA column
-    const int h = lane >> 5;                      // lane half
+// Q^T operands requested by explicit assembly (see load_q_async): lane (n, g) holds elements
+// 32 t + 8 g .. + 7 of query 16 q + n.  Rows that are not valid read row 0 and are zeroed.
+template <class S, int D>
+__device__ __forceinline__ void stream_load_q(const Rows& Q, int q0, int kv_len, int lane, u32x4 (&raw)[S::NQ][S::KS])
+{
+#pragma unroll
+    for (int q = 0; q < S::NQ; ++q) {
+        const int row = q0 + 16 * q + (lane & 15);
+        const __bf16* src = (const __bf16*)Q.row(row < kv_len ? row : 0) + 8 * (lane >> 4);
+#pragma unroll
+        for (int t = 0; t < S::KS; ++t)
+            asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(raw[q][t]) : "v"(src), "i"(64 * t));
+    }
+}
+template <class S, int D>
+__device__ __forceinline__ void stream_q_arrived(StreamRegs<S, D>& x, int q0, int kv_len, int lane, u32x4 (&raw)[S::NQ][S::KS])
+{
+#pragma unroll
+    for (int q = 0; q < S::NQ; ++q) {
+        const bool valid = q0 + 16 * q + (lane & 15) < kv_len;
+#pragma unroll
+        for (int t = 0; t < S::KS; ++t) {
+            asm volatile("" : "+v"(raw[q][t]));
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            x.qf[q][t] = __builtin_bit_cast(bf16x8, valid ? raw[q][t] : zero);
+        }
+    }
+}
+
+// O = acc / l as bf16, query rows q0 .. q0 + 16 NQ - 1 of this wavefront; rows at or beyond kv_len and
+// rows without any kept key become 0.  Through LDS (`stage`, 16 NQ rows of D * 2 + 16 bytes that nobody
+// else uses) so that a store instruction covers whole rows: a lane holds 8-byte pieces of NQ rows.
+template <class S, int D>
+__device__ __forceinline__ void stream_output_rows(const StreamRegs<S, D>& x, const Rows& O, int q0, int kv_len, int N, int lane,
+                                                   char* stage)
+{
+    constexpr int RS = D * 2 + 16;
+    const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int q = 0; q < S::NQ; ++q) {
+        const float l = x.ls[q][0];
+        const float inv = (q0 + 16 * q + n < kv_len && l > 0.f) ? 1.0f / l : 0.f;
+#pragma unroll
+        for (int b = 0; b < S::DT; ++b) {
+            bf16x4 ov;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ov[r] = (__bf16)(inv != 0.f ? x.acc[(b * S::NQ + q) >> 2][((b * S::NQ + q) & 3) * 4 + r] * inv : 0.f);
+            *(bf16x4*)(stage + (16 * q + n) * RS + (16 * b + 4 * g) * 2) = ov;
+        }
+    }
+    constexpr int CH = D * 2 / 16;                // 16-byte chunks of a row
+    constexpr int RPI = 64 / CH;                  // rows per store instruction
+    const int rr = lane / CH, cc = lane % CH;
+#pragma unroll
+    for (int i = 0; i < 16 * S::NQ / RPI; ++i) {
+        const int r = i * RPI + rr;
+        const u32x4 v = *(const u32x4*)(stage + r * RS + cc * 16);
+        if (q0 + r < N) *(u32x4*)(const_cast<char*>(O.row(q0 + r)) + cc * 16) = v;
+    }
+}
+
+// step(U), step(U + 1), .. at i + U, i + U + 1, ..
+template <int U, int TO, class Step>
+__device__ __forceinline__ void static_steps(Step& step, int& i)
+{
+    if constexpr (U < TO) {
+        step(std::integral_constant<int, U>(), i + U);
+        static_steps<U + 1, TO>(step, i);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The stream over a list of key tiles.  WQ x WK wavefronts: query group wq = wave / WK owns 16 NQ queries, key
+// group wk = wave % WK the wk-th 32 keys of every 32 WK; with WK > 1 the key groups keep softmax states of
+// their own and are merged at the end.  A tile = SPT steps of all key groups = 32 WK SPT keys, copied by
+// all wavefronts into a ring of NSK stages for K and one of NSV stages for V.
+//
+// One barrier per tile, in the middle of the tile's first step (after S_{i+1}, before O).  At the barrier of
+// tile t every wavefront has read K up to the rows of S_{i+1} and V_{t-1}, and has waited for its share of
+// the next tiles' copies, so after it
+//   SPT = 1: K_{t+2}, V_{t+1} may be read; the stages of K_{t+1}, V_{t-1} take K_{t+1+NSK}, V_{t-1+NSV}
+//   SPT = 2: K_{t+1}, V_{t+1} may be read; the stages of K_t,     V_{t-1} take K_{t+NSK},   V_{t-1+NSV}
+// Copies are issued V before K at every barrier and complete in order, which gives the counts below.
+// ---------------------------------------------------------------------------
+template <int D_, int NQ_, int WQ_, int WK_, int SPT_, int NSK_, int NSV_>
+struct StreamPlan {
+    static constexpr int D = D_, NQ = NQ_, WQ = WQ_, WK = WK_, SPT = SPT_, NSK = NSK_, NSV = NSV_;
+    typedef Stream<D, NQ, 3, 4> S;
+    static constexpr int NW = WQ * WK, QT = 16 * NQ * WQ, KTS = 32 * WK * SPT;
+    static constexpr int TILE = KTS * S::RB;
+    static constexpr int LC = TILE / 1024 / NW;   // copy instructions per wavefront per tile (K or V)
+    static constexpr int LDS = (NSK + NSV) * TILE;
+    static constexpr int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
+    static constexpr int UNROLL = NSK / gcd(NSK, NSV) * NSV * SPT;    // steps after which both rings are back at stage 0
+    static_assert(LC * NW * 1024 == TILE && (WK == 1 || SPT == 1) && NSK >= 2 && NSV >= 3, "");
+    static constexpr int KLEAD = SPT == 1 ? NSK + 1 : NSK, VLEAD = NSV - 1;    // tiles ahead of t that are copied at its barrier
+    // copy instructions that may still be on their way at a barrier
+    static constexpr int min(int a, int b) { return a < b ? a : b; }
+    static constexpr int LOOSE = min(LC + 2 * LC * (NSV - 3), 2 * LC * (NSK - 2));
+    // byte offset of the 32 rows of step i (of key group 0) in the K and the V ring
+    static constexpr __host__ __device__ int k_off(int i) { return (i / SPT % NSK) * TILE + (i % SPT) * 32 * S::RB; }
+    static constexpr __host__ __device__ int v_off(int i) { return (i / SPT % NSV) * TILE + (i % SPT) * 32 * S::RB; }
+};
+
+// Tiles in order: the dense path.
+template <class P>
+struct AllKeys {
+    __device__ __forceinline__ int at(int t) const { return t * P::KTS; }
+    __device__ __forceinline__ void advance(int) {}
+};
+
+// Steps 0 .. last of this workgroup's queries against the tiles keys.at(0), keys.at(1), .. (the first key of a
+// tile; tiles at or beyond kv_len are all masked).  ALIGNED: last + 1 is a multiple of P::UNROLL.
+template <class P, bool ALIGNED, class Keys>
+__device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x, char* lds, const Rows& Q, const Rows& K, const Rows& V,
+                                              int q0, int kv_len, float c, int last, Keys& keys, int wave, int lane)
+{
+    typedef typename P::S S;
+    constexpr int D = P::D, LC = P::LC;
+    constexpr int VBASE = P::NSK * P::TILE;
+    const int wk = wave % P::WK;
+#pragma unroll
+    for (int b = 0; b < S::DT * S::NQ / 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x.acc[b][r] = 0.f;
+#pragma unroll
+    for (int q = 0; q < S::NQ; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x.ls[q][r] = 0.f;
+
+    u32x4 qraw[S::NQ][S::KS];
+    stream_load_q<S, D>(Q, q0, kv_len, lane, qraw);
+    unsigned koff[LC], voff[LC];
+#pragma unroll
+    for (int e = 0; e < LC; ++e) {
+        koff[e] = stream_copy_offset<S, D, false>(K.row_bytes, wave * LC + e, lane);
+        voff[e] = stream_copy_offset<S, D, true>(V.row_bytes, wave * LC + e, lane);
+    }
+    const unsigned lds0 = (unsigned)(size_t)LDS_PTR(char, lds);
+    const unsigned dst0 = lds0 + (unsigned)(wave * LC) * 1024u;
+    auto copy_k = [&](const TileBuffer& b, int e, unsigned stage) { copy_1k(b, koff[e], dst0 + stage + e * 1024); };
+    auto copy_v = [&](const TileBuffer& b, int e, unsigned stage) { copy_1k(b, voff[e], dst0 + VBASE + stage + e * 1024); };
+    // what the barriers before tile 0 would have issued
+#pragma unroll
+    for (int b = -P::KLEAD; b < (P::SPT == 1 ? -1 : 0); ++b) {
+        if (b + P::VLEAD >= 0) {
+            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD), kv_len);
+#pragma unroll
+            for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + P::VLEAD) * P::TILE);
+        }
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD), kv_len);
+#pragma unroll
+        for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + P::KLEAD) * P::TILE);
+    }
+    // copies issued so far that are younger than K_0 (SPT = 1), or than K_0 and V_0
+    constexpr int ISSUED = P::SPT == 1 ? (P::NSK + (P::NSV - 2)) * LC : (P::NSK + P::NSV - 1) * LC;
+    stream_addresses<S, D>(x, lds0 + wk * 32 * S::RB, lds0 + VBASE + wk * 32 * S::RB, lane);
+    wait_vmcnt<ISSUED - (P::SPT == 1 ? LC : 2 * LC)>();
+    stream_q_arrived<S, D>(x, q0, kv_len, lane, qraw);
+    const u32x4 one = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    x.ones = __builtin_bit_cast(bf16x8, one);
+    asm volatile("" : "+v"(x.ones));              // kept in registers
+    phase_barrier();
+
+    Scores<S> st[2];
+    Probs<S> pw;
+    first_qk<S, D, 0, 0, true>(x, st[0]);
+    first_qk<S, D, 0, 0, false>(x, st[0]);
+    if constexpr (P::SPT == 1) {                  // the barrier before tile 0: K_1, V_0 may be read
+        const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1), kv_len);
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1), kv_len);
+        wait_vmcnt<P::LOOSE>();
+        phase_barrier();
+#pragma unroll
+        for (int e = 0; e < LC; ++e) copy_v(vb, e, (P::VLEAD - 1) * P::TILE);
+#pragma unroll
+        for (int e = 0; e < LC; ++e) copy_k(kb, e, 0);
+    }
+    mask_step<S>(st[0], keys.at(0) + wk * 32, kv_len, lane);
+#pragma unroll
+    for (int q = 0; q < S::NQ; ++q) {
+        x.m[q] = step_max<S>(st[0], q, c);
+        if constexpr (P::WK > 1) x.m[q] = fmaxf(x.m[q], -1e30f);       // a key group may have no valid key at all
+        x.m[q] += REF_UP;
+    }
+    x.seen = 0u;
+    soft_half<S, D, 0>(x, st[0], c, pw);
+
+    // Step i.  U = i % UNROLL where that is known when compiling; U = UNROLL: offsets in x, scores from
+    // st[0] to st[0].
+    TileBuffer kb, vb;                            // the tiles being copied
+    auto step = [&](auto u, int i) {
+        constexpr int U = decltype(u)::value;
+        constexpr bool RT = U == P::UNROLL;
+        constexpr bool FIRST_OF_TILE = U % P::SPT == 0;
+        Scores<S>& sc = st[RT ? 0 : U & 1];
+        Scores<S>& sn = st[RT ? 1 : (U + 1) & 1];
+        constexpr int KC = RT ? -1 : P::k_off(U + 1), KN = P::k_off(U + 2), VC = P::v_off(U);
+        // the copies of this tile's barrier, one every few items until the next barrier (SPT = 1: in the
+        // second half only)
+        constexpr int SLOTS = P::SPT == 1 ? S::NPV : S::NPV + S::NI;
+        constexpr int PER = (2 * LC + SLOTS - 1) / SLOTS, GAP = SLOTS / (2 * LC) > 0 ? SLOTS / (2 * LC) : 1;
+        constexpr int T0 = U / P::SPT;
+        auto hook = [&](auto item) {
+            constexpr int at = decltype(item)::value - S::NQK + (U % P::SPT) * S::NI;
+            if constexpr (!RT && at >= 0 && at % GAP == 0) {
+#pragma unroll
+                for (int e = at / GAP * PER; e < at / GAP * PER + PER && e < 2 * LC; ++e) {
+                    if (e < LC) copy_v(vb, e, (T0 + P::VLEAD) % P::NSV * P::TILE);
+                    else copy_k(kb, e - LC, (T0 + P::KLEAD) % P::NSK * P::TILE);
+                }
+            }
+        };
+        if constexpr (RT) { x.kc = P::k_off(i + 1); x.kn = P::k_off(i + 2); x.vc = P::v_off(i); }
+        if constexpr (FIRST_OF_TILE) step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, [](auto) {});
+        else step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, hook);
+        soft_close<S, D>(x, sc, c, pw);
+        const int t = i / P::SPT;
+        mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1) + wk * 32 : keys.at((i + 1) / 2) + (i + 1) % 2 * 32, kv_len, lane);
+        if (RT ? i % P::SPT == 0 : FIRST_OF_TILE) {
+            keys.advance(t);
+            vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD), kv_len);
+            kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD), kv_len);
+            wait_vmcnt<P::LOOSE>();
+            phase_barrier();
+            if constexpr (RT) {
+#pragma unroll
+                for (int e = 0; e < LC; ++e) copy_v(vb, e, (t + P::VLEAD) % P::NSV * P::TILE);
+#pragma unroll
+                for (int e = 0; e < LC; ++e) copy_k(kb, e, (t + P::KLEAD) % P::NSK * P::TILE);
+            }
+        }
+        Probs<S> pn;
+        step_pv<S, D, KC, KN, VC, S::NQK>(x, sn, c, pw, pn, hook);
+#pragma unroll
+        for (int q = 0; q < S::NQ; ++q) { pw.q[q][0] = pn.q[q][0]; pw.q[q][1] = pn.q[q][1]; }
+        if constexpr (RT) st[0] = st[1];
+    };
+    int i = 0;
+    if (last > 0) {
+        stream_pin<S, D>(x);
+        first_qk<S, D, P::k_off(1), 0, true>(x, st[1]);     // the first items of step 0's stream
+        stream_wait<S, D, 0, S::PD>(x);
+        for (; i + P::UNROLL <= last; i += P::UNROLL) {
+            stream_pin<S, D>(x);
+            static_steps<0, P::UNROLL>(step, i);
+        }
+        if constexpr (ALIGNED) static_steps<0, P::UNROLL - 1>(step, i);
+        else for (; i < last; ++i) step(std::integral_constant<int, P::UNROLL>(), i);
+        stream_drain<S, D>(x);
+    }
+    constexpr int END = (P::UNROLL - 1) & 1;      // where an aligned run leaves its scores
+    if constexpr (ALIGNED && END == 1) st[0] = st[1];
+    soft_half<S, D, 1>(x, st[0], c, pw);
+    soft_close<S, D>(x, st[0], c, pw);
+#pragma unroll
+    for (int b = 0; b < S::DT; ++b) x.vaddr[b] += ALIGNED ? P::v_off(P::UNROLL - 1) : P::v_off(i);
+    last_pv<S, D, S::NQK, true>(x, pw);
+    last_pv<S, D, S::NQK, false>(x, pw);
+    wait_vmcnt<0>();                              // no copy may land once the stages serve something else
+}
+
+// Key groups 1 .. WK-1 hand their states over through LDS, key group 0 adds them up in order (a group that
+// saw no valid key has l = 0 and a reference far below every other).  Every wavefront comes here, after a
+// barrier that ends the use of the stages; the result is key group 0's.
+template <class P>
+__device__ __forceinline__ void stream_merge(StreamRegs<typename P::S, P::D>& x, char* lds, int wave, int lane)
+{
+    typedef typename P::S S;
+    constexpr int QUADS = S::DT * S::NQ;          // 16-byte pieces of a lane's accumulators
+    constexpr int GROUP = 64 * (QUADS * 16 + S::NQ * 8);
+    static_assert((P::WK - 1) * P::WQ * GROUP <= P::LDS, "the states fit the stages");
+    const int wq = wave / P::WK, wk = wave % P::WK;
+    auto quads = [&](int k) -> f32x4* { return (f32x4*)(lds + ((k - 1) * P::WQ + wq) * GROUP) + lane; };
+    auto ml = [&](int k) -> float* { return (float*)(lds + ((k - 1) * P::WQ + wq) * GROUP + 64 * QUADS * 16) + lane * S::NQ * 2; };
+    if (wk > 0) {
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) {
+            f32x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = x.acc[i >> 2][(i & 3) * 4 + r];
+            quads(wk)[i * 64] = v;
+        }
+#pragma unroll
+        for (int q = 0; q < S::NQ; ++q) { ml(wk)[2 * q] = x.m[q]; ml(wk)[2 * q + 1] = x.ls[q][0]; }
+    }
+    __syncthreads();
+    if (wk > 0) return;
+    for (int k = 1; k < P::WK; ++k) {
+        float a0[S::NQ], a1[S::NQ];
+#pragma unroll
+        for (int q = 0; q < S::NQ; ++q) {
+            const float m1 = ml(k)[2 * q], m = fmaxf(x.m[q], m1);
+            a0[q] = __builtin_amdgcn_exp2f(x.m[q] - m);
+            a1[q] = __builtin_amdgcn_exp2f(m1 - m);
+            x.ls[q][0] = x.ls[q][0] * a0[q] + ml(k)[2 * q + 1] * a1[q];
+            x.m[q] = m;
+        }
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) {
+            const f32x4 v = quads(k)[i * 64];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float y = x.acc[i >> 2][(i & 3) * 4 + r];
+                x.acc[i >> 2][(i & 3) * 4 + r] = y * a0[i % S::NQ] + v[r] * a1[i % S::NQ];
+            }
+        }
+    }
+}
+
+// Dense plans.  D = 128: 8 wavefronts, 32 queries each, two per SIMD, 128 KB of LDS.  D = 64: 4 wavefronts of 64
+// queries (32 in the quarters), 64 KB, two workgroups per CU.
+template <int D> struct DensePlan {
+    typedef StreamPlan<128, 2, 8, 1, 2, 4, 4> Whole;
+    typedef StreamPlan<128, 2, 4, 2, 1, 4, 4> Half;
+    typedef StreamPlan<128, 1, 4, 2, 1, 4, 4> Quarter;
+    static constexpr int LDS = Whole::LDS;
+};
+template <> struct DensePlan<64> {
+    typedef StreamPlan<64, 4, 4, 1, 2, 4, 4> Whole;
+    typedef StreamPlan<64, 4, 2, 2, 1, 4, 4> Half;
+    typedef StreamPlan<64, 2, 2, 2, 1, 4, 4> Quarter;
+    static constexpr int LDS = Whole::LDS;
+};
+
+template <class P>
+__device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int bh, int q00)
+{
+    typedef typename P::S S;
+    constexpr int D = P::D;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int kv_len = p.kv_len;
     if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
         kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
         kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
     }
-
     const int smp = bh / p.H, head = bh % p.H;
     const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
     const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
-
-    const int T = (kv_len + KT - 1) / KT;
-    if (T == 0) {                                 // a sample without valid tokens: its rows are zero
-        f32x16 zero[DB];
+    const int q0 = q00 + wave / P::WK * 16 * P::NQ;        // this wavefront's queries
+    char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
+    StreamRegs<S, D> x;
+    if (q00 >= kv_len) {                          // padding rows only: zero
+        if (wave % P::WK != 0) return;
 #pragma unroll
-        for (int i = 0; i < DB; ++i)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) zero[i][j] = 0.f;
-        write_output<D>(O, zero, 0.f, q0 + (threadIdx.x >> 6) * 32 + (threadIdx.x & 31), false, p.N, (threadIdx.x & 63) >> 5);
+        for (int q = 0; q < S::NQ; ++q) x.ls[q][0] = 0.f;
+        stream_output_rows<S, D>(x, O, q0, 0, p.N, lane, out_stage);
         return;
     }
-
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        if (t < T) {
-            issue_tile<D, NW, false>(K, t * KT, kv_len, k_stage(t), wave, lane);
-            issue_tile<D, NW, true>(V, t * KT, kv_len, v_stage(t), wave, lane);
-        }
+    AllKeys<P> keys;
+    const int last = ((kv_len + 31) / 32 + P::WK - 1) / P::WK - 1;
+    stream_attend<P, false>(x, lds, Q, K, V, q0, kv_len, p.c, last, keys, wave, lane);
+    __syncthreads();                              // every wavefront has read its last tile
+    if constexpr (P::WK > 1) {
+        stream_merge<P>(x, lds, wave, lane);
+        if (wave % P::WK != 0) return;
+        // (its rows go through LDS that only it has read: see out_stage)
     }
-
-    const int qrow = q0 + wave * 32 + n;          // this lane's query row
-    const bool qvalid = qrow < kv_len;            // kv_len <= N
-    bf16x8 qf[KS];
-    load_q<D>(Q, qrow, qvalid, h, qf);
-
-    f32x16 acc[DB];
-#pragma unroll
-    for (int i = 0; i < DB; ++i)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
-    SoftmaxState sm;
-    sm.m = -INFINITY;
-    sm.l = 0.f;
-    const int tr_row = (lane & 15) >> 2;
-    const int tr_col = ((lane & 3) << 2) + (((lane >> 4) & 1) << 4);
-
-    // The Q fragments and the first tiles must have arrived before the loop (a wait for
-    // the Q loads inside the loop would also wait for every tile copy in flight).
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (group == 1) __syncthreads();              // group 1 runs one barrier behind
-
-    TileCtx<D, PD> ctx;
-    bf16x8 pb[4];
-    f32x16 st[2];
-    k_addresses<D>(k_stage(0), n, h, ctx);
-    items_prefetch<D, PD, TI::NPV, TI::NI>(ctx);
-    items_run<D, PD, TI::NPV, TI::NI>(ctx, pb, qf, acc, st);   // S_0
-    mask_tail(st, 0, kv_len, h);
-
-    // Where the tile copies are issued.  At D = 128 the A phase is the critical one (measured per
-    // phase: the copy instructions cost it ~270 cycles while the B phase had ~550 cycles of
-    // slack), so the copies go to the start of the B phases, split between the groups: in its
-    // B(j) group 0 copies K_{j+3} and group 1 copies V_{j+3}.  With b(n) the n-th barrier of the
-    // loop, group 0 runs B(j) after b(2j+1) and A(j) after b(2j+2), group 1 one barrier later.
-    //   K_{j+3} overwrites K_{j-1}, last read by S_{j-1} = K_{j-1} Q^T in A(j-2) (both groups are
-    //   through it before b(2j)); K_t is first read in group 0's A(t-1) after b(2t): group 0
-    //   waits for its K_{j+1} at the end of B(j), before b(2j+2).
-    //   V_{j+3} overwrites V_{j-1}, last read in group 1's A(j-1) (done before b(2j+2)); V_t is
-    //   first read in group 0's B(t) after b(2t+1), the barrier that ends group 1's B(t-1):
-    //   group 1 waits for its V_{j+1} at the end of B(j).
-    // At D = 64 the B phase is the longer one and every wavefront issues its share of tile j+3
-    // at the start of A(j).
-    constexpr bool COPY_IN_B = (D == 128);
-    constexpr int LC = G::LOADS / 4;              // copy instructions per wavefront for one K or V tile by one group
-    for (int j = 0; j < T; ++j) {
-        if constexpr (!COPY_IN_B) {
-            // my share of tile j+1 (outstanding: tiles j+1 and j+2, completing in order)
-            if (j + 2 < T) wait_vmcnt<LPT>();
-            else wait_vmcnt<0>();
-        }
-        phase_barrier();
-
-        // ---- B(j)
-        if constexpr (COPY_IN_B) {
-            if (j + 3 < T) {
-                if (group == 0) issue_tile<D, 4, false>(K, (j + 3) * KT, kv_len, k_stage(j + 3), wave, lane);
-                else issue_tile<D, 4, true>(V, (j + 3) * KT, kv_len, v_stage(j + 3), wave - 4, lane);
-            }
-        }
-        v_addresses<D>(v_stage(j), h, tr_row, tr_col, ctx.vaddr);
-        softmax_tile<D>(st, acc, sm, p.c, j == 0, pb);
-        pin_in_phase(pb, sm.l);
-        items_prefetch<D, PD, 0, TI::NI>(ctx);        // first V_j^T fragments of A(j)
-        if constexpr (COPY_IN_B) {
-            // my group's tile j+1 has landed; its tiles j+2 and j+3 may still be on their way
-            // (tiles 0..2 came with the prologue: in the loop tile t is issued in B(t-3))
-            const int newer = ((j >= 1 && j + 2 < T) ? 1 : 0) + ((j + 3 < T) ? 1 : 0);
-            if (newer == 2) wait_vmcnt<2 * LC>();
-            else if (newer == 1) wait_vmcnt<LC>();
-            else wait_vmcnt<0>();
-        }
-        phase_barrier();
-
-        // ---- A(j): matrix work first in line at the SIMD's issue arbiter
-        __builtin_amdgcn_s_setprio(3);
-        if constexpr (!COPY_IN_B) {
-            if (j + 3 < T) {
-                issue_tile<D, NW, false>(K, (j + 3) * KT, kv_len, k_stage(j + 3), wave, lane);
-                issue_tile<D, NW, true>(V, (j + 3) * KT, kv_len, v_stage(j + 3), wave, lane);
-            }
-        }
-        // PV(j) then QK(j+1) as one stream.  For the last tile the QK half re-reads a
-        // landed stage and its result is never used.
-        k_addresses<D>(k_stage((j + 1 < T) ? j + 1 : j), n, h, ctx);
-        items_run<D, PD, 0, TI::NI>(ctx, pb, qf, acc, st);
-        mask_tail(st, (j + 1) * KT, kv_len, h);
-        __builtin_amdgcn_s_setprio(0);
-    }
-    if (group == 0) __syncthreads();              // same number of barriers for every wavefront
-
-    if constexpr (D == 128) {
-        // row-wise through LDS (see write_output_rows); group 0 waits here until group 1 is
-        // through its last matrix phase and the stages are free, which costs nothing: the
-        // workgroup ends, and its CU takes the next one, when group 1 is done either way
-        __syncthreads();
-        write_output_rows<D>(O, acc, sm.l, q0 + wave * 32, qvalid, p.N, lane, lds + wave * ((D * 2 + 16) * 32));
-    } else {
-        write_output<D>(O, acc, sm.l, qrow, qvalid, p.N, h);
-    }
+    stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
 }
 
-// (D = 64: 64 KB of LDS and <= 128 VGPRs, so two workgroups share a CU: four wavefronts per
-// SIMD hide more of the softmax phase, which is the longer one at D = 64.)
+// 256 queries of one (sample, head) per workgroup; the items of an XCD that do not fill its CUs evenly are
+// cut into `cut` = 2 or 4 workgroups (p.whole of an XCD's items stay whole).
 template <int D>
-__global__ __launch_bounds__(512, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(const AttnParams p)
+__global__ __launch_bounds__(DensePlan<D>::Whole::NW * 64, 2) void attn_dense_stream_kernel(const AttnParams p)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[8 * Geo<D>::TILE_BYTES];
+    typedef DensePlan<D> DP;
+    __shared__ __attribute__((aligned(1024))) char lds[DP::LDS];
     // XCD-aware work mapping: the dispatcher deals consecutive workgroup ids round-robin
     // over the 8 XCDs, so give each XCD a contiguous run of items (query tiles of the same
     // head then share K/V in that XCD's L2).
-    const int wg = blockIdx.x;
-    const int item = (wg % XCDS) * p.chunk + wg / XCDS;
+    const int i = blockIdx.x / XCDS, first = (blockIdx.x % XCDS) * p.chunk;
+    if (i < p.whole) {
+        const int item = first + i;
+        if (item < p.items) dense_item<typename DP::Whole>(p, lds, item / p.nq, item % p.nq * DENSE_QT);
+        return;
+    }
+    const int item = first + p.whole + (i - p.whole) / p.cut;
     if (item >= p.items) return;
-    dense_item<D>(p, lds, item / p.nq, (item % p.nq) * DENSE_QT);
+    const int q0 = item % p.nq * DENSE_QT + (i - p.whole) % p.cut * (DENSE_QT / p.cut);
+    if (q0 >= p.N) return;
+    if (p.cut == 2) dense_item<typename DP::Half>(p, lds, item / p.nq, q0);
+    else dense_item<typename DP::Quarter>(p, lds, item / p.nq, q0);
+}
+
+// Small problems: 32 queries per workgroup of 2 x 2 wavefronts.
+template <int D>
+__global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(const AttnParams p)
+{
+    typedef StreamPlan<D, 1, 2, 2, 1, 2, 3> P;
+    __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
+    const int item = (blockIdx.x % XCDS) * p.chunk + blockIdx.x / XCDS;
+    if (item < p.items) dense_item<P>(p, lds, item / p.nq, item % p.nq * P::QT);
 }
 
 // ---------------------------------------------------------------------------
@@ -1301,6 +1955,7 @@ __global__ __launch_bounds__(128 * WPG, (D == 64 ? (WPG == 4 ? 4 : 2) : 1)) void
     if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
         kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
         kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
     }
 
     const int smp = bh / p.H, head = bh % p.H;
@@ -1502,6 +2157,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_sparse_sg_kernel(
     if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
         kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
         kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
     }
 
     const int smp = bh / p.H, head = bh % p.H;
@@ -1760,17 +2416,37 @@ int run_dense(const Problem& pr, void* stream)
 {
     AttnParams p{};
     fill_common(p, pr);
-    p.counts = nullptr; p.order = nullptr; p.index = nullptr;
+    hipStream_t s = (hipStream_t)stream;
+    const long long pairs = (long long)pr.B * pr.H, small = pairs * ((pr.N + 31) / 32);
+    // All 32-query workgroups resident at once: the shortest chain of steps per wavefront wins (D = 64 / 128,
+    // this kernel against the other: B = 1, H = 24, N = 512: 9.3 / 11.1 us at B = 2 and 11.0 / 11.8 us; H = 2,
+    // N = 256: 5.2 / 6.5 and 6.8 / 9.0 us).  At D = 128 its 16-query wavefronts read K and V from LDS twice as
+    // often per product and it loses on long sequences (H = 2, N = 8192: 93 / 79 us; D = 64: 55 / 57 us).
+    if (small <= (pr.D == 64 ? 4 : 2) * XCDS * CUS_PER_XCD && (pr.D == 64 || pr.N <= 1024)) {
+        p.nq = (pr.N + 31) / 32;
+        p.items = (int)small;
+        p.chunk = (p.items + XCDS - 1) / XCDS;
+        const dim3 grid((unsigned)p.chunk * XCDS);
+        if (pr.D == 64) hipLaunchKernelGGL((attn_dense_pp_kernel<64>), grid, dim3(256), 0, s, p);
+        else hipLaunchKernelGGL((attn_dense_pp_kernel<128>), grid, dim3(256), 0, s, p);
+        return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
+    }
     p.nq = (pr.N + DENSE_QT - 1) / DENSE_QT;
-    const long long items = (long long)pr.B * pr.H * p.nq;
-    if (items > 0x7fffffffLL / 2) return RAPID_ERR_SHAPE;
+    const long long items = pairs * p.nq;
+    if (items > 0x7fffffffLL / 8) return RAPID_ERR_SHAPE;
     p.items = (int)items;
     p.chunk = (p.items + XCDS - 1) / XCDS;
-    p.block = 0; p.nb = 0; p.sub_shift = 0;
-    hipStream_t s = (hipStream_t)stream;
-    const int grid = p.chunk * XCDS;
-    if (pr.D == 64) hipLaunchKernelGGL((attn_dense_pp_kernel<64>), dim3(grid), dim3(512), 0, s, p);
-    else hipLaunchKernelGGL((attn_dense_pp_kernel<128>), dim3(grid), dim3(512), 0, s, p);
+    // What is left over after every CU of an XCD got the same number of items is cut so that it still makes
+    // one workgroup per CU at most: a last round of an eighth of the CUs takes a quarter of the time.  us, items of an
+    // XCD: 33 (H = 24, N = 2816) whole 136, in 2 116, in 4 105 at D = 128, 81 / 60 / 55 at D = 64; 198 (N = 16896)
+    // 2875 / 2734 / 2703; 108 (B = 2, N = 4429, D = 64) 257 / 231 / 257.  More than half of a round stays whole: 54
+    // items (N = 4608) 218 / 247 / 255.
+    const int rest = p.chunk % CUS_PER_XCD;
+    p.cut = rest * 4 <= CUS_PER_XCD ? 4 : rest * 2 <= CUS_PER_XCD ? 2 : 1;
+    p.whole = p.cut == 1 ? p.chunk : p.chunk - rest;
+    const dim3 grid((unsigned)(p.whole + (p.chunk - p.whole) * p.cut) * XCDS);
+    if (pr.D == 64) hipLaunchKernelGGL((attn_dense_stream_kernel<64>), grid, dim3(DensePlan<64>::Whole::NW * 64), 0, s, p);
+    else hipLaunchKernelGGL((attn_dense_stream_kernel<128>), grid, dim3(DensePlan<128>::Whole::NW * 64), 0, s, p);
     return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
 }
 
