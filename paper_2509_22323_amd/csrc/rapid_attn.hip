@@ -29,7 +29,8 @@
 //                               two groups of wavefronts
 //   attn_sparse_sg_kernel<D>    sparse, 128-token mask tiles: one four-wavefront workgroup per plan
 //                               record (a query-block or a piece of its kept list); pieces are
-//                               merged by the last one to finish
+//                               merged by the last one to finish.  D = 128 on the 16x16x32 stream
+//   attn_sparse_wide_kernel     the same at D = 64 on the stream, for calls of many rows
 //   attn_sparse_pp_kernel<D,2>  sparse, 64-token mask tiles: one query-block per workgroup, the kept
 //                               list split between two wavefront groups and merged through LDS
 //   plan_small_kernel           mask compaction and launch plan in one launch (up to 64 blocks per side)
@@ -992,48 +993,6 @@ __device__ __forceinline__ void write_output(const Rows& O, const f32x16 (&acc)[
     }
 }
 
-// The same output through LDS, for a wavefront whose 32 queries are the rows row0 .. row0 + 31.
-// A lane holds 8-byte pieces of ONE row, so storing from registers sends 32 short stretches of
-// 32 different rows with every instruction (16 instructions, 512 memory requests per
-// wavefront); written to `stage` first (row stride D*2 + 16 bytes: the 8-byte writes of the
-// 32 rows spread over the banks) and read back 16 bytes per lane along the rows, a store
-// instruction covers whole rows (8 or 4 instructions, a quarter of the requests).  `stage`
-// is this wavefront's own region of (D*2 + 16) * 32 bytes; nobody else may still be reading it.
-template <int D>
-__device__ __forceinline__ void write_output_rows(const Rows& O, const f32x16 (&acc)[D / 32], float l_part,
-                                                  int row0, bool qvalid, int N, int lane, char* stage)
-{
-    constexpr int RS = D * 2 + 16;
-    const int n = lane & 31, h = lane >> 5;
-    float l_run = l_part;
-    {
-        auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-        l_run = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
-    const float inv = (qvalid && l_run > 0.f) ? 1.0f / l_run : 0.f;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            bf16x4 ov;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float x = acc[db][4 * j + r] * inv;
-                ov[r] = (__bf16)((inv != 0.f) ? x : 0.f);
-            }
-            *(bf16x4*)(stage + n * RS + (32 * db + 8 * j + 4 * h) * 2) = ov;
-        }
-    constexpr int CH = D * 2 / 16;                // 16-byte chunks of a row
-    constexpr int RPI = 64 / CH;                  // rows per store instruction
-    const int rr = lane / CH, cc = lane % CH;
-#pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
-        const int r = i * RPI + rr;
-        const u32x4 v = *(const u32x4*)(stage + r * RS + cc * 16);
-        if (row0 + r < N) *(u32x4*)(const_cast<char*>(O.row(row0 + r)) + cc * 16) = v;
-    }
-}
-
 // Q^T fragments (B operand of S^T = K Q^T): lane (n, h) holds Q[qrow][16t + 8h .. +8].
 template <int D>
 __device__ __forceinline__ void load_q(const Rows& Q, int qrow, bool qvalid, int h, bf16x8 (&qf)[D / 16])
@@ -1608,15 +1567,50 @@ struct StreamPlan {
     static constexpr __host__ __device__ int v_off(int i) { return (i / SPT % NSV) * TILE + (i % SPT) * 32 * S::RB; }
 };
 
+// Which tiles: at(t, u, moved) is the first key of tile t; the caller stands in tile t - u of the unrolled
+// steps' first tile, u known when compiling, and has called advance in tile UNROLL / SPT - 1 of them or not.
 // Tiles in order: the dense path.
 template <class P>
 struct AllKeys {
-    __device__ __forceinline__ int at(int t) const { return t * P::KTS; }
-    __device__ __forceinline__ void advance(int) {}
+    __device__ __forceinline__ int at(int t, int, bool) const { return t * P::KTS; }
+    __device__ __forceinline__ void advance() {}
 };
 
-// Steps 0 .. last of this workgroup's queries against the tiles keys.at(0), keys.at(1), .. (the first key of a
-// tile; tiles at or beyond kv_len are all masked).  ALIGNED: last + 1 is a multiple of P::UNROLL.
+// The 32-key steps of a list of kept 128-key blocks (four steps = one block = one run of the unrolled loop).
+// The first keys of the current and the next two blocks are at hand, that of the third is under way: a scalar
+// load has a block's time (about 2000 cycles) to arrive.  Past the end of the list: beyond every kv_len.
+template <class P>
+struct KeptKeys {
+    static_assert(P::KTS == 32 && P::UNROLL == 4, "");
+    static constexpr int NOWHERE = 1 << 30;
+    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+    cptr_t list;
+    int n, next;                                   // blocks; the next one to be requested
+    int b0, b1, b2, coming;
+    __device__ __forceinline__ KeptKeys(cptr_t list_, int n_) : list(list_), n(n_), next(4)
+    {
+        const int i1 = list[n > 1 ? 1 : 0], i2 = list[n > 2 ? 2 : 0];
+        coming = list[n > 3 ? 3 : 0];
+        b0 = list[0] * 128;
+        b1 = n > 1 ? i1 * 128 : NOWHERE;
+        b2 = n > 2 ? i2 * 128 : NOWHERE;
+    }
+    __device__ __forceinline__ int at(int, int u, bool moved) const
+    {
+        const int r = moved ? u - 4 : u;
+        return (r < 4 ? b0 : r < 8 ? b1 : b2) + r % 4 * 32;
+    }
+    __device__ __forceinline__ void advance()
+    {
+        b0 = b1;
+        b1 = b2;
+        b2 = next - 1 < n ? coming * 128 : NOWHERE;
+        coming = list[next < n ? next : 0];
+        ++next;
+    }
+};
+
+// Steps 0 .. last of this workgroup's queries against the tiles of `keys` (tiles at or beyond kv_len are all masked).  ALIGNED: last + 1 is a multiple of P::UNROLL.
 template <class P, bool ALIGNED, class Keys>
 __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x, char* lds, const Rows& Q, const Rows& K, const Rows& V,
                                               int q0, int kv_len, float c, int last, Keys& keys, int wave, int lane)
@@ -1650,11 +1644,11 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
 #pragma unroll
     for (int b = -P::KLEAD; b < (P::SPT == 1 ? -1 : 0); ++b) {
         if (b + P::VLEAD >= 0) {
-            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD), kv_len);
+            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD, b + P::VLEAD, false), kv_len);
 #pragma unroll
             for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + P::VLEAD) * P::TILE);
         }
-        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD), kv_len);
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD, b + P::KLEAD, false), kv_len);
 #pragma unroll
         for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + P::KLEAD) * P::TILE);
     }
@@ -1673,8 +1667,8 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     first_qk<S, D, 0, 0, true>(x, st[0]);
     first_qk<S, D, 0, 0, false>(x, st[0]);
     if constexpr (P::SPT == 1) {                  // the barrier before tile 0: K_1, V_0 may be read
-        const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1), kv_len);
-        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1), kv_len);
+        const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1, P::VLEAD - 1, false), kv_len);
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1, P::KLEAD - 1, false), kv_len);
         wait_vmcnt<P::LOOSE>();
         phase_barrier();
 #pragma unroll
@@ -1682,7 +1676,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
 #pragma unroll
         for (int e = 0; e < LC; ++e) copy_k(kb, e, 0);
     }
-    mask_step<S>(st[0], keys.at(0) + wk * 32, kv_len, lane);
+    mask_step<S>(st[0], keys.at(0, 0, false) + wk * 32, kv_len, lane);
 #pragma unroll
     for (int q = 0; q < S::NQ; ++q) {
         x.m[q] = step_max<S>(st[0], q, c);
@@ -1722,11 +1716,12 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         else step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, hook);
         soft_close<S, D>(x, sc, c, pw);
         const int t = i / P::SPT;
-        mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1) + wk * 32 : keys.at((i + 1) / 2) + (i + 1) % 2 * 32, kv_len, lane);
+        mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1, U + 1, false) + wk * 32 : keys.at((i + 1) / 2, 0, false) + (i + 1) % 2 * 32, kv_len, lane);
         if (RT ? i % P::SPT == 0 : FIRST_OF_TILE) {
-            keys.advance(t);
-            vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD), kv_len);
-            kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD), kv_len);
+            constexpr bool MOVE = !RT && U / P::SPT == P::UNROLL / P::SPT - 1;
+            if constexpr (MOVE) keys.advance();
+            vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, U / P::SPT + P::VLEAD, MOVE), kv_len);
+            kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, U / P::SPT + P::KLEAD, MOVE), kv_len);
             wait_vmcnt<P::LOOSE>();
             phase_barrier();
             if constexpr (RT) {
@@ -2108,13 +2103,145 @@ struct PartialSlot {
 };
 
 // ---------------------------------------------------------------------------
-// Sparse path, 128-token mask tiles: one workgroup of FOUR wavefronts per (b, h, query-block)
-// walks the whole kept-tile list of its item; 64 KB of LDS (32 KB at D = 64) and one
-// wavefront per SIMD, so two such workgroups (four at D = 64) share a CU.  The fixed cost
-// of an item (list lookup, first copies, Q load, output) is then hidden behind the tile loop
-// of the neighbour instead of leaving the CU idle, which is what matters when the lists are
-// short; the two wavefronts on a SIMD belong to different items and fall into the same
-// softmax-against-MFMA overlap as the two groups of the dense kernel.
+// Sparse path, 128-token mask tiles: one workgroup per plan record walks the kept-block list of its
+// piece on the 16x16x32 stream, 128 queries in four wavefronts of 32 (D = 128, 64 KB of LDS, two workgroups
+// per CU) or two of 64 (D = 64, 32 KB, four per CU): two wavefronts per SIMD, of different items, so the
+// fixed cost of an item (list lookup, first copies, Q load, output) hides behind the neighbour's loop.
+// us, B = 1, H = 24, D = 128 at densities 0.15 / 0.3 / 0.6, against 32x32x16 MFMAs alternating with softmax phases:
+// N = 4480 70.6 -> 66.8, 97.9 -> 90.9, 157 -> 145; N = 8960 194 -> 180, 321 -> 285, 590 -> 521; N = 384 17.7 -> 16.3.
+// ---------------------------------------------------------------------------
+template <int D> struct SparsePlan { typedef StreamPlan<128, 2, 4, 1, 1, 4, 4> P; };
+template <> struct SparsePlan<64> { typedef StreamPlan<64, 4, 2, 1, 1, 4, 4> P; };
+
+template <int D>
+__device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
+{
+    typedef typename SparsePlan<D>::P P;
+    typedef typename P::S S;
+    static_assert(P::QT == 128, "one record = 128 queries");
+    __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
+
+    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+    const int wg = blockIdx.x;
+    typedef const __attribute__((address_space(4))) i32x4* rptr_t;
+    static_assert(sizeof(PlanRec) == sizeof(i32x4), "one record = one 16-byte scalar load");
+    const i32x4 raw = ((rptr_t)p.order)[(size_t)(wg % XCDS) * p.chunk + wg / XCDS];
+    const PlanRec rec = {raw[0], raw[1], raw[2], raw[3]};
+    const int item = rec.item;
+    if (item < 0) return;
+    const int bh = item / p.nq;
+    const int qi = item % p.nq;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int kv_len = p.kv_len;
+    if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
+        kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
+        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
+    }
+
+    const int smp = bh / p.H, head = bh % p.H;
+    const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
+    const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
+    const int q0 = qi * 128 + wave * 16 * P::NQ;
+    char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
+
+    StreamRegs<S, D> x;
+    if (rec.nblk <= 0) {                          // nothing kept: the rows are zero
+#pragma unroll
+        for (int q = 0; q < P::NQ; ++q) x.ls[q][0] = 0.f;
+        stream_output_rows<S, D>(x, O, q0, 0, p.N, lane, out_stage);
+        return;
+    }
+    // Whole blocks: what lies at or beyond kv_len in a row's last block is masked, at most three steps.
+    KeptKeys<P> keys((cptr_t)(p.index + (size_t)item * p.nb + rec.blk0), rec.nblk);
+    stream_attend<P, true>(x, lds, Q, K, V, q0, kv_len, p.c, rec.nblk * 4 - 1, keys, wave, lane);
+    __syncthreads();                              // every wavefront has read its last tile
+    if (rec.w < 0) {                              // the whole item
+        stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
+        return;
+    }
+
+    // ---- a piece of a split item: leave (acc, m, l) in this piece's slot; the piece that
+    // finishes last adds all of them up, in piece order (so the sum does not depend on which
+    // one that is).  A piece has at least one valid key per query, so every m is finite.
+    // The slots are written and read with device-scope relaxed atomic accesses, each of which
+    // is coherent across the chip by itself, instead of plain accesses between device-scope
+    // fences: a release fence would write back every dirty line of the XCD's L2.  Order: a
+    // wavefront's stores are acknowledged (vmcnt 0) before the barrier after which one thread
+    // counts the piece in; the last piece reads only after it has seen the full count.
+    typedef unsigned long long u64;
+    constexpr size_t SLOT_BYTES = PartialSlot<D>::BYTES;
+    constexpr int PAIRS = S::DT * S::NQ * 2;      // 64-bit words of accumulators per lane
+    static_assert((size_t)P::NW * PAIRS * 64 * 8 == PartialSlot<D>::ML_OFF, "the slot holds the accumulators");
+    const int pieces = (rec.w & 15) + 1;
+    const int piece = (rec.w >> 4) & 15;
+    const int slot0 = rec.w >> 8;
+    auto slot_acc = [&](int k) -> u64* { return (u64*)(p.partial + (size_t)(slot0 + k) * SLOT_BYTES) + (size_t)wave * PAIRS * 64 + lane; };
+    // (m, l) of query 16 q + n, held by the four lanes n, n + 16, ..: once per query
+    auto slot_ml = [&](int k, int q) -> u64* {
+        return (u64*)(p.partial + (size_t)(slot0 + k) * SLOT_BYTES + PartialSlot<D>::ML_OFF) + (wave * P::NQ + q) * 16 + (lane & 15);
+    };
+    {
+        u64* pacc = slot_acc(piece);
+#pragma unroll
+        for (int i = 0; i < PAIRS; ++i) {
+            const u64 v = (u64)__float_as_uint(x.acc[i / 8][i % 8 * 2]) | ((u64)__float_as_uint(x.acc[i / 8][i % 8 * 2 + 1]) << 32);
+            __hip_atomic_store(pacc + i * 64, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (lane < 16) {
+#pragma unroll
+            for (int q = 0; q < P::NQ; ++q) {
+                const u64 ml = (u64)__float_as_uint(x.m[q]) | ((u64)__float_as_uint(x.ls[q][0]) << 32);
+                __hip_atomic_store(slot_ml(piece, q), ml, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    __shared__ int arrived_before;
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (tid == 0) arrived_before = __hip_atomic_fetch_add(&p.arrived[slot0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived_before != pieces - 1) return;
+
+#pragma unroll
+    for (int q = 0; q < P::NQ; ++q) { x.m[q] = -INFINITY; x.ls[q][0] = 0.f; }
+    for (int k = 0; k < pieces; ++k) {
+#pragma unroll
+        for (int q = 0; q < P::NQ; ++q) {
+            const u64 ml = __hip_atomic_load(slot_ml(k, q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            x.m[q] = fmaxf(x.m[q], __uint_as_float((unsigned)ml));
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < S::DT * S::NQ / 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x.acc[b][r] = 0.f;
+    for (int k = 0; k < pieces; ++k) {
+        float a[P::NQ];
+#pragma unroll
+        for (int q = 0; q < P::NQ; ++q) {
+            const u64 ml = __hip_atomic_load(slot_ml(k, q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            a[q] = __builtin_amdgcn_exp2f(__uint_as_float((unsigned)ml) - x.m[q]);
+            x.ls[q][0] += __uint_as_float((unsigned)(ml >> 32)) * a[q];
+        }
+        const u64* pacc = slot_acc(k);
+#pragma unroll
+        for (int i = 0; i < PAIRS; ++i) {
+            const u64 v = __hip_atomic_load(pacc + i * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            x.acc[i / 8][i % 8 * 2] += __uint_as_float((unsigned)v) * a[i / 2 % P::NQ];
+            x.acc[i / 8][i % 8 * 2 + 1] += __uint_as_float((unsigned)(v >> 32)) * a[i / 2 % P::NQ];
+        }
+    }
+    stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
+}
+
+// ---------------------------------------------------------------------------
+// Sparse path, 128-token mask tiles, D = 64, short calls: FOUR wavefronts of 32 queries per record, 32 KB of
+// LDS, four workgroups per CU.  A step of its loop takes half as long as one of 64 queries per wavefront, which
+// counts when every record is resident at once and the longest chain is the time.
 //
 // Per tile j two slots separated by workgroup barriers:
 //   B(j)  softmax of S_j; copies of V_{j+1} and K_{j+2} issued; first V_j^T fragments requested
@@ -2125,11 +2252,11 @@ struct PartialSlot {
 // for everything older: K_{j+1} (issued in B(j-1)) is awaited at the end of B(j) with this
 // slot's copies still in flight, V_{j+1} at the end of A(j) with K_{j+2} still in flight.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_sparse_sg_kernel(const AttnParams p)
+__device__ __forceinline__ void sparse_short_record(const AttnParams& p)
 {
+    constexpr int D = 64;
     typedef Geo<D> G;
-    constexpr int PD = D == 64 ? 3 : 6;           // see dense_item
+    constexpr int PD = 3;                         // (more does not fit 128 registers)
     typedef TileItems<D, PD> TI;
     constexpr int NW = 4, QT = 128, KS = D / 16, DB = D / 32;
     constexpr int LPT = G::LOADS / NW;            // copy instructions per wavefront per tile (K or V)
@@ -2138,7 +2265,6 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_sparse_sg_kernel(
 
     typedef const __attribute__((address_space(4))) int32_t* cptr_t;
     const int wg = blockIdx.x;
-    typedef int i32x4 __attribute__((ext_vector_type(4)));
     typedef const __attribute__((address_space(4))) i32x4* rptr_t;
     static_assert(sizeof(PlanRec) == sizeof(i32x4), "one record = one 16-byte scalar load");
     const i32x4 raw = ((rptr_t)p.order)[(size_t)(wg % XCDS) * p.chunk + wg / XCDS];
@@ -2245,16 +2371,9 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_sparse_sg_kernel(
         kn3 = (j + 4 < T) ? key_of(j + 4) : 0;
     }
 
-    // At D = 128 the output goes out row-wise through LDS (-1.5 % on a sparse call); at D = 64,
-    // with four workgroups on the CU and rows half as long, that was 2-3 % slower than direct.
-    char* out_stage = lds + wave * ((D * 2 + 16) * 32);
+    // Output straight from registers: with four workgroups on the CU, row-wise through LDS was 2-3 % slower.
     if (rec.w < 0) {                              // the whole item
-        if constexpr (D == 128) {
-            __syncthreads();                      // every wavefront has read its last tiles
-            write_output_rows<D>(O, acc, sm.l, qi * QT + wave * 32, qvalid, p.N, lane, out_stage);
-        } else {
-            write_output<D>(O, acc, sm.l, qrow, qvalid, p.N, h);
-        }
+        write_output<D>(O, acc, sm.l, qrow, qvalid, p.N, h);
         return;
     }
 
@@ -2317,8 +2436,19 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_sparse_sg_kernel(
                 acc[db][2 * j + 1] += __uint_as_float((unsigned)(v >> 32)) * a;
             }
     }
-    if constexpr (D == 128) write_output_rows<D>(O, acc, l, qi * QT + wave * 32, qvalid, p.N, lane, out_stage);   // after the barriers above
-    else write_output<D>(O, acc, l, qrow, qvalid, p.N, h);
+    write_output<D>(O, acc, l, qrow, qvalid, p.N, h);
+}
+
+// The record of a workgroup on the kernel of its head size and length.
+template <int D>
+__global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_sparse_sg_kernel(const AttnParams p)
+{
+    if constexpr (D == 64) sparse_short_record(p);
+    else sparse_stream_record<D>(p);
+}
+__global__ __launch_bounds__(SparsePlan<64>::P::NW * 64, 2) void attn_sparse_wide_kernel(const AttnParams p)
+{
+    sparse_stream_record<64>(p);
 }
 
 // ---------------------------------------------------------------------------
@@ -2499,8 +2629,13 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     p.block = block; p.nb = nb; p.sub_shift = block == 128 ? 1 : 0;
     const dim3 grid((unsigned)w.chunk * XCDS);
     if (block == 128) {
-        if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
-        else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(256), 0, s, p);
+        // D = 64: 64 queries per wavefront read LDS half as often, but a record takes longer; it wins where every place
+        // of the chip (four per CU) gets at least two records.  us, 32 / 64 queries per wavefront, H = 24, densities 0.15 to 1:
+        // 3072 rows (B = 8, N = 2048) 87 / 84 to 218 / 208; 6720 (B = 8, N = 4480) 267 / 267 to 973 / 939; 1536 rows
+        // (B = 8, N = 1024) 41 / 42 to 67 / 74; 840 rows of N = 896 26.4 / 29.7.
+        if (D == 64 && rows > 2 * 4 * XCDS * CUS_PER_XCD) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
+        else if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
+        else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(SparsePlan<128>::P::NW * 64), 0, s, p);
     } else {
         if (D == 64) hipLaunchKernelGGL((attn_sparse_pp_kernel<64, 2>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((attn_sparse_pp_kernel<128, 2>), grid, dim3(256), 0, s, p);
