@@ -1125,7 +1125,7 @@ struct StreamRegs {
     unsigned kc, kn, vc;                       // offsets of a step outside the unrolled loop
 };
 
-constexpr float REF_UP = 60.f;
+constexpr float REF_UP = 8.f;
 
 // Lane addresses in a K tile at byte address k0 and a V tile at v0.
 template <class S, int D>
@@ -1303,10 +1303,14 @@ __device__ __forceinline__ float step_max(const Scores<S>& st, int q, float c)
 }
 
 // Range of the exponents.  The reference m of a query is the maximum of its first step plus REF_UP, so
-// that probabilities of 2 and more mean a later maximum more than 61 above the first.  Such a value
+// that probabilities of 2 and more mean a later maximum more than 9 above the first.  Such a value
 // has the top bit of its bf16 exponent set, which the or over all packed words shows; only then the
 // references move up to the step's maximum (plus REF_UP), the sums and the accumulators are rescaled
-// and the step's probabilities are made again.  What lies 2^66 below a row's first maximum is lost.
+// and the step's probabilities are made again.  What lies 2^118 below a row's reference is lost.
+// REF_UP is small because the accumulators hold V times these weights, at most 2^-8 in an ordinary row: V of 2^-118
+// is still summed in normal numbers (with 60 in its place everything below 2^-89 came out as 0), and at the top
+// |V| up to 2^126 / number of keys.  The exact test for 2^8 that needs no REF_UP (a maximum over the packed words,
+// v_pk_maximum3_f16, in place of the or) costs 1.5 % of a dense call.
 template <class S, int D>
 __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
 {

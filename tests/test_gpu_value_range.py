@@ -1,0 +1,89 @@
+"""Attention over the range of its inputs: every output row is a weighted mean of values, so values scaled by a power
+of two give outputs scaled by it, from near the bottom of bf16's exponents to near their top, on every dense plan and
+every sparse kernel.  Against float32 attention of the unscaled bf16 inputs.  Tolerance: P and O are rounded to bf16
+(2^-9 each, relative), 2.3e-3 of the output's norm; twice that per 64 rows of a head."""
+import math
+
+import pytest
+import torch
+
+import paper_2509_22323_amd as ra
+from test_gpu_dense_plans import PLANS
+
+pytestmark = pytest.mark.gpu
+
+# A row's weights before the division by their sum are at most 2^-8 to 1 on the paths that take no row maximum: V * 2^-118
+# is the smallest whose products with them are normal numbers.  The top is what the same weights under climbing scores,
+# up to 2^60 on the kernel of short rows at D = 64, leave room for.
+SCALES = {False: [-118, -100, -80, 100], True: [-118, -100, -80, 50]}
+# name, heads, blocks per side, block; the last is cut into 128-token rows of the kernel for many rows at D = 64
+SPARSE = [("block 64", 3, 24, 64), ("block 128", 3, 24, 128), ("many rows", 100, 21, 128)]
+
+
+def attention(q, k, v, mask=None, block=1):
+    out = torch.zeros(q.shape, dtype=torch.float32, device=q.device)
+    for h in range(q.shape[1]):
+        s = (q[0, h].float() @ k[0, h].float().t()) * q.shape[3] ** -0.5
+        if mask is not None:
+            s = s.masked_fill(~mask[0, h].bool().repeat_interleave(block, 0).repeat_interleave(block, 1), -math.inf)
+        out[0, h] = torch.softmax(s, -1) @ v[0, h].float()
+    return out
+
+
+def check(o, ref, power, what):
+    scaled = o.float().double() * 2.0 ** -power
+    assert torch.isfinite(scaled).all(), what
+    N = o.shape[2]
+    for r in range(0, N, 64):
+        a, b = scaled[0, :, r:min(r + 64, N)].flatten(1), ref[0, :, r:min(r + 64, N)].flatten(1).double()
+        err = ((a - b).norm(dim=1) / b.norm(dim=1)).max().item()
+        assert err <= 5e-3, f"{what}, V * 2^{power}: rows {r}..: {err:.2e}"
+
+
+def inputs(H, N, D, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return g, *(torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+
+
+def climbing(q, k, D):
+    """Later keys score up to 100 (base 2) above the first ones, in steps of 50; odd rows the other way round."""
+    q[..., 0] = 8.0
+    q[:, :, 1::7, 0] = -8.0
+    k[..., 0] = 0.0
+    for i, at in enumerate((70, k.shape[2] // 2 + 3)):
+        k[:, :, at:, 0] = (i + 1) * 50.0 * math.log(2.0) * math.sqrt(D) / 8.0
+
+
+def mask_of(g, H, nb):
+    mask = (torch.rand((1, H, nb, nb), generator=g, device="cuda") < 0.3).to(torch.uint8)
+    mask[:, :, :, 0] = 1
+    mask[:, :, 5::9] = 1
+    return mask
+
+
+@pytest.mark.parametrize("climb", [False, True])
+@pytest.mark.parametrize("D,plan,H,N", [(D, *p) for D in (64, 128) for p in PLANS[D]])
+def test_dense_scales_with_v(D, plan, H, N, climb):
+    _, q, k, v = inputs(H, N, D, 5 + D)
+    if climb:
+        climbing(q, k, D)
+    ref = attention(q, k, v)
+    for power in SCALES[climb]:
+        o = torch.empty_like(q)
+        ra.rapid_attn_dense(q, k, (v.double() * 2.0 ** power).to(torch.bfloat16), o)
+        check(o, ref, power, f"{plan} D={D}")
+
+
+@pytest.mark.parametrize("climb", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("name,H,nb,block", SPARSE)
+def test_sparse_scales_with_v(D, name, H, nb, block, climb):
+    g, q, k, v = inputs(H, nb * block, D, 6 + D)
+    if climb:
+        climbing(q, k, D)
+    mask = mask_of(g, H, nb)
+    ref = attention(q, k, v, mask, block)
+    for power in SCALES[climb]:
+        o = torch.empty_like(q)
+        ra.rapid_attn_block_sparse(q, k, (v.double() * 2.0 ** power).to(torch.bfloat16), o, mask, block)
+        check(o, ref, power, f"{name} D={D}")
