@@ -1126,6 +1126,7 @@ struct StreamRegs {
 };
 
 constexpr float REF_UP = 8.f;
+constexpr float REF_LOWEST = -1e30f;           // of a query whose first step has no finite score
 
 // Lane addresses in a K tile at byte address k0 and a V tile at v0.
 template <class S, int D>
@@ -1286,7 +1287,7 @@ __device__ __forceinline__ void soft_half(StreamRegs<S, D>& x, const Scores<S>& 
     }
 }
 
-// Largest exponent of a query of group q over the step (a finite number: every step has a valid key).
+// Largest exponent of a query of group q over the step (-inf where none of its keys is valid).
 template <class S>
 __device__ __forceinline__ float step_max(const Scores<S>& st, int q, float c)
 {
@@ -1318,9 +1319,10 @@ __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>&
     if (__builtin_expect(out != 0ull, 0)) {
 #pragma unroll
         for (int q = 0; q < S::NQ; ++q) {
-            const float delta = fmaxf(step_max<S>(st, q, c) + REF_UP - x.m[q], 0.f);
-            const float alpha = __builtin_amdgcn_exp2f(-delta);
-            x.m[q] += delta;
+            const float m = fmaxf(x.m[q], step_max<S>(st, q, c) + REF_UP);
+            const float alpha = __builtin_amdgcn_exp2f(x.m[q] - m);
+            x.m[q] = m;
+            asm volatile("" : "+v"(x.m[q]));      // in place
             x.ls[q] *= alpha;
 #pragma unroll
             for (int b = 0; b < S::DT; ++b)
@@ -1683,9 +1685,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     mask_step<S>(st[0], keys.at(0, 0, false) + wk * 32, kv_len, lane);
 #pragma unroll
     for (int q = 0; q < S::NQ; ++q) {
-        x.m[q] = step_max<S>(st[0], q, c);
-        if constexpr (P::WK > 1) x.m[q] = fmaxf(x.m[q], -1e30f);       // a key group may have no valid key at all
-        x.m[q] += REF_UP;
+        x.m[q] = fmaxf(step_max<S>(st[0], q, c) + REF_UP, REF_LOWEST);  // (a key group may have no valid key at all)
     }
     x.seen = 0u;
     soft_half<S, D, 0>(x, st[0], c, pw);

@@ -1,7 +1,8 @@
 """Attention over the range of its inputs: every output row is a weighted mean of values, so values scaled by a power
 of two give outputs scaled by it, from near the bottom of bf16's exponents to near their top, on every dense plan and
-every sparse kernel.  Against float32 attention of the unscaled bf16 inputs.  Tolerance: P and O are rounded to bf16
-(2^-9 each, relative), 2.3e-3 of the output's norm; twice that per 64 rows of a head."""
+every sparse kernel; and rows whose first keys have no finite score.  Against float32 attention of the unscaled bf16
+inputs.  Tolerance: P and O are rounded to bf16 (2^-9 each, relative), 2.3e-3 of the output's norm; twice that per 64
+rows of a head."""
 import math
 
 import pytest
@@ -87,3 +88,31 @@ def test_sparse_scales_with_v(D, name, H, nb, block, climb):
         o = torch.empty_like(q)
         ra.rapid_attn_block_sparse(q, k, (v.double() * 2.0 ** power).to(torch.bfloat16), o, mask, block)
         check(o, ref, power, f"{name} D={D}")
+
+
+def without_finite_start(q, k, keys):
+    """The first `keys` keys score -inf for every query (their products leave fp32), the others are ordinary."""
+    q[..., 1] = 2.0 ** 80
+    k[..., 1] = 0.0
+    k[:, :, :keys, 1] = -(2.0 ** 80)
+
+
+@pytest.mark.parametrize("keys", [32, 40])
+@pytest.mark.parametrize("D,plan,H,N", [(D, *p) for D in (64, 128) for p in PLANS[D]])
+def test_dense_first_keys_at_minus_infinity(D, plan, H, N, keys):
+    _, q, k, v = inputs(H, N, D, 7 + D)
+    without_finite_start(q, k, keys)
+    o = torch.empty_like(q)
+    ra.rapid_attn_dense(q, k, v, o)
+    check(o, attention(q, k, v), 0, f"{plan} D={D}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("name,H,nb,block", SPARSE)
+def test_sparse_first_keys_at_minus_infinity(D, name, H, nb, block):
+    g, q, k, v = inputs(H, nb * block, D, 8 + D)
+    without_finite_start(q, k, 40)
+    mask = mask_of(g, H, nb)
+    o = torch.empty_like(q)
+    ra.rapid_attn_block_sparse(q, k, v, o, mask, block)
+    check(o, attention(q, k, v, mask, block), 0, f"{name} D={D}")
