@@ -24,9 +24,10 @@
  * Arithmetic: bf16 inputs, bf16 MFMA with fp32 accumulation, fp32 online
  * softmax, probabilities rounded to bf16 before the PV product and the
  * normaliser taken as the fp32 sum of those rounded probabilities, bf16 output.
- * Range of V: |V| from 2^-118 on is summed in normal fp32 numbers (smaller ones in
- * subnormals, down to bf16's own smallest); |V| up to 2^48 cannot overflow whatever the
- * scores, |V| up to 2^126 / N where no score climbs above those of a row's first keys.
+ * Range of V: weights enter the sums as 2^-16 at most where no score lies 2^17 above
+ * those of a row's first keys (2^-24 where one does), so |V| from 2^-110 (2^-102) on is
+ * summed in normal fp32 numbers and keeps bf16's precision down to about 2^-120
+ * (2^-114).  |V| up to 2^48 cannot overflow whatever the scores.
  *
  * Memory: every pointer except `stream` is a DEVICE pointer owned by the
  * caller.  Q, K, V, O are bf16 [B, H, N, D] contiguous, D fastest.  Q/K/V/mask

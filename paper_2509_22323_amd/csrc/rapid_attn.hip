@@ -1126,7 +1126,7 @@ struct StreamRegs {
     unsigned kc, kn, vc;                       // offsets of a step outside the unrolled loop
 };
 
-constexpr float REF_UP = 8.f;
+constexpr float REF_UP = 16.f, REF_UP_AGAIN = 24.f;    // see soft_close
 constexpr float REF_LOWEST = -1e30f;           // of a query whose first step has no finite score
 
 // Lane addresses in a K tile at byte address k0 and a V tile at v0.
@@ -1304,15 +1304,43 @@ __device__ __forceinline__ float step_max(const Scores<S>& st, int q, float c)
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1])) * c;
 }
 
-// Range of the exponents.  The reference m of a query is the maximum of its first step plus REF_UP, so
-// that probabilities of 2 and more mean a later maximum more than 9 above the first.  Such a value
-// has the top bit of its bf16 exponent set, which the or over all packed words shows; only then the
-// references move up to the step's maximum (plus REF_UP), the sums and the accumulators are rescaled
-// and the step's probabilities are made again.  What lies 2^118 below a row's reference is lost.
-// REF_UP is small because the accumulators hold V times these weights, at most 2^-8 in an ordinary row: V of 2^-118
-// is still summed in normal numbers (with 60 in its place everything below 2^-89 came out as 0), and at the top
-// |V| up to 2^126 / number of keys.  The exact test for 2^8 that needs no REF_UP (a maximum over the packed words,
-// v_pk_maximum3_f16, in place of the or) costs 1.5 % of a dense call.
+// Range of the exponents.  The reference m of a query is the maximum of its first step plus REF_UP, so that
+// probabilities of 2 and more mean a later maximum more than 17 above the first.  Such a value has the top bit of its
+// bf16 exponent set, which the or over all packed words shows; only then the references of that group of queries move
+// up to the step's maximum (plus REF_UP_AGAIN), the sums and the accumulators are rescaled and the step's
+// probabilities are made again.  What lies 2^110 below a row's first maximum (2^102 below a later one) is lost.
+// How far up: the accumulators hold V times these weights, at most 2^-16 in an ordinary row, so V of 2^-110 is summed
+// in normal numbers and smaller ones in subnormals with the precision of bf16 down to 2^-122 (with 60 in its place
+// everything below 2^-89 came out as 0); each step less makes peaked rows move more often.  us, dense, D = 128 (1, 24,
+// 4608) / D = 64 (2, 24, 4480), scores of standard deviation 1, 4, 16: 60 and 60 up 211 214 213 / 227 228 230; 8 and 8,
+// all groups moved at once 212 228 272 / 226 256 344; 16 and 24 212 217 242 / 228 234 271; the 32x32x16 kernels before
+// 235 245 253 / 269 274 275.  A test for 2^8 that needs no offset (a maximum over the packed words,
+// v_pk_maximum3_f16, in place of the or) costs every dense call 1.5 %.
+
+// Whether group q is among those.
+template <class S>
+__device__ __forceinline__ bool group_out(const Probs<S>& p, int q)
+{
+    const unsigned w = p.q[q][0] | p.q[q][1] | p.q[q][2] | p.q[q][3];
+    return __builtin_amdgcn_ballot_w64((w & 0x40004000u) != 0u) != 0ull;
+}
+// The step's probabilities of those groups again.
+template <class S, int D, int Q = 0, int I = 0>
+__device__ __forceinline__ void soft_group(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
+{
+    if constexpr (I < 16) {
+        soft_part<S, D, I / 8, 2 * Q + I / 4 % 2, I % 4>(x, st, c, p);
+        soft_group<S, D, Q, I + 1>(x, st, c, p);
+    }
+}
+template <class S, int D, int Q = 0>
+__device__ __forceinline__ void soft_groups(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
+{
+    if constexpr (Q < S::NQ) {
+        if (group_out<S>(p, Q)) soft_group<S, D, Q>(x, st, c, p);
+        soft_groups<S, D, Q + 1>(x, st, c, p);
+    }
+}
 template <class S, int D>
 __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>& st, float c, Probs<S>& p)
 {
@@ -1320,10 +1348,13 @@ __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>&
     if (__builtin_expect(out != 0ull, 0)) {
 #pragma unroll
         for (int q = 0; q < S::NQ; ++q) {
-            const float m = fmaxf(x.m[q], step_max<S>(st, q, c) + REF_UP);
-            const float alpha = __builtin_amdgcn_exp2f(x.m[q] - m);
-            x.m[q] = m;
-            asm volatile("" : "+v"(x.m[q]));      // in place
+            float alpha = 1.f;
+            if (group_out<S>(p, q)) {
+                const float m = fmaxf(x.m[q], step_max<S>(st, q, c) + REF_UP_AGAIN);
+                alpha = __builtin_amdgcn_exp2f(x.m[q] - m);
+                x.m[q] = m;
+            }
+            asm volatile("" : "+v"(x.m[q]), "+v"(alpha));
             x.ls[q] *= alpha;
 #pragma unroll
             for (int b = 0; b < S::DT; ++b)
@@ -1334,9 +1365,7 @@ __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>&
         asm volatile("" : "+s"(out));
     }
     if (__builtin_expect(out != 0ull, 0)) {       // (in a block of its own: together they need a second set of accumulators)
-        x.seen = 0u;
-        soft_half<S, D, 0>(x, st, c, p);
-        soft_half<S, D, 1>(x, st, c, p);
+        soft_groups<S, D>(x, st, c, p);
         x.seen = 0u;
     }
 }

@@ -49,7 +49,7 @@ def test_dense_plan_at_odd_lengths(D, plan, H, N, kv):
 
 @pytest.mark.parametrize("D,plan,H,N", [(D, *p) for D in (64, 128) for p in PLANS[D]])
 def test_reference_of_the_exponents_moves(D, plan, H, N):
-    """Scores that climb by more than 61 (base 2) above a row's first keys, twice, at keys that lie in the
+    """Scores that climb by 72 (base 2) above a row's first keys, twice, at keys that lie in the
     first and in the second half of a step, and a row whose first keys are the largest by far."""
     g = torch.Generator(device="cuda").manual_seed(17 + D)
     q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))

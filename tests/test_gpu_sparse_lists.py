@@ -64,7 +64,7 @@ def test_every_list_length_and_odd_tails(D, block, cut):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("block", [64, 128])
 def test_reference_of_the_exponents_moves(D, block):
-    """Scores that climb by more than 61 (base 2) above a row's first keys, inside a block, in a later block
+    """Scores that climb by 72 (base 2) above a row's first keys, inside a block, in a later block
     and in another piece of a split row, and rows whose first keys are the largest by far."""
     nb, H = 40, 2
     N = nb * block
