@@ -661,8 +661,9 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
     // global_load_lds_dwordx4: LDS address = M0 + 16 * lane.  Written as assembly so that the
     // copy pipeline is ordered only by the explicit vmcnt waits and barriers of the main loop
     // (the compiler would otherwise wait for all copies before LDS reads it cannot
-    // disambiguate).  M0 has no other user in these kernels; a copy may not be the next instruction after the
-    // scalar write of M0 (one wait state), and the compiler adds none inside an assembly statement.
+    // disambiguate).  M0 has no other user in these kernels.  A copy may not be the next instruction after the scalar
+    // write of M0 (one wait state) and the compiler does not look into assembly for that: s_nop 0.  M0 is an operand,
+    // so the compiler adds up the address in it: with s_mov of a sum made elsewhere the s_nop cost 1 % at 64-token masks.
     if (key0 + KT <= kv_len) {
         // whole tile valid: scalar tile base + a per-lane byte offset that does not depend
         // on the tile (no vector arithmetic per copy)
@@ -674,7 +675,7 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
             const int logical = (lane % G::CPR) ^ (IS_V ? G::swz_v(row) : G::swz_k(row));
             const unsigned off = (unsigned)row * src.row_bytes + (unsigned)logical * 16u;
             const unsigned dst = (unsigned)(size_t)LDS_PTR(char, lds + ld * 1024);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(tile));
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(dst), "v"(off), "s"(tile));
         }
     } else {
 #pragma unroll
@@ -686,7 +687,7 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
             grow = grow < kv_len ? grow : kv_len - 1;
             const char* g = (key0 < src.n0 ? src.base0 : src.base1) + (size_t)grow * src.row_bytes + logical * 16;
             const unsigned dst = (unsigned)(size_t)LDS_PTR(char, lds + ld * 1024);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(g));
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(dst), "v"(g));
         }
     }
 }
@@ -724,7 +725,7 @@ __device__ __forceinline__ unsigned copy_offset(unsigned row_bytes, int ld, int 
 __device__ __forceinline__ void copy_1k(const TileBuffer& b, unsigned off, unsigned dst)
 {
     const i32x4 rsrc = {(int)b.lo, (int)b.hi, (int)b.bytes, 0x00020000};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc));
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(dst), "v"(off), "s"(rsrc));
 }
 
 struct SoftmaxState {
