@@ -658,36 +658,45 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
 {
     typedef Geo<D> G;
     constexpr int PER_WAVE = G::LOADS / NW;
-    // global_load_lds_dwordx4: LDS address = M0 + 16 * lane.  Written as assembly so that the
-    // copy pipeline is ordered only by the explicit vmcnt waits and barriers of the main loop
-    // (the compiler would otherwise wait for all copies before LDS reads it cannot
-    // disambiguate).  M0 has no other user in these kernels.  A copy may not be the next instruction after the scalar
-    // write of M0 (one wait state) and the compiler does not look into assembly for that: s_nop 0.  M0 is an operand,
-    // so the compiler adds up the address in it: with s_mov of a sum made elsewhere the s_nop cost 1 % at 64-token masks.
+    // global_load_lds_dwordx4: LDS address = M0 + offset + 16 * lane, memory address + the same offset.  Written as
+    // assembly so that the copy pipeline is ordered only by the explicit vmcnt waits and barriers of the main loop
+    // (the compiler would otherwise wait for all copies before LDS reads it cannot disambiguate).  M0 has no other
+    // user in these kernels.  A copy may not be the next instruction after the scalar write of M0 (one wait state)
+    // and the compiler does not look into assembly for that: s_nop 0.  At D = 64 two copies share an M0 (one s_nop
+    // each cost calls under 64-token masks 1 to 1.4 %); at D = 128 each has its own (two or four behind one M0 cost 2
+    // and 3 %, the s_nop at most 0.7 %).
+    constexpr int STEP = D == 64 ? 2 : 1;
+    static_assert(PER_WAVE % STEP == 0, "");
+    const int ld0 = wave * PER_WAVE;                        // wave-uniform
+    auto row_of = [&](int i) { return (ld0 + i) * G::ROWS_PER_LOAD + lane / G::CPR; };
+    auto chunk_of = [&](int i) { return (unsigned)((lane % G::CPR) ^ (IS_V ? G::swz_v(row_of(i)) : G::swz_k(row_of(i)))) * 16u; };
+    auto dst = [&](int i) { return (unsigned)(size_t)LDS_PTR(char, lds + (ld0 + i) * 1024); };
     if (key0 + KT <= kv_len) {
         // whole tile valid: scalar tile base + a per-lane byte offset that does not depend
         // on the tile (no vector arithmetic per copy)
         const char* tile = src.row(key0);                  // a tile never straddles the segments
+        auto off = [&](int i) { return (unsigned)row_of(i) * src.row_bytes + chunk_of(i); };
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; ++i) {
-            const int ld = wave * PER_WAVE + i;             // wave-uniform
-            const int row = ld * G::ROWS_PER_LOAD + lane / G::CPR;
-            const int logical = (lane % G::CPR) ^ (IS_V ? G::swz_v(row) : G::swz_k(row));
-            const unsigned off = (unsigned)row * src.row_bytes + (unsigned)logical * 16u;
-            const unsigned dst = (unsigned)(size_t)LDS_PTR(char, lds + ld * 1024);
-            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(dst), "v"(off), "s"(tile));
+        for (int i = 0; i < PER_WAVE; i += STEP) {
+            if constexpr (STEP == 1)
+                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(dst(i)), "v"(off(i)), "s"(tile));
+            else                                           // (8 rows further on: the difference is not negative)
+                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
+                             ::"{m0}"(dst(i)), "v"(off(i)), "v"(off(i + 1) - 1024u), "s"(tile));
         }
     } else {
-#pragma unroll
-        for (int i = 0; i < PER_WAVE; ++i) {
-            const int ld = wave * PER_WAVE + i;
-            const int row = ld * G::ROWS_PER_LOAD + lane / G::CPR;
-            const int logical = (lane % G::CPR) ^ (IS_V ? G::swz_v(row) : G::swz_k(row));
-            int grow = key0 + row;
+        auto at = [&](int i) {
+            int grow = key0 + row_of(i);
             grow = grow < kv_len ? grow : kv_len - 1;
-            const char* g = (key0 < src.n0 ? src.base0 : src.base1) + (size_t)grow * src.row_bytes + logical * 16;
-            const unsigned dst = (unsigned)(size_t)LDS_PTR(char, lds + ld * 1024);
-            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(dst), "v"(g));
+            return (key0 < src.n0 ? src.base0 : src.base1) + (size_t)grow * src.row_bytes + chunk_of(i);
+        };
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; i += STEP) {
+            if constexpr (STEP == 1)
+                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(dst(i)), "v"(at(i)));
+            else
+                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\tglobal_load_lds_dwordx4 %2, off offset:1024"
+                             ::"{m0}"(dst(i)), "v"(at(i)), "v"(at(i + 1) - 1024));
         }
     }
 }
@@ -723,7 +732,7 @@ __device__ __forceinline__ unsigned copy_offset(unsigned row_bytes, int ld, int 
     return (unsigned)row * row_bytes + (unsigned)logical * 16u;
 }
 __device__ __forceinline__ void copy_1k(const TileBuffer& b, unsigned off, unsigned dst)
-{
+{                                                          // (s_nop: see issue_tile)
     const i32x4 rsrc = {(int)b.lo, (int)b.hi, (int)b.bytes, 0x00020000};
     asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(dst), "v"(off), "s"(rsrc));
 }
