@@ -652,7 +652,8 @@ struct Geo {
 // Issue the asynchronous copy of rows key0..key0+63 of `src` into an LDS tile.  Rows at or
 // beyond kv_len are replaced by row kv_len-1 (finite data; their probabilities are exactly
 // 0, and their scores are overwritten with -inf, so they never contribute).
-template <int D, int NW, bool IS_V>
+// PER_M0: copies behind one write of M0.
+template <int D, int NW, bool IS_V, int PER_M0 = 1>
 __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len,
                                            char* lds, int wave, int lane)
 {
@@ -662,11 +663,10 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
     // assembly so that the copy pipeline is ordered only by the explicit vmcnt waits and barriers of the main loop
     // (the compiler would otherwise wait for all copies before LDS reads it cannot disambiguate).  M0 has no other
     // user in these kernels.  A copy may not be the next instruction after the scalar write of M0 (one wait state)
-    // and the compiler does not look into assembly for that: s_nop 0.  At D = 64 two copies share an M0 (one s_nop
-    // each cost calls under 64-token masks 1 to 1.4 %); at D = 128 each has its own (two or four behind one M0 cost 2
-    // and 3 %, the s_nop at most 0.7 %).
-    constexpr int STEP = D == 64 ? 2 : 1;
-    static_assert(PER_WAVE % STEP == 0, "");
+    // and the compiler does not look into assembly for that: s_nop 0.  Under 64-token masks at D = 64 two copies share
+    // an M0 (one s_nop each cost those calls 1 to 1.4 %); elsewhere each has its own (two or four behind one M0 cost 2
+    // and 3 % at D = 128 and 0.7 % in the short records of 128-token masks, the s_nop under 1 %).
+    static_assert(PER_WAVE % PER_M0 == 0 && (PER_M0 == 1 || PER_M0 == 2), "");
     const int ld0 = wave * PER_WAVE;                        // wave-uniform
     auto row_of = [&](int i) { return (ld0 + i) * G::ROWS_PER_LOAD + lane / G::CPR; };
     auto chunk_of = [&](int i) { return (unsigned)((lane % G::CPR) ^ (IS_V ? G::swz_v(row_of(i)) : G::swz_k(row_of(i)))) * 16u; };
@@ -677,8 +677,8 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
         const char* tile = src.row(key0);                  // a tile never straddles the segments
         auto off = [&](int i) { return (unsigned)row_of(i) * src.row_bytes + chunk_of(i); };
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; i += STEP) {
-            if constexpr (STEP == 1)
+        for (int i = 0; i < PER_WAVE; i += PER_M0) {
+            if constexpr (PER_M0 == 1)
                 asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(dst(i)), "v"(off(i)), "s"(tile));
             else                                           // (8 rows further on: the difference is not negative)
                 asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
@@ -691,8 +691,8 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
             return (key0 < src.n0 ? src.base0 : src.base1) + (size_t)grow * src.row_bytes + chunk_of(i);
         };
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; i += STEP) {
-            if constexpr (STEP == 1)
+        for (int i = 0; i < PER_WAVE; i += PER_M0) {
+            if constexpr (PER_M0 == 1)
                 asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(dst(i)), "v"(at(i)));
             else
                 asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\tglobal_load_lds_dwordx4 %2, off offset:1024"
@@ -1970,6 +1970,7 @@ __global__ __launch_bounds__(128 * WPG, (D == 64 ? (WPG == 4 ? 4 : 2) : 1)) void
     constexpr int PD = 6;
     typedef TileItems<D, PD> TI;
     constexpr int NW = 2 * WPG, QT = 32 * WPG, KS = D / 16, DB = D / 32;
+    constexpr int PER_M0 = D == 64 ? 2 : 1;       // see issue_tile
     constexpr int NSK = 4, NSV = 5;
     constexpr int LPT = 2 * G::LOADS / NW;        // copy instructions per wavefront per slot (K + V)
     static_assert(WPG * DB * 16 * 64 * 4 + WPG * 64 * 8 <= (NSK + NSV) * G::TILE_BYTES, "merge buffer fits the rings");
@@ -2035,10 +2036,10 @@ __global__ __launch_bounds__(128 * WPG, (D == 64 ? (WPG == 4 ? 4 : 2) : 1)) void
     // prologue: K_0..K_2, V_0, V_1
 #pragma unroll
     for (int t = 0; t < 3; ++t)
-        if (t < T) issue_tile<D, NW, false>(K, kq[t], kv_len, k_stage(t), wave, lane);
+        if (t < T) issue_tile<D, NW, false, PER_M0>(K, kq[t], kv_len, k_stage(t), wave, lane);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
-        if (t < T) issue_tile<D, NW, true>(V, kq[t], kv_len, lds + (NSK + t) * G::TILE_BYTES, wave, lane);
+        if (t < T) issue_tile<D, NW, true, PER_M0>(V, kq[t], kv_len, lds + (NSK + t) * G::TILE_BYTES, wave, lane);
 
     bf16x8 qf[KS];
     load_q<D>(Q, qrow, qvalid, h, qf);
@@ -2052,8 +2053,8 @@ __global__ __launch_bounds__(128 * WPG, (D == 64 ? (WPG == 4 ? 4 : 2) : 1)) void
 
     int s = 0;                                    // current slot = slot barriers passed
     auto slot_begin = [&]() {                     // my share of K_{s+3} and V_{s+2}
-        if (s + 3 < T) issue_tile<D, NW, false>(K, kq[3], kv_len, k_stage(s + 3), wave, lane);
-        if (s + 2 < T) issue_tile<D, NW, true>(V, kq[2], kv_len, lds + (NSK + vst_issue) * G::TILE_BYTES, wave, lane);
+        if (s + 3 < T) issue_tile<D, NW, false, PER_M0>(K, kq[3], kv_len, k_stage(s + 3), wave, lane);
+        if (s + 2 < T) issue_tile<D, NW, true, PER_M0>(V, kq[2], kv_len, lds + (NSK + vst_issue) * G::TILE_BYTES, wave, lane);
     };
     auto slot_end = [&]() {                       // K_{s+1} and V_s complete, then the barrier
         if (s + 3 < T) wait_vmcnt<2 * LPT>();
