@@ -2677,8 +2677,11 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
         // D = 64: 64 queries per wavefront read LDS half as often, but a record takes longer; it wins where every place
         // of the chip (four per CU) gets at least two records.  us, 32 / 64 queries per wavefront, H = 24, densities 0.15 to 1:
         // 3072 rows (B = 8, N = 2048) 87 / 84 to 218 / 208; 6720 (B = 8, N = 4480) 267 / 267 to 973 / 939; 1536 rows
-        // (B = 8, N = 1024) 41 / 42 to 67 / 74; 840 rows of N = 896 26.4 / 29.7.
-        if (D == 64 && rows > 2 * 4 * XCDS * CUS_PER_XCD) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
+        // (B = 8, N = 1024) 41 / 42 to 67 / 74; 840 rows of N = 896 26.4 / 29.7.  Rows of one or two kept blocks are all
+        // fixed cost, of which two wavefronts hide less than four: density 0.1, B = 8, H = 38, N = 896 36.5 / 38.3, 1152
+        // 46.8 / 47.2, 1408 55.4 / 56.2 (0.3: 80.7 / 79.4; 1.0: 184 / 171), so not at 8 blocks per side and fewer; a mask of
+        // the diagonal alone, which the host cannot tell, is 7 % slower on it at any N (B = 4, H = 24, N = 4480 46.1 / 49.5).
+        if (D == 64 && rows > 2 * 4 * XCDS * CUS_PER_XCD && nb > 8) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
         else if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(SparsePlan<128>::P::NW * 64), 0, s, p);
     } else {
