@@ -2593,11 +2593,20 @@ int run_dense(const Problem& pr, void* stream)
     fill_common(p, pr);
     hipStream_t s = (hipStream_t)stream;
     const long long pairs = (long long)pr.B * pr.H, small = pairs * ((pr.N + 31) / 32);
-    // All 32-query workgroups resident at once: the shortest chain of steps per wavefront wins (D = 64 / 128,
-    // this kernel against the other: B = 1, H = 24, N = 512: 9.3 / 11.1 us at B = 2 and 11.0 / 11.8 us; H = 2,
-    // N = 256: 5.2 / 6.5 and 6.8 / 9.0 us).  At D = 128 its 16-query wavefronts read K and V from LDS twice as
-    // often per product and it loses on long sequences (H = 2, N = 8192: 93 / 79 us; D = 64: 55 / 57 us).
-    if (small <= (pr.D == 64 ? 4 : 2) * XCDS * CUS_PER_XCD && (pr.D == 64 || pr.N <= 1024)) {
+    const long long items = pairs * ((pr.N + DENSE_QT - 1) / DENSE_QT), chunk = (items + XCDS - 1) / XCDS;
+    // 32 queries per workgroup: while they are resident at once the shortest chain of steps per wavefront wins, as long
+    // as the other kernel has too few queries per workgroup to choose from.  us, this kernel / the other, H heads, B = 1:
+    //   N <= 64: three quarters of 256 queries do not exist (B = 64, H = 38, N = 64: 20.0 / 31.6 at D = 64, 45 / 61 at 128)
+    //   D = 64: N = 1024, H = 24 15.0 / 15.3; 2048, 12 23.5 / 23.6; past three quarters of the 1024 places the quarters of
+    //     the other win: 1152, 24 19.4 / 16.1; 2048, 16 29.6 / 25.0; so they do over many keys: 16384, 1 110 / 108
+    //   D = 64 again just above one place per quarter on the other (17 to 19 items of an XCD): 1361, 24 27.1 / 27.9;
+    //     1024, 38 22.2 / 23.5; 1792, 24 (21 items) 36.8 / 34.5
+    //   D = 128: N = 640, H = 24 13.3 / 15.6; its 16-query wavefronts read K and V from LDS twice as often per product and
+    //     it loses on long sequences: 8192, 2 93 / 79
+    const bool short_chain = pr.N <= 64 ||
+        (pr.D == 64 ? (small <= 768 && pr.kv_len <= 8192) || (small <= 1216 && chunk > CUS_PER_XCD / 2 && pr.N <= 2048)
+                    : small <= 2 * XCDS * CUS_PER_XCD && pr.N <= 1024);
+    if (short_chain) {
         p.nq = (pr.N + 31) / 32;
         p.items = (int)small;
         p.chunk = (p.items + XCDS - 1) / XCDS;
@@ -2607,17 +2616,20 @@ int run_dense(const Problem& pr, void* stream)
         return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
     }
     p.nq = (pr.N + DENSE_QT - 1) / DENSE_QT;
-    const long long items = pairs * p.nq;
     if (items > 0x7fffffffLL / 8) return RAPID_ERR_SHAPE;
     p.items = (int)items;
-    p.chunk = (p.items + XCDS - 1) / XCDS;
+    p.chunk = (int)chunk;
     // What is left over after every CU of an XCD got the same number of items is cut so that it still makes
     // one workgroup per CU at most: a last round of an eighth of the CUs takes a quarter of the time.  us, items of an
     // XCD: 33 (H = 24, N = 2816) whole 136, in 2 116, in 4 105 at D = 128, 81 / 60 / 55 at D = 64; 198 (N = 16896)
     // 2875 / 2734 / 2703; 108 (B = 2, N = 4429, D = 64) 257 / 231 / 257.  More than half of a round stays whole: 54
     // items (N = 4608) 218 / 247 / 255.
-    const int rest = p.chunk % CUS_PER_XCD;
-    p.cut = rest * 4 <= CUS_PER_XCD ? 4 : rest * 2 <= CUS_PER_XCD ? 2 : 1;
+    // D = 64, no full round: two workgroups share a CU, so quarters fill it up to 16 items and win up to 24, halves up to
+    // 32.  us, whole / 2 / 4, H = 24: N = 1152 (14 items) - / 18.3 / 16.1; 1792 (21) 36.0 / 35.1 / 34.5; 2048 (24) 40.2 /
+    // 38.9 / 38.9; 2304 (27) 44.4 / 43.1 / 49.5; 2560 (30) 48.7 / 48.1 / 55.3.
+    const bool one_round = pr.D == 64 && p.chunk <= CUS_PER_XCD;
+    const int rest = one_round ? p.chunk : p.chunk % CUS_PER_XCD;
+    p.cut = one_round ? (rest <= 24 ? 4 : 2) : rest * 4 <= CUS_PER_XCD ? 4 : rest * 2 <= CUS_PER_XCD ? 2 : 1;
     p.whole = p.cut == 1 ? p.chunk : p.chunk - rest;
     const dim3 grid((unsigned)(p.whole + (p.chunk - p.whole) * p.cut) * XCDS);
     if (pr.D == 64) hipLaunchKernelGGL((attn_dense_stream_kernel<64>), grid, dim3(DensePlan<64>::Whole::NW * 64), 0, s, p);
