@@ -731,10 +731,17 @@ __device__ __forceinline__ unsigned copy_offset(unsigned row_bytes, int ld, int 
     const int logical = (lane % G::CPR) ^ (IS_V ? G::swz_v(row) : G::swz_k(row));
     return (unsigned)row * row_bytes + (unsigned)logical * 16u;
 }
+// One copy, or two whose second KB is in the next KB of the stage, behind one write of M0 (see issue_tile).
 __device__ __forceinline__ void copy_1k(const TileBuffer& b, unsigned off, unsigned dst)
-{                                                          // (s_nop: see issue_tile)
+{
     const i32x4 rsrc = {(int)b.lo, (int)b.hi, (int)b.bytes, 0x00020000};
     asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(dst), "v"(off), "s"(rsrc));
+}
+__device__ __forceinline__ void copy_2k(const TileBuffer& b, unsigned off, unsigned off_next, unsigned dst)
+{
+    const i32x4 rsrc = {(int)b.lo, (int)b.hi, (int)b.bytes, 0x00020000};
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\tbuffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
+                 ::"{m0}"(dst), "v"(off), "v"(off_next - 1024u), "s"(rsrc));    // (a row is at least D elements: not negative)
 }
 
 struct SoftmaxState {
@@ -1603,7 +1610,10 @@ struct StreamPlan {
     static constexpr int LDS = (NSK + NSV) * TILE;
     static constexpr int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
     static constexpr int UNROLL = NSK / gcd(NSK, NSV) * NSV * SPT;    // steps after which both rings are back at stage 0
-    static_assert(LC * NW * 1024 == TILE && (WK == 1 || SPT == 1) && NSK >= 2 && NSV >= 3, "");
+    // Copies behind one write of M0.  Two: dense D = 64 0.5 to 3 % (most where items are cut), others up to 0.3 %; in the
+    // short rings of the small kernel they are 0.5 (D = 64) to 2.5 % slower than copies spread out singly.
+    static constexpr int PER_M0 = NSK >= 4 ? 2 : 1;
+    static_assert(LC % PER_M0 == 0 && LC * NW * 1024 == TILE && (WK == 1 || SPT == 1) && NSK >= 2 && NSV >= 3, "");
     static constexpr int KLEAD = SPT == 1 ? NSK + 1 : NSK, VLEAD = NSV - 1;    // tiles ahead of t that are copied at its barrier
     // copy instructions that may still be on their way at a barrier
     static constexpr int min(int a, int b) { return a < b ? a : b; }
@@ -1684,8 +1694,12 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     }
     const unsigned lds0 = (unsigned)(size_t)LDS_PTR(char, lds);
     const unsigned dst0 = lds0 + (unsigned)(wave * LC) * 1024u;
-    auto copy_k = [&](const TileBuffer& b, int e, unsigned stage) { copy_1k(b, koff[e], dst0 + stage + e * 1024); };
-    auto copy_v = [&](const TileBuffer& b, int e, unsigned stage) { copy_1k(b, voff[e], dst0 + VBASE + stage + e * 1024); };
+    auto copy = [&](const TileBuffer& b, const unsigned (&off)[LC], int e, unsigned dst) {
+        if constexpr (P::PER_M0 == 1) copy_1k(b, off[e], dst);
+        else if (e % 2 == 0) copy_2k(b, off[e], off[e + 1], dst);
+    };
+    auto copy_k = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, koff, e, dst0 + stage + e * 1024); };
+    auto copy_v = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, voff, e, dst0 + VBASE + stage + e * 1024); };
     // what the barriers before tile 0 would have issued
 #pragma unroll
     for (int b = -P::KLEAD; b < (P::SPT == 1 ? -1 : 0); ++b) {
