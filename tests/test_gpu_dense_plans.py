@@ -64,3 +64,28 @@ def test_reference_of_the_exponents_moves(D, plan, H, N):
     o = torch.empty_like(q)
     ra.rapid_attn_dense(q, k, v, o)
     check(o, reference(q, k, v, N, D ** -0.5), N, f"{plan} D={D}")
+
+
+@pytest.mark.parametrize("D,plan,H,N", [(D, *p) for D in (64, 128) for p in PLANS[D]])
+def test_dense_plan_on_joint_tensors_with_lengths(D, plan, H, N):
+    """The same plans on fused projections, image and text apart, with a length per sample: full, a short prompt,
+    none, inside the image."""
+    pairs = H
+    B = next(b for b in (4, 3, 2, 1) if pairs % b == 0)
+    H = pairs // B
+    n0 = (N - 1) // 128 * 128
+    if n0 == 0:
+        n0 = N
+    lens = [N, min(n0 + 5, N), 0, n0 // 3][:B]
+    g = torch.Generator(device="cuda").manual_seed(D + N)
+    tokens = [n for n in (n0, N - n0) if n]
+    fused = [torch.randn((B, n, 3, H, D), generator=g, device="cuda", dtype=torch.bfloat16) for n in tokens]
+    segs = [tuple(f[:, :, i].transpose(1, 2) for i in range(3)) + (torch.full((B, n, H, D), 7.0, device="cuda", dtype=torch.bfloat16).transpose(1, 2),)
+            for f, n in zip(fused, tokens)]
+    ra.rapid_attn_joint(segs, kv_lens=torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    q, k, v, o = (torch.cat([s[i] for s in segs], 2) for i in range(4))
+    for b, kv in enumerate(lens):
+        if kv == 0:
+            assert (o[b] == 0).all(), plan
+        else:
+            check(o[b:b + 1], reference(q[b:b + 1], k[b:b + 1], v[b:b + 1], kv, D ** -0.5), kv, f"{plan} D={D} sample {b}")

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import paper_2509_22323_amd as ra
+from test_gpu_parity import check_plan, read_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +82,116 @@ def test_reference_of_the_exponents_moves(D, block):
     mask[:, :, 5::9] = 1
     o = sparse(q, k, v, mask, block, N)
     check(o, reference(q, k, v, mask, block, N, D ** -0.5), N, f"D={D} block={block}")
+
+
+# ---- D = 64, 128-token masks, more than 2048 rows of more than 8 blocks: 64 queries per wavefront
+MANY = 96                                          # heads
+
+
+@pytest.mark.parametrize("cut", [0, 1, 31, 32, 33, 63, 64, 65, 127])
+def test_many_rows_every_list_length_and_odd_tails(cut):
+    D, block, nb = 64, 128, 24
+    N = nb * block
+    kv = N - cut
+    g = torch.Generator(device="cuda").manual_seed(cut)
+    q, k, v = (torch.randn((1, MANY, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    for t in (q, k, v):
+        t[:, :, kv:] = float("nan")
+    rank = torch.rand((1, MANY, nb, nb), generator=g, device="cuda").argsort(-1).argsort(-1)
+    length = (torch.arange(nb, device="cuda").view(1, 1, nb, 1) + torch.arange(MANY, device="cuda").view(1, MANY, 1, 1)) % (nb + 1)
+    mask = (rank < length).to(torch.uint8)
+    o = sparse(q, k, v, mask, block, kv)
+    assert torch.equal(o.view(torch.int16), sparse(q, k, v, mask, block, kv).view(torch.int16))
+    check(o, reference(q, k, v, mask, block, kv, D ** -0.5), kv, f"kv={kv}")
+
+
+@pytest.mark.parametrize("nb", [8, 9])
+def test_many_rows_on_either_side_of_the_rule(nb):
+    D, block, H = 64, 128, 272                     # 2176 and 2448 rows
+    N = nb * block
+    g = torch.Generator(device="cuda").manual_seed(nb)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = (torch.rand((1, H, nb, nb), generator=g, device="cuda") < 0.3).to(torch.uint8)
+    o = sparse(q, k, v, mask, block, N - 9)
+    check(o, reference(q, k, v, mask, block, N - 9, D ** -0.5), N - 9, f"nb={nb}")
+
+
+def test_many_rows_references_of_the_exponents_move():
+    D, block, nb = 64, 128, 24
+    N = nb * block
+    g = torch.Generator(device="cuda").manual_seed(18)
+    q, k, v = (torch.randn((1, MANY, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    q[..., 0] = 8.0
+    q[:, :, 1::7, 0] = -8.0
+    k[..., 0] = 0.0
+    for i, at in enumerate((70, 150, N // 2 + 211)):
+        k[:, :, at:, 0] = (i + 1) * 50.0 * math.sqrt(D) / 8.0
+    mask = (torch.rand((1, MANY, nb, nb), generator=g, device="cuda") < 0.3).to(torch.uint8)
+    mask[:, :, :, 0] = 1
+    o = sparse(q, k, v, mask, block, N)
+    check(o, reference(q, k, v, mask, block, N, D ** -0.5), N, "moving")
+
+
+@pytest.mark.parametrize("climb", [False, True])
+def test_many_rows_with_long_ones_cut_into_pieces(climb):
+    """A few full rows among rows of one to four blocks: the plan cuts the full ones; every piece count,
+    the merge of pieces whose references differ by up to 216 (base 2), and an odd last block."""
+    D, block, nb, H = 64, 128, 260, 8
+    N = nb * block
+    kv = N - 37
+    g = torch.Generator(device="cuda").manual_seed(21)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    if climb:
+        q[..., 0] = 8.0
+        q[:, :, 1::7, 0] = -8.0
+        k[..., 0] = 0.0
+        for i, at in enumerate((70, N // 3 + 5, N // 2 + 211)):
+            k[:, :, at:, 0] = (i + 1) * 50.0 * math.sqrt(D) / 8.0
+    mask = torch.zeros((1, H, nb, nb), dtype=torch.uint8, device="cuda")
+    mask.diagonal(dim1=2, dim2=3).fill_(1)
+    mask |= (torch.rand((1, H, nb, nb), generator=g, device="cuda") < 1.0 / nb).to(torch.uint8)
+    full = {h: [3, 100 + h, nb - 1] for h in range(H)}
+    for h, rows in full.items():
+        for i, r in enumerate(rows):               # all of it, a third, all but the first blocks
+            mask[0, h, r] = 1
+            if i == 1:
+                mask[0, h, r, nb // 3:] = 0
+            if i == 2:
+                mask[0, h, r, :40 + h] = 0
+    ws = torch.zeros(ra.rapid_attn_workspace_bytes(1, H, N, D, block), dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, 7.0)
+    ra.rapid_attn_block_sparse(q, k, v, o, mask, block, kv, workspace=ws)
+    counts, order, _, geometry = read_plan(ws.cpu().numpy(), 1, H, nb, D, block)
+    cut = check_plan(counts, order, geometry, 1, H, nb, block, D)
+    assert {h * nb + r for h, rows in full.items() for r in rows} <= set(cut), sorted(cut)
+    assert (o[:, :, kv:] == 0).all()
+    for h in range(H):
+        for r in full[h] + [0, 1, 50, nb - 2]:
+            a, e = r * block, min((r + 1) * block, kv)
+            keys = mask[0, h, r].bool().repeat_interleave(block)[:kv].nonzero()[:, 0]
+            s = (q[0, h, a:e].float() @ k[0, h, keys].float().t()) * D ** -0.5
+            want = torch.softmax(s, -1) @ v[0, h, keys].float()
+            for i in range(0, e - a, 64):
+                x, y = o[0, h, a + i:min(a + i + 64, e)].float(), want[i:i + 64]
+                assert ((x - y).norm() / y.norm()).item() <= 5e-3, (h, r, i)
+
+
+def test_many_rows_joint_tensors_and_lengths():
+    """Image and text apart, fused projections, per-sample lengths: 2160 rows of 9 blocks."""
+    B, H, D, block, n0, n1 = 4, 60, 64, 128, 1024, 100
+    N, nb = n0 + n1, 9
+    lens = [N, n0 + 5, 0, 300]
+    g = torch.Generator(device="cuda").manual_seed(60)
+    fused = [torch.randn((B, n, 3, H, D), generator=g, device="cuda", dtype=torch.bfloat16) for n in (n0, n1)]
+    segs = [tuple(f[:, :, i].transpose(1, 2) for i in range(3)) + (torch.full((B, n, H, D), 7.0, device="cuda", dtype=torch.bfloat16).transpose(1, 2),)
+            for f, n in zip(fused, (n0, n1))]
+    mask = (torch.rand((B, H, nb, nb), generator=g, device="cuda") < 0.4).to(torch.uint8)
+    ra.rapid_attn_joint(segs, mask, block, kv_lens=torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    q, k, v, o = (torch.cat([s[i] for s in segs], 2) for i in range(4))
+    for b, kv in enumerate(lens):
+        if kv == 0:
+            assert (o[b] == 0).all()
+            continue
+        grown = [torch.nn.functional.pad(t[b:b + 1], (0, 0, 0, nb * block - N)) for t in (q, k, v, o)]
+        ref = reference(*grown[:3], mask[b:b + 1], block, kv, D ** -0.5)
+        check(grown[3], ref, kv, f"sample {b}")

@@ -31,7 +31,8 @@ def usage(tmp_path_factory):
 
 
 WANT = {  # kernel name fragment -> waves per SIMD its launch plan counts on
-    "attn_dense_pp_kernelILi64E": 4, "attn_dense_pp_kernelILi128E": 2,
+    "attn_dense_stream_kernelILi64E": 2, "attn_dense_stream_kernelILi128E": 2,
+    "attn_dense_pp_kernelILi64E": 4, "attn_dense_pp_kernelILi128E": 2, "attn_sparse_wide_kernel": 2,
     "attn_sparse_sg_kernelILi64E": 4, "attn_sparse_sg_kernelILi128E": 2,
     "attn_sparse_pp_kernelILi64ELi2E": 2, "attn_sparse_pp_kernelILi128ELi2E": 1,
 }
@@ -44,6 +45,11 @@ def test_attention_kernels_stay_in_registers(usage, fragment, occupancy):
     u = usage[name[0]]
     assert u["ScratchSize [bytes/lane]"] == 0, u
     assert u["Occupancy [waves/SIMD]"] >= occupancy, u
+
+
+def test_every_attention_kernel_is_listed(usage):
+    found = [k for k in usage if "attn_" in k and "_kernel" in k]
+    assert len(found) == len(WANT), found
 
 
 def test_no_kernel_of_the_library_uses_scratch_memory(usage):
