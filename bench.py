@@ -42,12 +42,18 @@ def source_digest():
     return hashlib.sha256(open(path, "rb").read()).hexdigest()
 
 
-def measured_traffic(workload, D):
+def dense_kernel(w):
+    """The kernel a dense call of this workload runs on (the workloads lie far to either side of the
+    library's own rule, which also looks at the head size and the number of keys)."""
+    return "attn_dense_stream_kernel" if w.B * w.H * -(-w.N // 32) > 1216 else "attn_dense_pp_kernel"
+
+
+def measured_traffic(w):
     """HBM bytes per launch of the dense kernel, from the committed rocprofv3 --pmc summary
     (FETCH_SIZE and WRITE_SIZE runs scaled by a plain copy).  The counters cannot be read from
     inside this process, so the figure comes from a file: it is reported with the file's name and
     only if the file says it was taken from the kernel source that is being run now."""
-    name = f"attn_dense_pp_kernel_{workload}.txt"
+    name = f"{dense_kernel(w)}_{w.name}.txt"
     info = {"file": f"profiles/{name}", "kernel_source_sha256": None, "matches_source_in_tree": False}
     traffic = None
     try:
@@ -217,7 +223,7 @@ def main():
     # few microseconds between launches, which is why the timed region above has none inside)
     _, _, ev_min = time_calls(dense_call, min(args.steps, 200), 0)
 
-    traffic, traffic_info = measured_traffic(w.name, w.D)
+    traffic, traffic_info = measured_traffic(w)
     out = {
         "metric": "effective TFLOP/s (4*B*H*N^2*D*density), dense joint attention",
         "value": round(value, 2), "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,
@@ -227,7 +233,7 @@ def main():
                                f"dense (action 0), one layer's attention per step",
                    "flops_per_step": dense_flops, "entry": "rapid_attn_dense"},
         "pct_of_bf16_mfma_peak": round(100.0 * value / PEAK_BF16_TFLOPS, 2),
-        "roofline": {"bound": "mfma", "kernel": f"attn_dense_pp_kernel<{w.D}>", "achieved": round(achieved, 2),
+        "roofline": {"bound": "mfma", "kernel": f"{dense_kernel(w)}<{w.D}>", "achieved": round(achieved, 2),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": traffic, "traffic_source": traffic_info,
                      "algorithmic_bytes": 4 * dq.numel() * 2,
@@ -241,7 +247,7 @@ def main():
         import ctypes
         probe = ctypes.CDLL(os.path.join(ROOT, "paper_2509_22323_amd", "libmfma_probe.so"))
         probe.rapid_probe_mfma.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t,
-                                           ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+                                           ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
         # each thread reads 256 bytes of operands: size the grid to the tensor that supplies them
         blocks = int(min(512, dq.numel() * 2 // (256 * 256)))
         iters = 2000
@@ -249,10 +255,11 @@ def main():
         stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
         mfma_only = {}
         ones = torch.ones(blocks * 256 * 128, dtype=torch.bfloat16, device="cuda")
-        for kind, data in (("constant_operands", ones), ("unit_normal_operands", dq)):
+        for kind, data, shape in (("constant_operands", ones, 32), ("unit_normal_operands", dq, 32),
+                                  ("unit_normal_operands_16x16x32", dq, 16)):
             nbytes = data.numel() * data.element_size()
             run = lambda: probe.rapid_probe_mfma(data.data_ptr(), nbytes, pout.data_ptr(), pout.numel() * 4,
-                                                 blocks, iters, stream)
+                                                 blocks, iters, shape, stream)
             rc = run()
             if rc != 0:
                 raise RuntimeError(f"rapid_probe_mfma refused the launch: {rc}")

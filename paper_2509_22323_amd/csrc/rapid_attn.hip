@@ -5,7 +5,8 @@
 // per layer and per head).  The pruned map is given as a block mask; pruned tiles
 // are never read.
 //
-// Building blocks of the sparse kernels (a wavefront owns 32 queries and walks over 64-key tiles):
+// Building blocks of the 64-token sparse kernels and of attn_sparse_sg_kernel<64> (a wavefront owns 32 queries and
+// walks over 64-key tiles; the others are described at the stream):
 //   S^T = K Q^T    v_mfma_f32_32x32x16_bf16, A = K tile rows from LDS (128-bit
 //                  reads), B = the wavefront's Q rows held in registers for the
 //                  whole kernel.  Computing the TRANSPOSED score tile puts one
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
 // leaves most of the chip idle at the end: an item can be cut into P pieces (SplitRule
 // below).  Each piece is a record of its own; the pieces leave partial results in the
 // workspace and the last one to finish combines them.  A piece is expensive (its partial
-// result goes through memory: measured at D = 128, an entry costs about two key-blocks of
+// result goes through memory: at D = 128 an entry costs about two key-blocks of
 // time and a piece two more), so only rows several times the average (the text rows of a
 // sparse mask) are worth cutting.  Partial-result slots are handed out in item order (a
 // prefix sum, so the plan does not depend on timing); an item that no longer fits in the
@@ -272,7 +273,10 @@ constexpr int CUS_PER_XCD = 32;                  // MI355X: 256 CUs in 8 XCDs
 constexpr int SPLIT_MIN_BLOCKS = 8;
 constexpr int SPLIT_MAX_PIECES = 16;
 constexpr int SPLIT_SLOTS = 256;                 // partial-result slots per XCD (the rule needs < 256)
-constexpr int ENTRY_COST = 2, PIECE_COST = 2;    // measured, in key-blocks of time at D = 128
+constexpr int ENTRY_COST = 2, PIECE_COST = 2;    // in key-blocks of time at D = 128
+// (Taken from the loop of 32x32x16 MFMAs; on the stream, over 21 shapes by 6 densities at D = 128, costs of 1 and 1 are
+// 0.1 % faster on all-ones masks in the mean (3.4 % at best), 3 and 3 0.4 % slower there (10.9 % at worst), and 2 or 3
+// granules per CU in place of 2.5 within 0.3 % in the mean, -6 to +1 % case by case.)
 
 // The rule of one XCD.  P(c) = round(c * g / total) pieces for an item with c kept key-blocks
 // (g granules: pieces of about total / g), or p_all pieces for every item when that is set;
@@ -721,15 +725,6 @@ __device__ __forceinline__ TileBuffer tile_buffer(const Rows& src, int key0, int
     r.hi = (unsigned)((size_t)tile >> 32) & 0xffffu;
     r.bytes = (unsigned)rows * src.row_bytes;
     return r;
-}
-// Byte offset of this lane's chunk from the tile's first row, in copy instruction ld (1 KB of the stage).
-template <int D, bool IS_V>
-__device__ __forceinline__ unsigned copy_offset(unsigned row_bytes, int ld, int lane)
-{
-    typedef Geo<D> G;
-    const int row = ld * G::ROWS_PER_LOAD + lane / G::CPR;
-    const int logical = (lane % G::CPR) ^ (IS_V ? G::swz_v(row) : G::swz_k(row));
-    return (unsigned)row * row_bytes + (unsigned)logical * 16u;
 }
 // One copy, or two whose second KB is in the next KB of the stage, behind one write of M0 (see issue_tile).
 __device__ __forceinline__ void copy_1k(const TileBuffer& b, unsigned off, unsigned dst)
@@ -1959,7 +1954,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(c
 // two wavefront groups (even tiles -> group 0, odd tiles -> group 1) that work on the SAME
 // queries with separate softmax states and are merged through LDS at the end.  This halves
 // the critical path of a long list (a text row keeps every tile) and gives the same
-// anti-phase pairing of softmax and MFMA phases as the dense path.
+// anti-phase pairing of softmax and MFMA phases that the two groups of a workgroup are held in.
 //
 // Time is divided into slots by workgroup barriers; tile t (64 keys) is handled as
 //   slot t      S_t = K_t Q^T          (inside the A phase of tile t-2, or alone for t = 0, 1)
