@@ -1082,13 +1082,14 @@ __device__ __forceinline__ void phase_barrier()
 // this half: the second half of step i's probabilities beside the first items, the first half of
 // step i+1's beside the others.  The LDS reads of an item are requested PD items ahead, across the
 // end of a step.
-// What bounds it and why this form.  A full chip runs at its power limit, so energy per product counts as much
-// as cycles: on unit-normal data a loop of 32x32x16 MFMAs sustains 1.67 PFLOP/s, of 16x16x32 ones 1.97; with the
-// LDS reads of 32 queries per wavefront 1.50 and 1.72.  v_dot2 (the row sum of the 32x32 kernels) costs 17-20 cycles
-// next to MFMAs, hence the sum as an MFMA of ones (2-3 % of the call; as vector adds 5 % more than that).
-// Dense B = 1, H = 24, D = 128, against softmax and MFMA phases alternating between two groups of
-// wavefronts: N = 4608 242 -> 218 us (1.20 PFLOP/s), N = 16896 3166 -> 2689 us (1.30); D = 64, B = 2, N = 4480
-// 278 -> 231 us.  At D = 64 the issue port is busy 96 % of the time (the exponentials alone are a third of it).
+// What bounds it and why this form.  A full chip lowers its clock under this load (from 2.4 GHz to 2.11 at N = 4608 and
+// 1.82 at N = 16896, D = 128, with the matrix pipe busy 57 and 72 % of the cycles), so energy per product counts as much
+// as cycles: on unit-normal data a loop of nothing but 32x32x16 MFMAs sustains 1.65 PFLOP/s, of 16x16x32 ones 1.82
+// (mfma_probe.hip).  The row sum is an MFMA of ones: 2-3 % of the call faster than v_dot2 beside the MFMAs, and that 5 %
+// faster than vector adds.  Dense B = 1, H = 24, D = 128, against softmax and MFMA phases alternating between two groups
+// of wavefronts: N = 4608 242 -> 218 us (1.20 PFLOP/s), N = 16896 3166 -> 2689 us (1.30); D = 64, B = 2, N = 4480
+// 278 -> 231 us.  At D = 64 (B = 8, N = 4480) the vector port is busy 68 % of the cycles, two fifths of that with
+// exponentials, all issue ports together 86 %, the matrix pipe 60 %.
 // Layouts (lane = 16 g + n):
 //   K, V^T operand   lane holds row n of the 16-row fragment, its 8 elements 8 g .. 8 g + 7 of 32
 //   S^T              register r of tile kt, group q: key 16 kt + 4 g + r, query 16 q + n
