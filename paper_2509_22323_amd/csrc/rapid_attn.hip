@@ -2604,18 +2604,24 @@ int run_dense(const Problem& pr, void* stream)
     hipStream_t s = (hipStream_t)stream;
     const long long pairs = (long long)pr.B * pr.H, small = pairs * ((pr.N + 31) / 32);
     const long long items = pairs * ((pr.N + DENSE_QT - 1) / DENSE_QT), chunk = (items + XCDS - 1) / XCDS;
+    // of these, the ones with valid rows (padding costs next to nothing)
+    const long long small_live = pairs * ((pr.kv_len + 31) / 32);
+    const long long live = (pairs * ((pr.kv_len + DENSE_QT - 1) / DENSE_QT) + XCDS - 1) / XCDS;
     // 32 queries per workgroup: while they are resident at once the shortest chain of steps per wavefront wins, as long
     // as the other kernel has too few queries per workgroup to choose from.  us, this kernel / the other, H heads, B = 1:
     //   N <= 64: three quarters of 256 queries do not exist (B = 64, H = 38, N = 64: 20.0 / 31.6 at D = 64, 45 / 61 at 128)
     //   D = 64: N = 1024, H = 24 15.0 / 15.3; 2048, 12 23.5 / 23.6; past three quarters of the 1024 places the quarters of
     //     the other win: 1152, 24 19.4 / 16.1; 2048, 16 29.6 / 25.0; so they do over many keys: 16384, 1 110 / 108
-    //   D = 64 again just above one place per quarter on the other (17 to 19 items of an XCD): 1361, 24 27.1 / 27.9;
-    //     1024, 38 22.2 / 23.5; 1792, 24 (21 items) 36.8 / 34.5
+    //   D = 64 again where the other has more than one place per quarter (over 16 items of an XCD): 320, 96 10.0 / 10.7;
+    //     1024, 38 22.2 / 23.5; 1361, 24 27.1 / 27.9; but 384, 96 12.8 / 11.9; 512, 80 at 400 keys 13.8 / 12.6; 1792, 24
+    //     36.8 / 34.5
     //   D = 128: N = 640, H = 24 13.3 / 15.6; its 16-query wavefronts read K and V from LDS twice as often per product and
     //     it loses on long sequences: 8192, 2 93 / 79
+    const long long places = (pr.D == 64 ? 4 : 2) * XCDS * CUS_PER_XCD;
     const bool short_chain = pr.N <= 64 ||
-        (pr.D == 64 ? (small <= 768 && pr.kv_len <= 8192) || (small <= 1216 && chunk > CUS_PER_XCD / 2 && pr.N <= 2048)
-                    : small <= 2 * XCDS * CUS_PER_XCD && pr.N <= 1024);
+        (pr.D == 128 ? small <= places && pr.N <= 1024
+                     : (small_live <= places * 3 / 4 && small <= places && pr.kv_len <= 8192) ||
+                       (chunk > CUS_PER_XCD / 2 && pr.kv_len <= 2048 && small <= (pr.N >= 640 ? places * 5 / 4 : places)));
     if (short_chain) {
         p.nq = (pr.N + 31) / 32;
         p.items = (int)small;
@@ -2634,12 +2640,16 @@ int run_dense(const Problem& pr, void* stream)
     // XCD: 33 (H = 24, N = 2816) whole 136, in 2 116, in 4 105 at D = 128, 81 / 60 / 55 at D = 64; 198 (N = 16896)
     // 2875 / 2734 / 2703; 108 (B = 2, N = 4429, D = 64) 257 / 231 / 257.  More than half of a round stays whole: 54
     // items (N = 4608) 218 / 247 / 255.
-    // D = 64, no full round: two workgroups share a CU, so quarters fill it up to 16 items and win up to 24, halves up to
-    // 32.  us, whole / 2 / 4, H = 24: N = 1152 (14 items) - / 18.3 / 16.1; 1792 (21) 36.0 / 35.1 / 34.5; 2048 (24) 40.2 /
-    // 38.9 / 38.9; 2304 (27) 44.4 / 43.1 / 49.5; 2560 (30) 48.7 / 48.1 / 55.3.
+    // D = 64, no full round: two workgroups share a CU, so quarters fill it up to 16 items (with valid rows) and win up to
+    // 24, halves up to 32, once the sequence is long enough to pay for more prologues.  us, whole / 2 / 4, H heads: N =
+    // 1152, 24 (14 items) - / 18.3 / 16.1; 1792, 24 (21) 36.0 / 35.1 / 34.5; 2048, 24 40.2 / 38.9 / 38.9; 2304, 24 (27)
+    // 44.4 / 43.1 / 49.5; 2560, 24 (30) 48.7 / 48.1 / 55.3; of shorter ones 1024, 64 (32) 23.4 / 24.1 / 27.7; 512, 96 (24)
+    // 14.9 / 16.5 / 16.0; 256, 256 (32) 11.0 / 13.2 / 15.0; 858 keys of 2560, 24 (30, 12 of them with valid rows) 19.7 /
+    // 15.8 / -; 250 of 320, 128 (32, 16) 10.4 / 12.7 / 12.8.
     const bool one_round = pr.D == 64 && p.chunk <= CUS_PER_XCD;
     const int rest = one_round ? p.chunk : p.chunk % CUS_PER_XCD;
-    p.cut = one_round ? (rest <= 24 ? 4 : 2) : rest * 4 <= CUS_PER_XCD ? 4 : rest * 2 <= CUS_PER_XCD ? 2 : 1;
+    const bool fits = rest <= CUS_PER_XCD / 2 || (live <= CUS_PER_XCD / 2 && pr.kv_len >= 640);
+    p.cut = one_round ? (fits ? 4 : pr.kv_len < 1280 ? 1 : live <= 24 ? 4 : 2) : rest * 4 <= CUS_PER_XCD ? 4 : rest * 2 <= CUS_PER_XCD ? 2 : 1;
     p.whole = p.cut == 1 ? p.chunk : p.chunk - rest;
     const dim3 grid((unsigned)(p.whole + (p.chunk - p.whole) * p.cut) * XCDS);
     if (pr.D == 64) hipLaunchKernelGGL((attn_dense_stream_kernel<64>), grid, dim3(DensePlan<64>::Whole::NW * 64), 0, s, p);
