@@ -5,8 +5,8 @@
 // per layer and per head).  The pruned map is given as a block mask; pruned tiles
 // are never read.
 //
-// Building blocks of the 64-token sparse kernels and of attn_sparse_sg_kernel<64> (a wavefront owns 32 queries and
-// walks over 64-key tiles; the others are described at the stream):
+// Building blocks of attn_sparse_sg_kernel<64> (a wavefront owns 32 queries and walks over 64-key tiles; the others
+// are described at the stream):
 //   S^T = K Q^T    v_mfma_f32_32x32x16_bf16, A = K tile rows from LDS (128-bit
 //                  reads), B = the wavefront's Q rows held in registers for the
 //                  whole kernel.  Computing the TRANSPOSED score tile puts one
@@ -32,8 +32,8 @@
 //                               record (a query-block or a piece of its kept list); pieces are
 //                               merged by the last one to finish.  D = 128 on the 16x16x32 stream
 //   attn_sparse_wide_kernel     the same at D = 64 on the stream, for calls of many rows
-//   attn_sparse_pp_kernel<D,2>  sparse, 64-token mask tiles: one query-block per workgroup, the kept
-//                               list split between two wavefront groups and merged through LDS
+//   attn_sparse_pp_kernel<D,2>  sparse, 64-token mask tiles: one query-block per workgroup on the stream, the
+//                               keys of a block split between two groups of wavefronts
 //   plan_small_kernel           mask compaction and launch plan in one launch (up to 64 blocks per side)
 //   compact_mask_kernel, plan_split_kernel (128-token tiles), plan_kernel (64-token tiles)
 //                               the same in two launches for larger problems
@@ -62,11 +62,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-// Whether the common path of the softmax computes no row maximum (softmax_tile).  At D = 64 the
-// vector unit is the busiest one (half as many MFMA cycles per score as at D = 128) and every
-// instruction taken out of the softmax phase shows; at D = 128 it made no difference.
-template <int D> struct Optimistic { static constexpr bool value = D == 64; };
 
 constexpr int KT = 64;          // keys per LDS tile
 constexpr int XCDS = 8;         // L2 domains the dispatcher deals workgroups over
@@ -656,8 +651,7 @@ struct Geo {
 // Issue the asynchronous copy of rows key0..key0+63 of `src` into an LDS tile.  Rows at or
 // beyond kv_len are replaced by row kv_len-1 (finite data; their probabilities are exactly
 // 0, and their scores are overwritten with -inf, so they never contribute).
-// PER_M0: copies behind one write of M0.
-template <int D, int NW, bool IS_V, int PER_M0 = 1>
+template <int D, int NW, bool IS_V>
 __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len,
                                            char* lds, int wave, int lane)
 {
@@ -667,10 +661,7 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
     // assembly so that the copy pipeline is ordered only by the explicit vmcnt waits and barriers of the main loop
     // (the compiler would otherwise wait for all copies before LDS reads it cannot disambiguate).  M0 has no other
     // user in these kernels.  A copy may not be the next instruction after the scalar write of M0 (one wait state)
-    // and the compiler does not look into assembly for that: s_nop 0.  Under 64-token masks at D = 64 two copies share
-    // an M0 (one s_nop each cost those calls 1 to 1.4 %); elsewhere each has its own (two or four behind one M0 cost 2
-    // and 3 % at D = 128 and 0.7 % in the short records of 128-token masks, the s_nop under 1 %).
-    static_assert(PER_WAVE % PER_M0 == 0 && (PER_M0 == 1 || PER_M0 == 2), "");
+    // and the compiler does not look into assembly for that: s_nop 0, under 1 % (two copies behind one M0: 0.7 % slower).
     const int ld0 = wave * PER_WAVE;                        // wave-uniform
     auto row_of = [&](int i) { return (ld0 + i) * G::ROWS_PER_LOAD + lane / G::CPR; };
     auto chunk_of = [&](int i) { return (unsigned)((lane % G::CPR) ^ (IS_V ? G::swz_v(row_of(i)) : G::swz_k(row_of(i)))) * 16u; };
@@ -681,13 +672,8 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
         const char* tile = src.row(key0);                  // a tile never straddles the segments
         auto off = [&](int i) { return (unsigned)row_of(i) * src.row_bytes + chunk_of(i); };
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; i += PER_M0) {
-            if constexpr (PER_M0 == 1)
-                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(dst(i)), "v"(off(i)), "s"(tile));
-            else                                           // (8 rows further on: the difference is not negative)
-                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
-                             ::"{m0}"(dst(i)), "v"(off(i)), "v"(off(i + 1) - 1024u), "s"(tile));
-        }
+        for (int i = 0; i < PER_WAVE; ++i)
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(dst(i)), "v"(off(i)), "s"(tile));
     } else {
         auto at = [&](int i) {
             int grow = key0 + row_of(i);
@@ -695,13 +681,8 @@ __device__ __forceinline__ void issue_tile(const Rows& src, int key0, int kv_len
             return (key0 < src.n0 ? src.base0 : src.base1) + (size_t)grow * src.row_bytes + chunk_of(i);
         };
 #pragma unroll
-        for (int i = 0; i < PER_WAVE; i += PER_M0) {
-            if constexpr (PER_M0 == 1)
-                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(dst(i)), "v"(at(i)));
-            else
-                asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\tglobal_load_lds_dwordx4 %2, off offset:1024"
-                             ::"{m0}"(dst(i)), "v"(at(i)), "v"(at(i + 1) - 1024));
-        }
+        for (int i = 0; i < PER_WAVE; ++i)
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(dst(i)), "v"(at(i)));
     }
 }
 
@@ -902,13 +883,9 @@ __device__ __forceinline__ void mask_tail(f32x16 (&st)[2], int key0, int kv_len,
 // Online softmax of one tile (one query per lane; the two lane halves hold disjoint keys).
 // Probabilities are exp2(c * s - m) with c = scale * log2(e) and a per-query reference m (kept in
 // exponent units); any m gives the same quotient acc / l, and bf16 and fp32 share their exponent
-// range, so m need not be the running maximum.  Two ways to keep it in range:
-//   lazy (D = 128): the tile's maximum is computed, and m moves up to it only when it lies more
-//     than 8 above m (probabilities stay below 2^8);
-//   optimistic (D = 64): no maximum on the common path.  m comes from the first tile and moves
-//     only when a later tile's probabilities get large: their sum, which is needed anyway,
-//     exceeds 2^60 (or is not a number).  Then the tile's maximum becomes the reference and the
-//     tile's probabilities are computed again.
+// range, so m need not be the running maximum.  No maximum on the common path: m comes from the first tile and
+// moves only when a later tile's probabilities get large: their sum, which is needed anyway, exceeds 2^60 (or is not
+// a number).  Then the tile's maximum becomes the reference and the tile's probabilities are computed again.
 // When m moves, l and the accumulators are rescaled.  Leaves the probabilities as bf16 MFMA
 // operands: pb[2 rb + t] = keys 16t + {4h..4h+3, 8+4h..8+4h+3} of row block rb.
 template <int D>
@@ -951,17 +928,12 @@ __device__ __forceinline__ void softmax_tile(const f32x16 (&st)[2], f32x16 (&acc
     };
     float rs = 0.f, mx = 0.f;
     bool move = first;
-    if constexpr (Optimistic<D>::value) {
-        if (!first) {
-            rs = probabilities();
-            move = __builtin_amdgcn_ballot_w64(!(rs <= 0x1p60f)) != 0ull;     // also true for inf and NaN
-        }
-        if (move) mx = tile_max();
-    } else {
-        mx = tile_max();
-        if (!first) move = __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull;
+    if (!first) {
+        rs = probabilities();
+        move = __builtin_amdgcn_ballot_w64(!(rs <= 0x1p60f)) != 0ull;     // also true for inf and NaN
     }
     if (move) {
+        mx = tile_max();
         // mx is finite: every visited tile has a valid key.  On the first tile nothing has been
         // accumulated yet; later the reference only moves up.
         const float delta = first ? mx : fmaxf(mx, 0.f);
@@ -972,8 +944,8 @@ __device__ __forceinline__ void softmax_tile(const f32x16 (&st)[2], f32x16 (&acc
         for (int i = 0; i < DB; ++i)
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[i][j] *= alpha;
+        rs = probabilities();
     }
-    if (!Optimistic<D>::value || move) rs = probabilities();
     st_.l += rs;
 }
 
@@ -1006,20 +978,8 @@ __device__ __forceinline__ void write_output(const Rows& O, const f32x16 (&acc)[
     }
 }
 
-// Q^T fragments (B operand of S^T = K Q^T): lane (n, h) holds Q[qrow][16t + 8h .. +8].
-template <int D>
-__device__ __forceinline__ void load_q(const Rows& Q, int qrow, bool qvalid, int h, bf16x8 (&qf)[D / 16])
-{
-    const __bf16* qr = (const __bf16*)Q.row(qvalid ? qrow : 0);
-#pragma unroll
-    for (int t = 0; t < D / 16; ++t) {
-        u32x4 raw = {0u, 0u, 0u, 0u};
-        if (qvalid) raw = *(const u32x4*)(qr + 16 * t + 8 * h);
-        qf[t] = __builtin_bit_cast(bf16x8, raw);
-    }
-}
-
-// The same fragments requested by explicit assembly: the compiler then places no waits of
+// Q^T fragments (B operand of S^T = K Q^T): lane (n, h) holds Q[qrow][16t + 8h .. +8].  Requested by explicit
+// assembly: the compiler then places no waits of
 // its own for them (it cannot count the tile copies issued around them and would wait for
 // everything); the caller waits with wait_vmcnt and then passes the fragments through
 // q_arrived so that their uses stay behind that wait.  Rows that are not valid read row 0
@@ -1625,6 +1585,7 @@ struct StreamPlan {
 template <class P>
 struct AllKeys {
     __device__ __forceinline__ int at(int t, int, bool) const { return t * P::KTS; }
+    __device__ __forceinline__ void stand(int) {}
     __device__ __forceinline__ void advance() {}
 };
 
@@ -1660,6 +1621,33 @@ struct KeptKeys {
         coming = list[next < n ? next : 0];
         ++next;
     }
+    __device__ __forceinline__ void stand(int) {}
+};
+
+// A list of kept 64-key blocks, a block one tile.  Lane l of `first` holds the first key of entry base + l (past the end
+// of the list: beyond every kv_len); an entry is read out of its lane, so that the loop waits for no load of the list
+// (a scalar load shares its counter with the LDS reads in flight) until it has gone through nearly 64 of them.
+template <class P>
+struct KeptTiles {
+    static_assert(P::KTS == 64 && P::SPT == 1 && P::KLEAD >= P::VLEAD, "");
+    static constexpr int NOWHERE = 1 << 30;
+    const int32_t* list;
+    int n, base, first;
+    __device__ __forceinline__ KeptTiles(const int32_t* list_, int n_) : list(list_), n(n_) { load(0); }
+    __device__ __forceinline__ void load(int from)
+    {
+        base = from;
+        const int i = base + (int)(threadIdx.x & 63u);
+        asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=&v"(first) : "v"((i < n ? i : 0) * 4), "s"(list) : "memory");
+        first = i < n ? first * 64 : NOWHERE;
+    }
+    __device__ __forceinline__ int at(int t, int, bool) const { return __builtin_amdgcn_readlane(first, t - base); }
+    // tile t is the current one: from here to the next call entries up to t + 1 + KLEAD are asked for
+    __device__ __forceinline__ void stand(int t)
+    {
+        if (t - base >= 63 - P::KLEAD) load(t);
+    }
+    __device__ __forceinline__ void advance() {}
 };
 
 // Steps 0 .. last of this workgroup's queries against the tiles of `keys` (tiles at or beyond kv_len are all masked).  ALIGNED: last + 1 is a multiple of P::UNROLL.
@@ -1774,6 +1762,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         if (RT ? i % P::SPT == 0 : FIRST_OF_TILE) {
             constexpr bool MOVE = !RT && U / P::SPT == P::UNROLL / P::SPT - 1;
             if constexpr (MOVE) keys.advance();
+            keys.stand(t);
             vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, U / P::SPT + P::VLEAD, MOVE), kv_len);
             kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, U / P::SPT + P::KLEAD, MOVE), kv_len);
             wait_vmcnt<P::LOOSE>();
@@ -1951,41 +1940,28 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(c
 }
 
 // ---------------------------------------------------------------------------
-// Sparse path: one workgroup per (b, h, query-block); its kept-tile list is split between
-// two wavefront groups (even tiles -> group 0, odd tiles -> group 1) that work on the SAME
-// queries with separate softmax states and are merged through LDS at the end.  This halves
-// the critical path of a long list (a text row keeps every tile) and gives the same
-// anti-phase pairing of softmax and MFMA phases that the two groups of a workgroup are held in.
-//
-// Time is divided into slots by workgroup barriers; tile t (64 keys) is handled as
-//   slot t      S_t = K_t Q^T          (inside the A phase of tile t-2, or alone for t = 0, 1)
-//   slot t+1    B(t): softmax of S_t, first V_t^T fragments requested
-//   slot t+2    A(t): O^T += V_t^T P_t^T ; S_{t+2}
-// by group t % 2, so in every slot one group is in an A phase and the other in a B phase.
-// Every wavefront passes T+2 slot barriers (a group without work in a slot only does its
-// share of the copies and waits).  Copies: in slot s every wavefront issues its share of
-// K_{s+3} (4-stage ring) and V_{s+2} (5-stage ring) and, before the barrier that ends the
-// slot, waits for its share of K_{s+1} and V_s (both issued in slot s-2; copies complete
-// in order).  K_t is therefore complete at the start of slot t and V_t at the start of
-// slot t+1; stage reuse: K_{t+4} is issued in slot t+1 > t, V_{t+5} in slot t+3 > t+2.
-// All LDS traffic of the main loop is explicit assembly, so stages are plain runtime
-// offsets into one array.
+// Sparse path, 64-token mask tiles: one workgroup per (b, h, query-block) walks the kept list on the stream, a
+// block per tile, the 64 keys of a block split between two groups of wavefronts that are merged at the end.
+// Four wavefronts of 32 queries: 80 KB of stages at D = 128, two workgroups per CU and two wavefronts per SIMD; 40 KB at
+// D = 64, three per CU (a wavefront of 64 queries there needs six registers more than there are).  One group of
+// wavefronts per item instead would halve the rate of an item, and a row that keeps everything (the text rows) would be
+// longer than its CU's share.  Copies are a whole step ahead and no more: stages for longer leads (4 of K and V) leave
+// one workgroup per CU at D = 128 (1.2 to 1.7 times the time) and two at D = 64 (1.05 to 1.2 times); all copies at the
+// head of the half step in which they are spread out: 1 to 1.5 % slower.
+// us, B = 1, H = 24, densities 0.1 / 0.3 / 1, two wavefront groups on alternating phases of 32x32x16 MFMAs before and
+// now: D = 128, N = 2816 58.8 92.9 220 -> 35.0 54.3 122; N = 8960 272 589 1716 -> 159 331 935; D = 64, N = 2816 28.1 44.2
+// 106 -> 22.2 32.5 73.2; N = 384 16.3 (two planner launches and the host either way).
 // ---------------------------------------------------------------------------
-// (Waves per SIMD the register budget is set for: the 144 KB of stages at D = 128 leave room for
-// one workgroup per CU, 72 KB at D = 64 for two.)
-template <int D, int WPG>
-__global__ __launch_bounds__(128 * WPG, (D == 64 ? (WPG == 4 ? 4 : 2) : 1)) void attn_sparse_pp_kernel(const AttnParams p)
-{
-    typedef Geo<D> G;
-    constexpr int PD = 6;
-    typedef TileItems<D, PD> TI;
-    constexpr int NW = 2 * WPG, QT = 32 * WPG, KS = D / 16, DB = D / 32;
-    constexpr int PER_M0 = D == 64 ? 2 : 1;       // see issue_tile
-    constexpr int NSK = 4, NSV = 5;
-    constexpr int LPT = 2 * G::LOADS / NW;        // copy instructions per wavefront per slot (K + V)
-    static_assert(WPG * DB * 16 * 64 * 4 + WPG * 64 * 8 <= (NSK + NSV) * G::TILE_BYTES, "merge buffer fits the rings");
+template <int D> struct Sparse64Plan { typedef StreamPlan<128, 2, 2, 2, 1, 2, 3> P; };
+template <> struct Sparse64Plan<64> { typedef StreamPlan<64, 2, 2, 2, 1, 2, 3> P; };
 
-    __shared__ __attribute__((aligned(1024))) char lds[(NSK + NSV) * G::TILE_BYTES];
+template <int D, int WK>
+__global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) void attn_sparse_pp_kernel(const AttnParams p)
+{
+    typedef typename Sparse64Plan<D>::P P;
+    typedef typename P::S S;
+    static_assert(P::QT == 64 && P::WK == WK, "one item = 64 queries");
+    __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
     typedef const __attribute__((address_space(4))) int32_t* cptr_t;
     const int wg = blockIdx.x;
@@ -1993,160 +1969,35 @@ __global__ __launch_bounds__(128 * WPG, (D == 64 ? (WPG == 4 ? 4 : 2) : 1)) void
     if (item < 0) return;
     const int bh = item / p.nq;
     const int qi = item % p.nq;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int group = wave / WPG;
-    const int wq = wave % WPG;
-    const int n = lane & 31;
-    const int h = lane >> 5;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int kv_len = p.kv_len;
     if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
         kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
         kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
         kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
     }
-
     const int smp = bh / p.H, head = bh % p.H;
     const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
     const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
+    const int q0 = qi * 64 + wave / P::WK * 16 * P::NQ;
+    char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
+    const int n = ((cptr_t)p.counts)[item];
 
-    const int qrow = qi * QT + wq * 32 + n;       // groups share the queries
-    const bool qvalid = qrow < kv_len;
-
-    // 64-key tiles of this item: tile t -> first key
-    const int ss = p.sub_shift;
-    cptr_t list = (cptr_t)(p.index + (size_t)item * p.nb);
-    int T;
-    {
-        const int n_blocks = ((cptr_t)p.counts)[item];
-        T = n_blocks << ss;
-        if (n_blocks > 0 && (((list[n_blocks - 1] + 1) << ss) - 1) * KT >= kv_len) T -= 1;
-    }
-    f32x16 acc[DB];
+    StreamRegs<S, D> x;
+    if (n <= 0 || qi * 64 >= kv_len) {            // nothing kept, or padding rows only: the rows are zero
+        if (wave % P::WK != 0) return;
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
-    if (T <= 0) {                                 // nothing kept: the rows are zero
-        if (group == 0) write_output<D>(O, acc, 0.f, qrow, false, p.N, h);
+        for (int q = 0; q < P::NQ; ++q) x.ls[q][0] = 0.f;
+        stream_output_rows<S, D>(x, O, q0, 0, p.N, lane, out_stage);
         return;
     }
-    auto key_of = [&](int t) -> int { return ((list[t >> ss] << ss) + (t & ((1 << ss) - 1))) * KT; };
-    auto k_stage = [&](int t) -> char* { return lds + (t & (NSK - 1)) * G::TILE_BYTES; };
-    // kq[i] = first key of tile s+i for the current slot s (0 past the end); kq4 is loaded a slot ahead
-    int kq[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) kq[i] = (i < T) ? key_of(i) : 0;
-    int kq4 = (4 < T) ? key_of(4) : 0;
-    int vst_issue = 2;                            // V stage of tile s+2
-    int vst_use = 0;                              // V stage of this group's current tile
-
-    // prologue: K_0..K_2, V_0, V_1
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-        if (t < T) issue_tile<D, NW, false, PER_M0>(K, kq[t], kv_len, k_stage(t), wave, lane);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-        if (t < T) issue_tile<D, NW, true, PER_M0>(V, kq[t], kv_len, lds + (NSK + t) * G::TILE_BYTES, wave, lane);
-
-    bf16x8 qf[KS];
-    load_q<D>(Q, qrow, qvalid, h, qf);
-    SoftmaxState sm;
-    sm.m = -INFINITY;
-    sm.l = 0.f;
-    const int tr_row = (lane & 15) >> 2;
-    const int tr_col = ((lane & 3) << 2) + (((lane >> 4) & 1) << 4);
-    wait_vmcnt<0>();
-    __syncthreads();
-
-    int s = 0;                                    // current slot = slot barriers passed
-    auto slot_begin = [&]() {                     // my share of K_{s+3} and V_{s+2}
-        if (s + 3 < T) issue_tile<D, NW, false, PER_M0>(K, kq[3], kv_len, k_stage(s + 3), wave, lane);
-        if (s + 2 < T) issue_tile<D, NW, true, PER_M0>(V, kq[2], kv_len, lds + (NSK + vst_issue) * G::TILE_BYTES, wave, lane);
-    };
-    auto slot_end = [&]() {                       // K_{s+1} and V_s complete, then the barrier
-        if (s + 3 < T) wait_vmcnt<2 * LPT>();
-        else wait_vmcnt<0>();
-        phase_barrier();
-        ++s;
-        kq[0] = kq[1]; kq[1] = kq[2]; kq[2] = kq[3]; kq[3] = kq4;
-        kq4 = (s + 4 < T) ? key_of(s + 4) : 0;
-        vst_issue = (vst_issue == NSV - 1) ? 0 : vst_issue + 1;
-    };
-
-    TileCtx<D, PD> ctx;
-    bf16x8 pb[4];
-    f32x16 st[2];
-
-    if (group == 1) { slot_begin(); slot_end(); vst_use = 1; }   // group 1 runs one slot behind
-    int t = group;                                // this group's tiles: group, group + 2, ...
-    if (t < T) {                                  // slot t: S_t on its own
-        slot_begin();
-        k_addresses<D>(k_stage(t), n, h, ctx);
-        items_prefetch<D, PD, TI::NPV, TI::NI>(ctx);
-        items_run<D, PD, TI::NPV, TI::NI>(ctx, pb, qf, acc, st);
-        mask_tail(st, kq[0], kv_len, h);
-        slot_end();
-    }
-    while (t < T) {
-        // ---- slot t+1: B(t)
-        slot_begin();
-        v_addresses<D>(lds + (NSK + vst_use) * G::TILE_BYTES, h, tr_row, tr_col, ctx.vaddr);
-        softmax_tile<D>(st, acc, sm, p.c, t == group, pb);
-        pin_in_phase(pb, sm.l);
-        items_prefetch<D, PD, 0, TI::NI>(ctx);        // first V_t^T fragments of A(t)
-        slot_end();
-        // ---- slot t+2: A(t)
-        __builtin_amdgcn_s_setprio(3);
-        slot_begin();
-        // (without a tile t+2 the QK half re-reads K_t, which is landed, and is dropped)
-        k_addresses<D>(k_stage((t + 2 < T) ? t + 2 : t), n, h, ctx);
-        items_run<D, PD, 0, TI::NI>(ctx, pb, qf, acc, st);
-        mask_tail(st, kq[0], kv_len, h);
-        __builtin_amdgcn_s_setprio(0);
-        slot_end();
-        t += 2;
-        vst_use += 2;
-        if (vst_use >= NSV) vst_use -= NSV;
-    }
-    while (s < T + 2) { slot_begin(); slot_end(); }
-
-    // ---- merge the two groups (same queries, same register layout) through LDS
-    u32x4* mbuf = (u32x4*)lds;                                    // [wq][DB*4][64 lanes]
-    float* mlbuf = (float*)(lds + WPG * DB * 4 * 64 * 16);        // [wq][64 lanes][m, l]
-    if (group == 1) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                u32x4 v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = __float_as_uint(acc[db][4 * j + r]);
-                mbuf[(wq * DB * 4 + db * 4 + j) * 64 + lane] = v;
-            }
-        mlbuf[(wq * 64 + lane) * 2] = sm.m;
-        mlbuf[(wq * 64 + lane) * 2 + 1] = sm.l;
-    }
-    __syncthreads();
-    if (group == 0) {
-        const float m1 = mlbuf[(wq * 64 + lane) * 2];
-        const float l1 = mlbuf[(wq * 64 + lane) * 2 + 1];
-        const float m = fmaxf(sm.m, m1);                          // group 0 always has tile 0: finite
-        const float a0 = __builtin_amdgcn_exp2f(sm.m - m);
-        const float a1 = __builtin_amdgcn_exp2f(m1 - m);         // 0 if group 1 had no tile
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const u32x4 v = mbuf[(wq * DB * 4 + db * 4 + j) * 64 + lane];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    acc[db][4 * j + r] = acc[db][4 * j + r] * a0 + __uint_as_float(v[r]) * a1;
-            }
-        write_output<D>(O, acc, sm.l * a0 + l1 * a1, qrow, qvalid, p.N, h);
-    }
+    KeptTiles<P> keys(p.index + (size_t)item * p.nb, n);
+    stream_attend<P, false>(x, lds, Q, K, V, q0, kv_len, p.c, n - 1, keys, wave, lane);
+    __syncthreads();                              // every wavefront has read its last tile
+    stream_merge<P>(x, lds, wave, lane);
+    if (wave % P::WK != 0) return;
+    stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
 }
 
 // Partial result of one piece of a split item: the fp32 accumulators in register order
@@ -2717,8 +2568,8 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
         else if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(SparsePlan<128>::P::NW * 64), 0, s, p);
     } else {
-        if (D == 64) hipLaunchKernelGGL((attn_sparse_pp_kernel<64, 2>), grid, dim3(256), 0, s, p);
-        else hipLaunchKernelGGL((attn_sparse_pp_kernel<128, 2>), grid, dim3(256), 0, s, p);
+        if (D == 64) hipLaunchKernelGGL((attn_sparse_pp_kernel<64, 2>), grid, dim3(Sparse64Plan<64>::P::NW * 64), 0, s, p);
+        else hipLaunchKernelGGL((attn_sparse_pp_kernel<128, 2>), grid, dim3(Sparse64Plan<128>::P::NW * 64), 0, s, p);
     }
     return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
 }

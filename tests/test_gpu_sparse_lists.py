@@ -63,6 +63,21 @@ def test_every_list_length_and_odd_tails(D, block, cut):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+def test_lists_longer_than_a_wavefront_holds(D):
+    """64-token masks: a wavefront holds 64 entries of the list and reads on every 60; rows of 50 to 132 kept
+    blocks, the last of them cut."""
+    block, nb = 64, 132
+    N, kv = nb * block, nb * block - 45
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((1, 1, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    rank = torch.rand((1, 1, nb, nb), generator=g, device="cuda").argsort(-1).argsort(-1)
+    length = (torch.arange(nb, device="cuda").view(1, 1, nb, 1) * 5) % 83 + 50
+    mask = (rank < length).to(torch.uint8)
+    o = sparse(q, k, v, mask, block, kv)
+    check(o, reference(q, k, v, mask, block, kv, D ** -0.5), kv, f"D={D}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("block", [64, 128])
 def test_reference_of_the_exponents_moves(D, block):
     """Scores that climb by 72 (base 2) above a row's first keys, inside a block, in a later block
