@@ -89,10 +89,10 @@ RAPID_API int rapid_attn_dense(const void* q, const void* k, const void* v, void
  *           as the sparsity control is per layer and per head.
  *   workspace  device scratch of at least rapid_attn_workspace_bytes(...)
  *           bytes, 16-byte aligned.  Its contents on entry do not matter and
- *           nothing in it survives as state: every call first compacts the
- *           mask into it (kept key-blocks per query-block, blocks starting at
- *           or beyond kv_len dropped), lays out its launch plan there, and
- *           then runs attention over the kept tiles only; rows that keep many
+ *           nothing in it survives as state: every call compacts the mask
+ *           into it (kept key-blocks per query-block, blocks starting at or
+ *           beyond kv_len dropped), lays out its launch plan there, and
+ *           runs attention over the kept tiles only; rows that keep many
  *           tiles may be cut into pieces whose partial results pass through it.
  *           One workspace must not serve two calls that can run concurrently
  *           (different streams): each call rewrites all of it.  Calls on one

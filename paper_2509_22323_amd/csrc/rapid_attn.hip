@@ -34,9 +34,11 @@
 //   attn_sparse_wide_kernel     the same at D = 64 on the stream, for calls of many rows
 //   attn_sparse_pp_kernel<D,2>  sparse, 64-token mask tiles: one query-block per workgroup on the stream, the
 //                               keys of a block split between two groups of wavefronts
-//   plan_small_kernel           mask compaction and launch plan in one launch (up to 64 blocks per side)
+//   plan_small_kernel           launch plan in one launch, from the mask or from counts (up to 64 blocks per side); the
+//                               attention kernels then read their rows of the mask themselves, and where all rows
+//                               are on the chip at once they need no plan either
 //   compact_mask_kernel, plan_split_kernel (128-token tiles), plan_kernel (64-token tiles)
-//                               the same in two launches for larger problems
+//                               lists and plan in two launches for larger problems
 // Entry points (C ABI, bottom of the file): rapid_attn_dense, rapid_attn_block_sparse,
 // rapid_attn_block_sparse_static (scratch in a fixed array of this file), rapid_attn_joint,
 // rapid_attn_joint_select (selection kernels of rapid_mask.hip write the kept lists).
@@ -105,9 +107,10 @@ struct AttnParams {
     SegTensor q, k, v, o;
     const int32_t* kv_lens;  // per-sample valid tokens (device, [B]) or null: kv_len for all
     int n0;                  // tokens in the first segment (N when there is one)
-    const int32_t* counts;   // sparse: kept key-blocks per (b,h,query-block); dense: null
-    const int32_t* order;    // sparse: launch plan (64-token tiles: item ids; 128-token tiles: PlanRec records)
-    const int32_t* index;    // sparse: kept key-block lists, nb per row
+    const unsigned char* mask;    // sparse: the block mask where the kernels read their rows of it themselves, else null
+    int32_t* counts;         // sparse: kept key-blocks per (b,h,query-block); dense: null
+    int32_t* order;          // sparse: launch plan (64-token tiles: item ids; 128-token tiles: PlanRec records)
+    int32_t* index;          // sparse: kept key-block lists, nb per row
     int32_t* arrived;        // sparse, 128-token tiles: finished pieces per split item
     char* partial;           // sparse, 128-token tiles: partial results of the pieces of split items
     int H, N, kv_len;
@@ -115,8 +118,9 @@ struct AttnParams {
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
     int whole, cut;          // dense: whole items of an XCD, pieces of each of the others
-    int block, nb;           // mask tile edge, N / block (sparse only)
-    int sub_shift;           // log2(block / 64)
+    int nb;                  // mask blocks per side (sparse only)
+    int planned;             // sparse: 1 when the plan is in `order`, 0 when every workgroup plans for itself
+    int pmax;                // sparse, 128-token tiles: partial-result slots per XCD
     float c;                 // scale * log2(e)
 };
 
@@ -286,11 +290,12 @@ struct SplitRule {
     int p_all;     // 0: by length
 };
 
-// cost of cutting every one of n_items rows of max_c blocks into P pieces, D = 128
-__device__ __forceinline__ long long split_alike_cost(int n_items, int max_c, int P)
+// cost of cutting every one of n_items rows of max_c blocks into P pieces, D = 128 (T: wide enough for n_items * P * max_c)
+template <class T>
+__device__ __forceinline__ T split_alike_cost(int n_items, int max_c, int P)
 {
-    const long long places = CUS_PER_XCD * 2;
-    const long long rounds = ((long long)n_items * P + places - 1) / places;
+    const T places = CUS_PER_XCD * 2;
+    const T rounds = ((T)n_items * P + places - 1) / places;
     return rounds * ((max_c + P - 1) / P + ENTRY_COST + (P > 1 ? PIECE_COST : 0));
 }
 
@@ -300,8 +305,8 @@ __device__ __forceinline__ bool rows_alike(int n_items, int max_c, unsigned long
 }
 
 // `costs` holds split_alike_cost for P = 1 .. SPLIT_MAX_PIECES (used at D = 128 when the rows are alike)
-__device__ __forceinline__ SplitRule split_rule(int D, int n_items, int max_c, unsigned long long total,
-                                                const long long* costs)
+template <class T>
+__device__ __forceinline__ SplitRule split_rule(int D, int n_items, int max_c, unsigned long long total, const T* costs)
 {
     SplitRule r;
     r.p_all = 0;
@@ -309,7 +314,7 @@ __device__ __forceinline__ SplitRule split_rule(int D, int n_items, int max_c, u
     if (D == 128) {
         r.g = CUS_PER_XCD * 5 / 2;
         if (alike && total != 0ull) {
-            long long best = costs[0];
+            T best = costs[0];
             r.p_all = 1;
             const int top = max_c / SPLIT_MIN_BLOCKS < SPLIT_MAX_PIECES ? max_c / SPLIT_MIN_BLOCKS : SPLIT_MAX_PIECES;
             for (int P = 2; P <= top; ++P)
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(1024) void plan_split_kernel(const int32_t* __restr
     for (int i = tid; i < cap; i += 1024) out[i] = none;
     __syncthreads();
     const unsigned long long tot = total;
-    if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost(n_items, longest, tid + 1);
+    if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost<long long>(n_items, longest, tid + 1);
     __syncthreads();
     const SplitRule rule = split_rule(D, n_items, longest, tot, alike_cost);
     // partial-result slots in item order: thread t owns the items [lo, hi)
@@ -435,193 +440,239 @@ __global__ __launch_bounds__(1024) void plan_split_kernel(const int32_t* __restr
     }
 }
 
-// Small problems (the 1024x1024-image shapes: about a hundred items per XCD): compaction and
-// plan in ONE launch, written for latency.  Two launches with a trip through memory between
-// them cost 11 us of a sparse call that takes 80 .. 130 us.  Here every thread loads its
-// bytes of the XCD's mask rows at once and keeps them in registers; a kept block sets its
-// bit in the row's 64-bit word in LDS (nb <= 64), the rank of a block in its row's list is a
-// population count below its bit, and the plan is made one thread per item in 32-bit
-// arithmetic (same rule, same records as plan_split_kernel: the limits below keep every
-// intermediate below 2^32).  No loop in it depends on memory more than once.
+// Up to SMALL_NB mask blocks per side: the plan in ONE launch, written for latency, from the mask itself or from counts
+// that are there already.  The mask is read eight bytes per lane, all of an XCD's at once, and kept as one bit per
+// block in LDS; a row's count is a population count of its stretch of bits.  The lists are not written here: an
+// attention workgroup reads its own row of the mask (KeptBlocks).  Same rule and same records as plan_split_kernel and
+// plan_kernel, in 32-bit arithmetic (the limits keep every intermediate below 2^32).
 constexpr int SMALL_NB = 64;                     // mask blocks per side
-constexpr int SMALL_ITEMS = 1024;                // items of one XCD
-constexpr int SMALL_SWEEPS = 8;                  // mask bytes of one XCD's items: 1024 per sweep
-constexpr int SMALL_BYTES = 1024 * SMALL_SWEEPS;
+constexpr int SMALL_PER_THREAD = 4;              // items of one XCD per thread, at most
+constexpr int SMALL_ITEMS = 1024 * SMALL_PER_THREAD;
+constexpr int SMALL_PIECES = 8192;               // pieces of eight mask bytes of one XCD's items
 
+// eight mask bytes as eight bits
+__device__ __forceinline__ unsigned byte_bits(unsigned lo, unsigned hi)
+{
+    auto four = [](unsigned v) {
+        v |= v >> 4;
+        v |= v >> 2;
+        v |= v >> 1;
+        return ((v & 0x01010101u) * 0x10204080u) >> 28;    // bit 8 i to bit 28 + i
+    };
+    return four(lo) | four(hi) << 4;
+}
+
+// PT items per thread, SWEEPS times 1024 pieces.
+template <bool PIECES, int PT, int SWEEPS>
 __global__ __launch_bounds__(1024) void plan_small_kernel(
     const unsigned char* __restrict__ mask, const int32_t* __restrict__ kv_lens, int kv_len, int N, int block,
     int H, int BH, int nb, int cap, int pmax, int D,
-    int32_t* __restrict__ counts, int32_t* __restrict__ index, PlanRec* __restrict__ recs,
-    int32_t* __restrict__ arrived)
+    int32_t* __restrict__ counts, int32_t* __restrict__ order, int32_t* __restrict__ arrived)
 {
-    __shared__ unsigned rowbits[2 * SMALL_ITEMS]; // kept key-blocks of item i: bits of words 2i, 2i+1
-    __shared__ int live[SMALL_ITEMS];            // per (b,h) pair: key-blocks that start below kv_len
-    __shared__ int hist[128];                    // by r = nb - length; hist[nb + 1] = number of records
+    __shared__ unsigned bits[1024 * SWEEPS / 4 + 4]; // pair g: one bit per mask block from byte g * pad on
+    __shared__ int hist[SMALL_NB + 1], to[SMALL_NB + 1];    // by r = nb - length: records, and where the next one goes
     __shared__ int wave_sum[16], kept_sum[16], wave_max[16];
-    __shared__ long long alike_cost[SPLIT_MAX_PIECES];
-    const int x = blockIdx.x, tid = threadIdx.x;
+    __shared__ unsigned alike_cost[SPLIT_MAX_PIECES];
+    const int x = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int n_bh = BH > x ? (BH - x + XCDS - 1) / XCDS : 0;
     const int n_items = n_bh * nb;
     const unsigned per_bh = (unsigned)(nb * nb);
-    const unsigned bytes = (unsigned)n_bh * per_bh;
-    PlanRec* out = recs + (size_t)x * cap;
-    // f / nb^2 for f * nb^2 < 2^32 by one multiplication (nb = 1: the product wraps, handled
-    // apart); f / nb for f < 2^13, nb <= 64 by a full-rate 24-bit multiplication: with
-    // m = ceil(2^19 / nb), f * (m * nb - 2^19) < 2^13 * 64 = 2^19, so the quotient is exact
-    const unsigned magic_bh = 0xffffffffu / per_bh + 1u, magic_nb = ((1u << 19) + (unsigned)nb - 1u) / (unsigned)nb;
-    auto div_bh = [&](unsigned f) { return per_bh == 1u ? f : __umulhi(f, magic_bh); };
+    const unsigned ppb = (per_bh + 7u) / 8u, pad = (ppb + 3u) & ~3u;    // pieces of a pair, and their bytes of bits
+    PlanRec* out = (PlanRec*)order + (size_t)x * cap;
+    int32_t* ids = order + (size_t)x * cap;
+    // f / ppb for f < 2^13 and i / nb for i < 2^12, nb <= 64, by 24-bit multiplications: with m = ceil(2^19 / d) the
+    // quotient is exact as long as f * (m * d - 2^19) < 2^19, and m * d - 2^19 < d <= 2^6; ppb goes up to 2^9, whose
+    // quotients come from one 32-bit multiplication (2^13 * 2^9 < 2^32; ppb = 1: the product wraps, handled apart)
+    const unsigned magic_p = 0xffffffffu / ppb + 1u, magic_nb = ((1u << 19) + (unsigned)nb - 1u) / (unsigned)nb;
+    auto div_p = [&](unsigned f) { return ppb == 1u ? f : __umulhi(f, magic_p); };
     auto div_nb = [&](unsigned f) { return __umul24(f, magic_nb) >> 19; };
 
-    // byte f of this XCD's rows: pair g = f / nb^2, then row-major inside the pair.  Lanes past
-    // the end load the last byte again, so that no load sits behind a branch.
-    unsigned v[SMALL_SWEEPS];
+    int c[PT], item[PT];
+    int live[PT];                                // key-blocks that start below the valid length
 #pragma unroll
-    for (int t = 0; t < SMALL_SWEEPS; ++t) {
-        v[t] = 0;
-        if (1024u * t < bytes) {                  // the same for the whole workgroup
-            const unsigned f = (unsigned)tid + 1024u * t, fc = f < bytes ? f : bytes - 1u;
-            const unsigned g = div_bh(fc);
-            v[t] = mask[(size_t)(g * XCDS + x) * per_bh + (fc - g * per_bh)];
+    for (int k = 0; k < PT; ++k) {
+        const unsigned i = (unsigned)tid + 1024u * k, in = i < (unsigned)n_items ? i : 0u;
+        const unsigned g = div_nb(in);
+        item[k] = (int)(__umul24(g * XCDS + x, nb) + (in - __umul24(g, nb)));
+        c[k] = 0;
+        live[k] = kv_len;
+        if (1024 * k < n_items) {                 // the same for the whole workgroup
+            if (mask == nullptr) c[k] = counts[item[k]];
+            else if (kv_lens != nullptr) live[k] = kv_lens[(int)(g * XCDS + x) / H];
         }
     }
-    for (int g = tid; g < n_bh; g += 1024) {
-        int len = kv_len;
-        if (kv_lens != nullptr) {
-            len = kv_lens[(g * XCDS + x) / H];
-            len = len < 0 ? 0 : (len > N ? N : len);
-        }
-        const int lv = (len + block - 1) / block;
-        live[g] = lv < nb ? lv : nb;
-    }
-    for (int i = tid; i < pmax; i += 1024) arrived[(size_t)x * pmax + i] = 0;
-    rowbits[tid] = 0u;
-    rowbits[tid + 1024] = 0u;
-    if (tid < 128) hist[tid] = 0;
-    __syncthreads();
-
-    // 64 consecutive bytes are the ends of at most a few rows: one ballot, and the first lane
-    // of each row's stretch adds the stretch to the row's word (same-address LDS atomics from
-    // every lane would serialise)
-    int kept = 0;                                 // kept blocks seen by this wavefront
+    if (mask != nullptr) {
+        const unsigned total = (unsigned)n_bh * ppb;
+        unsigned lo[SWEEPS], hi[SWEEPS];
 #pragma unroll
-    for (int t = 0; t < SMALL_SWEEPS; ++t) {
-        if (1024u * t < bytes) {                  // the same for the whole workgroup
+        for (int t = 0; t < SWEEPS; ++t) {
+            lo[t] = hi[t] = 0u;
+            if (1024u * t < total) {              // the same for the whole workgroup
+                // lanes past the end load the last piece again, so that no load sits behind a branch; the last piece
+                // of a pair ends with it: what belongs to the piece before is shifted out
+                const unsigned f = (unsigned)tid + 1024u * t, fc = f < total ? f : total - 1u;
+                const unsigned g = div_p(fc), r = (fc - __umul24(g, ppb)) * 8u;
+                const unsigned char* src = mask + (size_t)(g * XCDS + x) * per_bh;
+                if (nb >= 3) {
+                    const unsigned over = r + 8u > per_bh ? r + 8u - per_bh : 0u;
+                    unsigned long long v;
+                    __builtin_memcpy(&v, src + (r - over), 8);
+                    v >>= 8u * over;
+                    lo[t] = (unsigned)v;
+                    hi[t] = (unsigned)(v >> 32);
+                } else {
+                    for (unsigned e = 0; e < per_bh; ++e) lo[t] |= (unsigned)src[e] << (8u * e);
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < SWEEPS; ++t) {
             const unsigned f = (unsigned)tid + 1024u * t;
-            const bool in = f < bytes;
-            const unsigned i = div_nb(in ? f : 0u), j = (in ? f : 0u) - __umul24(i, nb);
-            const bool keep = in && v[t] != 0u && (int)j < live[div_nb(i)];
-            const unsigned long long bal = __ballot(keep);
-            const unsigned lane = (unsigned)tid & 63u;
-            kept += __popcll(bal);
-            if (in && (j == 0u || lane == 0u)) {
-                const unsigned left = (unsigned)nb - j, room = 64u - lane;
-                const unsigned len = left < room ? left : room;
-                const unsigned long long seg = (bal >> lane) & (len >= 64u ? ~0ull : (1ull << len) - 1ull);
-                const unsigned long long word = seg << j;                      // j + len <= nb <= 64
-                if ((unsigned)word) atomicOr(&rowbits[2u * i], (unsigned)word);
-                if ((unsigned)(word >> 32)) atomicOr(&rowbits[2u * i + 1u], (unsigned)(word >> 32));
+            if (f < total) {
+                const unsigned g = div_p(f);
+                ((unsigned char*)bits)[__umul24(g, pad) + (f - __umul24(g, ppb))] = (unsigned char)byte_bits(lo[t], hi[t]);
             }
         }
     }
-    if ((tid & 63) == 0) kept_sum[tid >> 6] = kept;
+    if (tid <= SMALL_NB) hist[tid] = 0;
     __syncthreads();
+
+    int kept = 0, longest = 0;
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+        const unsigned i = (unsigned)tid + 1024u * k;
+        const bool has = i < (unsigned)n_items;
+        if (mask != nullptr && 1024 * k < n_items) {
+            const unsigned in = has ? i : 0u, g = div_nb(in), at = __umul24(in - __umul24(g, nb), nb), w = (g * pad >> 2) + (at >> 5);
+            const unsigned long long b = ((unsigned long long)bits[w + 1] << 32) | bits[w], up = bits[w + 2];
+            const unsigned s = at & 31u;
+            const unsigned long long row = s ? (b >> s) | (up << (64u - s)) : b;
+            int len = live[k];
+            len = len < 0 ? 0 : (len > N ? N : len);
+            const int blocks = (len + block - 1) / block;
+            const int cols = blocks < nb ? blocks : nb;
+            c[k] = __popcll(row & (cols >= 64 ? ~0ull : (1ull << cols) - 1ull));
+        }
+        if (!has) c[k] = 0;
+        if (has && mask != nullptr) counts[item[k]] = c[k];
+        kept += c[k];
+        longest = c[k] > longest ? c[k] : longest;
+    }
     unsigned tot = 0u;                            // kept key-blocks of this XCD's items
+    int P[PT], slot0[PT];
 #pragma unroll
-    for (int w = 0; w < 16; ++w) tot += (unsigned)kept_sum[w];
-
-#pragma unroll
-    for (int t = 0; t < SMALL_SWEEPS; ++t) {
-        const unsigned f = (unsigned)tid + 1024u * t;
-        if (f < bytes && v[t] != 0u) {
-            const unsigned i = div_nb(f), j = f - __umul24(i, nb), g = div_nb(i);
-            const unsigned lo = rowbits[2u * i], hi = rowbits[2u * i + 1u];
-            const unsigned long long bits = ((unsigned long long)hi << 32) | lo;
-            if ((bits >> j) & 1ull) {
-                const unsigned row = __umul24(g * XCDS + x, nb) + (i - __umul24(g, nb));   // < 2^13
-                index[__umul24(row, nb) + __popcll(bits & ((1ull << j) - 1ull))] = (int)j;
-            }
-        }
-    }
-
-    // plan: thread i takes item i.  Pieces as in split_pieces(), in 32 bits.
-    const bool has = tid < n_items;
-    const int item = has ? (int)(__umul24(div_nb(tid) * XCDS + x, nb) + (tid - __umul24(div_nb(tid), nb))) : 0;
-    const int c = has ? __popc(rowbits[2 * tid]) + __popc(rowbits[2 * tid + 1]) : 0;
-    if (has) counts[item] = c;
-    {                                             // the longest row, to every thread
-        const int mx = wave_max_to_last(c);
-        if ((tid & 63) == 63) wave_max[tid >> 6] = mx;
-    }
-    __syncthreads();
-    int longest = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) longest = wave_max[w] > longest ? wave_max[w] : longest;
-    if (D == 128 && rows_alike(n_items, longest, tot)) {   // the same for the whole workgroup
-        if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost(n_items, longest, tid + 1);
+    for (int k = 0; k < PT; ++k) { P[k] = 1; slot0[k] = -1; }
+    if constexpr (PIECES) {
+        const int sum = wave_scan_inclusive(kept);
+        longest = wave_max_to_last(longest);
+        if (lane == 63) { kept_sum[tid >> 6] = sum; wave_max[tid >> 6] = longest; }
         __syncthreads();
-    }
-    const SplitRule rule = split_rule(D, n_items, longest, tot, alike_cost);
-    int want = 1;
-    if (has && tot != 0u) {
-        unsigned P = rule.p_all ? (unsigned)rule.p_all : (2u * (unsigned)c * (unsigned)rule.g + tot) / (2u * tot);
-        const unsigned by_len = (unsigned)c / SPLIT_MIN_BLOCKS;
-        P = P > by_len ? by_len : P;
-        P = P > (unsigned)SPLIT_MAX_PIECES ? SPLIT_MAX_PIECES : P;
-        want = P < 1u ? 1 : (int)P;
-    }
-    const int first_slot = plan_block_scan(want > 1 ? want : 0, wave_sum, tid);
-    int P = want, slot0 = -1;
-    if (want > 1) {
-        if (first_slot + want <= pmax) slot0 = first_slot; else P = 1;
-    }
-    // piece k holds c(k+1)/P - ck/P key-blocks: c/P, plus one whenever the running remainder wraps
-    const int q = c / P, r = c - q * P;
-    if (has) {
-        int e = 0;
-        for (int k = 0; k < P; ++k) {
-            e += r;
-            const int extra = e >= P;
-            e -= extra ? P : 0;
-            atomicAdd(&hist[nb - (q + extra)], 1);
+        longest = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) { tot += (unsigned)kept_sum[w]; longest = wave_max[w] > longest ? wave_max[w] : longest; }
+        if (D == 128 && rows_alike(n_items, longest, tot)) {   // the same for the whole workgroup
+            if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost<unsigned>(n_items, longest, tid + 1);
+            __syncthreads();
         }
-    }
-    __syncthreads();
-    {
-        const int mine = tid <= nb ? hist[tid] : 0;
-        const int before = plan_block_scan(mine, wave_sum, tid);
-        if (tid <= nb + 1) hist[tid] = before;   // entry nb + 1: all records
-    }
-    __syncthreads();
-    const int n_rec = hist[nb + 1];
-    __syncthreads();                              // everyone has read it before the bins move
-    if (has) {
-        int e = 0, b0 = 0;
-        for (int k = 0; k < P; ++k) {
-            e += r;
-            const int extra = e >= P;
-            e -= extra ? P : 0;
-            PlanRec rec;
-            rec.item = item;
-            rec.blk0 = b0;
-            rec.nblk = q + extra;
-            rec.w = (P > 1) ? (((x * pmax + slot0) << 8) | (k << 4) | (P - 1)) : -1;
-            b0 += rec.nblk;
-            // At launch the dispatcher deals the XCD's workgroups out to its 32 CUs in turn (seen in
-            // the hardware ids of traced launches): CU i starts with the records i, i + 32, ...
-            // Longest-first order would give CU 0 the longest record of every round of 32, so the
-            // odd rounds of the first wave (as many records as the XCD has places) run backwards.
-            // Later records go wherever a place frees up first and stay longest first.
-            int pos = atomicAdd(&hist[nb - rec.nblk], 1);
-            const int round = pos >> 5;
-            if (pos < CUS_PER_XCD * (D == 128 ? 2 : 4) && (round & 1)) {
-                const int left = n_rec - (round << 5);
-                pos = (round << 5) + (left < 32 ? left : 32) - 1 - (pos & 31);
+        const SplitRule rule = split_rule(D, n_items, longest, tot, alike_cost);
+        int want[PT], mine = 0;
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            want[k] = 1;
+            if (1024 * k < n_items && tot != 0u) {
+                unsigned n = rule.p_all ? (unsigned)rule.p_all : (2u * (unsigned)c[k] * (unsigned)rule.g + tot) / (2u * tot);
+                const unsigned by_len = (unsigned)c[k] / SPLIT_MIN_BLOCKS;
+                n = n > by_len ? by_len : n;
+                n = n > (unsigned)SPLIT_MAX_PIECES ? SPLIT_MAX_PIECES : n;
+                want[k] = n < 1u ? 1 : (int)n;
             }
-            out[pos] = rec;
+            mine += want[k] > 1 ? want[k] : 0;
+        }
+        // slots: a scan inside each wavefront, then the totals of the wavefronts before
+        const int incl = wave_scan_inclusive(mine);
+        if (lane == 63) wave_sum[tid >> 6] = incl;
+        __syncthreads();
+        int run = incl - mine;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int t = wave_sum[w];
+            run += w < tid >> 6 ? t : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            if (want[k] > 1) {
+                if (run + want[k] <= pmax) { slot0[k] = run; P[k] = want[k]; }
+                run += want[k];                   // the prefix counts every candidate
+            }
         }
     }
-    const PlanRec none = {-1, 0, 0, -1};
-    for (int i = n_rec + tid; i < cap; i += 1024) out[i] = none;
+    // piece j holds c(j+1)/P - cj/P key-blocks: c/P, plus one whenever the running remainder wraps
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+        if ((unsigned)tid + 1024u * k < (unsigned)n_items) {
+            if (!PIECES || P[k] == 1) {
+                atomicAdd(&hist[nb - c[k]], 1);
+            } else {
+                const int q = c[k] / P[k], r = c[k] - q * P[k];
+                int e = 0;
+                for (int j = 0; j < P[k]; ++j) {
+                    e += r;
+                    const int extra = e >= P[k];
+                    e -= extra ? P[k] : 0;
+                    atomicAdd(&hist[nb - (q + extra)], 1);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int mine = lane < nb ? hist[lane] : 0, upto = wave_scan_inclusive(mine);
+    const int longer = __builtin_amdgcn_readlane(upto, 63), n_rec = longer + hist[nb];
+    if (tid < nb) to[tid] = upto - mine;          // (nb <= 64: wavefront 0)
+    if (tid == 0) to[nb] = longer;
+    __syncthreads();
+    // At launch the dispatcher deals the XCD's workgroups out to its 32 CUs in turn (seen in
+    // the hardware ids of traced launches): CU i starts with the records i, i + 32, ...
+    // Longest-first order would give CU 0 the longest record of every round of 32, so the
+    // odd rounds of the first wave (as many records as the XCD has places) run backwards.
+    // Later records go wherever a place frees up first and stay longest first.
+    auto place = [&](int len) {
+        int pos = atomicAdd(&to[nb - len], 1);
+        const int round = pos >> 5;
+        if (pos < CUS_PER_XCD * (PIECES ? (D == 128 ? 2 : 4) : (D == 128 ? 2 : 3)) && (round & 1)) {
+            const int left = n_rec - (round << 5);
+            pos = (round << 5) + (left < 32 ? left : 32) - 1 - (pos & 31);
+        }
+        return pos;
+    };
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+        if ((unsigned)tid + 1024u * k < (unsigned)n_items) {
+            if constexpr (!PIECES) {
+                ids[place(c[k])] = item[k];
+            } else if (P[k] == 1) {
+                const PlanRec rec = {item[k], 0, c[k], -1};
+                out[place(c[k])] = rec;
+            } else {
+                const int q = c[k] / P[k], r = c[k] - q * P[k];
+                int e = 0, b0 = 0;
+                for (int j = 0; j < P[k]; ++j) {
+                    e += r;
+                    const int extra = e >= P[k];
+                    e -= extra ? P[k] : 0;
+                    const PlanRec rec = {item[k], b0, q + extra, ((x * pmax + slot0[k]) << 8) | (j << 4) | (P[k] - 1)};
+                    b0 += rec.nblk;
+                    out[place(rec.nblk)] = rec;
+                }
+            }
+        }
+    }
+    if constexpr (PIECES) {
+        const PlanRec none = {-1, 0, 0, -1};
+        for (int i = n_rec + tid; i < cap; i += 1024) out[i] = none;
+        for (int i = tid; i < pmax; i += 1024) arrived[(size_t)x * pmax + i] = 0;
+    } else {
+        for (int i = n_rec + tid; i < cap; i += 1024) ids[i] = -1;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1579,36 +1630,152 @@ struct StreamPlan {
     static constexpr __host__ __device__ int v_off(int i) { return (i / SPT % NSV) * TILE + (i % SPT) * 32 * S::RB; }
 };
 
-// Which tiles: at(t, u, moved) is the first key of tile t; the caller stands in tile t - u of the unrolled
-// steps' first tile, u known when compiling, and has called advance in tile UNROLL / SPT - 1 of them or not.
+// Which tiles: at(t, u, moved, ahead) is the first key of tile t; the caller stands in tile t - ahead, which is tile
+// u - ahead of the unrolled steps, both known when compiling, and has called advance in tile UNROLL / SPT - 1 of them or
+// not; next_tile when it has done with a tile.
 // Tiles in order: the dense path.
 template <class P>
 struct AllKeys {
-    __device__ __forceinline__ int at(int t, int, bool) const { return t * P::KTS; }
-    __device__ __forceinline__ void stand(int) {}
+    __device__ __forceinline__ int at(int t, int, bool, int) const { return t * P::KTS; }
+    __device__ __forceinline__ void next_tile() {}
     __device__ __forceinline__ void advance() {}
 };
 
-// The 32-key steps of a list of kept 128-key blocks (four steps = one block = one run of the unrolled loop).
-// The first keys of the current and the next two blocks are at hand, that of the third is under way: a scalar
-// load has a block's time (about 2000 cycles) to arrive.  Past the end of the list: beyond every kv_len.
+// The kept blocks of a row (or of a piece of one), in order.  Up to 64 blocks per side they are the bits of one scalar:
+// from the row of the mask itself (a byte per lane, one ballot) or, where selection wrote lists, from the list; nothing in
+// the loop then waits for memory.  Beyond, they come from the list, the next entry under way (128-token masks: a block is
+// four steps) or 64 at a time, one per lane of `first` (a scalar load shares its counter with the LDS reads in flight, and
+// a 64-key block is one step).  Past the end: NOWHERE, beyond every kv_len.
+template <int BLOCK>
+struct KeptBlocks {
+    static constexpr int NOWHERE = 1 << 23;        // times 128 keys
+    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+    unsigned long long bits;
+    const int32_t* list;                           // null: the bits
+    int n, at, first;
+    __device__ __forceinline__ void load()
+    {
+        if (BLOCK == 128) { first = ((cptr_t)list)[at < n ? at : 0]; return; }
+        const int i = at + (int)(threadIdx.x & 63u);
+        asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=&v"(first) : "v"((i < n ? i : 0) * 4), "s"(list) : "memory");
+        first = i < n ? first : NOWHERE;
+    }
+    __device__ __forceinline__ int next()
+    {
+        if (list == nullptr) {
+            const int j = bits != 0ull ? __builtin_ctzll(bits) : NOWHERE;
+            bits &= bits - 1ull;
+            return j;
+        }
+        if (BLOCK == 128) {
+            const int j = at < n ? first : NOWHERE;
+            ++at;
+            load();
+            return j;
+        }
+        if ((at & 63) == 0) load();
+        return __builtin_amdgcn_readlane(first, at++ & 63);
+    }
+};
+
+// What workgroup wg does: an entry of the plan, or, where every workgroup plans for itself (planned = 0: all rows are
+// on the chip at once and none is long enough to be cut, so their order says little), a row of XCD wg % 8.
+// In the second case, and for the lists wherever the rows come from the mask, it also leaves in the workspace what the
+// planner kernels would have left there.
+template <int BLOCK>
+struct SparseWork {
+    PlanRec rec;
+    KeptBlocks<BLOCK> kept;
+    unsigned long long row;                        // all kept blocks of the row, where they come from the mask
+};
+template <int BLOCK>
+__device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
+{
+    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+    typedef const __attribute__((address_space(4))) i32x4* rptr_t;
+    static_assert(sizeof(PlanRec) == sizeof(i32x4), "one record = one 16-byte scalar load");
+    const int wg = blockIdx.x, slot = (wg % XCDS) * p.chunk + wg / XCDS, lane = threadIdx.x & 63;
+    SparseWork<BLOCK> w;
+    w.rec = {-1, 0, 0, -1};
+    if (!p.planned) {
+        // The dispatcher deals the workgroups of an XCD out to its 32 CUs in turn; rows with the same number (text rows,
+        // the long ones) would meet on the same CU where 32 is a multiple of nb, so every 32 workgroups start 3/8 of the rows on.
+        const int i = wg / XCDS, g = i / p.nb, pair = g * XCDS + wg % XCDS;
+        if (pair * p.nb < p.items) {
+            w.rec.item = pair * p.nb + (i + g * p.nb / CUS_PER_XCD * ((3 * p.nb + 7) / 8)) % p.nb;
+            if (p.mask == nullptr) w.rec.nblk = ((cptr_t)p.counts)[w.rec.item];
+        }
+    } else if (BLOCK == 64) {
+        w.rec.item = ((cptr_t)p.order)[slot];
+        if (w.rec.item >= 0) w.rec.nblk = ((cptr_t)p.counts)[w.rec.item];
+    } else {
+        const i32x4 raw = ((rptr_t)p.order)[slot];
+        w.rec = {raw[0], raw[1], raw[2], raw[3]};
+    }
+    const int item = w.rec.item;
+    w.kept.list = nullptr;
+    w.kept.bits = w.row = 0ull;
+    w.kept.n = w.rec.nblk;
+    w.kept.at = w.kept.first = 0;
+    if (item >= 0) {
+        if (p.mask != nullptr) {                   // nb <= 64
+            int kv_len = p.kv_len;
+            if (p.kv_lens != nullptr) kv_len = ((cptr_t)p.kv_lens)[item / p.nb / p.H];
+            kv_len = kv_len > p.N ? p.N : kv_len;
+            const unsigned char byte = p.mask[(size_t)item * p.nb + (lane < p.nb ? lane : 0)];
+            const bool keep = byte != 0 && lane < p.nb && lane * BLOCK < kv_len;
+            w.kept.bits = w.row = __builtin_amdgcn_ballot_w64(keep);
+            if (!p.planned) {
+                w.rec.nblk = __popcll(w.row);
+            } else if (BLOCK == 128 && w.rec.w >= 0) {
+                const int rank = __popcll(w.row & ((1ull << lane) - 1ull)) - w.rec.blk0;
+                w.kept.bits = __builtin_amdgcn_ballot_w64(keep && rank >= 0 && rank < w.rec.nblk);
+            }
+        } else if (p.nb <= 64) {
+            // every lane sends a 1 to the lane of its entry (lanes without one to that of the first)
+            const int j = p.index[(size_t)item * p.nb + w.rec.blk0 + (lane < w.rec.nblk ? lane : 0)];
+            const unsigned long long row = __builtin_amdgcn_ballot_w64(__builtin_amdgcn_ds_permute(4 * j, 1) != 0);
+            w.kept.bits = w.rec.nblk > 0 ? row : 0ull;
+        } else {
+            w.kept.list = p.index + (size_t)item * p.nb + w.rec.blk0;
+            if (BLOCK == 128 && w.rec.nblk > 0) w.kept.load();
+        }
+    }
+    return w;
+}
+
+// The workspace as the planner kernels would have left it: called behind the loop, whose waits for copies would wait for
+// these stores as well.
+template <int BLOCK>
+__device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork<BLOCK>& w)
+{
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    if (p.mask != nullptr && (w.row >> lane & 1ull) != 0ull && w.rec.blk0 == 0)
+        p.index[(size_t)w.rec.item * p.nb + __popcll(w.row & ((1ull << lane) - 1ull))] = lane;
+    if (!p.planned && lane == 0) {
+        const int x = blockIdx.x % XCDS, i = blockIdx.x / XCDS;
+        if (BLOCK == 64) p.order[x * p.chunk + i] = w.rec.item;
+        else ((PlanRec*)p.order)[x * p.chunk + i] = w.rec;
+        if (w.rec.item >= 0) p.counts[w.rec.item] = w.rec.nblk;
+        if (BLOCK == 128 && i < p.pmax) p.arrived[x * p.pmax + i] = 0;
+    }
+}
+
+// The 32-key steps of kept 128-key blocks (four steps = one block = one run of the unrolled loop).  The first keys of
+// the current and the next two blocks are at hand.
 template <class P>
 struct KeptKeys {
     static_assert(P::KTS == 32 && P::UNROLL == 4, "");
-    static constexpr int NOWHERE = 1 << 30;
-    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
-    cptr_t list;
-    int n, next;                                   // blocks; the next one to be requested
-    int b0, b1, b2, coming;
-    __device__ __forceinline__ KeptKeys(cptr_t list_, int n_) : list(list_), n(n_), next(4)
+    KeptBlocks<128> kept;
+    int b0, b1, b2;
+    __device__ __forceinline__ KeptKeys(const KeptBlocks<128>& kept_) : kept(kept_)
     {
-        const int i1 = list[n > 1 ? 1 : 0], i2 = list[n > 2 ? 2 : 0];
-        coming = list[n > 3 ? 3 : 0];
-        b0 = list[0] * 128;
-        b1 = n > 1 ? i1 * 128 : NOWHERE;
-        b2 = n > 2 ? i2 * 128 : NOWHERE;
+        b0 = kept.next() * 128;
+        b1 = kept.next() * 128;
+        b2 = kept.next() * 128;
     }
-    __device__ __forceinline__ int at(int, int u, bool moved) const
+    __device__ __forceinline__ int at(int, int u, bool moved, int) const
     {
         const int r = moved ? u - 4 : u;
         return (r < 4 ? b0 : r < 8 ? b1 : b2) + r % 4 * 32;
@@ -1617,35 +1784,31 @@ struct KeptKeys {
     {
         b0 = b1;
         b1 = b2;
-        b2 = next - 1 < n ? coming * 128 : NOWHERE;
-        coming = list[next < n ? next : 0];
-        ++next;
+        b2 = kept.next() * 128;
     }
-    __device__ __forceinline__ void stand(int) {}
+    __device__ __forceinline__ void next_tile() {}
 };
 
-// A list of kept 64-key blocks, a block one tile.  Lane l of `first` holds the first key of entry base + l (past the end
-// of the list: beyond every kv_len); an entry is read out of its lane, so that the loop waits for no load of the list
-// (a scalar load shares its counter with the LDS reads in flight) until it has gone through nearly 64 of them.
+// Kept 64-key blocks, a block one tile: the first keys of the current tile and the three after it.
 template <class P>
 struct KeptTiles {
-    static_assert(P::KTS == 64 && P::SPT == 1 && P::KLEAD >= P::VLEAD, "");
-    static constexpr int NOWHERE = 1 << 30;
-    const int32_t* list;
-    int n, base, first;
-    __device__ __forceinline__ KeptTiles(const int32_t* list_, int n_) : list(list_), n(n_) { load(0); }
-    __device__ __forceinline__ void load(int from)
+    static_assert(P::KTS == 64 && P::SPT == 1 && P::KLEAD == 3 && P::VLEAD == 2, "");
+    KeptBlocks<64> kept;
+    int b0, b1, b2, b3;
+    __device__ __forceinline__ KeptTiles(const KeptBlocks<64>& kept_) : kept(kept_)
     {
-        base = from;
-        const int i = base + (int)(threadIdx.x & 63u);
-        asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=&v"(first) : "v"((i < n ? i : 0) * 4), "s"(list) : "memory");
-        first = i < n ? first * 64 : NOWHERE;
+        b0 = kept.next() * 64;
+        b1 = kept.next() * 64;
+        b2 = kept.next() * 64;
+        b3 = kept.next() * 64;
     }
-    __device__ __forceinline__ int at(int t, int, bool) const { return __builtin_amdgcn_readlane(first, t - base); }
-    // tile t is the current one: from here to the next call entries up to t + 1 + KLEAD are asked for
-    __device__ __forceinline__ void stand(int t)
+    __device__ __forceinline__ int at(int, int, bool, int ahead) const { return ahead == 0 ? b0 : ahead == 1 ? b1 : ahead == 2 ? b2 : b3; }
+    __device__ __forceinline__ void next_tile()
     {
-        if (t - base >= 63 - P::KLEAD) load(t);
+        b0 = b1;
+        b1 = b2;
+        b2 = b3;
+        b3 = kept.next() * 64;
     }
     __device__ __forceinline__ void advance() {}
 };
@@ -1688,11 +1851,11 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
 #pragma unroll
     for (int b = -P::KLEAD; b < (P::SPT == 1 ? -1 : 0); ++b) {
         if (b + P::VLEAD >= 0) {
-            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD, b + P::VLEAD, false), kv_len);
+            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD, b + P::VLEAD, false, b + P::VLEAD), kv_len);
 #pragma unroll
             for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + P::VLEAD) * P::TILE);
         }
-        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD, b + P::KLEAD, false), kv_len);
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD, b + P::KLEAD, false, b + P::KLEAD), kv_len);
 #pragma unroll
         for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + P::KLEAD) * P::TILE);
     }
@@ -1711,8 +1874,8 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     first_qk<S, D, 0, 0, true>(x, st[0]);
     first_qk<S, D, 0, 0, false>(x, st[0]);
     if constexpr (P::SPT == 1) {                  // the barrier before tile 0: K_1, V_0 may be read
-        const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1, P::VLEAD - 1, false), kv_len);
-        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1, P::KLEAD - 1, false), kv_len);
+        const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1, P::VLEAD - 1, false, P::VLEAD - 1), kv_len);
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1, P::KLEAD - 1, false, P::KLEAD - 1), kv_len);
         wait_vmcnt<P::LOOSE>();
         phase_barrier();
 #pragma unroll
@@ -1720,7 +1883,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
 #pragma unroll
         for (int e = 0; e < LC; ++e) copy_k(kb, e, 0);
     }
-    mask_step<S>(st[0], keys.at(0, 0, false) + wk * 32, kv_len, lane);
+    mask_step<S>(st[0], keys.at(0, 0, false, 0) + wk * 32, kv_len, lane);
 #pragma unroll
     for (int q = 0; q < S::NQ; ++q) {
         x.m[q] = fmaxf(step_max<S>(st[0], q, c) + REF_UP, REF_LOWEST);  // (a key group may have no valid key at all)
@@ -1758,13 +1921,13 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         else step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, hook);
         soft_close<S, D>(x, sc, c, pw);
         const int t = i / P::SPT;
-        mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1, U + 1, false) + wk * 32 : keys.at((i + 1) / 2, 0, false) + (i + 1) % 2 * 32, kv_len, lane);
+        mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1, U + 1, false, 1) + wk * 32 : keys.at((i + 1) / 2, 0, false, 0) + (i + 1) % 2 * 32, kv_len, lane);
         if (RT ? i % P::SPT == 0 : FIRST_OF_TILE) {
             constexpr bool MOVE = !RT && U / P::SPT == P::UNROLL / P::SPT - 1;
             if constexpr (MOVE) keys.advance();
-            keys.stand(t);
-            vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, U / P::SPT + P::VLEAD, MOVE), kv_len);
-            kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, U / P::SPT + P::KLEAD, MOVE), kv_len);
+            vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, U / P::SPT + P::VLEAD, MOVE, P::VLEAD), kv_len);
+            kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, U / P::SPT + P::KLEAD, MOVE, P::KLEAD), kv_len);
+            keys.next_tile();
             wait_vmcnt<P::LOOSE>();
             phase_barrier();
             if constexpr (RT) {
@@ -1963,9 +2126,9 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     static_assert(P::QT == 64 && P::WK == WK, "one item = 64 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
-    const int wg = blockIdx.x;
-    const int item = ((cptr_t)p.order)[(size_t)(wg % XCDS) * p.chunk + wg / XCDS];
+    const auto work = sparse_work<64>(p);
+    const int item = work.rec.item;
+    if (item < 0 || work.rec.nblk <= 0) leave_plan<64>(p, work);
     if (item < 0) return;
     const int bh = item / p.nq;
     const int qi = item % p.nq;
@@ -1982,18 +2145,20 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
     const int q0 = qi * 64 + wave / P::WK * 16 * P::NQ;
     char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
-    const int n = ((cptr_t)p.counts)[item];
+    const int n = work.rec.nblk;
 
     StreamRegs<S, D> x;
     if (n <= 0 || qi * 64 >= kv_len) {            // nothing kept, or padding rows only: the rows are zero
+        if (n > 0) leave_plan<64>(p, work);
         if (wave % P::WK != 0) return;
 #pragma unroll
         for (int q = 0; q < P::NQ; ++q) x.ls[q][0] = 0.f;
         stream_output_rows<S, D>(x, O, q0, 0, p.N, lane, out_stage);
         return;
     }
-    KeptTiles<P> keys(p.index + (size_t)item * p.nb, n);
+    KeptTiles<P> keys(work.kept);
     stream_attend<P, false>(x, lds, Q, K, V, q0, kv_len, p.c, n - 1, keys, wave, lane);
+    leave_plan<64>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
     stream_merge<P>(x, lds, wave, lane);
     if (wave % P::WK != 0) return;
@@ -2027,13 +2192,10 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     static_assert(P::QT == 128, "one record = 128 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
-    const int wg = blockIdx.x;
-    typedef const __attribute__((address_space(4))) i32x4* rptr_t;
-    static_assert(sizeof(PlanRec) == sizeof(i32x4), "one record = one 16-byte scalar load");
-    const i32x4 raw = ((rptr_t)p.order)[(size_t)(wg % XCDS) * p.chunk + wg / XCDS];
-    const PlanRec rec = {raw[0], raw[1], raw[2], raw[3]};
+    const auto work = sparse_work<128>(p);
+    const PlanRec rec = work.rec;
     const int item = rec.item;
+    if (rec.nblk <= 0) leave_plan<128>(p, work);
     if (item < 0) return;
     const int bh = item / p.nq;
     const int qi = item % p.nq;
@@ -2062,8 +2224,9 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
         return;
     }
     // Whole blocks: what lies at or beyond kv_len in a row's last block is masked, at most three steps.
-    KeptKeys<P> keys((cptr_t)(p.index + (size_t)item * p.nb + rec.blk0), rec.nblk);
+    KeptKeys<P> keys(work.kept);
     stream_attend<P, true>(x, lds, Q, K, V, q0, kv_len, p.c, rec.nblk * 4 - 1, keys, wave, lane);
+    leave_plan<128>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
     if (rec.w < 0) {                              // the whole item
         stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
@@ -2169,13 +2332,10 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
 
     __shared__ __attribute__((aligned(1024))) char lds[4 * G::TILE_BYTES];
 
-    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
-    const int wg = blockIdx.x;
-    typedef const __attribute__((address_space(4))) i32x4* rptr_t;
-    static_assert(sizeof(PlanRec) == sizeof(i32x4), "one record = one 16-byte scalar load");
-    const i32x4 raw = ((rptr_t)p.order)[(size_t)(wg % XCDS) * p.chunk + wg / XCDS];
-    const PlanRec rec = {raw[0], raw[1], raw[2], raw[3]};
+    auto work = sparse_work<128>(p);
+    const PlanRec rec = work.rec;
     const int item = rec.item;
+    if (rec.nblk <= 0) leave_plan<128>(p, work);
     if (item < 0) return;
     const int bh = item / p.nq;
     const int qi = item % p.nq;
@@ -2200,9 +2360,12 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
     const bool qvalid = qrow < kv_len;
 
     // 64-key tiles of this piece (two per kept 128-key block; the item's last block may have one)
-    cptr_t list = (cptr_t)(p.index + (size_t)item * p.nb + rec.blk0);
     int T = rec.nblk * 2;
-    if (rec.nblk > 0 && (list[rec.nblk - 1] * 2 + 1) * KT >= kv_len) T -= 1;
+    if (rec.nblk > 0) {
+        typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+        const int end = work.kept.list != nullptr ? ((cptr_t)work.kept.list)[rec.nblk - 1] : 63 - __builtin_clzll(work.kept.bits);
+        if ((end * 2 + 1) * KT >= kv_len) T -= 1;
+    }
     f32x16 acc[DB];
 #pragma unroll
     for (int i = 0; i < DB; ++i)
@@ -2212,14 +2375,13 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
         write_output<D>(O, acc, 0.f, qrow, false, p.N, h);
         return;
     }
-    auto key_of = [&](int t) -> int { return (list[t >> 1] * 2 + (t & 1)) * KT; };
     auto k_stage = [&](int t) -> char* { return lds + (t & 1) * G::TILE_BYTES; };
     auto v_stage = [&](int t) -> char* { return lds + (2 + (t & 1)) * G::TILE_BYTES; };
-    // first keys of tiles j+1, j+2, j+3 (0 past the end), fetched ahead of their use
-    const int key0 = key_of(0);
-    int kn1 = (1 < T) ? key_of(1) : 0;
-    int kn2 = (2 < T) ? key_of(2) : 0;
-    int kn3 = (3 < T) ? key_of(3) : 0;
+    // first keys of tiles j+1, j+2, j+3 (not used from tile T on)
+    const int key0 = work.kept.next() * 128;
+    int kn1 = key0 + KT;
+    int kn2 = work.kept.next() * 128;
+    int kn3 = kn2 + KT;
 
     // Q and K_0 first: S_0 needs only these; V_0 and K_1 land while it is computed.
     u32x4 qraw[KS];
@@ -2274,9 +2436,10 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
         if (j + 2 < T) wait_vmcnt<LPT>();         // V_{j+1} landed
         else wait_vmcnt<0>();
         kn1 = kn2; kn2 = kn3;
-        kn3 = (j + 4 < T) ? key_of(j + 4) : 0;
+        kn3 = (j & 1) == 0 ? work.kept.next() * 128 : kn3 + KT;
     }
 
+    leave_plan<128>(p, work);
     // Output straight from registers: with four workgroups on the CU, row-wise through LDS was 2-3 % slower.
     if (rec.w < 0) {                              // the whole item
         write_output<D>(O, acc, sm.l, qrow, qvalid, p.N, h);
@@ -2528,33 +2691,46 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     hipStream_t s = (hipStream_t)stream;
 
     const int xcd_items = plan_items(B, H, nb);
-    if (mask != nullptr && block == 128 && nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && xcd_items * nb <= SMALL_BYTES) {
-        hipLaunchKernelGGL(plan_small_kernel, dim3(XCDS), dim3(1024), 0, s, mask, pr.kv_lens, pr.kv_len, N, block,
-                           H, B * H, nb, w.chunk, w.pmax, D, counts, index, (PlanRec*)order,
-                           (int32_t*)(ws + w.arrived_off));
-    } else {
-        if (mask != nullptr) {
-            hipLaunchKernelGGL(compact_mask_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
-                               mask, (int)rows, nb, block, pr.kv_len, pr.kv_lens, H * nb, N, counts, index);
-            if (hipGetLastError() != hipSuccess) return RAPID_ERR_DEVICE;
-        }
-        if (block == 128)
-            hipLaunchKernelGGL(plan_split_kernel, dim3(XCDS), dim3(1024), 0, s, counts, B * H, nb, w.chunk,
-                               w.pmax, D, (PlanRec*)order, (int32_t*)(ws + w.arrived_off));
-        else
-            hipLaunchKernelGGL(plan_kernel, dim3(XCDS), dim3(1024), 0, s, counts, B * H, nb, w.chunk, order);
+    int32_t* arrived = (int32_t*)(ws + w.arrived_off);
+    // All rows on the chip at once and none that could be cut: no plan, every workgroup finds its row by itself.  us, plan
+    // launches / without: H = 2, N = 256 16.5 / 10.5; D = 64, H = 4, N = 2048 under 64-token masks 15.4 / 10.2 (density 0.1),
+    // 23.6 / 18.5 (all ones); B = 2, H = 24, N = 1024 under 64-token masks, D = 64, 768 rows 18.3 / 15 (0.3).
+    const int places = CUS_PER_XCD * (block == 64 ? (D == 128 ? 2 : 3) : (D == 128 ? 2 : 4));
+    const bool planned = xcd_items > places || (block == 128 && nb >= 2 * SPLIT_MIN_BLOCKS);
+    const long long mask_pieces = nb <= SMALL_NB ? (long long)(xcd_items / nb) * (((nb * nb + 7) / 8 + 3) / 4 * 4) : 0;
+    const bool small = nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && mask_pieces <= SMALL_PIECES;
+    const bool lists = mask != nullptr && (planned ? !small : nb > SMALL_NB);      // compacted by a kernel of its own
+    if (lists)
+        hipLaunchKernelGGL(compact_mask_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
+                           mask, (int)rows, nb, block, pr.kv_len, pr.kv_lens, H * nb, N, counts, index);
+    if (lists && hipGetLastError() != hipSuccess) return RAPID_ERR_DEVICE;
+    if (planned && small) {
+        // (the instructions of this kernel are fetched anew in every call: a third of the code, 6.3 -> 5.2 us at H = 24, N = 4608)
+        const bool one = xcd_items <= 1024 && mask_pieces <= 4096;
+        const auto kernel = block == 128 ? (one ? plan_small_kernel<true, 1, 4> : plan_small_kernel<true, SMALL_PER_THREAD, SMALL_PIECES / 1024>)
+                                         : (one ? plan_small_kernel<false, 1, 4> : plan_small_kernel<false, SMALL_PER_THREAD, SMALL_PIECES / 1024>);
+        hipLaunchKernelGGL(kernel, dim3(XCDS), dim3(1024), 0, s, mask, pr.kv_lens, pr.kv_len, N, block,
+                           H, B * H, nb, w.chunk, w.pmax, D, counts, order, arrived);
     }
+    else if (planned && block == 128)
+        hipLaunchKernelGGL(plan_split_kernel, dim3(XCDS), dim3(1024), 0, s, counts, B * H, nb, w.chunk,
+                           w.pmax, D, (PlanRec*)order, arrived);
+    else if (planned)
+        hipLaunchKernelGGL(plan_kernel, dim3(XCDS), dim3(1024), 0, s, counts, B * H, nb, w.chunk, order);
     if (hipGetLastError() != hipSuccess) return RAPID_ERR_DEVICE;
 
     AttnParams p{};
     fill_common(p, pr);
+    p.mask = lists ? nullptr : mask;
     p.counts = counts; p.order = order; p.index = index;
-    p.arrived = (int32_t*)(ws + w.arrived_off);
+    p.planned = planned;
+    p.arrived = arrived;
+    p.pmax = w.pmax;
     p.partial = ws + w.partial_off;
     p.nq = nb;
     p.items = (int)rows;
     p.chunk = w.chunk;
-    p.block = block; p.nb = nb; p.sub_shift = block == 128 ? 1 : 0;
+    p.nb = nb;
     const dim3 grid((unsigned)w.chunk * XCDS);
     if (block == 128) {
         // D = 64: 64 queries per wavefront read LDS half as often, but a record takes longer; it wins where every place

@@ -210,3 +210,40 @@ def test_many_rows_joint_tensors_and_lengths():
         grown = [torch.nn.functional.pad(t[b:b + 1], (0, 0, 0, nb * block - N)) for t in (q, k, v, o)]
         ref = reference(*grown[:3], mask[b:b + 1], block, kv, D ** -0.5)
         check(grown[3], ref, kv, f"sample {b}")
+
+
+# ---- where the plan comes from: every workgroup for itself (all rows on the chip at once), one planner launch from the
+# mask, or compaction and a planner; edges of each rule, with per-sample lengths
+@pytest.mark.parametrize("block,B,H,nb,D", [
+    (64, 1, 1, 1, 64), (64, 3, 5, 2, 128), (64, 3, 8, 21, 128), (64, 3, 8, 22, 128), (64, 4, 8, 24, 64), (64, 4, 8, 25, 64),
+    (64, 2, 40, 64, 64), (64, 2, 40, 63, 128), (64, 1, 8, 65, 64), (64, 3, 8, 65, 128), (64, 300, 8, 2, 64), (64, 200, 40, 3, 64),
+    (64, 9, 120, 33, 64), (128, 2, 32, 8, 128), (128, 5, 13, 8, 128), (128, 4, 32, 8, 64), (128, 3, 8, 15, 64), (128, 3, 8, 16, 64),
+    (128, 64, 40, 1, 64), (128, 900, 40, 1, 64), (128, 8, 24, 36, 64), (128, 8, 40, 64, 64), (128, 2, 8, 65, 128)])
+def test_counts_lists_and_plan_wherever_they_are_made(block, B, H, nb, D):
+    N = nb * block - 5
+    g = torch.Generator(device="cuda").manual_seed(B + H + nb)
+    q, k, v = (torch.randn((B, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    lens = torch.randint(0, N + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lens[0], lens[-1] = N + 3, N - block // 2
+    density = torch.rand((B, H, nb, 1), generator=g, device="cuda")
+    mask = (torch.rand((B, H, nb, nb), generator=g, device="cuda") < density).to(torch.uint8) * 200
+    mask[:, :, -1] = 1
+    ws = torch.full((ra.rapid_attn_joint_workspace_bytes(B, H, N, D, block),), 0xa5, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, 7.0)
+    ra.rapid_attn_joint([(q, k, v, o)], mask, block, kv_lens=lens, workspace=ws)
+    counts, order, index, geometry = read_plan(ws.cpu().numpy(), B, H, nb, D, block)
+    kv = lens.clamp(0, N).view(B, 1, 1, 1)
+    kept = (mask != 0) & (torch.arange(nb, device="cuda") * block < kv)
+    assert (torch.from_numpy(counts.copy()) == kept.sum(-1).flatten().cpu()).all()
+    kept = kept.reshape(-1, nb).cpu()
+    for r in torch.randint(0, kept.shape[0], (300,)).tolist() + [0, kept.shape[0] - 1]:
+        assert index[r, :counts[r]].tolist() == kept[r].nonzero()[:, 0].tolist(), r
+    check_plan(counts, order, geometry, B, H, nb, block, D)
+    for b in sorted({0, B // 2, B - 1}):
+        n = int(kv[b])
+        if n == 0:
+            assert (o[b] == 0).all()
+            continue
+        for h in sorted({0, H - 1}):
+            one = [torch.nn.functional.pad(t[b:b + 1, h:h + 1], (0, 0, 0, 5)) for t in (q, k, v, o)]
+            check(one[3], reference(*one[:3], mask[b:b + 1, h:h + 1], block, n, D ** -0.5), n, f"sample {b} head {h}")
