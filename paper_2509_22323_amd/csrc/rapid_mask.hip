@@ -4,12 +4,14 @@
 //
 // Two kernels.  block_mean_kernel streams Q and K once (HBM-bound: 2 bytes per element read,
 // 4 * D bytes per block written) and leaves fp32 block means in the workspace.
-// select_blocks_kernel gives every mask row to one wavefront: scores against all key-block
-// means, softmax, and the cumulative-mass cut found without sorting, by bisection over the
-// bit patterns of the (positive) probabilities.
+// select_blocks_small_kernel (up to 256 blocks per side) and select_blocks_kernel give every mask
+// row to one wavefront: scores against all key-block means, softmax, and the cumulative-mass cut
+// found without sorting, by bisection over the bit patterns of the (positive) probabilities.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "rapid_internal.h"
 #include "rapid_mask.h"
@@ -48,40 +50,55 @@ __device__ __forceinline__ void sample_blocks(const QKView& v, int b, int block,
     first_text = v.text_start < kv ? v.text_start / block : nb;
 }
 
-// means[(which, bh, i), :] = mean over the valid rows of block i of Q (which = 0) or K (1).
-// 256 threads: D/8 column groups of 8 elements x 256/(D/8) row groups; every thread adds up
-// its rows in increasing order, the row groups are then added in increasing order.
-template <int D>
-__global__ __launch_bounds__(256) void block_mean_kernel(const QKView v, int block, int nb, float* __restrict__ means,
-                                                         size_t which_stride)
+// means[(which, bh, i), :] = mean over the valid rows of block i of Q (which = 0) or K (1).  256 threads: D/8 column
+// groups of 8 elements x 256/(D/8) row groups; every thread adds up its rows in increasing order, the row groups are
+// then added in increasing order.  Bound by HBM: all loads of a whole block are requested before the first is used, and
+// STREAMED ones are non-temporal (H = 24, N = 16896, D = 128, 208 MB: 39.0 us in a loop, 36.8 requested at once, 33.1 =
+// 6.3 TB/s non-temporal; N = 4608 13.9 / 13.0 / 11.0).  Not where attention reads the same Q and K next in the same call:
+// what the caches keep of them is worth more there (123.2 us against 124.1 for the whole call at N = 4608).
+template <int D, int BLOCK, bool STREAMED>
+__global__ __launch_bounds__(256) void block_mean_kernel(const QKView v, int nb, float* __restrict__ means, size_t which_stride)
 {
-    constexpr int CG = D / 8, RG = 256 / CG;
+    constexpr int CG = D / 8, RG = 256 / CG, RPT = BLOCK / RG;
     __shared__ float red[RG][D];
     const int i = blockIdx.x % nb, bh = blockIdx.x / nb, which = blockIdx.y;
     const int b = bh / v.H, h = bh % v.H;
-    const uint16_t* s0 = (which ? v.k0 : v.q0) + (size_t)b * v.sb0 + (size_t)h * v.sh;
-    const uint16_t* s1 = v.q1 ? (which ? v.k1 : v.q1) + (size_t)b * v.sb1 + (size_t)h * v.sh - (size_t)v.n0 * v.sn : s0;
+    const int lo = i * BLOCK;
+    // (two segments: the first ends at a multiple of 128 tokens, so a block lies in one of them)
+    const uint16_t* src = lo < v.n0 ? (which ? v.k0 : v.q0) + (size_t)b * v.sb0 : (which ? v.k1 : v.q1) + (size_t)b * v.sb1 - (size_t)v.n0 * v.sn;
     const int kv = valid_tokens(v, b);
-    const int lo = i * block;
-    int hi = lo + block;
+    int hi = lo + BLOCK;
     hi = hi < kv ? hi : kv;                        // kv <= N: a ragged last block ends at N
     const int c = threadIdx.x % CG, g = threadIdx.x / CG;
+    src += (size_t)h * v.sh + c * 8;
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    for (int r = lo + g; r < hi; r += RG) {
-        const u32x4 x = *(const u32x4*)((r < v.n0 ? s0 : s1) + (size_t)r * v.sn + c * 8);
+    auto add = [&](u32x4 x) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             acc[2 * e] += __uint_as_float(x[e] << 16);
             acc[2 * e + 1] += __uint_as_float(x[e] & 0xffff0000u);
         }
+    };
+    if (hi - lo == BLOCK) {
+        u32x4 x[RPT];
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const u32x4* at = (const u32x4*)(src + (size_t)(lo + g + u * RG) * v.sn);
+            x[u] = STREAMED ? __builtin_nontemporal_load(at) : *at;
+        }
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) add(x[u]);
+    } else {
+        for (int r = lo + g; r < hi; r += RG) add(*(const u32x4*)(src + (size_t)r * v.sn));
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[g][c * 8 + e] = acc[e];
     __syncthreads();
     if (threadIdx.x < D) {
         float s = 0.f;
+#pragma unroll
         for (int gg = 0; gg < RG; ++gg) s += red[gg][threadIdx.x];
         const int cnt = hi - lo;
         means[which * which_stride + ((size_t)bh * nb + i) * D + threadIdx.x] = cnt > 0 ? s / (float)cnt : 0.f;
@@ -204,113 +221,133 @@ __global__ __launch_bounds__(256) void select_blocks_kernel(const float* __restr
     });
 }
 
-// The same for up to SMALL_NB mask blocks per side (every shape of the paper's models): one
-// workgroup per 16 rows of one (sample, head).  The key-block means of the head pass through
-// LDS in chunks of 64 (coalesced loads, rows padded by four floats so that the 16-byte reads
-// of consecutive lanes fall on different banks) and serve all 16 rows; a wavefront owns four
-// rows.  The cut needs neither a sort nor a search here: block j is kept iff the blocks with
-// a strictly larger probability hold less than tau of the mass, a sum each lane forms for its
-// own blocks over all the others (nb^2 work per row, trivial at this size).
+// The same for up to SMALL_NB mask blocks per side (every shape of the paper's models): 16 wavefronts take 16 rows of one
+// (sample, head).  Scores by fp32 MFMAs, a tile of 16 key-blocks per wavefront straight from the means in memory (a lane's
+// 16 bytes of a row serve four MFMAs: the contraction index is a dummy); then a row per wavefront, its scores in registers.
+// The cut: up to 64 blocks, block j is kept iff the blocks with a strictly larger probability hold less than tau of
+// the mass, a sum each lane forms over all the others; beyond, the bisection of select_blocks_kernel, which ends as soon
+// as one value is left between the bounds (a dozen rounds of the thirty for scores that are spread out).  H = 24, 132
+// blocks, D = 128: 19.2 us with scores by vector instructions from LDS and the first cut, 13.0 by MFMAs and thirty rounds,
+// 11.6 now; 36 blocks 6.7 / 6.5 now.
 constexpr int SMALL_NB = 256;
-constexpr int SMALL_RPW = 1;                   // mask rows per wavefront
-constexpr int SMALL_ROWS = 4 * SMALL_RPW;     // per workgroup
+constexpr int SMALL_ROWS = 16;                 // per workgroup
 
-template <int D>
-__global__ __launch_bounds__(256) void select_blocks_small_kernel(const float* __restrict__ qmean,
-                                                                  const float* __restrict__ kmean, const QKView v,
-                                                                  int block, int nb, float tau, float scale,
-                                                                  const RowSink sink)
+// v of all 64 lanes combined, the same in all of them: shifts inside rows of 16 lanes, then the last lane of rows 0 and 2
+// to rows 1 and 3, then lane 31 to rows 2 and 3; a lane without a source takes `none`.  All lanes active.
+template <class Op>
+__device__ __forceinline__ float wave_combine(float v, float none, Op op)
 {
-    constexpr int KROW = D + 4;
-    __shared__ __attribute__((aligned(16))) float kch[64 * KROW];
-    __shared__ __attribute__((aligned(16))) float qs[SMALL_ROWS][D];
-    __shared__ float ps[SMALL_ROWS][SMALL_NB];
+    auto moved = [&](auto ctrl, auto rows) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+    };
+    typedef std::integral_constant<int, 0xf> all;
+    v = op(v, moved(std::integral_constant<int, 0x111>(), all()));
+    v = op(v, moved(std::integral_constant<int, 0x112>(), all()));
+    v = op(v, moved(std::integral_constant<int, 0x114>(), all()));
+    v = op(v, moved(std::integral_constant<int, 0x118>(), all()));
+    v = op(v, moved(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xa>()));
+    v = op(v, moved(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xc>()));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float wave_total(float v) { return wave_combine(v, 0.f, [](float a, float b) { return a + b; }); }
+
+template <int D, int U>                        // U: 64-block stretches of a row
+__global__ __launch_bounds__(1024, 4) void select_blocks_small_kernel(const float* __restrict__ qmean,
+                                                                   const float* __restrict__ kmean, const QKView v,
+                                                                   int block, int nb, float tau, float scale,
+                                                                   const RowSink sink)
+{
+    constexpr int ROW = 64 * U + 4;
+    __shared__ __attribute__((aligned(16))) float ps[SMALL_ROWS][ROW];
     const int groups = (nb + SMALL_ROWS - 1) / SMALL_ROWS;
     const size_t bh = blockIdx.x / groups;
     int live, first_text;
     sample_blocks(v, (int)(bh / v.H), block, nb, live, first_text);
     const int i0 = (blockIdx.x % groups) * SMALL_ROWS;
-    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    if (wv * 16 < live) {                          // (U <= 4: a tile per wavefront)
+        const int kr = wv * 16 + n, qr = i0 + n;
+        const f32x4* kp = (const f32x4*)(kmean + (bh * nb + (kr < live ? kr : live - 1)) * D) + g;
+        const f32x4* qp = (const f32x4*)(qmean + (bh * nb + (qr < live ? qr : live - 1)) * D) + g;
+        f32x4 kf[D / 16], qf[D / 16];
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) { kf[t] = kp[4 * t]; qf[t] = qp[4 * t]; }
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) asm volatile("" : "+v"(kf[t]), "+v"(qf[t]));    // all on their way at once
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][e], qf[t][e], acc, 0, 0, 0);
+        f32x4 out;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[r] = scale * acc[r];
+        *(f32x4*)(&ps[n][wv * 16 + 4 * g]) = out;  // key-blocks 4 g .. of the tile, query row n
+    }
+    __syncthreads();
 
-    constexpr int KPT = 64 * (D / 4) / 256;                    // 16-byte pieces of a chunk per thread
-    const float* kb = kmean + bh * nb * D;
-    f32x4 kreg[KPT];
-    auto fetch_chunk = [&](int j0) {                           // requested early, stored to LDS later
-#pragma unroll
-        for (int u = 0; u < KPT; ++u) {
-            const int e = tid + u * 256, jr = e / (D / 4), d4 = e % (D / 4);
-            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-            kreg[u] = (j0 + jr < live) ? *(const f32x4*)(kb + (size_t)(j0 + jr) * D + 4 * d4) : zero;
-        }
-    };
-    fetch_chunk(0);
-    for (int e = tid; e < SMALL_ROWS * D; e += 256) {
-        const int r = e / D, d = e % D;
-        qs[r][d] = (i0 + r < live) ? qmean[(bh * nb + i0 + r) * D + d] : 0.f;
+    const int i = i0 + wv;
+    if (i >= nb) return;
+    const size_t mrow = bh * nb + i;
+    if (i >= live) {
+        write_row(sink, mrow, nb, lane, [](int) { return false; });
+        return;
     }
-    for (int j0 = 0; j0 < live; j0 += 64) {
-        __syncthreads();                                       // previous chunk consumed (and qs written)
+    float e[U], mx = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < KPT; ++u) {
-            const int e = tid + u * 256, jr = e / (D / 4), d4 = e % (D / 4);
-            *(f32x4*)(kch + jr * KROW + 4 * d4) = kreg[u];
+    for (int u = 0; u < U; ++u) {
+        e[u] = lane + 64 * u < live ? ps[wv][lane + 64 * u] : -INFINITY;
+        mx = fmaxf(mx, e[u]);
+    }
+    mx = wave_combine(mx, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+    float part = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        e[u] = lane + 64 * u < live ? expf(e[u] - mx) : 0.f;
+        part += e[u];
+    }
+    const float target = tau * wave_total(part);
+    const bool text_row = i >= first_text;
+    bool kept[U];
+    if constexpr (U == 1) {
+        ps[wv][lane] = e[0];                       // (a wavefront's own row; zeros past the live blocks)
+        __builtin_amdgcn_wave_barrier();
+        float above = 0.f;                         // mass of the blocks that come before this one
+        for (int j = 0; j < live; j += 4) {
+            const f32x4 x = *(const f32x4*)(&ps[wv][j]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) above += x[r] > e[0] ? x[r] : 0.f;
         }
-        if (j0 + 64 < live) fetch_chunk(j0 + 64);              // the next chunk travels during this one's work
-        __syncthreads();
-        float dot[SMALL_RPW];
+        kept[0] = above < target;
+    } else {
+        unsigned lo = 0u, hi = 0x3F800001u;        // mass(lo) >= target > mass(hi) = 0
+        int from_lo = 64 * U, from_hi = 0;         // values at or above either
+        if (!(target > 0.f)) lo = hi = ~0u;        // not a number: only what is kept in any case
+        while (hi - lo > 1u && from_lo - from_hi > 1) {
+            const unsigned mid = lo + (hi - lo) / 2u;
+            float m = 0.f;
+            int from_mid = 0;
 #pragma unroll
-        for (int r = 0; r < SMALL_RPW; ++r) dot[r] = 0.f;
-        const float* kr = kch + lane * KROW;
-#pragma unroll 4
-        for (int d4 = 0; d4 < D / 4; ++d4) {
-            const f32x4 kv = *(const f32x4*)(kr + 4 * d4);
-#pragma unroll
-            for (int r = 0; r < SMALL_RPW; ++r) {
-                const f32x4 qv = *(const f32x4*)(&qs[wv * SMALL_RPW + r][4 * d4]);
-                dot[r] += qv[0] * kv[0];
-                dot[r] += qv[1] * kv[1];
-                dot[r] += qv[2] * kv[2];
-                dot[r] += qv[3] * kv[3];
+            for (int u = 0; u < U; ++u) {
+                const bool in = __float_as_uint(e[u]) >= mid;
+                m += in ? e[u] : 0.f;
+                from_mid += __popcll(__builtin_amdgcn_ballot_w64(in));
             }
+            const bool enough = wave_total(m) >= target;
+            if (enough) { lo = mid; from_lo = from_mid; }
+            else { hi = mid; from_hi = from_mid; }
         }
-        if (j0 + lane < live) {
 #pragma unroll
-            for (int r = 0; r < SMALL_RPW; ++r) ps[wv * SMALL_RPW + r][j0 + lane] = scale * dot[r];
-        }
+        for (int u = 0; u < U; ++u) kept[u] = __float_as_uint(e[u]) >= lo;
     }
-    __builtin_amdgcn_wave_barrier();                           // a wavefront reads only the rows it wrote
-
-    for (int r = 0; r < SMALL_RPW; ++r) {
-        const int row = wv * SMALL_RPW + r, i = i0 + row;
-        if (i >= nb) break;
-        const size_t mrow = bh * nb + i;
-        if (i >= live) {
-            write_row(sink, mrow, nb, lane, [](int) { return false; });
-            continue;
-        }
-        float mx = -INFINITY;
-        for (int j = lane; j < live; j += 64) mx = fmaxf(mx, ps[row][j]);
-        mx = wave_max(mx);
-        float part = 0.f;
-        for (int j = lane; j < live; j += 64) {
-            const float e = expf(ps[row][j] - mx);
-            ps[row][j] = e;
-            part += e;
-        }
-        const float target = tau * wave_sum(part);
-        const bool text_row = i >= first_text;
-        write_row(sink, mrow, nb, lane, [&](int j) {
-            if (j >= live) return false;
-            if (text_row || j >= first_text || j == i || tau >= 1.0f) return true;
-            const float mine = ps[row][j];
-            float above = 0.f;                             // mass of the blocks that come before j
-            for (int k2 = 0; k2 < live; ++k2) {
-                const float e = ps[row][k2];
-                above += (e > mine) ? e : 0.f;
-            }
-            return above < target;
-        });
-    }
+    write_row(sink, mrow, nb, lane, [&](int j) {
+        if (j >= live) return false;
+        bool k = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) k = j / 64 == u ? kept[u] : k;
+        return k || text_row || j >= first_text || j == i || tau >= 1.0f;
+    });
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -344,19 +381,27 @@ int run_select(const QKView& v, int B, int D, int block, float tau, float scale,
     const size_t which_stride = (size_t)B * H * nb * D;
     hipStream_t s = (hipStream_t)stream;
     const dim3 g1((unsigned)(nb * B * H), 2u);
-    if (D == 64) hipLaunchKernelGGL((block_mean_kernel<64>), g1, dim3(256), 0, s, v, block, nb, means, which_stride);
-    else hipLaunchKernelGGL((block_mean_kernel<128>), g1, dim3(256), 0, s, v, block, nb, means, which_stride);
+    const auto pick_mean = [&](auto d, auto bl) {
+        constexpr int DD = decltype(d)::value, BB = decltype(bl)::value;
+        return sink.counts != nullptr ? block_mean_kernel<DD, BB, false> : block_mean_kernel<DD, BB, true>;
+    };
+    typedef std::integral_constant<int, 64> c64;
+    typedef std::integral_constant<int, 128> c128;
+    const auto mean = D == 64 ? (block == 64 ? pick_mean(c64(), c64()) : pick_mean(c64(), c128()))
+                              : (block == 64 ? pick_mean(c128(), c64()) : pick_mean(c128(), c128()));
+    hipLaunchKernelGGL(mean, g1, dim3(256), 0, s, v, nb, means, which_stride);
     if (hipGetLastError() != hipSuccess) return RAPID_ERR_DEVICE;
 
     const int rows = B * H * nb;
     if (nb <= SMALL_NB) {
         const dim3 gs((unsigned)(B * H * ((nb + SMALL_ROWS - 1) / SMALL_ROWS)));
-        if (D == 64)
-            hipLaunchKernelGGL((select_blocks_small_kernel<64>), gs, dim3(256), 0, s, means, means + which_stride, v, block,
-                               nb, tau, scale, sink);
-        else
-            hipLaunchKernelGGL((select_blocks_small_kernel<128>), gs, dim3(256), 0, s, means, means + which_stride, v, block,
-                               nb, tau, scale, sink);
+        const auto pick = [&](auto d) {
+            constexpr int DD = decltype(d)::value;
+            return nb <= 64 ? select_blocks_small_kernel<DD, 1> : nb <= 128 ? select_blocks_small_kernel<DD, 2>
+                 : nb <= 192 ? select_blocks_small_kernel<DD, 3> : select_blocks_small_kernel<DD, 4>;
+        };
+        const auto select = D == 64 ? pick(c64()) : pick(c128());
+        hipLaunchKernelGGL(select, gs, dim3(1024), 0, s, means, means + which_stride, v, block, nb, tau, scale, sink);
         return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
     }
     const dim3 g2((unsigned)((rows + 3) / 4));

@@ -58,6 +58,40 @@ def test_mask_matches_the_oracle(B, H, N, D, block, kv_len, text_start, gain, ta
         assert got[:, :, :live, :live].mean() < 0.95           # it does prune on these inputs
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("nb", [1, 15, 16, 17, 63, 64, 65, 128, 129, 192, 193, 256])
+def test_edges_of_row_tiles_and_stretches(nb, D):
+    """16 rows per workgroup, 16 key-blocks per wavefront, 64 blocks per stretch of a row; a cut last block."""
+    N = 64 * nb
+    q, k, _ = wl.make_qkv(1, 2, N, D, N - 19, seed=nb, gain=3.0, pad_fill="nan")
+    check(q, k, 64, N - 19, N, 0.8)
+
+
+@pytest.mark.parametrize("nb", [40, 65, 132])
+def test_equal_scores_and_rows_without_a_number(nb):
+    """Blocks of equal probability come or go together; a query-block whose mean is not a number keeps only what is
+    kept in any case."""
+    D, N = 64, 64 * nb
+    q = torch.randn((1, 1, N, D), generator=torch.Generator().manual_seed(nb)).cuda().to(torch.bfloat16)
+    k = torch.zeros_like(q)
+    k[:, :, 64 * 7:64 * 9] = 1.0                   # two blocks alike, the others alike
+    q[:, :, 64 * 3] = float("nan")
+    q[:, :, 64 * 5:64 * 6] = 4.0                   # looks at the two, and at nothing else
+    m = torch.full((1, 1, nb, nb), 9, dtype=torch.uint8, device="cuda")
+    ra.rapid_mask_select(q, k, m, 64, N, N - 64, 0.9)
+    m = m[0, 0].cpu()
+    forced = torch.eye(nb, dtype=torch.uint8)
+    forced[:, -1] = 1
+    assert (m[3] == forced[3]).all()
+    forced[5, 7:9] = 1
+    assert (m[5] == forced[5]).all()
+    rest = [j for j in range(nb - 1) if j not in (7, 8)]
+    for i in range(nb - 1):
+        if i not in (3, 5):
+            assert m[i, 7] == m[i, 8] or i in (7, 8)
+            assert len({int(m[i, j]) for j in rest if j != i}) == 1, i
+
+
 def test_more_than_256_blocks_per_row_take_the_bisection_kernel():
     B, H, N, D, block, kv_len = 1, 1, 64 * 300, 64, 64, 64 * 300 - 17
     q, k, _ = wl.make_qkv(B, H, N, D, kv_len, seed=19, gain=3.0)
