@@ -59,21 +59,23 @@ __global__ __launch_bounds__(THREADS) void cache_residual_kernel(const uint16_t*
         const u32x4* av = (const u32x4*)a;
         const u32x4* bv = (const u32x4*)b;
         u32x4* ov = (u32x4*)out;
-        // consecutive lanes touch consecutive 16-byte vectors; the UNROLL accesses of a lane
-        // are one grid-width apart
-        for (size_t v0 = tid; v0 < nvec; v0 += nthreads * UNROLL) {
+        // consecutive lanes touch consecutive 16-byte vectors; the UNROLL accesses of a lane are one workgroup apart, so
+        // that a workgroup reads and writes one stretch of 16 KB per tensor (one grid apart: 15.6 -> 14.6 us at one layer's
+        // hidden states, 28 MB per tensor, 118 -> 110 us at eight of them = 6.2 TB/s; 2 or 8 accesses are up to 5 % slower)
+        for (size_t v0 = (size_t)blockIdx.x * THREADS * UNROLL + threadIdx.x; v0 < nvec; v0 += nthreads * UNROLL) {
             u32x4 x[UNROLL], y[UNROLL];
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
-                const size_t v = v0 + (size_t)u * nthreads;
+                const size_t v = v0 + (size_t)u * THREADS;
                 // read once, never again: non-temporal loads keep the two input streams from
                 // displacing each other and the output in the caches (+14 % at one layer's hidden
-                // states, +20 % on large tensors; the same hint on the stores made it slower)
+                // states, +20 % on large tensors; the same hint on the stores only moves the time to whoever
+                // reads the output next: 6 % off this call on large tensors, 7 to 17 % onto the two together)
                 if (v < nvec) { x[u] = __builtin_nontemporal_load(&av[v]); y[u] = __builtin_nontemporal_load(&bv[v]); }
             }
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
-                const size_t v = v0 + (size_t)u * nthreads;
+                const size_t v = v0 + (size_t)u * THREADS;
                 if (v < nvec) {
                     u32x4 r;
 #pragma unroll
