@@ -54,8 +54,8 @@ __device__ __forceinline__ void sample_blocks(const QKView& v, int b, int block,
 // groups of 8 elements x 256/(D/8) row groups; every thread adds up its rows in increasing order, the row groups are
 // then added in increasing order.  Bound by HBM: all loads of a whole block are requested before the first is used, and
 // STREAMED ones are non-temporal (H = 24, N = 16896, D = 128, 208 MB: 39.0 us in a loop, 36.8 requested at once, 33.1 =
-// 6.3 TB/s non-temporal; N = 4608 13.9 / 13.0 / 11.0).  Not where attention reads the same Q and K next in the same call:
-// what the caches keep of them is worth more there (123.2 us against 124.1 for the whole call at N = 4608).
+// 6.3 TB/s non-temporal; N = 4608 13.9 / 13.0 / 11.0).  Only where Q and K are more than the caches keep for the attention
+// that reads them next: at N = 4608 (57 MB) selection and attention in one call take 123.2 us, 124.1 when streamed.
 template <int D, int BLOCK, bool STREAMED>
 __global__ __launch_bounds__(256) void block_mean_kernel(const QKView v, int nb, float* __restrict__ means, size_t which_stride)
 {
@@ -381,9 +381,10 @@ int run_select(const QKView& v, int B, int D, int block, float tau, float scale,
     const size_t which_stride = (size_t)B * H * nb * D;
     hipStream_t s = (hipStream_t)stream;
     const dim3 g1((unsigned)(nb * B * H), 2u);
+    const bool streamed = 4.0 * B * H * v.N * D > 128e6;       // half of the 256 MB memory-side cache
     const auto pick_mean = [&](auto d, auto bl) {
         constexpr int DD = decltype(d)::value, BB = decltype(bl)::value;
-        return sink.counts != nullptr ? block_mean_kernel<DD, BB, false> : block_mean_kernel<DD, BB, true>;
+        return streamed ? block_mean_kernel<DD, BB, true> : block_mean_kernel<DD, BB, false>;
     };
     typedef std::integral_constant<int, 64> c64;
     typedef std::integral_constant<int, 128> c128;
