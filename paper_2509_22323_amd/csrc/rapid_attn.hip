@@ -119,6 +119,8 @@ struct AttnParams {
     int chunk;               // ceil(items / XCDS)
     int whole, cut;          // dense: whole items of an XCD, pieces of each of the others
     int nb;                  // mask blocks per side (sparse only)
+    int segs;                // sparse: plan segments that hold items, min(XCDS, B*H)
+    unsigned seg_magic;      // ceil(2^32 / segs)
     int planned;             // sparse: 1 when the plan is in `order`, 0 when every workgroup plans for itself
     int pmax;                // sparse, 128-token tiles: partial-result slots per XCD
     float c;                 // scale * log2(e)
@@ -269,6 +271,13 @@ struct PlanRec {
     int w;        // -1: the whole item; else (first partial slot << 8) | (piece << 4) | (P - 1)
 };
 constexpr int CUS_PER_XCD = 32;                  // MI355X: 256 CUs in 8 XCDs
+// Segments of the plan that the chip is dealt out to, and the CUs that work on one: an XCD's, or, with few (sample, head)
+// pairs, its share of all of them (see entry_of).
+constexpr __host__ __device__ int segments(int BH, int nb, int block)
+{
+    return nb >= 24 && BH < (block == 128 ? XCDS : XCDS / 2 + 1) ? BH : XCDS;
+}
+constexpr __host__ __device__ int segment_cus(int BH, int nb, int block) { return CUS_PER_XCD * XCDS / segments(BH, nb, block); }
 constexpr int SPLIT_MIN_BLOCKS = 8;
 constexpr int SPLIT_MAX_PIECES = 16;
 constexpr int SPLIT_SLOTS = 256;                 // partial-result slots per XCD (the rule needs < 256)
@@ -279,7 +288,9 @@ constexpr int ENTRY_COST = 2, PIECE_COST = 2;    // in key-blocks of time at D =
 
 // The rule of one XCD.  P(c) = round(c * g / total) pieces for an item with c kept key-blocks
 // (g granules: pieces of about total / g), or p_all pieces for every item when that is set;
-// in both cases at most c / SPLIT_MIN_BLOCKS and SPLIT_MAX_PIECES, at least 1.
+// in both cases at most c / SPLIT_MIN_BLOCKS and SPLIT_MAX_PIECES, at least 1.  A segment of more than 32 CUs: as many in
+// place of 32, but no more granules than partial-result slots: they are handed out in item order, and the text rows, which
+// need them most, come last (H = 2, N = 16896, density 0.1, D = 128: 282 us without that limit).
 //   D = 128: g = 32 CUs x 2.5.  Rows that are all about alike (the longest within 1/9 of the
 //     mean: an all-ones mask) are not told apart by their lengths; what matters then is how
 //     many rounds the 64 places of the XCD need, so p_all is the P that minimises
@@ -292,9 +303,9 @@ struct SplitRule {
 
 // cost of cutting every one of n_items rows of max_c blocks into P pieces, D = 128 (T: wide enough for n_items * P * max_c)
 template <class T>
-__device__ __forceinline__ T split_alike_cost(int n_items, int max_c, int P)
+__device__ __forceinline__ T split_alike_cost(int cus, int n_items, int max_c, int P)
 {
-    const T places = CUS_PER_XCD * 2;
+    const T places = cus * 2;
     const T rounds = ((T)n_items * P + places - 1) / places;
     return rounds * ((max_c + P - 1) / P + ENTRY_COST + (P > 1 ? PIECE_COST : 0));
 }
@@ -306,13 +317,12 @@ __device__ __forceinline__ bool rows_alike(int n_items, int max_c, unsigned long
 
 // `costs` holds split_alike_cost for P = 1 .. SPLIT_MAX_PIECES (used at D = 128 when the rows are alike)
 template <class T>
-__device__ __forceinline__ SplitRule split_rule(int D, int n_items, int max_c, unsigned long long total, const T* costs)
+__device__ __forceinline__ SplitRule split_rule(int D, int cus, int pmax, int n_items, int max_c, unsigned long long total, const T* costs)
 {
     SplitRule r;
     r.p_all = 0;
     const bool alike = rows_alike(n_items, max_c, total);
     if (D == 128) {
-        r.g = CUS_PER_XCD * 5 / 2;
         if (alike && total != 0ull) {
             T best = costs[0];
             r.p_all = 1;
@@ -320,9 +330,10 @@ __device__ __forceinline__ SplitRule split_rule(int D, int n_items, int max_c, u
             for (int P = 2; P <= top; ++P)
                 if (costs[P - 1] < best) { best = costs[P - 1]; r.p_all = P; }
         }
-    } else {
-        r.g = CUS_PER_XCD * (alike ? 12 : 4);
     }
+    const auto granules = [&](int n) { return D == 128 ? n * 5 / 2 : n * (alike ? 12 : 4); };
+    const int one = granules(CUS_PER_XCD), all = granules(cus) < pmax ? granules(cus) : pmax;
+    r.g = all > one ? all : one;
     return r;
 }
 
@@ -387,9 +398,9 @@ __global__ __launch_bounds__(1024) void plan_split_kernel(const int32_t* __restr
     for (int i = tid; i < cap; i += 1024) out[i] = none;
     __syncthreads();
     const unsigned long long tot = total;
-    if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost<long long>(n_items, longest, tid + 1);
+    if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost<long long>(segment_cus(BH, nb, 128), n_items, longest, tid + 1);
     __syncthreads();
-    const SplitRule rule = split_rule(D, n_items, longest, tot, alike_cost);
+    const SplitRule rule = split_rule(D, segment_cus(BH, nb, 128), pmax, n_items, longest, tot, alike_cost);
     // partial-result slots in item order: thread t owns the items [lo, hi)
     const int per = (n_items + 1023) / 1024;
     const int lo = tid * per < n_items ? tid * per : n_items;
@@ -571,10 +582,10 @@ __global__ __launch_bounds__(1024) void plan_small_kernel(
 #pragma unroll
         for (int w = 0; w < 16; ++w) { tot += (unsigned)kept_sum[w]; longest = wave_max[w] > longest ? wave_max[w] : longest; }
         if (D == 128 && rows_alike(n_items, longest, tot)) {   // the same for the whole workgroup
-            if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost<unsigned>(n_items, longest, tid + 1);
+            if (tid < SPLIT_MAX_PIECES) alike_cost[tid] = split_alike_cost<unsigned>(segment_cus(BH, nb, 128), n_items, longest, tid + 1);
             __syncthreads();
         }
-        const SplitRule rule = split_rule(D, n_items, longest, tot, alike_cost);
+        const SplitRule rule = split_rule(D, segment_cus(BH, nb, 128), pmax, n_items, longest, tot, alike_cost);
         int want[PT], mine = 0;
 #pragma unroll
         for (int k = 0; k < PT; ++k) {
@@ -632,15 +643,16 @@ __global__ __launch_bounds__(1024) void plan_small_kernel(
     __syncthreads();
     // At launch the dispatcher deals the XCD's workgroups out to its 32 CUs in turn (seen in
     // the hardware ids of traced launches): CU i starts with the records i, i + 32, ...
-    // Longest-first order would give CU 0 the longest record of every round of 32, so the
-    // odd rounds of the first wave (as many records as the XCD has places) run backwards.
+    // Longest-first order would give CU 0 the longest record of every round of 32, so the second
+    // and the fourth round of the first wave (as many records as the XCD has places) run backwards.
     // Later records go wherever a place frees up first and stay longest first.
+    const int cus = segment_cus(BH, nb, PIECES ? 128 : 64);              // records of a round
     auto place = [&](int len) {
         int pos = atomicAdd(&to[nb - len], 1);
-        const int round = pos >> 5;
-        if (pos < CUS_PER_XCD * (PIECES ? (D == 128 ? 2 : 4) : (D == 128 ? 2 : 3)) && (round & 1)) {
-            const int left = n_rec - (round << 5);
-            pos = (round << 5) + (left < 32 ? left : 32) - 1 - (pos & 31);
+        const int first = pos < 3 * cus ? cus : 3 * cus, at = pos - first;    // of the second, of the fourth round
+        if (at >= 0 && at < cus && (first == cus || (PIECES && D == 64))) {
+            const int left = n_rec - first;
+            pos = first + (left < cus ? left : cus) - 1 - at;
         }
         return pos;
     };
@@ -1682,7 +1694,7 @@ struct KeptBlocks {
 };
 
 // What workgroup wg does: an entry of the plan, or, where every workgroup plans for itself (planned = 0: all rows are
-// on the chip at once and none is long enough to be cut, so their order says little), a row of XCD wg % 8.
+// on the chip at once and none is long enough to be cut, so their order says little), a row of its segment.
 // In the second case, and for the lists wherever the rows come from the mask, it also leaves in the workspace what the
 // planner kernels would have left there.
 template <int BLOCK>
@@ -1691,19 +1703,48 @@ struct SparseWork {
     KeptBlocks<BLOCK> kept;
     unsigned long long row;                        // all kept blocks of the row, where they come from the mask
 };
+// Its entry: the dispatcher deals workgroups out to the 8 XCDs in turn, so segment x = wg % 8 is XCD x's.  Fewer (sample,
+// head) pairs than XCDs (a rank of a model whose heads are dealt out over ranks) would leave XCDs idle: from 24 rows per pair
+// on the workgroups are dealt out to the segments that hold items, each of which then runs on its share of the chip.  The
+// K/V of a head are in several L2s then, which pays least where little is kept of many keys and pairs and XCDs do not
+// divide, so not for 5 to 7 pairs under 64-token masks.  us, one XCD per pair / spread, densities 0.1 0.3 0.8:
+//   128-token masks, D = 128, H = 1, N = 16896 127 297 746 / 63 123 275; 2, 8192 57 104 211 / 42 63 126; B = 2, H = 2,
+//     N = 16896 147 350 894 / 92 211 547; 3, 2, 4480 41 48 90 / 37 45 86; D = 64, 1, 2, 16896 94 219 537 / 58 112 247
+//   64-token masks, D = 128, 1, 2, 16896 186 357 875 / 177 186 313; 2, 2, 3840 47 51 61 / 39 40 40; the slowest of 1 to 4
+//     pairs 1, 3, 16896 186 359 874 / 191 199 377, of 6 pairs 3, 2, 16896 191 369 899 / 225 349 712
+//   few rows: D = 128, 1, 2, 1024 (8 rows per pair) 20.8 / 21.2, 2048 30.6 30.9 39.8 / 31.1 31.0 40.4
+// The segments without items come last.
+__device__ __forceinline__ void entry_of(const AttnParams& p, int& seg, int& i)
+{
+    const unsigned wg = blockIdx.x;
+    seg = wg % XCDS;
+    i = wg / XCDS;
+    if (p.segs < XCDS) {                           // the same for the whole launch
+        // (the quotient is exact below 2^32 / segs; segs = 1: the magic number wraps to 0)
+        i = p.segs == 1 ? wg : __umulhi(wg, p.seg_magic);
+        seg = wg - i * p.segs;
+        if (i >= p.chunk) {
+            const int over = wg - p.segs * p.chunk;
+            seg = __builtin_amdgcn_readfirstlane(p.segs + over / p.chunk);    // (a division is vector instructions)
+            i = __builtin_amdgcn_readfirstlane(over % p.chunk);
+        }
+    }
+}
 template <int BLOCK>
 __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
 {
     typedef const __attribute__((address_space(4))) int32_t* cptr_t;
     typedef const __attribute__((address_space(4))) i32x4* rptr_t;
     static_assert(sizeof(PlanRec) == sizeof(i32x4), "one record = one 16-byte scalar load");
-    const int wg = blockIdx.x, slot = (wg % XCDS) * p.chunk + wg / XCDS, lane = threadIdx.x & 63;
+    int seg, i;
+    entry_of(p, seg, i);
+    const int slot = seg * p.chunk + i, lane = threadIdx.x & 63;
     SparseWork<BLOCK> w;
     w.rec = {-1, 0, 0, -1};
     if (!p.planned) {
         // The dispatcher deals the workgroups of an XCD out to its 32 CUs in turn; rows with the same number (text rows,
         // the long ones) would meet on the same CU where 32 is a multiple of nb, so every 32 workgroups start 3/8 of the rows on.
-        const int i = wg / XCDS, g = i / p.nb, pair = g * XCDS + wg % XCDS;
+        const int g = i / p.nb, pair = g * XCDS + seg;
         if (pair * p.nb < p.items) {
             w.rec.item = pair * p.nb + (i + g * p.nb / CUS_PER_XCD * ((3 * p.nb + 7) / 8)) % p.nb;
             if (p.mask == nullptr) w.rec.nblk = ((cptr_t)p.counts)[w.rec.item];
@@ -1757,7 +1798,8 @@ __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork
     if (p.mask != nullptr && (w.row >> lane & 1ull) != 0ull && w.rec.blk0 == 0)
         p.index[(size_t)w.rec.item * p.nb + __popcll(w.row & ((1ull << lane) - 1ull))] = lane;
     if (!p.planned && lane == 0) {
-        const int x = blockIdx.x % XCDS, i = blockIdx.x / XCDS;
+        int x, i;
+        entry_of(p, x, i);
         if (BLOCK == 64) p.order[x * p.chunk + i] = w.rec.item;
         else ((PlanRec*)p.order)[x * p.chunk + i] = w.rec;
         if (w.rec.item >= 0) p.counts[w.rec.item] = w.rec.nblk;
@@ -2698,7 +2740,7 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     // All rows on the chip at once and none that could be cut: no plan, every workgroup finds its row by itself.  us, plan
     // launches / without: H = 2, N = 256 16.5 / 10.5; D = 64, H = 4, N = 2048 under 64-token masks 15.4 / 10.2 (density 0.1),
     // 23.6 / 18.5 (all ones); B = 2, H = 24, N = 1024 under 64-token masks, D = 64, 768 rows 18.3 / 15 (0.3).
-    const int places = CUS_PER_XCD * (block == 64 ? (D == 128 ? 2 : 3) : (D == 128 ? 2 : 4));
+    const int places = segment_cus(B * H, nb, block) * (block == 64 ? (D == 128 ? 2 : 3) : (D == 128 ? 2 : 4));
     const bool planned = xcd_items > places || (block == 128 && nb >= 2 * SPLIT_MIN_BLOCKS);
     const long long mask_pieces = nb <= SMALL_NB ? (long long)(xcd_items / nb) * (((nb * nb + 7) / 8 + 3) / 4 * 4) : 0;
     const bool small = nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && mask_pieces <= SMALL_PIECES;
@@ -2727,6 +2769,8 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     p.mask = lists ? nullptr : mask;
     p.counts = counts; p.order = order; p.index = index;
     p.planned = planned;
+    p.segs = segments(B * H, nb, block);
+    p.seg_magic = 0xffffffffu / (unsigned)p.segs + 1u;
     p.arrived = arrived;
     p.pmax = w.pmax;
     p.partial = ws + w.partial_off;

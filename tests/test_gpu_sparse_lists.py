@@ -77,6 +77,29 @@ def test_lists_longer_than_a_wavefront_holds(D):
     check(o, reference(q, k, v, mask, block, kv, D ** -0.5), kv, f"D={D}")
 
 
+@pytest.mark.parametrize("nb", [23, 24, 66])
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("H", [1, 2, 3, 4, 5, 7, 8])
+def test_pairs_dealt_out_over_the_chip(H, block, nb):
+    """Fewer (sample, head) pairs than XCDs, on either side of the rows from which they are dealt out to all of them,
+    with one planner launch and with two, long rows cut: every entry done once, lists and plan as ever."""
+    D = 128 if (H + nb) % 2 else 64
+    N, kv = nb * block, nb * block - 45
+    g = torch.Generator(device="cuda").manual_seed(H * nb + block)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = (torch.rand((1, H, nb, nb), generator=g, device="cuda") < 0.2).to(torch.uint8)
+    mask[:, :, -3:] = 1                            # (text rows)
+    mask[:, 0, 5] = 0
+    ws = torch.full((ra.rapid_attn_workspace_bytes(1, H, N, D, block),), 0xa5, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, 7.0)
+    ra.rapid_attn_block_sparse(q, k, v, o, mask, block, kv, workspace=ws)
+    check(o, reference(q, k, v, mask, block, kv, D ** -0.5), kv, f"H={H} nb={nb} block={block}")
+    counts, order, index, geo = read_plan(ws.cpu().numpy(), 1, H, nb, D, block)
+    assert (counts == mask.sum(-1).flatten().cpu().numpy()).all()
+    cut = check_plan(counts, order, geo, 1, H, nb, block, D)
+    assert cut or block == 64
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("block", [64, 128])
 def test_reference_of_the_exponents_moves(D, block):
