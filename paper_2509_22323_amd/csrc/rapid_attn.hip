@@ -25,7 +25,7 @@
 //                  several tiles ahead of their use.
 // Kernels:
 //   attn_dense_stream_kernel<D> dense: 256 queries per workgroup (the last, partly filled round of an XCD
-//                               in halves or quarters), on the 16x16x32 stream described there
+//                               in halves, quarters or pieces of 192), on the 16x16x32 stream described there
 //   attn_dense_pp_kernel<D>     dense, small problems: 32 queries per workgroup, the keys split between
 //                               two groups of wavefronts
 //   attn_sparse_sg_kernel<D>    sparse, 128-token mask tiles: one four-wavefront workgroup per plan
@@ -117,7 +117,7 @@ struct AttnParams {
     int nq;                  // query tiles per (sample, head)
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
-    int whole, cut;          // dense: whole items of an XCD, pieces of each of the others
+    int whole, cut;          // dense: whole items of an XCD, pieces of each of the others (3: pieces of 192 queries)
     int nb;                  // mask blocks per side (sparse only)
     int segs;                // sparse: plan segments that hold items, min(XCDS, B*H)
     unsigned seg_magic;      // ceil(2^32 / segs)
@@ -2064,6 +2064,7 @@ __device__ __forceinline__ void stream_merge(StreamRegs<typename P::S, P::D>& x,
 // queries (32 in the quarters), 64 KB, two workgroups per CU.
 template <int D> struct DensePlan {
     typedef StreamPlan<128, 2, 8, 1, 2, 4, 4> Whole;
+    typedef StreamPlan<128, 1, 8, 1, 2, 4, 4> Whole1;    // (dense_item_192)
     typedef StreamPlan<128, 2, 4, 2, 1, 4, 4> Half;
     typedef StreamPlan<128, 1, 4, 2, 1, 4, 4> Quarter;
     static constexpr int LDS = Whole::LDS;
@@ -2075,13 +2076,14 @@ template <> struct DensePlan<64> {
     static constexpr int LDS = Whole::LDS;
 };
 
+// One wavefront's part of an item whose first query is q00: the queries from q0 on, stored up to `end`; `stage` bytes into the
+// LDS its output goes through.
 template <class P>
-__device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int bh, int q00)
+__device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int bh, int q00, int q0, int end, int wave, int stage)
 {
     typedef typename P::S S;
     constexpr int D = P::D;
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int kv_len = p.kv_len;
     if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
         kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
@@ -2091,14 +2093,13 @@ __device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int b
     const int smp = bh / p.H, head = bh % p.H;
     const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
     const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
-    const int q0 = q00 + wave / P::WK * 16 * P::NQ;        // this wavefront's queries
-    char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
+    char* out_stage = lds + stage;
     StreamRegs<S, D> x;
     if (q00 >= kv_len) {                          // padding rows only: zero
         if (wave % P::WK != 0) return;
 #pragma unroll
         for (int q = 0; q < S::NQ; ++q) x.ls[q][0] = 0.f;
-        stream_output_rows<S, D>(x, O, q0, 0, p.N, lane, out_stage);
+        stream_output_rows<S, D>(x, O, q0, 0, end, lane, out_stage);
         return;
     }
     AllKeys<P> keys;
@@ -2110,11 +2111,50 @@ __device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int b
         if (wave % P::WK != 0) return;
         // (its rows go through LDS that only it has read: see out_stage)
     }
-    stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
+    stream_output_rows<S, D>(x, O, q0, kv_len, end, lane, out_stage);
+}
+template <class P>
+__device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int bh, int q00)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    dense_wave<P>(p, lds, bh, q00, q00 + wave / P::WK * 16 * P::NQ, p.N, wave, wave * (16 * P::NQ * (P::D * 2 + 16)));
+}
+
+// 192 queries: the wavefronts of a SIMD take 32 and 16 (of 32 and 32, or none, a SIMD with two wavefronts would take as long
+// as for 256); the same barriers and copies in both halves of the workgroup.
+constexpr int DENSE_192 = 192;
+template <class P, class P1>
+__device__ __forceinline__ void dense_item_192(const AttnParams& p, char* lds, int bh, int q00, int end)
+{
+    static_assert(P::NW == 8 && P1::NW == 8 && P::NQ == 2 && P1::NQ == 1 && P::WK == 1 && P1::WK == 1, "");
+    static_assert(P::UNROLL == P1::UNROLL && P::LC == P1::LC && P::LDS == P1::LDS, "the same barriers and copies");
+    constexpr int ROW = P::D * 2 + 16;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < 4) dense_wave<P>(p, lds, bh, q00, q00 + 32 * wave, end, wave, 32 * wave * ROW);
+    else dense_wave<P1>(p, lds, bh, q00, q00 + 64 + 16 * wave, end, wave, (64 + 16 * wave) * ROW);
+}
+
+// Piece i of the pieces of 192 queries that items `first` .. `last` - 1 make, a (sample, head) at a time; without one, their number.
+struct Piece192 {
+    int bh, q0, end;                              // end: of the items' queries in this (sample, head)
+    int n;
+};
+constexpr __host__ __device__ Piece192 piece_192(int i, int first, int last, int nq, int N)
+{
+    int n = 0;
+    while (first < last) {
+        const int at = first % nq, run = nq - at < last - first ? nq - at : last - first;
+        const int q0 = at * DENSE_QT, end = (at + run) * DENSE_QT < N ? (at + run) * DENSE_QT : N;
+        const int pieces = (end - q0 + DENSE_192 - 1) / DENSE_192;
+        if (i < n + pieces) return {first / nq, q0 + (i - n) * DENSE_192, end, 0};
+        n += pieces;
+        first += run;
+    }
+    return {-1, 0, 0, n};
 }
 
 // 256 queries of one (sample, head) per workgroup; the items of an XCD that do not fill its CUs evenly are
-// cut into `cut` = 2 or 4 workgroups (p.whole of an XCD's items stay whole).
+// cut into `cut` = 2 or 4 workgroups each, or into pieces of 192 queries (p.whole of an XCD's items stay whole).
 template <int D>
 __global__ __launch_bounds__(DensePlan<D>::Whole::NW * 64, 2) void attn_dense_stream_kernel(const AttnParams p)
 {
@@ -2128,6 +2168,15 @@ __global__ __launch_bounds__(DensePlan<D>::Whole::NW * 64, 2) void attn_dense_st
         const int item = first + i;
         if (item < p.items) dense_item<typename DP::Whole>(p, lds, item / p.nq, item % p.nq * DENSE_QT);
         return;
+    }
+    if constexpr (D == 128) {
+        if (p.cut == 3) {
+            const int last = first + p.chunk < p.items ? first + p.chunk : p.items;
+            const Piece192 a = piece_192(i - p.whole, first + p.whole, last, p.nq, p.N);
+            const int bh = __builtin_amdgcn_readfirstlane(a.bh), q0 = __builtin_amdgcn_readfirstlane(a.q0), end = __builtin_amdgcn_readfirstlane(a.end);
+            if (bh >= 0) dense_item_192<typename DP::Whole, typename DP::Whole1>(p, lds, bh, q0, end);
+            return;
+        }
     }
     const int item = first + p.whole + (i - p.whole) / p.cut;
     if (item >= p.items) return;
@@ -2697,8 +2746,12 @@ int run_dense(const Problem& pr, void* stream)
     // What is left over after every CU of an XCD got the same number of items is cut so that it still makes
     // one workgroup per CU at most: a last round of an eighth of the CUs takes a quarter of the time.  us, items of an
     // XCD: 33 (H = 24, N = 2816) whole 136, in 2 116, in 4 105 at D = 128, 81 / 60 / 55 at D = 64; 198 (N = 16896)
-    // 2875 / 2734 / 2703; 108 (B = 2, N = 4429, D = 64) 257 / 231 / 257.  More than half of a round stays whole: 54
-    // items (N = 4608) 218 / 247 / 255.
+    // 2875 / 2734 / 2703; 108 (B = 2, N = 4429, D = 64) 257 / 231 / 257.  More than half of a round is not cut in two: 54
+    // items (N = 4608) 218 / 247 / 255.  At D = 128 up to three quarters of a round make pieces of 192 queries, still one per CU
+    // at most (the rest of one (sample, head) after the other, so a few more than 4 for 3 items).  us, whole / 192: 18 items
+    // (H = 24, N = 1536) 42.1 / 38.2; 20 (B = 4, H = 2, N = 5000) 98.1 / 91.8; 24 (N = 1800) 46.4 / 43.7; 54 (N = 4608) 212.9 /
+    // 211.8; 84 (N = 7168) 473 / 466; 147 (N = 12544) 1399 / 1380: after full rounds the chip is warm and its clock gives
+    // most of it back.
     // D = 64, no full round: two workgroups share a CU, so quarters fill it up to 16 items (with valid rows) and win up to
     // 24, halves up to 32, once the sequence is long enough to pay for more prologues.  us, whole / 2 / 4, H heads: N =
     // 1152, 24 (14 items) - / 18.3 / 16.1; 1792, 24 (21) 36.0 / 35.1 / 34.5; 2048, 24 40.2 / 38.9 / 38.9; 2304, 24 (27)
@@ -2710,7 +2763,17 @@ int run_dense(const Problem& pr, void* stream)
     const bool fits = rest <= CUS_PER_XCD / 2 || (live <= CUS_PER_XCD / 2 && pr.kv_len >= 640);
     p.cut = one_round ? (fits ? 4 : pr.kv_len < 1280 ? 1 : live <= 24 ? 4 : 2) : rest * 4 <= CUS_PER_XCD ? 4 : rest * 2 <= CUS_PER_XCD ? 2 : 1;
     p.whole = p.cut == 1 ? p.chunk : p.chunk - rest;
-    const dim3 grid((unsigned)(p.whole + (p.chunk - p.whole) * p.cut) * XCDS);
+    int groups = p.whole + (p.chunk - p.whole) * p.cut;
+    if (pr.D == 128 && p.cut == 1 && rest > CUS_PER_XCD / 2 && rest <= CUS_PER_XCD * 3 / 4) {
+        int pieces = 0;
+        for (int x = 0; x < XCDS; ++x) {
+            const int first = x * p.chunk, last = first + p.chunk < p.items ? first + p.chunk : p.items;
+            const int n = piece_192(0x7fffffff, first + p.chunk - rest, last, p.nq, p.N).n;
+            pieces = n > pieces ? n : pieces;
+        }
+        if (pieces <= CUS_PER_XCD) { p.cut = 3; p.whole = p.chunk - rest; groups = p.whole + pieces; }
+    }
+    const dim3 grid((unsigned)groups * XCDS);
     if (pr.D == 64) hipLaunchKernelGGL((attn_dense_stream_kernel<64>), grid, dim3(DensePlan<64>::Whole::NW * 64), 0, s, p);
     else hipLaunchKernelGGL((attn_dense_stream_kernel<128>), grid, dim3(DensePlan<128>::Whole::NW * 64), 0, s, p);
     return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;

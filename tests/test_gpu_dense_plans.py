@@ -11,12 +11,13 @@ import paper_2509_22323_amd as ra
 
 pytestmark = pytest.mark.gpu
 
-# heads, tokens allocated: small kernel; whole items; full rounds with the rest in halves, in quarters; one round
+# heads, tokens allocated: small kernel; whole items; pieces of 192 queries; full rounds with the rest in halves, in quarters; one round
 # of whole items, of halves, of quarters (run_dense)
 PLANS = {64: [("small", 3, 300), ("small, many", 200, 64), ("small, second round", 30, 1100), ("whole", 80, 1100),
               ("half", 70, 1100), ("quarter", 64, 1100), ("one round, whole", 40, 1100), ("one round of halves", 40, 1300),
               ("one round of quarters", 32, 1300)],
-         128: [("small", 3, 300), ("small, many", 200, 64), ("whole", 30, 1100), ("half", 24, 1100), ("quarter", 8, 1100)]}
+         128: [("small", 3, 300), ("small, many", 200, 64), ("whole", 45, 1100), ("pieces of 192", 30, 1100),
+               ("a round and pieces of 192", 82, 1100), ("half", 24, 1100), ("quarter", 8, 1100)]}
 CASES = [(D, plan, H, N, kv) for D in (64, 128) for plan, H, N in PLANS[D]
          for kv in (N, N - 13, N // 2 + 1, 257, 96, 65, 64, 33, 32, 31, 1) if kv <= N]
 
