@@ -2803,8 +2803,16 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     // All rows on the chip at once and none that could be cut: no plan, every workgroup finds its row by itself.  us, plan
     // launches / without: H = 2, N = 256 16.5 / 10.5; D = 64, H = 4, N = 2048 under 64-token masks 15.4 / 10.2 (density 0.1),
     // 23.6 / 18.5 (all ones); B = 2, H = 24, N = 1024 under 64-token masks, D = 64, 768 rows 18.3 / 15 (0.3).
+    // More than one row per CU and long rows: the order of a plan is worth more than its launch.  us, without a plan / with,
+    // densities 0.15 0.3 0.7: D = 64, 128-token masks, N = 768, 126 rows of an XCD 31.6 32.4
+    // 35.4 / 34.1 34.3 38.7; N = 1920, 120 rows 47.5 52.9 65.3 / 43.7 47.1 64.3, 45 rows 33.2 33.7 34.2 / 36.6 37.0 37.9;
+    // 64-token masks, 96 rows, N = 1024 17.2 18.8 20.5 / 18.5 19.6 22.7, 1536 22.8 24.4 27.3 / 21.3 22.4 28.1; D = 128, N = 1536,
+    // 48 rows 25.4 26.2 28.1 / 26.7 26.8 27.9, 2560, 40 rows 33.4 34.7 38.9 / 34.3 34.6 36.4; 128-token masks at D = 128 gain up to
+    // 15 blocks.  (Rows dealt out over several XCDs: not told apart.)
+    const bool short_rows = D == 128 ? block == 128 || nb <= 24 : nb * block <= 1024;
     const int places = segment_cus(B * H, nb, block) * (block == 64 ? (D == 128 ? 2 : 3) : (D == 128 ? 2 : 4));
-    const bool planned = xcd_items > places || (block == 128 && nb >= 2 * SPLIT_MIN_BLOCKS);
+    const bool planned = xcd_items > places || (block == 128 && nb >= 2 * SPLIT_MIN_BLOCKS) ||
+                         (xcd_items > CUS_PER_XCD && !short_rows && segments(B * H, nb, block) == XCDS);
     const long long mask_pieces = nb <= SMALL_NB ? (long long)(xcd_items / nb) * (((nb * nb + 7) / 8 + 3) / 4 * 4) : 0;
     const bool small = nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && mask_pieces <= SMALL_PIECES;
     const bool lists = mask != nullptr && (planned ? !small : nb > SMALL_NB);      // compacted by a kernel of its own
