@@ -1120,9 +1120,10 @@ __device__ __forceinline__ void phase_barrier()
 //                    contraction index 8 g + e stands for key 16 (e / 4) + 4 g + e % 4, and V^T is
 //                    fetched in that order
 // ---------------------------------------------------------------------------
-template <int D, int NQ_, int PD_, int NBUF_>
+template <int D, int NQ_, int PD_, int NBUF_, int UP_, int UP_AGAIN_>
 struct Stream {
     static constexpr int NQ = NQ_;
+    static constexpr float UP = UP_, UP_AGAIN = UP_AGAIN_;     // see soft_close
     static constexpr int KS = D / 32;          // k-steps of a score
     static constexpr int DT = D / 16;          // 16-row blocks of O^T
     static constexpr int NQK = 2 * KS, NPV = DT, NI = NQK + NPV;
@@ -1162,7 +1163,6 @@ struct StreamRegs {
     unsigned kc, kn, vc;                       // offsets of a step outside the unrolled loop
 };
 
-constexpr float REF_UP = 16.f, REF_UP_AGAIN = 24.f;    // see soft_close
 constexpr float REF_LOWEST = -1e30f;           // of a query whose first step has no finite score
 
 // Lane addresses in a K tile at byte address k0 and a V tile at v0.
@@ -1340,11 +1340,12 @@ __device__ __forceinline__ float step_max(const Scores<S>& st, int q, float c)
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1])) * c;
 }
 
-// Range of the exponents.  The reference m of a query is the maximum of its first step plus REF_UP, so that
-// probabilities of 2 and more mean a later maximum more than 17 above the first.  Such a value has the top bit of its
-// bf16 exponent set, which the or over all packed words shows; only then the references of that group of queries move
-// up to the step's maximum (plus REF_UP_AGAIN), the sums and the accumulators are rescaled and the step's
-// probabilities are made again.  What lies 2^110 below a row's first maximum (2^102 below a later one) is lost.
+// Range of the exponents.  The reference m of a query is the maximum of its first step plus UP (of the stream: 16 unless said
+// otherwise), so that probabilities of 2 and more mean a later maximum more than UP + 1 above the first.  Such a value has the
+// top bit of its bf16 exponent set, which the or over all packed words shows; only then the references of that group of
+// queries move up to the step's maximum (plus UP_AGAIN, 24), the sums and the accumulators are rescaled and the step's
+// probabilities are made again.  What lies 2^(126 - UP) below a row's first maximum (2^(126 - UP_AGAIN) below a later one) is
+// lost.
 // How far up: the accumulators hold V times these weights, at most 2^-16 in an ordinary row, so V of 2^-110 is summed
 // in normal numbers and smaller ones in subnormals with the precision of bf16 down to 2^-122 (with 60 in its place
 // everything below 2^-89 came out as 0); each step less makes peaked rows move more often.  us, dense, D = 128 (1, 24,
@@ -1352,6 +1353,11 @@ __device__ __forceinline__ float step_max(const Scores<S>& st, int q, float c)
 // all groups moved at once 212 228 272 / 226 256 344; 16 and 24 212 217 242 / 228 234 271; the 32x32x16 kernels before
 // 235 245 253 / 269 274 275.  A test for 2^8 that needs no offset (a maximum over the packed words,
 // v_pk_maximum3_f16, in place of the or) costs every dense call 1.5 %.
+// 64-token masks take 4 and 4: values of V keep bf16's precision down to 2^-120 where scores climb (16 and 24: 2^-114), and
+// the largest weight of a peaked row, which is exact where it is a reference, is one more often.  Error against 64 bits
+// (10^-3 of the norm), H = 24, N = 2816, all ones, D = 128, scores of standard deviation 1, 2, 4, 8, 16: 32x32x16 kernel before
+// 2.328 2.196 1.857 1.700 1.497 at 223 224 234 252 263 us; 16 and 24 2.332 2.212 1.913 1.749 1.527 at 122 122 123 129 140;
+// 8 and 8 2.332 2.204 1.868 1.713 1.507 at 122 122 132 146 155; 4 and 4 2.331 2.093 1.812 1.691 1.499 at 121 130 143 154 159.
 
 // Whether group q is among those.
 template <class S>
@@ -1386,7 +1392,7 @@ __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>&
         for (int q = 0; q < S::NQ; ++q) {
             float alpha = 1.f;
             if (group_out<S>(p, q)) {
-                const float m = fmaxf(x.m[q], step_max<S>(st, q, c) + REF_UP_AGAIN);
+                const float m = fmaxf(x.m[q], step_max<S>(st, q, c) + S::UP_AGAIN);
                 alpha = __builtin_amdgcn_exp2f(x.m[q] - m);
                 x.m[q] = m;
             }
@@ -1622,10 +1628,10 @@ __device__ __forceinline__ void static_steps(Step& step, int& i)
 //   SPT = 2: K_{t+1}, V_{t+1} may be read; the stages of K_t,     V_{t-1} take K_{t+NSK},   V_{t-1+NSV}
 // Copies are issued V before K at every barrier and complete in order, which gives the counts below.
 // ---------------------------------------------------------------------------
-template <int D_, int NQ_, int WQ_, int WK_, int SPT_, int NSK_, int NSV_>
+template <int D_, int NQ_, int WQ_, int WK_, int SPT_, int NSK_, int NSV_, int UP = 16, int UP_AGAIN = 24>
 struct StreamPlan {
     static constexpr int D = D_, NQ = NQ_, WQ = WQ_, WK = WK_, SPT = SPT_, NSK = NSK_, NSV = NSV_;
-    typedef Stream<D, NQ, 3, 4> S;
+    typedef Stream<D, NQ, 3, 4, UP, UP_AGAIN> S;
     static constexpr int NW = WQ * WK, QT = 16 * NQ * WQ, KTS = 32 * WK * SPT;
     static constexpr int TILE = KTS * S::RB;
     static constexpr int LC = TILE / 1024 / NW;   // copy instructions per wavefront per tile (K or V)
@@ -1931,7 +1937,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     mask_step<S>(st[0], keys.at(0, 0, false, 0) + wk * 32, kv_len, lane);
 #pragma unroll
     for (int q = 0; q < S::NQ; ++q) {
-        x.m[q] = fmaxf(step_max<S>(st[0], q, c) + REF_UP, REF_LOWEST);  // (a key group may have no valid key at all)
+        x.m[q] = fmaxf(step_max<S>(st[0], q, c) + S::UP, REF_LOWEST);  // (a key group may have no valid key at all)
     }
     x.seen = 0u;
     soft_half<S, D, 0>(x, st[0], c, pw);
@@ -2209,8 +2215,8 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(c
 // now: D = 128, N = 2816 58.8 92.9 220 -> 35.0 54.3 122; N = 8960 272 589 1716 -> 159 331 935; D = 64, N = 2816 28.1 44.2
 // 106 -> 22.2 32.5 73.2; N = 384 16.3 (two planner launches and the host either way).
 // ---------------------------------------------------------------------------
-template <int D> struct Sparse64Plan { typedef StreamPlan<128, 2, 2, 2, 1, 2, 3> P; };
-template <> struct Sparse64Plan<64> { typedef StreamPlan<64, 2, 2, 2, 1, 2, 3> P; };
+template <int D> struct Sparse64Plan { typedef StreamPlan<128, 2, 2, 2, 1, 2, 3, 4, 4> P; };
+template <> struct Sparse64Plan<64> { typedef StreamPlan<64, 2, 2, 2, 1, 2, 3, 4, 4> P; };
 
 template <int D, int WK>
 __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) void attn_sparse_pp_kernel(const AttnParams p)

@@ -90,6 +90,42 @@ def test_sparse_scales_with_v(D, name, H, nb, block, climb):
         check(o, ref, power, f"{name} D={D}")
 
 
+@pytest.mark.parametrize("climb", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("nb", [8, 24, 70])
+def test_64_token_masks_keep_small_values(nb, D, climb):
+    """A row's largest weight is at least 2^-5 there (the reference lies 4 above a first or a later maximum), so sums over
+    V * 2^-120 lie 20 bits and more above the last subnormal of fp32; much below, the outputs, means of up to 1400 values,
+    leave bf16's own normal numbers."""
+    g, q, k, v = inputs(3, nb * 64, D, 6 + D)
+    if climb:
+        climbing(q, k, D)
+    mask = mask_of(g, 3, nb)
+    o = torch.empty_like(q)
+    ra.rapid_attn_block_sparse(q, k, (v.double() * 2.0 ** -120).to(torch.bfloat16), o, mask, 64)
+    check(o, attention(q, k, v, mask, 64), -120, f"D={D} nb={nb}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_64_token_masks_largest_weights_of_peaked_rows(D):
+    """Scores of standard deviation 4: one weight carries a row, and its rounding to bf16 (1.7e-3 in the mean) the row's
+    error, unless it is a reference of the exponents and so a power of two.  With every reference at a row's first maximum
+    the outputs are off by 1.91e-3, with references that follow within 8 of the running maximum by 1.86e-3, within 4
+    by 1.81e-3 (24 x 2816 rows: the figure itself varies by 2e-6)."""
+    H, N = 24, 2816
+    g, q, k, v = inputs(H, N, D, 9 + D)
+    q *= 4
+    mask = torch.ones((1, H, N // 64, N // 64), dtype=torch.uint8, device="cuda")
+    o = torch.empty_like(q)
+    ra.rapid_attn_block_sparse(q, k, v, o, mask, 64)
+    off = size = 0.0
+    for h in range(H):
+        w = torch.softmax(q[0, h].double() @ k[0, h].double().t() * D ** -0.5, -1) @ v[0, h].double()
+        off += (o[0, h].double() - w).square().sum().item()
+        size += w.square().sum().item()
+    assert (off / size) ** 0.5 <= 1.86e-3, (off / size) ** 0.5
+
+
 def without_finite_start(q, k, keys):
     """The first `keys` keys score -inf for every query (their products leave fp32), the others are ordinary."""
     q[..., 1] = 2.0 ** 80
