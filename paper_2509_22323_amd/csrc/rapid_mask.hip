@@ -221,16 +221,22 @@ __global__ __launch_bounds__(256) void select_blocks_kernel(const float* __restr
     });
 }
 
-// The same for up to SMALL_NB mask blocks per side (every shape of the paper's models): 16 wavefronts take 16 rows of one
-// (sample, head).  Scores by fp32 MFMAs, a tile of 16 key-blocks per wavefront straight from the means in memory (a lane's
-// 16 bytes of a row serve four MFMAs: the contraction index is a dummy); then a row per wavefront, its scores in registers.
+// The same for up to SMALL_NB mask blocks per side (every shape of the paper's models): ROWS wavefronts take ROWS rows of one
+// (sample, head).  Scores by fp32 MFMAs, tiles of 16 key-blocks dealt out to the wavefronts straight from the means in memory
+// (a lane's 16 bytes of a row serve four MFMAs: the contraction index is a dummy); then a row per wavefront, its scores in
+// registers.
 // The cut: up to 64 blocks, block j is kept iff the blocks with a strictly larger probability hold less than tau of
-// the mass, a sum each lane forms over all the others; beyond, the bisection of select_blocks_kernel, which ends as soon
-// as one value is left between the bounds (a dozen rounds of the thirty for scores that are spread out).  H = 24, 132
-// blocks, D = 128: 19.2 us with scores by vector instructions from LDS and the first cut, 13.0 by MFMAs and thirty rounds,
-// 11.6 now; 36 blocks 6.7 / 6.5 now.
+// the mass, a sum each lane forms over all the others; beyond, the bisection of select_blocks_kernel between the smallest and
+// the largest probability, which ends as soon as one value is left between the bounds (a dozen rounds of the thirty for scores
+// that are spread out; from 0 on, near-equal scores, whose probabilities differ in their last bits only, took more).
+// The kernel alone, us, H = 24, 132 blocks, D = 128: scores by vector instructions from LDS and the first cut 22.2; by MFMAs,
+// bisection from 0 11.3, near-equal scores 11.9; from the smallest 10.5 and 10.0.
+// ROWS = 16 reads the means of the keys a quarter as often.  ROWS = 4 where its workgroups are still at most one per CU: four
+// wavefronts share the vector unit of a CU, not sixteen, which counts once rows are long.  4 / 16 rows, D = 128, (sample, head)
+// pairs x blocks: 2 x 16 3.8 / 3.6, 32 4.2 / 4.4, 48 5.0 / 5.4, 65 7.2 / 7.5, 128 8.4 / 9.6, 256 10.7 / 14.1; 8 x 128 (64
+// workgroups of 16 rows) 7.9 / 9.1, 129 (72) 10.9 / 10.7, 192 (96) 12.7 / 11.2; 24 x 32 (48) 4.3 / 4.7, 48 (72) 5.8 / 5.2, 65
+// (120) 8.9 / 8.2, 132 (216) 16.1 / 10.5.  (Scores by vector instructions, 4 rows: 2 x 65 7.4, 24 x 65 8.4.)
 constexpr int SMALL_NB = 256;
-constexpr int SMALL_ROWS = 16;                 // per workgroup
 
 // v of all 64 lanes combined, the same in all of them: shifts inside rows of 16 lanes, then the last lane of rows 0 and 2
 // to rows 1 and 3, then lane 31 to rows 2 and 3; a lane without a source takes `none`.  All lanes active.
@@ -251,23 +257,23 @@ __device__ __forceinline__ float wave_combine(float v, float none, Op op)
 }
 __device__ __forceinline__ float wave_total(float v) { return wave_combine(v, 0.f, [](float a, float b) { return a + b; }); }
 
-template <int D, int U>                        // U: 64-block stretches of a row
-__global__ __launch_bounds__(1024, 4) void select_blocks_small_kernel(const float* __restrict__ qmean,
+template <int D, int U, int ROWS>              // U: 64-block stretches of a row; ROWS: per workgroup
+__global__ __launch_bounds__(64 * ROWS, 4) void select_blocks_small_kernel(const float* __restrict__ qmean,
                                                                    const float* __restrict__ kmean, const QKView v,
                                                                    int block, int nb, float tau, float scale,
                                                                    const RowSink sink)
 {
     constexpr int ROW = 64 * U + 4;
-    __shared__ __attribute__((aligned(16))) float ps[SMALL_ROWS][ROW];
-    const int groups = (nb + SMALL_ROWS - 1) / SMALL_ROWS;
+    __shared__ __attribute__((aligned(16))) float ps[ROWS][ROW];
+    const int groups = (nb + ROWS - 1) / ROWS;
     const size_t bh = blockIdx.x / groups;
     int live, first_text;
     sample_blocks(v, (int)(bh / v.H), block, nb, live, first_text);
-    const int i0 = (blockIdx.x % groups) * SMALL_ROWS;
+    const int i0 = (blockIdx.x % groups) * ROWS;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
-    if (wv * 16 < live) {                          // (U <= 4: a tile per wavefront)
-        const int kr = wv * 16 + n, qr = i0 + n;
+    for (int k0 = wv * 16; k0 < live; k0 += ROWS * 16) {
+        const int kr = k0 + n, qr = i0 + n % ROWS; // (columns from ROWS on of the product: the rows again, not stored)
         const f32x4* kp = (const f32x4*)(kmean + (bh * nb + (kr < live ? kr : live - 1)) * D) + g;
         const f32x4* qp = (const f32x4*)(qmean + (bh * nb + (qr < live ? qr : live - 1)) * D) + g;
         f32x4 kf[D / 16], qf[D / 16];
@@ -283,7 +289,7 @@ __global__ __launch_bounds__(1024, 4) void select_blocks_small_kernel(const floa
         f32x4 out;
 #pragma unroll
         for (int r = 0; r < 4; ++r) out[r] = scale * acc[r];
-        *(f32x4*)(&ps[n][wv * 16 + 4 * g]) = out;  // key-blocks 4 g .. of the tile, query row n
+        if (n < ROWS) *(f32x4*)(&ps[n][k0 + 4 * g]) = out;      // key-blocks 4 g .. of the tile, query row n
     }
     __syncthreads();
 
@@ -301,10 +307,12 @@ __global__ __launch_bounds__(1024, 4) void select_blocks_small_kernel(const floa
         mx = fmaxf(mx, e[u]);
     }
     mx = wave_combine(mx, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
-    float part = 0.f;
+    float part = 0.f, least = INFINITY;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        e[u] = lane + 64 * u < live ? expf(e[u] - mx) : 0.f;
+        const bool in = lane + 64 * u < live;
+        e[u] = in ? expf(e[u] - mx) : 0.f;
+        least = in ? fminf(least, e[u]) : least;
         part += e[u];
     }
     const float target = tau * wave_total(part);
@@ -321,8 +329,9 @@ __global__ __launch_bounds__(1024, 4) void select_blocks_small_kernel(const floa
         }
         kept[0] = above < target;
     } else {
-        unsigned lo = 0u, hi = 0x3F800001u;        // mass(lo) >= target > mass(hi) = 0
-        int from_lo = 64 * U, from_hi = 0;         // values at or above either
+        unsigned lo = __float_as_uint(wave_combine(least, INFINITY, [](float a, float b) { return fminf(a, b); }));
+        unsigned hi = 0x3F800001u;                 // mass(lo) >= target > mass(hi) = 0
+        int from_lo = 64 * U, from_hi = 0;         // values at or above either, at most
         if (!(target > 0.f)) lo = hi = ~0u;        // not a number: only what is kept in any case
         while (hi - lo > 1u && from_lo - from_hi > 1) {
             const unsigned mid = lo + (hi - lo) / 2u;
@@ -381,7 +390,11 @@ int run_select(const QKView& v, int B, int D, int block, float tau, float scale,
     const size_t which_stride = (size_t)B * H * nb * D;
     hipStream_t s = (hipStream_t)stream;
     const dim3 g1((unsigned)(nb * B * H), 2u);
-    const bool streamed = 4.0 * B * H * v.N * D > 128e6;       // half of the 256 MB memory-side cache
+    // Half of the 256 MB memory-side cache.  us, plain loads / streamed, selection alone right after Q and K were written, H = 24,
+    // D = 128, MB of Q and K: 28 13.2 14.0; 57 17.5 17.9; 88 22.6 22.6; 126 30.6 30.3; 151 34.4 34.6; 208 49.6 46.0; 415 118.5
+    // 90.9 (the same tensors again and again, 208: 43.4 47.0; others in turn: 49.5 46.7).  Selection and attention in one call:
+    // 28 67.3 69.8; 57 124.5 125.9; 126 to 415 the same within 1 %.
+    const bool streamed = 4.0 * B * H * v.N * D > 128e6;
     const auto pick_mean = [&](auto d, auto bl) {
         constexpr int DD = decltype(d)::value, BB = decltype(bl)::value;
         return streamed ? block_mean_kernel<DD, BB, true> : block_mean_kernel<DD, BB, false>;
@@ -395,14 +408,18 @@ int run_select(const QKView& v, int B, int D, int block, float tau, float scale,
 
     const int rows = B * H * nb;
     if (nb <= SMALL_NB) {
-        const dim3 gs((unsigned)(B * H * ((nb + SMALL_ROWS - 1) / SMALL_ROWS)));
-        const auto pick = [&](auto d) {
-            constexpr int DD = decltype(d)::value;
-            return nb <= 64 ? select_blocks_small_kernel<DD, 1> : nb <= 128 ? select_blocks_small_kernel<DD, 2>
-                 : nb <= 192 ? select_blocks_small_kernel<DD, 3> : select_blocks_small_kernel<DD, 4>;
+        typedef std::integral_constant<int, 4> c4;
+        typedef std::integral_constant<int, 16> c16;
+        const int per = nb > 32 && (long long)B * H * ((nb + 15) / 16) <= 64 ? 4 : 16;
+        const dim3 gs((unsigned)(B * H * ((nb + per - 1) / per)));
+        const auto pick = [&](auto d, auto r) {
+            constexpr int DD = decltype(d)::value, RR = decltype(r)::value;
+            return nb <= 64 ? select_blocks_small_kernel<DD, 1, RR> : nb <= 128 ? select_blocks_small_kernel<DD, 2, RR>
+                 : nb <= 192 ? select_blocks_small_kernel<DD, 3, RR> : select_blocks_small_kernel<DD, 4, RR>;
         };
-        const auto select = D == 64 ? pick(c64()) : pick(c128());
-        hipLaunchKernelGGL(select, gs, dim3(1024), 0, s, means, means + which_stride, v, block, nb, tau, scale, sink);
+        const auto select = D == 64 ? (per == 4 ? pick(c64(), c4()) : pick(c64(), c16()))
+                                    : (per == 4 ? pick(c128(), c4()) : pick(c128(), c16()));
+        hipLaunchKernelGGL(select, gs, dim3(64 * per), 0, s, means, means + which_stride, v, block, nb, tau, scale, sink);
         return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
     }
     const dim3 g2((unsigned)((rows + 3) / 4));

@@ -67,6 +67,21 @@ def test_edges_of_row_tiles_and_stretches(nb, D):
     check(q, k, 64, N - 19, N, 0.8)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,nb", [(2, 32), (2, 33), (21, 33), (22, 33), (16, 64), (17, 64), (12, 65), (13, 65), (7, 129), (8, 129), (4, 193),
+                                  (5, 193), (4, 256), (5, 256)])
+def test_rows_per_workgroup_on_either_side_of_the_rule(H, nb, D):
+    """4 rows per workgroup from 33 blocks on while workgroups of 16 would be at most 64, else 16; a cut last block.
+    Probabilities far apart, and nearly equal ones: those of neighbouring rank lie about 1e-3 / nb apart there and fp32 scores
+    are off by up to 1e-7, so a row in a few hundred is cut between the other two of a pair, two blocks of its nb."""
+    N = 64 * nb
+    q, k, _ = wl.make_qkv_block_structured(1, H, N, D, 64, N - 19, seed=nb + H, n_text_blocks=1, pad_fill="nan")
+    check(q, k, 64, N - 19, N - 64, 0.8)
+    q, k, _ = wl.make_qkv(1, H, N, D, N - 19, seed=nb + H, pad_fill="nan")
+    got = run(q, k, 64, N - 19, N - 64, 0.8)
+    assert (got == mo.select_mask(q, k, 64, N - 19, N - 64, 0.8, 0.0)).mean() >= 0.999
+
+
 @pytest.mark.parametrize("nb", [40, 65, 132])
 def test_equal_scores_and_rows_without_a_number(nb):
     """Blocks of equal probability come or go together; a query-block whose mean is not a number keeps only what is
