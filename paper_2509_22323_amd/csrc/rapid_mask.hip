@@ -52,7 +52,8 @@ __device__ __forceinline__ void sample_blocks(const QKView& v, int b, int block,
 
 // means[(which, bh, i), :] = mean over the valid rows of block i of Q (which = 0) or K (1).  256 threads: D/8 column
 // groups of 8 elements x 256/(D/8) row groups; every thread adds up its rows in increasing order, the row groups are
-// then added in increasing order.  Bound by HBM: all loads of a whole block are requested before the first is used, and
+// then added in increasing order.  Bound by HBM: all loads of a block are requested before the first is used (one after the
+// other where a last block is cut, a call of D = 128, 128-token blocks, N = 4221 took 15.4 us in place of 14.4), and
 // STREAMED ones are non-temporal (H = 24, N = 16896, D = 128, 208 MB: 39.0 us in a loop, 36.8 requested at once, 33.1 =
 // 6.3 TB/s non-temporal; N = 4608 13.9 / 13.0 / 11.0).  Only where Q and K are more than the caches keep for the attention
 // that reads them next: at N = 4608 (57 MB) selection and attention in one call take 123.2 us, 124.1 when streamed.
@@ -81,17 +82,17 @@ __global__ __launch_bounds__(256) void block_mean_kernel(const QKView v, int nb,
             acc[2 * e + 1] += __uint_as_float(x[e] & 0xffff0000u);
         }
     };
-    if (hi - lo == BLOCK) {
+    if (lo < hi) {                                 // (rows past the last valid one: that one again, not added)
         u32x4 x[RPT];
 #pragma unroll
         for (int u = 0; u < RPT; ++u) {
-            const u32x4* at = (const u32x4*)(src + (size_t)(lo + g + u * RG) * v.sn);
+            const int r = lo + g + u * RG;
+            const u32x4* at = (const u32x4*)(src + (size_t)(r < hi ? r : hi - 1) * v.sn);
             x[u] = STREAMED ? __builtin_nontemporal_load(at) : *at;
         }
 #pragma unroll
-        for (int u = 0; u < RPT; ++u) add(x[u]);
-    } else {
-        for (int r = lo + g; r < hi; r += RG) add(*(const u32x4*)(src + (size_t)r * v.sn));
+        for (int u = 0; u < RPT; ++u)
+            if (lo + g + u * RG < hi) add(x[u]);
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[g][c * 8 + e] = acc[e];

@@ -82,6 +82,22 @@ def test_rows_per_workgroup_on_either_side_of_the_rule(H, nb, D):
     assert (got == mo.select_mask(q, k, 64, N - 19, N - 64, 0.8, 0.0)).mean() >= 0.999
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("left", [1, 7, 8, 9, 31, 33, 63])
+def test_means_of_a_cut_block(left, block, D):
+    """The rows of a last block that do not exist are asked for nowhere: the joint tensor ends with the last valid token, and
+    the token after the valid ones is not a number.  Rows of the block in and beyond each group of rows of a thread."""
+    nb, left = 5, left if block == 64 else 2 * left
+    N = (nb - 1) * block + left
+    q, k, _ = wl.make_qkv_block_structured(1, 3, nb * block, D, block, N, seed=left, pad_fill="nan")
+    check(q, k, block, N, nb * block, 0.6)
+    cut = [to_dev(np.ascontiguousarray(x[:, :, :N])) for x in (q, k)]
+    m = torch.full((1, 3, nb, nb), 9, dtype=torch.uint8, device="cuda")
+    ra.rapid_mask_select_joint([(*cut, cut[0], torch.empty_like(cut[0]))], m, block, text_start=nb * block, tau=0.6)
+    assert (m.cpu().numpy() == run(q, k, block, N, nb * block, 0.6)).all()
+
+
 @pytest.mark.parametrize("nb", [40, 65, 132])
 def test_equal_scores_and_rows_without_a_number(nb):
     """Blocks of equal probability come or go together; a query-block whose mean is not a number keeps only what is
