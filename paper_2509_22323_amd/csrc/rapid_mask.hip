@@ -232,11 +232,10 @@ __global__ __launch_bounds__(256) void select_blocks_kernel(const float* __restr
 // that are spread out; from 0 on, near-equal scores, whose probabilities differ in their last bits only, took more).
 // The kernel alone, us, H = 24, 132 blocks, D = 128: scores by vector instructions from LDS and the first cut 22.2; by MFMAs,
 // bisection from 0 11.3, near-equal scores 11.9; from the smallest 10.5 and 10.0.
-// ROWS = 16 reads the means of the keys a quarter as often.  ROWS = 4 where its workgroups are still at most one per CU: four
-// wavefronts share the vector unit of a CU, not sixteen, which counts once rows are long.  4 / 16 rows, D = 128, (sample, head)
-// pairs x blocks: 2 x 16 3.8 / 3.6, 32 4.2 / 4.4, 48 5.0 / 5.4, 65 7.2 / 7.5, 128 8.4 / 9.6, 256 10.7 / 14.1; 8 x 128 (64
-// workgroups of 16 rows) 7.9 / 9.1, 129 (72) 10.9 / 10.7, 192 (96) 12.7 / 11.2; 24 x 32 (48) 4.3 / 4.7, 48 (72) 5.8 / 5.2, 65
-// (120) 8.9 / 8.2, 132 (216) 16.1 / 10.5.  (Scores by vector instructions, 4 rows: 2 x 65 7.4, 24 x 65 8.4.)
+// ROWS = 16 reads the means of the keys half as often.  ROWS = 8 where its workgroups are still at most one per CU: half as many
+// wavefronts share the vector unit of a CU, which counts once rows are long.  8 / 16 rows (and 4, no better), D = 128, (sample,
+// head) pairs x blocks: 2 x 33 4.6 / 5.3 (4.8), 65 7.2 / 7.5 (7.5), 128 8.9 / 9.6 (8.4), 256 11.0 / 14.1 (10.4); 8 x 129 9.6 /
+// 10.7 (10.9), 256 (128 workgroups of 16 rows) 10.8 / 13.8 (14.9); 24 x 48 5.0 / 5.4 (5.8), 65 7.7 / 8.1 (8.9).
 constexpr int SMALL_NB = 256;
 
 // v of all 64 lanes combined, the same in all of them: shifts inside rows of 16 lanes, then the last lane of rows 0 and 2
@@ -409,17 +408,17 @@ int run_select(const QKView& v, int B, int D, int block, float tau, float scale,
 
     const int rows = B * H * nb;
     if (nb <= SMALL_NB) {
-        typedef std::integral_constant<int, 4> c4;
+        typedef std::integral_constant<int, 8> c8;
         typedef std::integral_constant<int, 16> c16;
-        const int per = nb > 32 && (long long)B * H * ((nb + 15) / 16) <= 64 ? 4 : 16;
+        const int per = nb > 32 && (long long)B * H * ((nb + 15) / 16) <= 128 ? 8 : 16;
         const dim3 gs((unsigned)(B * H * ((nb + per - 1) / per)));
         const auto pick = [&](auto d, auto r) {
             constexpr int DD = decltype(d)::value, RR = decltype(r)::value;
             return nb <= 64 ? select_blocks_small_kernel<DD, 1, RR> : nb <= 128 ? select_blocks_small_kernel<DD, 2, RR>
                  : nb <= 192 ? select_blocks_small_kernel<DD, 3, RR> : select_blocks_small_kernel<DD, 4, RR>;
         };
-        const auto select = D == 64 ? (per == 4 ? pick(c64(), c4()) : pick(c64(), c16()))
-                                    : (per == 4 ? pick(c128(), c4()) : pick(c128(), c16()));
+        const auto select = D == 64 ? (per == 8 ? pick(c64(), c8()) : pick(c64(), c16()))
+                                    : (per == 8 ? pick(c128(), c8()) : pick(c128(), c16()));
         hipLaunchKernelGGL(select, gs, dim3(64 * per), 0, s, means, means + which_stride, v, block, nb, tau, scale, sink);
         return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
     }

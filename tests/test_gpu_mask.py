@@ -67,19 +67,21 @@ def test_edges_of_row_tiles_and_stretches(nb, D):
     check(q, k, 64, N - 19, N, 0.8)
 
 
-@pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("H,nb", [(2, 32), (2, 33), (21, 33), (22, 33), (16, 64), (17, 64), (12, 65), (13, 65), (7, 129), (8, 129), (4, 193),
-                                  (5, 193), (4, 256), (5, 256)])
+@pytest.mark.parametrize("H,nb,D", [(2, 32, 64), (2, 33, 128), (42, 33, 64), (43, 33, 64), (32, 64, 128), (33, 64, 64), (25, 65, 64), (26, 65, 128),
+                                    (14, 129, 128), (15, 129, 64), (9, 193, 64), (10, 193, 64), (8, 256, 64), (9, 256, 64)])
 def test_rows_per_workgroup_on_either_side_of_the_rule(H, nb, D):
-    """4 rows per workgroup from 33 blocks on while workgroups of 16 would be at most 64, else 16; a cut last block.
-    Probabilities far apart, and nearly equal ones: those of neighbouring rank lie about 1e-3 / nb apart there and fp32 scores
-    are off by up to 1e-7, so a row in a few hundred is cut between the other two of a pair, two blocks of its nb."""
+    """8 rows per workgroup from 33 blocks on while workgroups of 16 would be at most 128, else 16; a cut last block.
+    Over this many rows two blocks whose scores differ by less than fp32 resolves (about 1e-6) meet at a cut here and there:
+    their scores spread over 1 (linked blocks) or 0.1 (independent tokens), neighbours in rank lie 1 / nb of that apart, so
+    a row is off with a probability of 1e-6 nb / 0.1, at most 0.3 %."""
     N = 64 * nb
-    q, k, _ = wl.make_qkv_block_structured(1, H, N, D, 64, N - 19, seed=nb + H, n_text_blocks=1, pad_fill="nan")
-    check(q, k, 64, N - 19, N - 64, 0.8)
-    q, k, _ = wl.make_qkv(1, H, N, D, N - 19, seed=nb + H, pad_fill="nan")
-    got = run(q, k, 64, N - 19, N - 64, 0.8)
-    assert (got == mo.select_mask(q, k, 64, N - 19, N - 64, 0.8, 0.0)).mean() >= 0.999
+    for make in (lambda: wl.make_qkv_block_structured(1, H, N, D, 64, N - 19, seed=nb + H, n_text_blocks=1, pad_fill="nan"),
+                 lambda: wl.make_qkv(1, H, N, D, N - 19, seed=nb + H, pad_fill="nan")):
+        q, k, _ = make()
+        got = run(q, k, 64, N - 19, N - 64, 0.8)
+        lo, hi = (mo.select_mask(q, k, 64, N - 19, N - 64, t) for t in (0.8 - DELTA, 0.8 + DELTA))
+        off = ((lo > got) | (got > hi)).sum(-1)
+        assert off.max() <= 2 and (off > 0).mean() <= 3e-3, (off.max(), (off > 0).mean())
 
 
 @pytest.mark.parametrize("D", [64, 128])
