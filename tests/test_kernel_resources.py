@@ -34,7 +34,7 @@ WANT = {  # kernel name fragment -> waves per SIMD its launch plan counts on
     "attn_dense_stream_kernelILi64E": 2, "attn_dense_stream_kernelILi128E": 2,
     "attn_dense_pp_kernelILi64E": 4, "attn_dense_pp_kernelILi128E": 2, "attn_sparse_wide_kernel": 2,
     "attn_sparse_sg_kernelILi64E": 4, "attn_sparse_sg_kernelILi128E": 2,
-    "attn_sparse_pp_kernelILi64ELi2E": 2, "attn_sparse_pp_kernelILi128ELi2E": 1,
+    "attn_sparse_pp_kernelILi64ELi2E": 3, "attn_sparse_pp_kernelILi128ELi2E": 2,
 }
 
 
@@ -45,6 +45,9 @@ def test_attention_kernels_stay_in_registers(usage, fragment, occupancy):
     u = usage[name[0]]
     assert u["ScratchSize [bytes/lane]"] == 0, u
     assert u["Occupancy [waves/SIMD]"] >= occupancy, u
+    # (a workgroup of four wavefronts is one per SIMD, of eight two; LDS: 160 KB per CU)
+    workgroups = occupancy // (2 if "attn_dense_stream_kernelILi128E" in fragment else 1)
+    assert u["LDS Size [bytes/block]"] * workgroups <= 160 * 1024, u
 
 
 def test_every_attention_kernel_is_listed(usage):
