@@ -2809,16 +2809,23 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     // All rows on the chip at once and none that could be cut: no plan, every workgroup finds its row by itself.  us, plan
     // launches / without: H = 2, N = 256 16.5 / 10.5; D = 64, H = 4, N = 2048 under 64-token masks 15.4 / 10.2 (density 0.1),
     // 23.6 / 18.5 (all ones); B = 2, H = 24, N = 1024 under 64-token masks, D = 64, 768 rows 18.3 / 15 (0.3).
-    // More than one row per CU and long rows: the order of a plan is worth more than its launch.  us, without a plan / with,
-    // densities 0.15 0.3 0.7: D = 64, 128-token masks, N = 768, 126 rows of an XCD 31.6 32.4
-    // 35.4 / 34.1 34.3 38.7; N = 1920, 120 rows 47.5 52.9 65.3 / 43.7 47.1 64.3, 45 rows 33.2 33.7 34.2 / 36.6 37.0 37.9;
-    // 64-token masks, 96 rows, N = 1024 17.2 18.8 20.5 / 18.5 19.6 22.7, 1536 22.8 24.4 27.3 / 21.3 22.4 28.1; D = 128, N = 1536,
-    // 48 rows 25.4 26.2 28.1 / 26.7 26.8 27.9, 2560, 40 rows 33.4 34.7 38.9 / 34.3 34.6 36.4; 128-token masks at D = 128 gain up to
-    // 15 blocks.  (Rows dealt out over several XCDs: not told apart.)
-    const bool short_rows = D == 128 ? block == 128 || nb <= 24 : nb * block <= 1024;
+    // More rows than that, and long ones: the order of a plan is worth more than its launch, most of all where samples differ.  us,
+    // without a plan / with, densities 0.15, 0.7 and by sample 1 0.5 0.3 0.15 in turn, rows of an XCD, blocks of a row:
+    //   128-token masks, D = 64: 54 x 6 18.9 18.9 18.6 / 22.3 22.9 22.1, 126 x 6 31.5 35.2 35.1 / 34.3 39.2 36.8; 64 x 8 23.2 24.9
+    //     23.0 / 26.4 27.7 26.4, 72 x 8 25.9 30.7 30.9 / 27.4 30.9 28.7, 104 x 8 34.2 39.9 40.4 / 31.7 40.3 36.0; 60 x 15 33.9 36.3
+    //     34.5 / 37.2 40.0 37.7, 75 x 15 38.6 48.8 45.8 / 38.8 45.8 42.2, 120 x 15 48.2 65.6 58.3 / 44.2 64.0 56.2: a line at two
+    //     rows per CU, and at 6 blocks
+    //   64-token masks, D = 64: 96 x 16 17.3 20.4 21.0 / 18.4 22.6 21.1; 60 x 20 17.5 17.7 17.5 / 18.1 19.8 18.4, 80 x 20 19.8 22.5
+    //     22.3 / 18.7 23.3 20.2; 64 x 32 21.7 23.8 24.7 / 22.9 24.5 27.9, 96 x 32 24.3 31.5 31.5 / 24.2 32.5 31.0; 80 x 40 27.5 35.6
+    //     38.4 / 27.4 34.8 34.5: two rows per CU, and 16 blocks
+    //   D = 128: 128-token masks 40 x 10 29.9 33.1 33.1 / 32.0 34.2 32.5, 60 x 15 42.1 51.8 49.5 / 44.3 52.4 47.8 (up to 15 blocks
+    //     there is none to cut); 64-token masks 48 x 24 25.4 27.9 28.6 / 26.5 28.0 28.1, 40 x 40 33.3 37.5 (0.3 34.7) / 34.0 36.4
+    //     (34.5): one row per CU, and 24 blocks
+    // (Rows dealt out over several XCDs: not told apart.)
+    const bool short_rows = D == 128 ? block == 128 || nb <= 24 : nb <= (block == 128 ? 6 : 16);
     const int places = segment_cus(B * H, nb, block) * (block == 64 ? (D == 128 ? 2 : 3) : (D == 128 ? 2 : 4));
     const bool planned = xcd_items > places || (block == 128 && nb >= 2 * SPLIT_MIN_BLOCKS) ||
-                         (xcd_items > CUS_PER_XCD && !short_rows && segments(B * H, nb, block) == XCDS);
+                         (xcd_items > CUS_PER_XCD * (D == 128 ? 1 : 2) && !short_rows && segments(B * H, nb, block) == XCDS);
     const long long mask_pieces = nb <= SMALL_NB ? (long long)(xcd_items / nb) * (((nb * nb + 7) / 8 + 3) / 4 * 4) : 0;
     const bool small = nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && mask_pieces <= SMALL_PIECES;
     const bool lists = mask != nullptr && (planned ? !small : nb > SMALL_NB);      // compacted by a kernel of its own

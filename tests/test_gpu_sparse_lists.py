@@ -4,6 +4,7 @@ expanded mask.  Tolerance: P and O are rounded to bf16 (2^-9 each, relative), 2.
 twice that per 64 rows of a head (a wrong row shows as 1)."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
@@ -64,8 +65,8 @@ def test_every_list_length_and_odd_tails(D, block, cut):
 
 @pytest.mark.parametrize("D", [64, 128])
 def test_lists_longer_than_a_wavefront_holds(D):
-    """64-token masks: a wavefront holds 64 entries of the list and reads on every 60; rows of 50 to 132 kept
-    blocks, the last of them cut."""
+    """64-token masks: a wavefront holds 64 entries of the list and reads on every 64, up to four entries ahead of their
+    use; rows of every length from 50 to 132 kept blocks, the last block of all cut."""
     block, nb = 64, 132
     N, kv = nb * block, nb * block - 45
     g = torch.Generator(device="cuda").manual_seed(D)
@@ -236,13 +237,8 @@ def test_many_rows_joint_tensors_and_lengths():
 
 
 # ---- where the plan comes from: every workgroup for itself (all rows on the chip at once), one planner launch from the
-# mask, or compaction and a planner; edges of each rule, with per-sample lengths
-@pytest.mark.parametrize("block,B,H,nb,D", [
-    (64, 1, 1, 1, 64), (64, 3, 5, 2, 128), (64, 3, 8, 21, 128), (64, 3, 8, 22, 128), (64, 4, 8, 24, 64), (64, 4, 8, 25, 64),
-    (64, 2, 40, 64, 64), (64, 2, 40, 63, 128), (64, 1, 8, 65, 64), (64, 3, 8, 65, 128), (64, 300, 8, 2, 64), (64, 200, 40, 3, 64),
-    (64, 9, 120, 33, 64), (128, 2, 32, 8, 128), (128, 5, 13, 8, 128), (128, 4, 32, 8, 64), (128, 3, 8, 15, 64), (128, 3, 8, 16, 64),
-    (128, 64, 40, 1, 64), (128, 900, 40, 1, 64), (128, 8, 24, 36, 64), (128, 8, 40, 64, 64), (128, 2, 8, 65, 128)])
-def test_counts_lists_and_plan_wherever_they_are_made(block, B, H, nb, D):
+# mask, or compaction and a planner; sizes on either side of each, with per-sample lengths
+def counts_lists_and_plan(block, B, H, nb, D):
     N = nb * block - 5
     g = torch.Generator(device="cuda").manual_seed(B + H + nb)
     q, k, v = (torch.randn((B, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
@@ -270,3 +266,32 @@ def test_counts_lists_and_plan_wherever_they_are_made(block, B, H, nb, D):
         for h in sorted({0, H - 1}):
             one = [torch.nn.functional.pad(t[b:b + 1, h:h + 1], (0, 0, 0, 5)) for t in (q, k, v, o)]
             check(one[3], reference(*one[:3], mask[b:b + 1, h:h + 1], block, n, D ** -0.5), n, f"sample {b} head {h}")
+    return order
+
+
+@pytest.mark.parametrize("block,B,H,nb,D", [
+    (64, 1, 1, 1, 64), (64, 3, 5, 2, 128), (64, 3, 8, 21, 128), (64, 3, 8, 22, 128), (64, 4, 8, 24, 64), (64, 4, 8, 25, 64),
+    (64, 2, 40, 64, 64), (64, 2, 40, 63, 128), (64, 1, 8, 65, 64), (64, 3, 8, 65, 128), (64, 300, 8, 2, 64), (64, 200, 40, 3, 64),
+    (64, 9, 120, 33, 64), (128, 2, 32, 8, 128), (128, 5, 13, 8, 128), (128, 4, 32, 8, 64), (128, 3, 8, 15, 64), (128, 3, 8, 16, 64),
+    (128, 64, 40, 1, 64), (128, 900, 40, 1, 64), (128, 8, 24, 36, 64), (128, 8, 40, 64, 64), (128, 2, 8, 65, 128)])
+def test_counts_lists_and_plan_wherever_they_are_made(block, B, H, nb, D):
+    counts_lists_and_plan(block, B, H, nb, D)
+
+
+# the rules of run_sparse: more rows of an XCD than places (2 to 4 per CU), rows long enough to be cut, more than one (D = 128) or
+# two rows per CU that are not short; fewer pairs than XCDs spread over the chip; from the list and from the mask
+@pytest.mark.parametrize("block,B,H,nb,D,planned", [
+    (64, 6, 8, 16, 64, False), (64, 7, 8, 14, 64, True), (64, 5, 8, 16, 64, False), (64, 5, 8, 17, 64, True), (64, 3, 8, 21, 64, False),
+    (64, 2, 8, 32, 64, False), (64, 2, 8, 33, 64, True), (64, 2, 8, 24, 128, False), (64, 2, 8, 25, 128, True), (64, 1, 8, 32, 128, False),
+    (64, 1, 8, 33, 128, True), (64, 1, 4, 128, 128, False), (64, 1, 4, 130, 128, True), (64, 1, 3, 172, 128, True), (64, 1, 2, 65, 64, False),
+    (128, 21, 8, 6, 64, False), (128, 22, 8, 6, 64, True), (128, 9, 8, 7, 64, False), (128, 10, 8, 7, 64, True), (128, 4, 8, 15, 64, False),
+    (128, 5, 8, 15, 64, True), (128, 1, 8, 15, 128, False), (128, 1, 8, 16, 128, True), (128, 4, 8, 15, 128, False), (128, 5, 8, 13, 128, True)])
+def test_either_side_of_the_plan_rules(block, B, H, nb, D, planned):
+    order = counts_lists_and_plan(block, B, H, nb, D)[..., 0]
+    own = np.full(order.shape, -1)                 # a workgroup's row where there is no plan
+    for x in range(8):
+        for i in range(order.shape[1]):
+            g = i // nb
+            if (g * 8 + x) < B * H:
+                own[x, i] = (g * 8 + x) * nb + (i + g * nb // 32 * ((3 * nb + 7) // 8)) % nb
+    assert (order == own).all() == (not planned)
