@@ -122,7 +122,7 @@ struct AttnParams {
     int segs;                // sparse: plan segments that hold items, min(XCDS, B*H)
     unsigned seg_magic;      // ceil(2^32 / segs)
     int planned;             // sparse: 1 when the plan is in `order`, 0 when every workgroup plans for itself
-    int pmax;                // sparse, 128-token tiles: partial-result slots per XCD
+    int pmax;                // sparse, 128-token tiles: partial-result slots per segment
     float c;                 // scale * log2(e)
 };
 
@@ -280,7 +280,7 @@ constexpr __host__ __device__ int segments(int BH, int nb, int block)
 constexpr __host__ __device__ int segment_cus(int BH, int nb, int block) { return CUS_PER_XCD * XCDS / segments(BH, nb, block); }
 constexpr int SPLIT_MIN_BLOCKS = 8;
 constexpr int SPLIT_MAX_PIECES = 16;
-constexpr int SPLIT_SLOTS = 256;                 // partial-result slots per XCD (the rule needs < 256)
+constexpr int SPLIT_SLOTS = 256;                 // partial-result slots per segment, at most (and one per item: workspace_layout)
 constexpr int ENTRY_COST = 2, PIECE_COST = 2;    // in key-blocks of time at D = 128
 // (Taken from the loop of 32x32x16 MFMAs; on the stream, over 21 shapes by 6 densities at D = 128, costs of 1 and 1 are
 // 0.1 % faster on all-ones masks in the mean (3.4 % at best), 3 and 3 0.4 % slower there (10.9 % at worst), and 2 or 3
@@ -289,12 +289,17 @@ constexpr int ENTRY_COST = 2, PIECE_COST = 2;    // in key-blocks of time at D =
 // The rule of one XCD.  P(c) = round(c * g / total) pieces for an item with c kept key-blocks
 // (g granules: pieces of about total / g), or p_all pieces for every item when that is set;
 // in both cases at most c / SPLIT_MIN_BLOCKS and SPLIT_MAX_PIECES, at least 1.  A segment of more than 32 CUs: as many in
-// place of 32, but no more granules than partial-result slots: they are handed out in item order, and the text rows, which
-// need them most, come last (H = 2, N = 16896, density 0.1, D = 128: 282 us without that limit).
+// place of 32, but no more granules than partial-result slots (or than 32 CUs get): they are handed out in item order, and the
+// text rows, which need them most, come last (H = 2, N = 16896, density 0.1, D = 128: 282 us without that limit).  The slots of
+// a segment are not more for having more CUs, so long rows that are nearly alike stay whole there and leave CUs idle.
 //   D = 128: g = 32 CUs x 2.5.  Rows that are all about alike (the longest within 1/9 of the
 //     mean: an all-ones mask) are not told apart by their lengths; what matters then is how
 //     many rounds the 64 places of the XCD need, so p_all is the P that minimises
-//     rounds(P) * (piece length + cost of an entry), the first such P.
+//     rounds(P) * (piece length + cost of an entry), the first such P.  There may be slots for the pieces of the first rows
+//     only.  Where rows outnumber CUs that still fills the last round; with a CU for every row the call lasts as long as
+//     the rows that stay whole, so then a P counts only if all of them get their slots.  us, H heads, all ones, some rows in pieces
+//     / none: rows <= CUs 4, N = 6144 113.5 / 105.7; 5, 4608 88.5 / 82.2; 7, 4608 93.6 / 84.0; rows > CUs 2, 16896 298 / 341;
+//     4, 16896 480 / 678; 6, 12288 402 / 496.
 //   D = 64: g = 32 x 4; rows all alike: 32 x 12 (fewer items than the 128 places: cut them all).
 struct SplitRule {
     int g;
@@ -328,7 +333,7 @@ __device__ __forceinline__ SplitRule split_rule(int D, int cus, int pmax, int n_
             r.p_all = 1;
             const int top = max_c / SPLIT_MIN_BLOCKS < SPLIT_MAX_PIECES ? max_c / SPLIT_MIN_BLOCKS : SPLIT_MAX_PIECES;
             for (int P = 2; P <= top; ++P)
-                if (costs[P - 1] < best) { best = costs[P - 1]; r.p_all = P; }
+                if (costs[P - 1] < best && (n_items > cus || n_items * P <= pmax)) { best = costs[P - 1]; r.p_all = P; }
         }
     }
     const auto granules = [&](int n) { return D == 128 ? n * 5 / 2 : n * (alike ? 12 : 4); };
@@ -2628,7 +2633,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 struct WorkspaceLayout {
     size_t counts_off, order_off, index_off, arrived_off, partial_off, total;
     int chunk;    // plan entries per XCD
-    int pmax;     // partial-result slots per XCD (128-token tiles)
+    int pmax;     // partial-result slots per segment (128-token tiles)
 };
 
 // items of one XCD: (b,h) pairs are dealt round-robin over the XCDs
@@ -2636,8 +2641,8 @@ inline int plan_items(int B, int H, int nb) { return ((B * H + XCDS - 1) / XCDS)
 
 // 64-token tiles:  counts | order int32[8*chunk]   | index
 // 128-token tiles: counts | records PlanRec[8*chunk] | index | arrived int32[8*pmax] | partial slots [8*pmax]
-// `slots` < 0: as many partial-result slots per XCD as the split rule can ever use
-// (min(256, items)); otherwise that many at most (fewer slots = fewer items cut).
+// `slots` < 0: min(256, items) partial-result slots per segment; otherwise that many at most.  The split rule may ask for
+// more (an item that gets none stays whole): of rows by length it cuts a few, of rows all alike up to every one.
 inline WorkspaceLayout workspace_layout(int B, int H, int nb, int D, int block, int slots = -1)
 {
     const size_t rows = (size_t)B * H * nb;

@@ -101,6 +101,22 @@ def test_pairs_dealt_out_over_the_chip(H, block, nb):
     assert cut or block == 64
 
 
+@pytest.mark.parametrize("H,nb,cut", [(4, 48, False), (7, 36, False), (8, 24, False), (4, 65, True), (7, 37, True), (8, 33, True), (24, 24, True)])
+def test_rows_all_alike_are_cut_where_it_helps(H, nb, cut):
+    """All ones, D = 128: with a CU for every row none is cut, as there are too few slots for the pieces of all of them."""
+    D, block = 128, 128
+    N = nb * block
+    g = torch.Generator(device="cuda").manual_seed(H * nb)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = torch.ones((1, H, nb, nb), dtype=torch.uint8, device="cuda")
+    ws = torch.full((ra.rapid_attn_workspace_bytes(1, H, N, D, block),), 0xa5, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, 7.0)
+    ra.rapid_attn_block_sparse(q, k, v, o, mask, block, N, workspace=ws)
+    check(o, reference(q, k, v, mask, block, N, D ** -0.5), N, f"H={H} nb={nb}")
+    counts, order, _, geo = read_plan(ws.cpu().numpy(), 1, H, nb, D, block)
+    assert bool(check_plan(counts, order, geo, 1, H, nb, block, D)) == cut
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("block", [64, 128])
 def test_reference_of_the_exponents_moves(D, block):
