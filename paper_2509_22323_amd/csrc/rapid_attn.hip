@@ -32,7 +32,7 @@
 //                               record (a query-block or a piece of its kept list); pieces are
 //                               merged by the last one to finish.  D = 128 on the 16x16x32 stream
 //   attn_sparse_wide_kernel     the same at D = 64 on the stream, for calls of many rows
-//   attn_sparse_pp_kernel<D,2>  sparse, 64-token mask tiles: one query-block per workgroup on the stream, the
+//   attn_sparse_pp_kernel<D>    sparse, 64-token mask tiles: one query-block per workgroup on the stream, the
 //                               keys of a block split between two groups of wavefronts
 //   plan_small_kernel           launch plan in one launch, from the mask or from counts (up to 64 blocks per side); the
 //                               attention kernels then read their rows of the mask themselves, and where all rows
@@ -651,7 +651,7 @@ __global__ __launch_bounds__(1024) void plan_small_kernel(
     // Longest-first order would give CU 0 the longest record of every round of 32, so the second
     // and the fourth round of the first wave (as many records as the XCD has places) run backwards.
     // Later records go wherever a place frees up first and stay longest first.
-    const int cus = segment_cus(BH, nb, PIECES ? 128 : 64);              // records of a round
+    const int cus = PIECES ? segment_cus(BH, nb, 128) : CUS_PER_XCD;      // records of a round (few pairs of up to 64 64-token blocks: no plan)
     auto place = [&](int len) {
         int pos = atomicAdd(&to[nb - len], 1);
         const int first = pos < 3 * cus ? cus : 3 * cus, at = pos - first;    // of the second, of the fourth round
@@ -708,12 +708,13 @@ struct Geo {
     static constexpr int TILE_BYTES = KT * ROW_BYTES;       // 16384 | 8192
     static constexpr int ROWS_PER_LOAD = 1024 / ROW_BYTES;  // 4 | 8
     static constexpr int LOADS = TILE_BYTES / 1024;         // 16 | 8
+    // (The swizzles are those of attn_sparse_sg_kernel<64>; the stream has its own.)
     // K is read 16 bytes per lane, lanes = consecutive rows at one logical chunk:
     // 16 consecutive rows must land on 16 different chunks of the 256-byte bank line.
-    static __device__ __forceinline__ int swz_k(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+    static __device__ __forceinline__ int swz_k(int row) { static_assert(D == 64, ""); return (row >> 1) & 7; }
     // V is read by the transpose read as 4-row x 64-byte patches: consecutive rows must
     // land on different 64-byte groups of the bank line.
-    static __device__ __forceinline__ int swz_v(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
+    static __device__ __forceinline__ int swz_v(int row) { static_assert(D == 64, ""); return ((row >> 1) & 1) << 2; }
 };
 
 // Issue the asynchronous copy of rows key0..key0+63 of `src` into an LDS tile.  Rows at or
@@ -2216,19 +2217,19 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(c
 // longer than its CU's share.  Copies are a whole step ahead and no more: stages for longer leads (4 of K and V) leave
 // one workgroup per CU at D = 128 (1.2 to 1.7 times the time) and two at D = 64 (1.05 to 1.2 times); all copies at the
 // head of the half step in which they are spread out: 1 to 1.5 % slower.
-// us, B = 1, H = 24, densities 0.1 / 0.3 / 1, two wavefront groups on alternating phases of 32x32x16 MFMAs before and
-// now: D = 128, N = 2816 58.8 92.9 220 -> 35.0 54.3 122; N = 8960 272 589 1716 -> 159 331 935; D = 64, N = 2816 28.1 44.2
-// 106 -> 22.2 32.5 73.2; N = 384 16.3 (two planner launches and the host either way).
+// us, B = 1, H = 24, no text rows, densities 0.1 / 0.3 / 1, two wavefront groups on alternating phases of 32x32x16 MFMAs behind two
+// planner launches before and now: D = 128, N = 384 16.3 16.5 18.6 -> 7.5 9.2 11.4; 2816 56 90 221 -> 33 51 122; 8960 261 579
+// 1727 -> 156 328 952; D = 64, N = 2816 27 43 106 -> 20 29 71.
 // ---------------------------------------------------------------------------
 template <int D> struct Sparse64Plan { typedef StreamPlan<128, 2, 2, 2, 1, 2, 3, 4, 4> P; };
 template <> struct Sparse64Plan<64> { typedef StreamPlan<64, 2, 2, 2, 1, 2, 3, 4, 4> P; };
 
-template <int D, int WK>
+template <int D>
 __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) void attn_sparse_pp_kernel(const AttnParams p)
 {
     typedef typename Sparse64Plan<D>::P P;
     typedef typename P::S S;
-    static_assert(P::QT == 64 && P::WK == WK, "one item = 64 queries");
+    static_assert(P::QT == 64, "one item = 64 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
     const auto work = sparse_work<64>(p);
@@ -2880,8 +2881,8 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
         else if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(SparsePlan<128>::P::NW * 64), 0, s, p);
     } else {
-        if (D == 64) hipLaunchKernelGGL((attn_sparse_pp_kernel<64, 2>), grid, dim3(Sparse64Plan<64>::P::NW * 64), 0, s, p);
-        else hipLaunchKernelGGL((attn_sparse_pp_kernel<128, 2>), grid, dim3(Sparse64Plan<128>::P::NW * 64), 0, s, p);
+        if (D == 64) hipLaunchKernelGGL((attn_sparse_pp_kernel<64>), grid, dim3(Sparse64Plan<64>::P::NW * 64), 0, s, p);
+        else hipLaunchKernelGGL((attn_sparse_pp_kernel<128>), grid, dim3(Sparse64Plan<128>::P::NW * 64), 0, s, p);
     }
     return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
 }

@@ -34,7 +34,7 @@ WANT = {  # kernel name fragment -> waves per SIMD its launch plan counts on
     "attn_dense_stream_kernelILi64E": 2, "attn_dense_stream_kernelILi128E": 2,
     "attn_dense_pp_kernelILi64E": 4, "attn_dense_pp_kernelILi128E": 2, "attn_sparse_wide_kernel": 2,
     "attn_sparse_sg_kernelILi64E": 4, "attn_sparse_sg_kernelILi128E": 2,
-    "attn_sparse_pp_kernelILi64ELi2E": 3, "attn_sparse_pp_kernelILi128ELi2E": 2,
+    "attn_sparse_pp_kernelILi64E": 3, "attn_sparse_pp_kernelILi128E": 2,
 }
 
 
