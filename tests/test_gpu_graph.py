@@ -13,7 +13,7 @@ from gpu_common import from_dev, to_dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,N", [(128, 1152), (64, 8320)])     # one-launch planner / compaction + planner
+@pytest.mark.parametrize("D,N", [(128, 1152), (128, 2304), (64, 8320)])     # no plan launch / one / compaction + planner
 def test_select_attend_and_cache_in_a_graph(D, N):
     B, H, block, kv_len, text_start = 2, 3, 128, N - 40, N - 256
     nb = N // block
