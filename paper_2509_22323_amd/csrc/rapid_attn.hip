@@ -1166,7 +1166,6 @@ struct StreamRegs {
     bf16x8 ones;                               // 1.0 everywhere
     unsigned seen;                             // all packed probabilities since the references last moved, or-ed
     float x0, x1, e0, e1;                      // pairs under way
-    unsigned kc, kn, vc;                       // offsets of a step outside the unrolled loop
 };
 
 constexpr float REF_LOWEST = -1e30f;           // of a query whose first step has no finite score
@@ -1186,18 +1185,12 @@ __device__ __forceinline__ void stream_addresses(StreamRegs<S, D>& x, unsigned k
 }
 
 // Request item I (I >= NI: item I - NI of the next step); KC, KN, VC: byte offsets of the 32 rows
-// of K_{i+1}, K_{i+2} and V_i from the addresses of the context; KC < 0: they are in x.kc, x.kn, x.vc.
+// of K_{i+1}, K_{i+2} and V_i from the addresses of the context.
 template <class S, int D, int KC, int KN, int VC, int I>
 __device__ __forceinline__ void stream_request(StreamRegs<S, D>& x)
 {
     constexpr int J = I % S::NI, slot = J % S::NBUF;
-    if constexpr (KC < 0 && J < S::NQK) {
-        asm volatile("ds_read_b128 %0, %1 offset:%2"
-                     : "=&v"(x.kf[slot]) : "v"(x.kaddr[J / 2] + (I < S::NI ? x.kc : x.kn)), "i"(J % 2 * 16 * S::RB));
-    } else if constexpr (KC < 0) {
-        asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:%3"
-                     : "=&v"(x.lo[slot]), "=&v"(x.hi[slot]) : "v"(x.vaddr[J - S::NQK] + x.vc), "i"(16 * S::RB));
-    } else if constexpr (J < S::NQK) {
+    if constexpr (J < S::NQK) {
         constexpr int t = J / 2, kt = J % 2;
         asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(x.kf[slot]) : "v"(x.kaddr[t]), "i"((I < S::NI ? KC : KN) + kt * 16 * S::RB));
     } else {
@@ -1632,11 +1625,26 @@ __device__ __forceinline__ void stream_output_rows(const StreamRegs<S, D>& x, co
 
 // step(U), step(U + 1), .. at i + U, i + U + 1, ..
 template <int U, int TO, class Step>
-__device__ __forceinline__ void static_steps(Step& step, int& i)
+__device__ __forceinline__ void static_steps(Step& step, int i)
 {
     if constexpr (U < TO) {
         step(std::integral_constant<int, U>(), i + U);
         static_steps<U + 1, TO>(step, i);
+    }
+}
+// The same until step last - 1 has run: then end(U + 1) and true.
+template <int U, int TO, class Step, class End>
+__device__ __forceinline__ bool static_steps_until(Step& step, End& end, int i, int last)
+{
+    if constexpr (U < TO) {
+        step(std::integral_constant<int, U>(), i + U);
+        if (i + U + 1 == last) {
+            end(std::integral_constant<int, U + 1>());
+            return true;
+        }
+        return static_steps_until<U + 1, TO>(step, end, i, last);
+    } else {
+        return false;
     }
 }
 
@@ -1676,12 +1684,20 @@ struct StreamPlan {
     static constexpr __host__ __device__ int v_off(int i) { return (i / SPT % NSV) * TILE + (i % SPT) * 32 * S::RB; }
 };
 
+// Where a run ends, as Keys::LAST: the number of its last step modulo UNROLL where that is known when compiling; ANY: what is left
+// over after whole runs of the unrolled loop goes through a second copy of it that can be left after every step; SHORT: so few
+// steps that the loop itself can be.  (Steps outside the unrolled loop added up LDS addresses, moved the scores and issued their copies
+// all at once.)  us, such steps / now: SHORT, rows of 2, 4, 24 64-token blocks, D = 128, H = 64, N = 2048 39.9 48.7 120.8 / 37.5 44.0
+// 113.9; ANY, dense, D = 128, N = 4608 (7 of 143 steps) 216.3 / 213.3, D = 64, B = 2, N = 4480 226.5 / 224.5.  SHORT for dense calls:
+// 0.4 to 1 % slower there, N = 16896, D = 128 0.5 %.
+enum { ANY = -1, SHORT = -2 };
 // Which tiles: at(t, u, moved, ahead) is the first key of tile t; the caller stands in tile t - ahead, which is tile
 // u - ahead of the unrolled steps, both known when compiling, and has called advance in tile UNROLL / SPT - 1 of them or
 // not; next_tile when it has done with a tile.
 // Tiles in order: the dense path.
 template <class P>
 struct AllKeys {
+    static constexpr int LAST = ANY;
     __device__ __forceinline__ int at(int t, int, bool, int) const { return t * P::KTS; }
     __device__ __forceinline__ void next_tile() {}
     __device__ __forceinline__ void advance() {}
@@ -1843,6 +1859,7 @@ __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork
 template <class P>
 struct KeptKeys {
     static_assert(P::KTS == 32 && P::UNROLL == 4, "");
+    static constexpr int LAST = 3;
     KeptBlocks<128> kept;
     int b0, b1, b2;
     __device__ __forceinline__ KeptKeys(const KeptBlocks<128>& kept_) : kept(kept_)
@@ -1869,6 +1886,7 @@ struct KeptKeys {
 template <class P>
 struct KeptTiles {
     static_assert(P::KTS == 64 && P::SPT == 1 && P::KLEAD == 3 && P::VLEAD == 2, "");
+    static constexpr int LAST = SHORT;
     KeptBlocks<64> kept;
     int b0, b1, b2, b3;
     __device__ __forceinline__ KeptTiles(const KeptBlocks<64>& kept_) : kept(kept_)
@@ -1889,8 +1907,9 @@ struct KeptTiles {
     __device__ __forceinline__ void advance() {}
 };
 
-// Steps 0 .. last of this workgroup's queries against the tiles of `keys` (tiles at or beyond kv_len are all masked).  ALIGNED: last + 1 is a multiple of P::UNROLL.
-template <class P, bool ALIGNED, class Keys>
+// Steps 0 .. last of this workgroup's queries against the tiles of `keys` (tiles at or beyond kv_len are all masked).  The
+// unrolled loop is left behind whichever of its steps is the last but one.
+template <class P, class Keys>
 __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x, char* lds, const Rows& Q, const Rows& K, const Rows& V,
                                               int q0, int kv_len, float c, int last, Keys& keys, int wave, int lane)
 {
@@ -1967,16 +1986,14 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     x.seen = 0u;
     soft_half<S, D, 0>(x, st[0], c, pw);
 
-    // Step i.  U = i % UNROLL where that is known when compiling; U = UNROLL: offsets in x, scores from
-    // st[0] to st[0].
+    // Step i.  U = i % UNROLL.
     TileBuffer kb, vb;                            // the tiles being copied
     auto step = [&](auto u, int i) {
         constexpr int U = decltype(u)::value;
-        constexpr bool RT = U == P::UNROLL;
         constexpr bool FIRST_OF_TILE = U % P::SPT == 0;
-        Scores<S>& sc = st[RT ? 0 : U & 1];
-        Scores<S>& sn = st[RT ? 1 : (U + 1) & 1];
-        constexpr int KC = RT ? -1 : P::k_off(U + 1), KN = P::k_off(U + 2), VC = P::v_off(U);
+        Scores<S>& sc = st[U & 1];
+        Scores<S>& sn = st[(U + 1) & 1];
+        constexpr int KC = P::k_off(U + 1), KN = P::k_off(U + 2), VC = P::v_off(U);
         // the copies of this tile's barrier, one every few items until the next barrier (SPT = 1: in the
         // second half only)
         constexpr int SLOTS = P::SPT == 1 ? S::NPV : S::NPV + S::NI;
@@ -1984,7 +2001,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         constexpr int T0 = U / P::SPT;
         auto hook = [&](auto item) {
             constexpr int at = decltype(item)::value - S::NQK + (U % P::SPT) * S::NI;
-            if constexpr (!RT && at >= 0 && at % GAP == 0) {
+            if constexpr (at >= 0 && at % GAP == 0) {
 #pragma unroll
                 for (int e = at / GAP * PER; e < at / GAP * PER + PER && e < 2 * LC; ++e) {
                     if (e < LC) copy_v(vb, e, (T0 + P::VLEAD) % P::NSV * P::TILE);
@@ -1992,52 +2009,54 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
                 }
             }
         };
-        if constexpr (RT) { x.kc = P::k_off(i + 1); x.kn = P::k_off(i + 2); x.vc = P::v_off(i); }
         if constexpr (FIRST_OF_TILE) step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, [](auto) {});
         else step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, hook);
         soft_close<S, D>(x, sc, c, pw);
         const int t = i / P::SPT;
         mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1, U + 1, false, 1) + wk * 32 : keys.at((i + 1) / 2, 0, false, 0) + (i + 1) % 2 * 32, kv_len, lane);
-        if (RT ? i % P::SPT == 0 : FIRST_OF_TILE) {
-            constexpr bool MOVE = !RT && U / P::SPT == P::UNROLL / P::SPT - 1;
+        if constexpr (FIRST_OF_TILE) {
+            constexpr bool MOVE = U / P::SPT == P::UNROLL / P::SPT - 1;
             if constexpr (MOVE) keys.advance();
             vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, U / P::SPT + P::VLEAD, MOVE, P::VLEAD), kv_len);
             kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, U / P::SPT + P::KLEAD, MOVE, P::KLEAD), kv_len);
             keys.next_tile();
             wait_vmcnt<P::LOOSE>();
             phase_barrier();
-            if constexpr (RT) {
-#pragma unroll
-                for (int e = 0; e < LC; ++e) copy_v(vb, e, (t + P::VLEAD) % P::NSV * P::TILE);
-#pragma unroll
-                for (int e = 0; e < LC; ++e) copy_k(kb, e, (t + P::KLEAD) % P::NSK * P::TILE);
-            }
         }
         Probs<S> pn;
         step_pv<S, D, KC, KN, VC, S::NQK>(x, sn, c, pw, pn, hook);
 #pragma unroll
         for (int q = 0; q < S::NQ; ++q) { pw.q[q][0] = pn.q[q][0]; pw.q[q][1] = pn.q[q][1]; }
-        if constexpr (RT) st[0] = st[1];
     };
-    int i = 0;
     if (last > 0) {
         stream_pin<S, D>(x);
         first_qk<S, D, P::k_off(1), 0, true>(x, st[1]);     // the first items of step 0's stream
         stream_wait<S, D, 0, S::PD>(x);
-        for (; i + P::UNROLL <= last; i += P::UNROLL) {
-            stream_pin<S, D>(x);
-            static_steps<0, P::UNROLL>(step, i);
+        auto end = [&](auto u) { if constexpr (decltype(u)::value & 1) st[0] = st[1]; };
+        int i = 0;
+        if constexpr (Keys::LAST == SHORT) {
+            for (;; i += P::UNROLL) {
+                stream_pin<S, D>(x);
+                if (static_steps_until<0, P::UNROLL>(step, end, i, last)) break;
+            }
+        } else {
+            for (; i + P::UNROLL <= last; i += P::UNROLL) {
+                stream_pin<S, D>(x);
+                static_steps<0, P::UNROLL>(step, i);
+            }
+            if constexpr (Keys::LAST == ANY) {
+                if (i < last) static_steps_until<0, P::UNROLL - 1>(step, end, i, last);
+            } else {
+                static_steps<0, Keys::LAST>(step, i);
+                end(std::integral_constant<int, Keys::LAST>());
+            }
         }
-        if constexpr (ALIGNED) static_steps<0, P::UNROLL - 1>(step, i);
-        else for (; i < last; ++i) step(std::integral_constant<int, P::UNROLL>(), i);
         stream_drain<S, D>(x);
     }
-    constexpr int END = (P::UNROLL - 1) & 1;      // where an aligned run leaves its scores
-    if constexpr (ALIGNED && END == 1) st[0] = st[1];
     soft_half<S, D, 1>(x, st[0], c, pw);
     soft_close<S, D>(x, st[0], c, pw);
 #pragma unroll
-    for (int b = 0; b < S::DT; ++b) x.vaddr[b] += ALIGNED ? P::v_off(P::UNROLL - 1) : P::v_off(i);
+    for (int b = 0; b < S::DT; ++b) x.vaddr[b] += P::v_off(last);
     last_pv<S, D, S::NQK, true>(x, pw);
     last_pv<S, D, S::NQK, false>(x, pw);
     wait_vmcnt<0>();                              // no copy may land once the stages serve something else
@@ -2135,7 +2154,7 @@ __device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int b
     }
     AllKeys<P> keys;
     const int last = ((kv_len + 31) / 32 + P::WK - 1) / P::WK - 1;
-    stream_attend<P, false>(x, lds, Q, K, V, q0, kv_len, p.c, last, keys, wave, lane);
+    stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, last, keys, wave, lane);
     __syncthreads();                              // every wavefront has read its last tile
     if constexpr (P::WK > 1) {
         stream_merge<P>(x, lds, wave, lane);
@@ -2282,7 +2301,7 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
         return;
     }
     KeptTiles<P> keys(work.kept);
-    stream_attend<P, false>(x, lds, Q, K, V, q0, kv_len, p.c, n - 1, keys, wave, lane);
+    stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, n - 1, keys, wave, lane);
     leave_plan<64>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
     stream_merge<P>(x, lds, wave, lane);
@@ -2350,7 +2369,7 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     }
     // Whole blocks: what lies at or beyond kv_len in a row's last block is masked, at most three steps.
     KeptKeys<P> keys(work.kept);
-    stream_attend<P, true>(x, lds, Q, K, V, q0, kv_len, p.c, rec.nblk * 4 - 1, keys, wave, lane);
+    stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, rec.nblk * 4 - 1, keys, wave, lane);
     leave_plan<128>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
     if (rec.w < 0) {                              // the whole item
