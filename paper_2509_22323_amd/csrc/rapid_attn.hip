@@ -73,12 +73,14 @@ constexpr float LOG2E = 1.44269504088896340736f;
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
 // A [B, H, tokens, D] tensor handed over as one or two token segments: token t < n0 is row t
-// of segment 0, any other token is row t - n0 of segment 1 (MM-DiT keeps the image and the
+// of segment 0, any other token row t - n0 of segment 1 (MM-DiT keeps the image and the
 // text stream in separate tensors and joins them only for attention).  Strides in elements,
-// D contiguous; head and token strides are common to both segments.
+// D contiguous; head and token strides are common to both segments, all strides to Q, K and V.
 struct SegTensor {
     const __bf16* seg0;
-    const __bf16* seg1;      // null when there is one segment
+    const __bf16* seg1;      // of no use when there is one segment
+};
+struct SegStrides {
     long long sb0, sb1;      // batch strides
     long long sh, sn;        // head stride, token stride
 };
@@ -93,18 +95,37 @@ struct Rows {
     __device__ __forceinline__ const char* row(int r) const { return (r < n0 ? base0 : base1) + (size_t)r * row_bytes; }
 };
 
-__device__ __forceinline__ Rows rows_of(const SegTensor& t, int b, int h, int n0)
+__device__ __forceinline__ Rows rows_of(const SegTensor& t, const SegStrides& s, int b, int h, int n0)
 {
+    const long long head = h * s.sh;
     Rows r;
-    r.base0 = (const char*)(t.seg0 + (size_t)b * t.sb0 + (size_t)h * t.sh);
-    r.base1 = t.seg1 ? (const char*)(t.seg1 + (size_t)b * t.sb1 + (size_t)h * t.sh) - (size_t)n0 * t.sn * 2 : r.base0;
+    r.base0 = (const char*)(t.seg0 + (b * s.sb0 + head));
+    r.base1 = (const char*)(t.seg1 + (b * s.sb1 + head - n0 * s.sn));
     r.n0 = n0;
-    r.row_bytes = (unsigned)(t.sn * 2);
+    r.row_bytes = (unsigned)(s.sn * 2);
     return r;
+}
+
+// A divisor that only the host knows.  n / d in scalar code is a division by way of vector floats, 35 instructions; as a high
+// product with magic = ceil(2^32 / d) it is exact while n * d < 2^32 (what it is too large by is less than n * d / 2^32 / d).
+// magic = 0: by division (d = 1, or dividends that large).
+struct Divisor {
+    int d;
+    unsigned magic;
+    __device__ __forceinline__ int of(int n) const
+    {
+        if (magic != 0u) return (int)__umulhi((unsigned)n, magic);
+        return d == 1 ? n : __builtin_amdgcn_readfirstlane(n / d);
+    }
+};
+inline Divisor divisor(int d, long long dividends)
+{
+    return {d, d > 1 && dividends * d < 0x100000000LL ? 0xffffffffu / (unsigned)d + 1u : 0u};
 }
 
 struct AttnParams {
     SegTensor q, k, v, o;
+    SegStrides in, out;      // of Q, K and V; of O
     const int32_t* kv_lens;  // per-sample valid tokens (device, [B]) or null: kv_len for all
     int n0;                  // tokens in the first segment (N when there is one)
     const unsigned char* mask;    // sparse: the block mask where the kernels read their rows of it themselves, else null
@@ -113,8 +134,9 @@ struct AttnParams {
     int32_t* index;          // sparse: kept key-block lists, nb per row
     int32_t* arrived;        // sparse, 128-token tiles: finished pieces per split item
     char* partial;           // sparse, 128-token tiles: partial results of the pieces of split items
-    int H, N, kv_len;
-    int nq;                  // query tiles per (sample, head)
+    int N, kv_len;
+    Divisor H;
+    Divisor nq;              // query tiles per (sample, head)
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
     int whole, cut;          // dense: whole items of an XCD, pieces of each of the others (3: pieces of 192 queries)
@@ -125,6 +147,18 @@ struct AttnParams {
     int pmax;                // sparse, 128-token tiles: partial-result slots per segment
     float c;                 // scale * log2(e)
 };
+
+// Valid tokens of a sample: clamped to 0..N where they are given per sample.
+__device__ __forceinline__ int valid_tokens(const AttnParams& p, int smp)
+{
+    int kv_len = p.kv_len;
+    if (p.kv_lens != nullptr) {
+        kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[smp];
+        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
+    }
+    return kv_len;
+}
 
 // ---------------------------------------------------------------------------
 // Mask compaction: one wavefront per (b, h, query-block) row of the mask.
@@ -1533,43 +1567,39 @@ __device__ __forceinline__ void first_qk(StreamRegs<S, D>& x, Scores<S>& sn)
     }
 }
 
-// Byte offset of this lane's chunk from the tile's first row, in copy instruction ld (1 KB of the stage).
+// Byte offset of this lane's chunk in its row, in a copy instruction (1 KB of the stage) whose row of this lane is `row`.
 template <class S, int D, bool IS_V>
-__device__ __forceinline__ unsigned stream_copy_offset(unsigned row_bytes, int ld, int lane)
+__device__ __forceinline__ unsigned stream_copy_chunk(int row, int lane)
 {
     typedef Geo<D> G;
-    const int row = ld * G::ROWS_PER_LOAD + lane / G::CPR;
-    const int logical = (lane % G::CPR) ^ (IS_V ? S::swz_v(row) : S::swz_k(row));
-    return (unsigned)row * row_bytes + (unsigned)logical * 16u;
+    return (unsigned)((lane % G::CPR) ^ (IS_V ? S::swz_v(row) : S::swz_k(row))) * 16u;
 }
 
 // Q^T operands requested by explicit assembly (see load_q_async): lane (n, g) holds elements
-// 32 t + 8 g .. + 7 of query 16 q + n.  Rows that are not valid read row 0 and are zeroed.
+// 32 t + 8 g .. + 7 of query 16 q + n.  Rows at or beyond kv_len lie outside the buffer and come as zeros.
 template <class S, int D>
 __device__ __forceinline__ void stream_load_q(const Rows& Q, int q0, int kv_len, int lane, u32x4 (&raw)[S::NQ][S::KS])
 {
+    const TileBuffer b = tile_buffer<16 * S::NQ>(Q, q0, kv_len);
+    const i32x4 rsrc = {(int)b.lo, (int)b.hi, (int)b.bytes, 0x00020000};
+    const unsigned off = (unsigned)(lane & 15) * Q.row_bytes + (unsigned)(lane >> 4) * 16u;
 #pragma unroll
-    for (int q = 0; q < S::NQ; ++q) {
-        const int row = q0 + 16 * q + (lane & 15);
-        const __bf16* src = (const __bf16*)Q.row(row < kv_len ? row : 0) + 8 * (lane >> 4);
+    for (int q = 0; q < S::NQ; ++q)
 #pragma unroll
         for (int t = 0; t < S::KS; ++t)
-            asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(raw[q][t]) : "v"(src), "i"(64 * t));
-    }
+            asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen offset:%3"
+                         : "=v"(raw[q][t]) : "v"(off + (unsigned)(16 * q) * Q.row_bytes), "s"(rsrc), "i"(64 * t));
 }
 template <class S, int D>
-__device__ __forceinline__ void stream_q_arrived(StreamRegs<S, D>& x, int q0, int kv_len, int lane, u32x4 (&raw)[S::NQ][S::KS])
+__device__ __forceinline__ void stream_q_arrived(StreamRegs<S, D>& x, u32x4 (&raw)[S::NQ][S::KS])
 {
 #pragma unroll
-    for (int q = 0; q < S::NQ; ++q) {
-        const bool valid = q0 + 16 * q + (lane & 15) < kv_len;
+    for (int q = 0; q < S::NQ; ++q)
 #pragma unroll
         for (int t = 0; t < S::KS; ++t) {
             asm volatile("" : "+v"(raw[q][t]));
-            const u32x4 zero = {0u, 0u, 0u, 0u};
-            x.qf[q][t] = __builtin_bit_cast(bf16x8, valid ? raw[q][t] : zero);
+            x.qf[q][t] = __builtin_bit_cast(bf16x8, raw[q][t]);
         }
-    }
 }
 
 // O = acc / l as bf16, query rows q0 .. q0 + 16 NQ - 1 of this wavefront; rows at or beyond kv_len and
@@ -1791,9 +1821,10 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
     if (!p.planned) {
         // The dispatcher deals the workgroups of an XCD out to its 32 CUs in turn; rows with the same number (text rows,
         // the long ones) would meet on the same CU where 32 is a multiple of nb, so every 32 workgroups start 3/8 of the rows on.
-        const int g = i / p.nb, pair = g * XCDS + seg;
+        const int g = p.nq.of(i), pair = g * XCDS + seg;    // (nq = nb)
         if (pair * p.nb < p.items) {
-            w.rec.item = pair * p.nb + (i + g * p.nb / CUS_PER_XCD * ((3 * p.nb + 7) / 8)) % p.nb;
+            const int turned = i + g * p.nb / CUS_PER_XCD * ((3 * p.nb + 7) / 8);
+            w.rec.item = pair * p.nb + turned - p.nq.of(turned) * p.nb;
             if (p.mask == nullptr) w.rec.nblk = ((cptr_t)p.counts)[w.rec.item];
         }
     } else if (BLOCK == 64) {
@@ -1811,7 +1842,7 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
     if (item >= 0) {
         if (p.mask != nullptr) {                   // nb <= 64
             int kv_len = p.kv_len;
-            if (p.kv_lens != nullptr) kv_len = ((cptr_t)p.kv_lens)[item / p.nb / p.H];
+            if (p.kv_lens != nullptr) kv_len = ((cptr_t)p.kv_lens)[p.H.of(p.nq.of(item))];    // (nq = nb)
             kv_len = kv_len > p.N ? p.N : kv_len;
             const unsigned char byte = p.mask[(size_t)item * p.nb + (lane < p.nb ? lane : 0)];
             const bool keep = byte != 0 && lane < p.nb && lane * BLOCK < kv_len;
@@ -1929,10 +1960,13 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     u32x4 qraw[S::NQ][S::KS];
     stream_load_q<S, D>(Q, q0, kv_len, lane, qraw);
     unsigned koff[LC], voff[LC];
+    const int copy_row = wave * LC * Geo<D>::ROWS_PER_LOAD + lane / Geo<D>::CPR;
+    const unsigned copy_off = (unsigned)copy_row * K.row_bytes;    // (V's rows are as far apart)
 #pragma unroll
     for (int e = 0; e < LC; ++e) {
-        koff[e] = stream_copy_offset<S, D, false>(K.row_bytes, wave * LC + e, lane);
-        voff[e] = stream_copy_offset<S, D, true>(V.row_bytes, wave * LC + e, lane);
+        const int more = e * Geo<D>::ROWS_PER_LOAD;
+        koff[e] = copy_off + (unsigned)more * K.row_bytes + stream_copy_chunk<S, D, false>(copy_row + more, lane);
+        voff[e] = copy_off + (unsigned)more * K.row_bytes + stream_copy_chunk<S, D, true>(copy_row + more, lane);
     }
     const unsigned lds0 = (unsigned)(size_t)LDS_PTR(char, lds);
     const unsigned dst0 = lds0 + (unsigned)(wave * LC) * 1024u;
@@ -1958,7 +1992,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     constexpr int ISSUED = P::SPT == 1 ? (P::NSK + (P::NSV - 2)) * LC : (P::NSK + P::NSV - 1) * LC;
     stream_addresses<S, D>(x, lds0 + wk * 32 * S::RB, lds0 + VBASE + wk * 32 * S::RB, lane);
     wait_vmcnt<ISSUED - (P::SPT == 1 ? LC : 2 * LC)>();
-    stream_q_arrived<S, D>(x, q0, kv_len, lane, qraw);
+    stream_q_arrived<S, D>(x, qraw);
     const u32x4 one = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
     x.ones = __builtin_bit_cast(bf16x8, one);
     asm volatile("" : "+v"(x.ones));              // kept in registers
@@ -2134,15 +2168,10 @@ __device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int b
     typedef typename P::S S;
     constexpr int D = P::D;
     const int lane = threadIdx.x & 63;
-    int kv_len = p.kv_len;
-    if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
-        kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
-        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
-        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
-    }
-    const int smp = bh / p.H, head = bh % p.H;
-    const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
-    const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
+    const int smp = p.H.of(bh), head = bh - smp * p.H.d;
+    const int kv_len = valid_tokens(p, smp);
+    const Rows Q = rows_of(p.q, p.in, smp, head, p.n0), K = rows_of(p.k, p.in, smp, head, p.n0);
+    const Rows V = rows_of(p.v, p.in, smp, head, p.n0), O = rows_of(p.o, p.out, smp, head, p.n0);
     char* out_stage = lds + stage;
     StreamRegs<S, D> x;
     if (q00 >= kv_len) {                          // padding rows only: zero
@@ -2163,9 +2192,12 @@ __device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int b
     }
     stream_output_rows<S, D>(x, O, q0, kv_len, end, lane, out_stage);
 }
+// A (sample, head)'s `tile` queries number item % nq, from `ahead` on.
 template <class P>
-__device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int bh, int q00)
+__device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int item, int tile, int ahead)
 {
+    const int bh = p.nq.of(item), q00 = (item - bh * p.nq.d) * tile + ahead;
+    if (q00 >= p.N) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     dense_wave<P>(p, lds, bh, q00, q00 + wave / P::WK * 16 * P::NQ, p.N, wave, wave * (16 * P::NQ * (P::D * 2 + 16)));
 }
@@ -2216,24 +2248,22 @@ __global__ __launch_bounds__(DensePlan<D>::Whole::NW * 64, 2) void attn_dense_st
     const int i = blockIdx.x / XCDS, first = (blockIdx.x % XCDS) * p.chunk;
     if (i < p.whole) {
         const int item = first + i;
-        if (item < p.items) dense_item<typename DP::Whole>(p, lds, item / p.nq, item % p.nq * DENSE_QT);
+        if (item < p.items) dense_item<typename DP::Whole>(p, lds, item, DENSE_QT, 0);
         return;
     }
     if constexpr (D == 128) {
         if (p.cut == 3) {
             const int last = first + p.chunk < p.items ? first + p.chunk : p.items;
-            const Piece192 a = piece_192(i - p.whole, first + p.whole, last, p.nq, p.N);
+            const Piece192 a = piece_192(i - p.whole, first + p.whole, last, p.nq.d, p.N);
             const int bh = __builtin_amdgcn_readfirstlane(a.bh), q0 = __builtin_amdgcn_readfirstlane(a.q0), end = __builtin_amdgcn_readfirstlane(a.end);
             if (bh >= 0) dense_item_192<typename DP::Whole, typename DP::Whole1>(p, lds, bh, q0, end);
             return;
         }
     }
-    const int item = first + p.whole + (i - p.whole) / p.cut;
+    const int item = first + p.whole + (p.cut == 2 ? (i - p.whole) / 2 : (i - p.whole) / 4);
     if (item >= p.items) return;
-    const int q0 = item % p.nq * DENSE_QT + (i - p.whole) % p.cut * (DENSE_QT / p.cut);
-    if (q0 >= p.N) return;
-    if (p.cut == 2) dense_item<typename DP::Half>(p, lds, item / p.nq, q0);
-    else dense_item<typename DP::Quarter>(p, lds, item / p.nq, q0);
+    if (p.cut == 2) dense_item<typename DP::Half>(p, lds, item, DENSE_QT, (i - p.whole) % 2 * (DENSE_QT / 2));
+    else dense_item<typename DP::Quarter>(p, lds, item, DENSE_QT, (i - p.whole) % 4 * (DENSE_QT / 4));
 }
 
 // Small problems: 32 queries per workgroup of 2 x 2 wavefronts.
@@ -2243,7 +2273,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(c
     typedef StreamPlan<D, 1, 2, 2, 1, 2, 3> P;
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
     const int item = (blockIdx.x % XCDS) * p.chunk + blockIdx.x / XCDS;
-    if (item < p.items) dense_item<P>(p, lds, item / p.nq, item % p.nq * P::QT);
+    if (item < p.items) dense_item<P>(p, lds, item, P::QT, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -2274,19 +2304,14 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     const int item = work.rec.item;
     if (item < 0 || work.rec.nblk <= 0) leave_plan<64>(p, work);
     if (item < 0) return;
-    const int bh = item / p.nq;
-    const int qi = item % p.nq;
+    const int bh = p.nq.of(item);
+    const int qi = item - bh * p.nq.d;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int kv_len = p.kv_len;
-    if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
-        kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
-        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
-        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
-    }
-    const int smp = bh / p.H, head = bh % p.H;
-    const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
-    const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
+    const int smp = p.H.of(bh), head = bh - smp * p.H.d;
+    const int kv_len = valid_tokens(p, smp);
+    const Rows Q = rows_of(p.q, p.in, smp, head, p.n0), K = rows_of(p.k, p.in, smp, head, p.n0);
+    const Rows V = rows_of(p.v, p.in, smp, head, p.n0), O = rows_of(p.o, p.out, smp, head, p.n0);
     const int q0 = qi * 64 + wave / P::WK * 16 * P::NQ;
     char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
     const int n = work.rec.nblk;
@@ -2341,22 +2366,17 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     const int item = rec.item;
     if (rec.nblk <= 0) leave_plan<128>(p, work);
     if (item < 0) return;
-    const int bh = item / p.nq;
-    const int qi = item % p.nq;
+    const int bh = p.nq.of(item);
+    const int qi = item - bh * p.nq.d;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int kv_len = p.kv_len;
-    if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
-        kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
-        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
-        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
-    }
 
-    const int smp = bh / p.H, head = bh % p.H;
-    const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
-    const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
+    const int smp = p.H.of(bh), head = bh - smp * p.H.d;
+    const int kv_len = valid_tokens(p, smp);
+    const Rows Q = rows_of(p.q, p.in, smp, head, p.n0), K = rows_of(p.k, p.in, smp, head, p.n0);
+    const Rows V = rows_of(p.v, p.in, smp, head, p.n0), O = rows_of(p.o, p.out, smp, head, p.n0);
     const int q0 = qi * 128 + wave * 16 * P::NQ;
     char* out_stage = lds + wave * (16 * P::NQ * (D * 2 + 16));
 
@@ -2481,24 +2501,19 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
     const int item = rec.item;
     if (rec.nblk <= 0) leave_plan<128>(p, work);
     if (item < 0) return;
-    const int bh = item / p.nq;
-    const int qi = item % p.nq;
+    const int bh = p.nq.of(item);
+    const int qi = item - bh * p.nq.d;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31;
     const int h = lane >> 5;
-    int kv_len = p.kv_len;
-    if (p.kv_lens != nullptr) {                   // per-sample length, clamped to 0..N
-        kv_len = ((const __attribute__((address_space(4))) int32_t*)p.kv_lens)[bh / p.H];
-        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
-        kv_len = __builtin_amdgcn_readfirstlane(kv_len);   // (the clamp is a vector instruction)
-    }
 
-    const int smp = bh / p.H, head = bh % p.H;
-    const Rows Q = rows_of(p.q, smp, head, p.n0), K = rows_of(p.k, smp, head, p.n0);
-    const Rows V = rows_of(p.v, smp, head, p.n0), O = rows_of(p.o, smp, head, p.n0);
+    const int smp = p.H.of(bh), head = bh - smp * p.H.d;
+    const int kv_len = valid_tokens(p, smp);
+    const Rows Q = rows_of(p.q, p.in, smp, head, p.n0), K = rows_of(p.k, p.in, smp, head, p.n0);
+    const Rows V = rows_of(p.v, p.in, smp, head, p.n0), O = rows_of(p.o, p.out, smp, head, p.n0);
 
     const int qrow = qi * QT + wave * 32 + n;
     const bool qvalid = qrow < kv_len;
@@ -2730,6 +2745,7 @@ int check_common(const void* q, const void* k, const void* v, const void* o,
 // One validated call: tensors as segment views, sizes, lengths.
 struct Problem {
     SegTensor q, k, v, o;
+    SegStrides in, out;
     int n0;
     int B, H, N, D;
     int kv_len;
@@ -2737,21 +2753,14 @@ struct Problem {
     float scale;
 };
 
-SegTensor contiguous_bhnd(const void* ptr, int H, int N, int D)
-{
-    SegTensor t;
-    t.seg0 = (const __bf16*)ptr; t.seg1 = nullptr;
-    t.sb0 = (long long)H * N * D; t.sb1 = 0;
-    t.sh = (long long)N * D; t.sn = D;
-    return t;
-}
-
 void fill_common(AttnParams& p, const Problem& pr)
 {
     p.q = pr.q; p.k = pr.k; p.v = pr.v; p.o = pr.o;
+    p.in = pr.in; p.out = pr.out;
     p.kv_lens = pr.kv_lens;
     p.n0 = pr.n0;
-    p.H = pr.H; p.N = pr.N; p.kv_len = pr.kv_len;
+    p.H = divisor(pr.H, (long long)pr.B * pr.H);
+    p.N = pr.N; p.kv_len = pr.kv_len;
     p.c = pr.scale * LOG2E;
 }
 
@@ -2781,7 +2790,7 @@ int run_dense(const Problem& pr, void* stream)
                      : (small_live <= places * 3 / 4 && small <= places && pr.kv_len <= 8192) ||
                        (chunk > CUS_PER_XCD / 2 && pr.kv_len <= 2048 && small <= (pr.N >= 640 ? places * 5 / 4 : places)));
     if (short_chain) {
-        p.nq = (pr.N + 31) / 32;
+        p.nq = divisor((pr.N + 31) / 32, small);
         p.items = (int)small;
         p.chunk = (p.items + XCDS - 1) / XCDS;
         const dim3 grid((unsigned)p.chunk * XCDS);
@@ -2789,7 +2798,7 @@ int run_dense(const Problem& pr, void* stream)
         else hipLaunchKernelGGL((attn_dense_pp_kernel<128>), grid, dim3(256), 0, s, p);
         return hipGetLastError() == hipSuccess ? RAPID_OK : RAPID_ERR_DEVICE;
     }
-    p.nq = (pr.N + DENSE_QT - 1) / DENSE_QT;
+    p.nq = divisor((pr.N + DENSE_QT - 1) / DENSE_QT, items);
     if (items > 0x7fffffffLL / 8) return RAPID_ERR_SHAPE;
     p.items = (int)items;
     p.chunk = (int)chunk;
@@ -2818,7 +2827,7 @@ int run_dense(const Problem& pr, void* stream)
         int pieces = 0;
         for (int x = 0; x < XCDS; ++x) {
             const int first = x * p.chunk, last = first + p.chunk < p.items ? first + p.chunk : p.items;
-            const int n = piece_192(0x7fffffff, first + p.chunk - rest, last, p.nq, p.N).n;
+            const int n = piece_192(0x7fffffff, first + p.chunk - rest, last, p.nq.d, p.N).n;
             pieces = n > pieces ? n : pieces;
         }
         if (pieces <= CUS_PER_XCD) { p.cut = 3; p.whole = p.chunk - rest; groups = p.whole + pieces; }
@@ -2902,7 +2911,8 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     p.arrived = arrived;
     p.pmax = w.pmax;
     p.partial = ws + w.partial_off;
-    p.nq = nb;
+    // (dividends: items, and where every workgroup plans for itself its number in the segment, turned on: see sparse_work)
+    p.nq = divisor(nb, rows + w.chunk + (long long)(w.chunk / CUS_PER_XCD + 1) * (3 * nb + 7));
     p.items = (int)rows;
     p.chunk = w.chunk;
     p.nb = nb;
@@ -2929,8 +2939,9 @@ Problem contiguous_problem(const void* q, const void* k, const void* v, void* o,
                            int kv_len, float scale)
 {
     Problem pr;
-    pr.q = contiguous_bhnd(q, H, N, D); pr.k = contiguous_bhnd(k, H, N, D);
-    pr.v = contiguous_bhnd(v, H, N, D); pr.o = contiguous_bhnd(o, H, N, D);
+    auto whole = [](const void* ptr) { return SegTensor{(const __bf16*)ptr, (const __bf16*)ptr}; };
+    pr.q = whole(q); pr.k = whole(k); pr.v = whole(v); pr.o = whole(o);
+    pr.in = pr.out = {(long long)H * N * D, 0, (long long)N * D, D};
     pr.n0 = N;
     pr.B = B; pr.H = H; pr.N = N; pr.D = D;
     pr.kv_len = kv_len; pr.kv_lens = nullptr;
@@ -2982,16 +2993,15 @@ int joint_problem(const rapid_attn_segment* segments, int n_segments, int B, int
         const rapid_attn_segment& a = segments[0];
         const rapid_attn_segment* b2 = n_segments == 2 ? &segments[1] : nullptr;
         const void* p0 = which == 0 ? a.q : which == 1 ? a.k : which == 2 ? a.v : (const void*)a.o;
-        const void* p1 = !b2 ? nullptr : which == 0 ? b2->q : which == 1 ? b2->k : which == 2 ? b2->v : (const void*)b2->o;
+        const void* p1 = !b2 ? p0 : which == 0 ? b2->q : which == 1 ? b2->k : which == 2 ? b2->v : (const void*)b2->o;
         t.seg0 = (const __bf16*)p0; t.seg1 = (const __bf16*)p1;
-        const bool out = which == 3;
-        t.sb0 = out ? a.out_stride_b : a.in_stride_b;
-        t.sb1 = !b2 ? 0 : (out ? b2->out_stride_b : b2->in_stride_b);
-        t.sh = out ? a.out_stride_h : a.in_stride_h;
-        t.sn = out ? a.out_stride_n : a.in_stride_n;
         return t;
     };
     pr.q = view(0); pr.k = view(1); pr.v = view(2); pr.o = view(3);
+    const rapid_attn_segment& a = segments[0];
+    const rapid_attn_segment& b = segments[n_segments - 1];
+    pr.in = {a.in_stride_b, b.in_stride_b, a.in_stride_h, a.in_stride_n};
+    pr.out = {a.out_stride_b, b.out_stride_b, a.out_stride_h, a.out_stride_n};
     pr.n0 = n_segments == 2 ? segments[0].n : (int)N;
     pr.B = B; pr.H = H; pr.N = (int)N; pr.D = D;
     pr.kv_len = kv_len; pr.kv_lens = kv_lens;
