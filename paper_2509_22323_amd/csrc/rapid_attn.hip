@@ -1610,11 +1610,12 @@ __device__ __forceinline__ void stream_q_arrived(StreamRegs<S, D>& x, u32x4 (&ra
 // written over in LDS, where there is one, and the rows (all in one segment: 16 NQ divides 128) are one scalar base and
 // 32-bit offsets.  us, rows of n kept blocks, before / now: D = 128, 64-token masks, N = 2048, H = 64, n = 4 48.6 / 46.5, 24 120.1 /
 // 116.9; 128-token masks, N = 4096, n = 4 83.9 / 82.0, 24 342.7 / 340.8; D = 64, H = 256, n = 4 192.3 / 189.4.
-template <class S, int D>
+// The columns of blocks B0 .. B1 - 1 of a row alone take RS = (B1 - B0) * 32 + 16 bytes of the stage.
+template <class S, int D, int B0 = 0, int B1 = S::DT>
 __device__ __forceinline__ void stream_output_rows(const StreamRegs<S, D>& x, const Rows& O, int q0, int kv_len, int N, int lane,
                                                    char* stage)
 {
-    constexpr int RS = D * 2 + 16;
+    constexpr int RS = (B1 - B0) * 32 + 16;
     const int n = lane & 15, g = lane >> 4;
     const u32x2 none = {0u, 0u};
 #pragma unroll
@@ -1624,23 +1625,23 @@ __device__ __forceinline__ void stream_output_rows(const StreamRegs<S, D>& x, co
         const bool valid = q0 + 16 * q + n < kv_len && l > 0.f && inv != 0.f;
         char* const at = stage + (16 * q + n) * RS + 8 * g;
 #pragma unroll
-        for (int b = 0; b < S::DT; ++b) {
+        for (int b = B0; b < B1; ++b) {
             bf16x4 ov;
 #pragma unroll
             for (int r = 0; r < 4; ++r) ov[r] = (__bf16)(x.acc[(b * S::NQ + q) >> 2][((b * S::NQ + q) & 3) * 4 + r] * inv);
-            *(bf16x4*)(at + 32 * b) = ov;
+            *(bf16x4*)(at + 32 * (b - B0)) = ov;
         }
         if (__builtin_amdgcn_ballot_w64(!valid) != 0ull) {
             if (!valid) {
 #pragma unroll
-                for (int b = 0; b < S::DT; ++b) *(u32x2*)(at + 32 * b) = none;
+                for (int b = B0; b < B1; ++b) *(u32x2*)(at + 32 * (b - B0)) = none;
             }
         }
     }
-    constexpr int CH = D * 2 / 16;                // 16-byte chunks of a row
+    constexpr int CH = (B1 - B0) * 2;             // 16-byte chunks of a row
     constexpr int RPI = 64 / CH;                  // rows per store instruction
     const int rr = lane / CH, cc = lane % CH;
-    char* const base = const_cast<char*>(O.row(q0));
+    char* const base = const_cast<char*>(O.row(q0)) + B0 * 32;
     const unsigned off = (unsigned)rr * O.row_bytes + (unsigned)cc * 16u;
     auto store = [&](auto all) {
 #pragma unroll
@@ -2096,52 +2097,57 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     wait_vmcnt<0>();                              // no copy may land once the stages serve something else
 }
 
-// Key groups 1 .. WK-1 hand their states over through LDS, key group 0 adds them up in order (a group that
-// saw no valid key has l = 0 and a reference far below every other).  Every wavefront comes here, after a
-// barrier that ends the use of the stages; the result is key group 0's.
+// The two key groups of a workgroup add their states up through LDS and store the result, each one half of the columns: it
+// hands the other half of its accumulators over (with its references and sums), and the rows it stores go through what it has
+// read of that.  (A group that saw no valid key has l = 0 and a reference far below every other.)  Every wavefront comes here,
+// after a barrier that ends the use of the stages.  us, one group doing it all / now: rows of 2, 8, 16 64-token blocks,
+// N = 2048, D = 128, H = 64 36.6 57.3 84.1 / 35.2 55.9 82.5; dense, in a graph, N = 256, H = 2, D = 128 5.40 / 5.18; 640, 24 11.6 / 11.1.
 template <class P>
-__device__ __forceinline__ void stream_merge(StreamRegs<typename P::S, P::D>& x, char* lds, int wave, int lane)
+__device__ __forceinline__ void stream_merge_rows(StreamRegs<typename P::S, P::D>& x, char* lds, const Rows& O, int q0, int kv_len, int N,
+                                                  int wave, int lane)
 {
     typedef typename P::S S;
-    constexpr int QUADS = S::DT * S::NQ;          // 16-byte pieces of a lane's accumulators
-    constexpr int GROUP = 64 * (QUADS * 16 + S::NQ * 8);
-    static_assert((P::WK - 1) * P::WQ * GROUP <= P::LDS, "the states fit the stages");
-    const int wq = wave / P::WK, wk = wave % P::WK;
-    auto quads = [&](int k) -> f32x4* { return (f32x4*)(lds + ((k - 1) * P::WQ + wq) * GROUP) + lane; };
-    auto ml = [&](int k) -> float* { return (float*)(lds + ((k - 1) * P::WQ + wq) * GROUP + 64 * QUADS * 16) + lane * S::NQ * 2; };
-    if (wk > 0) {
+    constexpr int D = P::D, HALF = S::DT / 2;
+    constexpr int GIVEN = 64 * (HALF * S::NQ * 16 + S::NQ * 8);    // bytes that a wavefront hands over
+    static_assert(P::WK == 2 && P::NW * GIVEN <= P::LDS, "the states fit the stages");
+    static_assert(16 * S::NQ * (HALF * 32 + 16) <= GIVEN, "and a wavefront's rows what it was given");
+    const int wq = wave / 2;
+    auto part = [&](auto group) {
+        constexpr int WK = decltype(group)::value, KEEP = WK * HALF, GIVE = (1 - WK) * HALF;    // first blocks
+        char* const mine = lds + (wq * 2 + WK) * GIVEN;             // what it is given
+        char* const other = lds + (wq * 2 + 1 - WK) * GIVEN;
+        auto quads = [&](char* at) { return (f32x4*)at + lane; };
+        auto ml = [&](char* at) { return (float*)(at + 64 * HALF * S::NQ * 16) + lane * S::NQ * 2; };
 #pragma unroll
-        for (int i = 0; i < QUADS; ++i) {
+        for (int i = 0; i < HALF * S::NQ; ++i) {
             f32x4 v;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = x.acc[i >> 2][(i & 3) * 4 + r];
-            quads(wk)[i * 64] = v;
+            for (int r = 0; r < 4; ++r) v[r] = x.acc[(GIVE * S::NQ + i) >> 2][((GIVE * S::NQ + i) & 3) * 4 + r];
+            quads(other)[i * 64] = v;
         }
 #pragma unroll
-        for (int q = 0; q < S::NQ; ++q) { ml(wk)[2 * q] = x.m[q]; ml(wk)[2 * q + 1] = x.ls[q][0]; }
-    }
-    __syncthreads();
-    if (wk > 0) return;
-    for (int k = 1; k < P::WK; ++k) {
-        float a0[S::NQ], a1[S::NQ];
+        for (int q = 0; q < S::NQ; ++q) { ml(other)[2 * q] = x.m[q]; ml(other)[2 * q + 1] = x.ls[q][0]; }
+        __syncthreads();
+        float a[2][S::NQ];                        // factors of group 0's and of group 1's
+        auto sum = [&](float kept, float given, int q) { return WK == 0 ? kept * a[0][q] + given * a[1][q] : given * a[0][q] + kept * a[1][q]; };
 #pragma unroll
         for (int q = 0; q < S::NQ; ++q) {
-            const float m1 = ml(k)[2 * q], m = fmaxf(x.m[q], m1);
-            a0[q] = __builtin_amdgcn_exp2f(x.m[q] - m);
-            a1[q] = __builtin_amdgcn_exp2f(m1 - m);
-            x.ls[q][0] = x.ls[q][0] * a0[q] + ml(k)[2 * q + 1] * a1[q];
-            x.m[q] = m;
+            const float m1 = ml(mine)[2 * q], m = fmaxf(x.m[q], m1);
+            a[WK][q] = __builtin_amdgcn_exp2f(x.m[q] - m);
+            a[1 - WK][q] = __builtin_amdgcn_exp2f(m1 - m);
+            x.ls[q][0] = sum(x.ls[q][0], ml(mine)[2 * q + 1], q);
         }
 #pragma unroll
-        for (int i = 0; i < QUADS; ++i) {
-            const f32x4 v = quads(k)[i * 64];
+        for (int i = 0; i < HALF * S::NQ; ++i) {
+            const f32x4 v = quads(mine)[i * 64];
+            const int k = KEEP * S::NQ + i;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float y = x.acc[i >> 2][(i & 3) * 4 + r];
-                x.acc[i >> 2][(i & 3) * 4 + r] = y * a0[i % S::NQ] + v[r] * a1[i % S::NQ];
-            }
+            for (int r = 0; r < 4; ++r) x.acc[k >> 2][(k & 3) * 4 + r] = sum(x.acc[k >> 2][(k & 3) * 4 + r], v[r], i % S::NQ);
         }
-    }
+        stream_output_rows<S, D, KEEP, KEEP + HALF>(x, O, q0, kv_len, N, lane, mine);
+    };
+    if (wave % 2 == 0) part(std::integral_constant<int, 0>());
+    else part(std::integral_constant<int, 1>());
 }
 
 // Dense plans.  D = 128: 8 wavefronts, 32 queries each, two per SIMD, 128 KB of LDS.  D = 64: 4 wavefronts of 64
@@ -2185,12 +2191,8 @@ __device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int b
     const int last = ((kv_len + 31) / 32 + P::WK - 1) / P::WK - 1;
     stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, last, keys, wave, lane);
     __syncthreads();                              // every wavefront has read its last tile
-    if constexpr (P::WK > 1) {
-        stream_merge<P>(x, lds, wave, lane);
-        if (wave % P::WK != 0) return;
-        // (its rows go through LDS that only it has read: see out_stage)
-    }
-    stream_output_rows<S, D>(x, O, q0, kv_len, end, lane, out_stage);
+    if constexpr (P::WK > 1) stream_merge_rows<P>(x, lds, O, q0, kv_len, end, wave, lane);
+    else stream_output_rows<S, D>(x, O, q0, kv_len, end, lane, out_stage);
 }
 // A (sample, head)'s `tile` queries number item % nq, from `ahead` on.
 template <class P>
@@ -2329,9 +2331,7 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, n - 1, keys, wave, lane);
     leave_plan<64>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
-    stream_merge<P>(x, lds, wave, lane);
-    if (wave % P::WK != 0) return;
-    stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
+    stream_merge_rows<P>(x, lds, O, q0, kv_len, p.N, wave, lane);
 }
 
 // Partial result of one piece of a split item: the fp32 accumulators in register order
