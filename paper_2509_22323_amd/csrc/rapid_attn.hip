@@ -143,10 +143,15 @@ struct AttnParams {
     int nb;                  // mask blocks per side (sparse only)
     int segs;                // sparse: plan segments that hold items, min(XCDS, B*H)
     unsigned seg_magic;      // ceil(2^32 / segs)
-    int planned;             // sparse: 1 when the plan is in `order`, 0 when every workgroup plans for itself
+    int planned;             // sparse: PLAN_NONE, PLAN_FOUND or PLAN_READ
+    int pairs;               // sparse: (sample, head) pairs
     int pmax;                // sparse, 128-token tiles: partial-result slots per segment
     float c;                 // scale * log2(e)
 };
+
+// Where a workgroup of the sparse path has its row from (see sparse_work): its number; what every workgroup finds out about all rows
+// of its segment; the plan in `order`.
+enum { PLAN_NONE, PLAN_FOUND, PLAN_READ };
 
 // Valid tokens of a sample: clamped to 0..N where they are given per sample.
 __device__ __forceinline__ int valid_tokens(const AttnParams& p, int smp)
@@ -1808,8 +1813,72 @@ __device__ __forceinline__ void entry_of(const AttnParams& p, int& seg, int& i)
         }
     }
 }
+// The entry of a plan of whole rows that nobody has made: every workgroup counts all rows of its segment, one per thread
+// (8 <= nb <= 64, at most 256 rows), and looks up the one that comes i-th, longest first (with the second round of 32
+// backwards: see plan_small_kernel).  `at`: LDS that no copy uses yet, for FOUND_BYTES.
+// Some 1.5 us of every workgroup in place of a launch: run_sparse holds both sides of the line.
+struct FoundRow {
+    int hist[SMALL_NB + 2];                        // rows by length, longest first
+    int before[4];                                 // rows of the length looked for, by wavefront
+    int item, n;
+    unsigned long long row;
+};
+__device__ __forceinline__ void find_row(const AttnParams& p, int seg, int i, SparseWork<64>& w, FoundRow* at)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nb = p.nb;
+    const int items = (p.pairs - seg + XCDS - 1) / XCDS * nb;
+    if (i >= items) return;
+    const bool has = tid < items;
+    const int t = has ? tid : 0;
+    const int pair = (int)__umulhi((unsigned)t, p.nq.magic) * XCDS + seg;    // (nq = nb)
+    const int item = pair * nb + t - (pair - seg) / XCDS * nb;
+    unsigned long long row = 0ull;
+    int c;
+    if (p.mask != nullptr) {
+        int kv_len = p.kv_len;
+        if (p.kv_lens != nullptr) kv_len = p.kv_lens[p.H.d == 1 ? pair : (int)__umulhi((unsigned)pair, p.H.magic)];
+        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        const unsigned char* src = p.mask + (size_t)item * nb;
+        unsigned long long v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)                // all on their way at once; the last eight bytes of a row end with it
+            if (8 * k < nb) __builtin_memcpy(&v[k], src + (8 * k + 8 <= nb ? 8 * k : nb - 8), 8);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (8 * k < nb) row |= (unsigned long long)byte_bits((unsigned)v[k], (unsigned)(v[k] >> 32)) << (8 * k + 8 <= nb ? 8 * k : nb - 8);
+        const int live = (kv_len + 63) / 64;
+        row &= live >= 64 ? ~0ull : (1ull << live) - 1ull;
+        c = __popcll(row);
+    } else {
+        c = p.counts[item];
+    }
+    for (int k = tid; k <= nb; k += 256) at->hist[k] = 0;
+    __syncthreads();
+    if (has) atomicAdd(&at->hist[nb - c], 1);
+    __syncthreads();
+    if (i >= CUS_PER_XCD && i < 2 * CUS_PER_XCD) { // backwards
+        const int left = items - CUS_PER_XCD < CUS_PER_XCD ? items - CUS_PER_XCD : CUS_PER_XCD;
+        i = 2 * CUS_PER_XCD + left - CUS_PER_XCD - 1 - (i - CUS_PER_XCD);
+    }
+    const int upto = wave_scan_inclusive(lane < nb ? at->hist[lane] : 0);
+    const int shorter = __popcll(__builtin_amdgcn_ballot_w64(lane < nb && upto <= i));    // nb - the length of the i-th row
+    const int start = shorter > 0 ? __builtin_amdgcn_readlane(upto, shorter - 1) : 0;
+    const unsigned long long same = __builtin_amdgcn_ballot_w64(has && nb - c == shorter);
+    if (lane == 0) at->before[wave] = __popcll(same);
+    __syncthreads();
+    int rank = __popcll(same & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) rank += k < wave ? at->before[k] : 0;
+    if (has && nb - c == shorter && rank == i - start) { at->item = item; at->n = c; at->row = row; }
+    __syncthreads();
+    w.rec.item = __builtin_amdgcn_readfirstlane(at->item);
+    w.rec.nblk = __builtin_amdgcn_readfirstlane(at->n);
+    unsigned long long r = at->row;
+    w.row = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(r >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)r);
+}
+
 template <int BLOCK>
-__device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
+__device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, char* scratch)
 {
     typedef const __attribute__((address_space(4))) int32_t* cptr_t;
     typedef const __attribute__((address_space(4))) i32x4* rptr_t;
@@ -1819,7 +1888,10 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
     const int slot = seg * p.chunk + i, lane = threadIdx.x & 63;
     SparseWork<BLOCK> w;
     w.rec = {-1, 0, 0, -1};
-    if (!p.planned) {
+    w.row = 0ull;
+    if (BLOCK == 64 && p.planned == PLAN_FOUND) {
+        if constexpr (BLOCK == 64) find_row(p, seg, i, w, (FoundRow*)scratch);
+    } else if (p.planned == PLAN_NONE) {
         // The dispatcher deals the workgroups of an XCD out to its 32 CUs in turn; rows with the same number (text rows,
         // the long ones) would meet on the same CU where 32 is a multiple of nb, so every 32 workgroups start 3/8 of the rows on.
         const int g = p.nq.of(i), pair = g * XCDS + seg;    // (nq = nb)
@@ -1837,10 +1909,10 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
     }
     const int item = w.rec.item;
     w.kept.list = nullptr;
-    w.kept.bits = w.row = 0ull;
+    w.kept.bits = w.row;
     w.kept.n = w.rec.nblk;
     w.kept.at = w.kept.first = 0;
-    if (item >= 0) {
+    if (item >= 0 && !(BLOCK == 64 && p.planned == PLAN_FOUND && p.mask != nullptr)) {
         if (p.mask != nullptr) {                   // nb <= 64
             int kv_len = p.kv_len;
             if (p.kv_lens != nullptr) kv_len = ((cptr_t)p.kv_lens)[p.H.of(p.nq.of(item))];    // (nq = nb)
@@ -1848,7 +1920,7 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p)
             const unsigned char byte = p.mask[(size_t)item * p.nb + (lane < p.nb ? lane : 0)];
             const bool keep = byte != 0 && lane < p.nb && lane * BLOCK < kv_len;
             w.kept.bits = w.row = __builtin_amdgcn_ballot_w64(keep);
-            if (!p.planned) {
+            if (p.planned == PLAN_NONE) {
                 w.rec.nblk = __popcll(w.row);
             } else if (BLOCK == 128 && w.rec.w >= 0) {
                 const int rank = __popcll(w.row & ((1ull << lane) - 1ull)) - w.rec.blk0;
@@ -1876,7 +1948,7 @@ __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork
     const int lane = threadIdx.x;
     if (p.mask != nullptr && (w.row >> lane & 1ull) != 0ull && w.rec.blk0 == 0)
         p.index[(size_t)w.rec.item * p.nb + __popcll(w.row & ((1ull << lane) - 1ull))] = lane;
-    if (!p.planned && lane == 0) {
+    if (p.planned != PLAN_READ && lane == 0) {
         int x, i;
         entry_of(p, x, i);
         if (BLOCK == 64) p.order[x * p.chunk + i] = w.rec.item;
@@ -2302,7 +2374,7 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     static_assert(P::QT == 64, "one item = 64 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    const auto work = sparse_work<64>(p);
+    const auto work = sparse_work<64>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
     const int item = work.rec.item;
     if (item < 0 || work.rec.nblk <= 0) leave_plan<64>(p, work);
     if (item < 0) return;
@@ -2361,7 +2433,7 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     static_assert(P::QT == 128, "one record = 128 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    const auto work = sparse_work<128>(p);
+    const auto work = sparse_work<128>(p, nullptr);
     const PlanRec rec = work.rec;
     const int item = rec.item;
     if (rec.nblk <= 0) leave_plan<128>(p, work);
@@ -2496,7 +2568,7 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
 
     __shared__ __attribute__((aligned(1024))) char lds[4 * G::TILE_BYTES];
 
-    auto work = sparse_work<128>(p);
+    auto work = sparse_work<128>(p, nullptr);
     const PlanRec rec = work.rec;
     const int item = rec.item;
     if (rec.nblk <= 0) leave_plan<128>(p, work);
@@ -2881,12 +2953,18 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
                          (xcd_items > CUS_PER_XCD * (D == 128 ? 1 : 2) && !short_rows && segments(B * H, nb, block) == XCDS);
     const long long mask_pieces = nb <= SMALL_NB ? (long long)(xcd_items / nb) * (((nb * nb + 7) / 8 + 3) / 4 * 4) : 0;
     const bool small = nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && mask_pieces <= SMALL_PIECES;
-    const bool lists = mask != nullptr && (planned ? !small : nb > SMALL_NB);      // compacted by a kernel of its own
+    // 64-token masks: every workgroup looks its row up by itself, while a place works through few of them.  us, plan launch /
+    // looked up, H = 24 unless said otherwise, rows of an XCD x blocks: D = 128 (64 places) 96 x 32 30.3 / 28.1; 132 x 44 62.4 / 61.9; 192 x 64
+    // 92.0 / 93.2; B = 8, 240 x 10 42.0 / 42.6; D = 64 (96 places) 96 x 32 23.0 / 20.7; 132 x 44 38.9 / 36.9; 192 x 64 56.6 / 54.5; B = 4,
+    // 192 x 16 25.9 / 24.3; B = 8, 240 x 10 23.0 / 21.5; with 2 or 3 pairs the same within 0.5 %.
+    const bool found = planned && block == 64 && nb >= 8 && nb <= SMALL_NB && xcd_items <= (D == 128 ? 144 : 256) &&
+                       (H == 1 || divisor(H, (long long)B * H).magic != 0u);
+    const bool lists = mask != nullptr && (planned && !found ? !small : nb > SMALL_NB);      // compacted by a kernel of its own
     if (lists)
         hipLaunchKernelGGL(compact_mask_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
                            mask, (int)rows, nb, block, pr.kv_len, pr.kv_lens, H * nb, N, counts, index);
     if (lists && hipGetLastError() != hipSuccess) return RAPID_ERR_DEVICE;
-    if (planned && small) {
+    if (planned && small && !found) {
         // (the instructions of this kernel are fetched anew in every call: a third of the code, 6.3 -> 5.2 us at H = 24, N = 4608)
         const bool one = xcd_items <= 1024 && mask_pieces <= 4096;
         const auto kernel = block == 128 ? (one ? plan_small_kernel<true, 1, 4> : plan_small_kernel<true, SMALL_PER_THREAD, SMALL_PIECES / 1024>)
@@ -2894,10 +2972,10 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
         hipLaunchKernelGGL(kernel, dim3(XCDS), dim3(1024), 0, s, mask, pr.kv_lens, pr.kv_len, N, block,
                            H, B * H, nb, w.chunk, w.pmax, D, counts, order, arrived);
     }
-    else if (planned && block == 128)
+    else if (planned && !found && block == 128)
         hipLaunchKernelGGL(plan_split_kernel, dim3(XCDS), dim3(1024), 0, s, counts, B * H, nb, w.chunk,
                            w.pmax, D, (PlanRec*)order, arrived);
-    else if (planned)
+    else if (planned && !found)
         hipLaunchKernelGGL(plan_kernel, dim3(XCDS), dim3(1024), 0, s, counts, B * H, nb, w.chunk, order);
     if (hipGetLastError() != hipSuccess) return RAPID_ERR_DEVICE;
 
@@ -2905,7 +2983,8 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     fill_common(p, pr);
     p.mask = lists ? nullptr : mask;
     p.counts = counts; p.order = order; p.index = index;
-    p.planned = planned;
+    p.planned = found ? PLAN_FOUND : planned ? PLAN_READ : PLAN_NONE;
+    p.pairs = B * H;
     p.segs = segments(B * H, nb, block);
     p.seg_magic = 0xffffffffu / (unsigned)p.segs + 1u;
     p.arrived = arrived;

@@ -311,3 +311,56 @@ def test_either_side_of_the_plan_rules(block, B, H, nb, D, planned):
             if (g * 8 + x) < B * H:
                 own[x, i] = (g * 8 + x) * nb + (i + g * nb // 32 * ((3 * nb + 7) // 8)) % nb
     assert (order == own).all() == (not planned)
+
+
+@pytest.mark.parametrize("D,H,nb", [(128, 16, 36), (128, 88, 13), (128, 24, 48), (128, 24, 49), (64, 16, 64), (64, 100, 8), (64, 32, 64), (64, 40, 52)])
+@pytest.mark.parametrize("alike", [False, True])
+def test_64_token_rows_looked_up_without_a_plan(D, H, nb, alike):
+    """Either side of the line up to which workgroups look their rows up by themselves (more rows than places): every row
+    done once, longest first, rows without a block and ties among them, lists, counts and plan left as ever."""
+    block = 64
+    N, kv = nb * block, nb * block - 29
+    g = torch.Generator(device="cuda").manual_seed(H * nb + D)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = (torch.rand((1, H, nb, nb), generator=g, device="cuda") < 0.3).to(torch.uint8) * 3
+    mask[:, :, 4], mask[:, 1, 5], mask[:, :, -2:] = 0, 0, 255
+    if alike:
+        mask[:] = 1
+    ws = torch.full((ra.rapid_attn_workspace_bytes(1, H, N, D, block),), 0xa5, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, 7.0)
+    ra.rapid_attn_block_sparse(q, k, v, o, mask, block, kv, workspace=ws)
+    check(o, reference(q, k, v, mask, block, kv, D ** -0.5), kv, f"D={D} H={H} nb={nb}")
+    counts, order, index, geo = read_plan(ws.cpu().numpy(), 1, H, nb, D, block)
+    host = mask.cpu().numpy().reshape(H * nb, nb) != 0
+    assert (counts == host.sum(-1)).all()
+    check_plan(counts, order, geo, 1, H, nb, block, D)
+    for x in range(8):                             # (the second round of 32 backwards)
+        items = order[x][order[x][:, 0] >= 0, 0]
+        lengths = counts[items]
+        lengths[32:64] = lengths[32:64][::-1]
+        assert (np.diff(lengths) <= 0).all(), x
+    for r in range(H * nb):
+        assert (index[r, :counts[r]] == np.flatnonzero(host[r])).all(), r
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_64_token_rows_of_a_selected_mask_looked_up_without_a_plan(D):
+    """Counts and lists from the selection, samples of different length (an empty one too): as under the mask it reports."""
+    B, H, block = 3, 16, 64
+    N = 22 * block - 5                             # 6 pairs of an XCD: 132 rows
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((B, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    lens = torch.tensor([N, 0, N - 700], dtype=torch.int32, device="cuda")
+    mask = torch.empty((B, H, 22, 22), dtype=torch.uint8, device="cuda")
+    out = [torch.full_like(q, 7.0) for _ in range(2)]
+    ra.rapid_attn_joint_select([(q, k, v, out[0])], block, kv_lens=lens, text_start=20 * block, tau=0.7, mask_out=mask)
+    ra.rapid_attn_joint([(q, k, v, out[1])], mask=mask, block=block, kv_lens=lens)
+    assert torch.equal(out[0], out[1])
+    for b, n in enumerate(lens.tolist()):
+        if n == 0:
+            assert (out[0][b] == 0).all()
+            continue
+        pad = torch.zeros((1, H, 22 * block, D), dtype=torch.bfloat16, device="cuda")
+        full = [torch.cat([x[b:b + 1], pad], 2)[:, :, :22 * block] for x in (q, k, v)]
+        ref = reference(*full, mask[b:b + 1], block, n, D ** -0.5)
+        check(torch.cat([out[0][b:b + 1], pad], 2)[:, :, :22 * block], ref, n, f"D={D} sample {b}")
