@@ -136,6 +136,7 @@ struct AttnParams {
     char* partial;           // sparse, 128-token tiles: partial results of the pieces of split items
     int N, kv_len;
     Divisor H;
+    Divisor B;               // dense
     Divisor nq;              // query tiles per (sample, head)
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
@@ -2238,15 +2239,21 @@ template <> struct DensePlan<64> {
     static constexpr int LDS = Whole::LDS;
 };
 
+// Samples of different length: consecutive (sample, head) pairs are those of one head, so that an XCD's run of items holds
+// short samples and long ones.  us, sample by sample / head by head, prompts of 1/B, 2/B, .. of the text tokens, H = 24: B = 2,
+// D = 64, 1024 + 333 tokens 31.2 / 31.3, 2048 + 333 72.4 / 70.4; B = 8, 1024 + 333 93.3 / 83.4; D = 128, B = 2, 1024 + 512 59.1 / 55.0;
+// B = 4, 4096 + 512 782 / 746.
 // One wavefront's part of an item whose first query is q00: the queries from q0 on, stored up to `end`; `stage` bytes into the
 // LDS its output goes through.
 template <class P>
-__device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int bh, int q00, int q0, int end, int wave, int stage)
+__device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int pair, int q00, int q0, int end, int wave, int stage)
 {
     typedef typename P::S S;
     constexpr int D = P::D;
     const int lane = threadIdx.x & 63;
-    const int smp = p.H.of(bh), head = bh - smp * p.H.d;
+    int smp, head;
+    if (p.kv_lens != nullptr) { head = p.B.of(pair); smp = pair - head * p.B.d; }
+    else { smp = p.H.of(pair); head = pair - smp * p.H.d; }
     const int kv_len = valid_tokens(p, smp);
     const Rows Q = rows_of(p.q, p.in, smp, head, p.n0), K = rows_of(p.k, p.in, smp, head, p.n0);
     const Rows V = rows_of(p.v, p.in, smp, head, p.n0), O = rows_of(p.o, p.out, smp, head, p.n0);
@@ -2270,24 +2277,24 @@ __device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int b
 template <class P>
 __device__ __forceinline__ void dense_item(const AttnParams& p, char* lds, int item, int tile, int ahead)
 {
-    const int bh = p.nq.of(item), q00 = (item - bh * p.nq.d) * tile + ahead;
+    const int pair = p.nq.of(item), q00 = (item - pair * p.nq.d) * tile + ahead;
     if (q00 >= p.N) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    dense_wave<P>(p, lds, bh, q00, q00 + wave / P::WK * 16 * P::NQ, p.N, wave, wave * (16 * P::NQ * (P::D * 2 + 16)));
+    dense_wave<P>(p, lds, pair, q00, q00 + wave / P::WK * 16 * P::NQ, p.N, wave, wave * (16 * P::NQ * (P::D * 2 + 16)));
 }
 
 // 192 queries: the wavefronts of a SIMD take 32 and 16 (of 32 and 32, or none, a SIMD with two wavefronts would take as long
 // as for 256); the same barriers and copies in both halves of the workgroup.
 constexpr int DENSE_192 = 192;
 template <class P, class P1>
-__device__ __forceinline__ void dense_item_192(const AttnParams& p, char* lds, int bh, int q00, int end)
+__device__ __forceinline__ void dense_item_192(const AttnParams& p, char* lds, int pair, int q00, int end)
 {
     static_assert(P::NW == 8 && P1::NW == 8 && P::NQ == 2 && P1::NQ == 1 && P::WK == 1 && P1::WK == 1, "");
     static_assert(P::UNROLL == P1::UNROLL && P::LC == P1::LC && P::LDS == P1::LDS, "the same barriers and copies");
     constexpr int ROW = P::D * 2 + 16;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wave < 4) dense_wave<P>(p, lds, bh, q00, q00 + 32 * wave, end, wave, 32 * wave * ROW);
-    else dense_wave<P1>(p, lds, bh, q00, q00 + 64 + 16 * wave, end, wave, (64 + 16 * wave) * ROW);
+    if (wave < 4) dense_wave<P>(p, lds, pair, q00, q00 + 32 * wave, end, wave, 32 * wave * ROW);
+    else dense_wave<P1>(p, lds, pair, q00, q00 + 64 + 16 * wave, end, wave, (64 + 16 * wave) * ROW);
 }
 
 // Piece i of the pieces of 192 queries that items `first` .. `last` - 1 make, a (sample, head) at a time; without one, their number.
@@ -2832,6 +2839,7 @@ void fill_common(AttnParams& p, const Problem& pr)
     p.kv_lens = pr.kv_lens;
     p.n0 = pr.n0;
     p.H = divisor(pr.H, (long long)pr.B * pr.H);
+    p.B = divisor(pr.B, (long long)pr.B * pr.H);
     p.N = pr.N; p.kv_len = pr.kv_len;
     p.c = pr.scale * LOG2E;
 }
