@@ -1592,9 +1592,12 @@ __device__ __forceinline__ void stream_load_q(const Rows& Q, int q0, int kv_len,
 #pragma unroll
     for (int q = 0; q < S::NQ; ++q)
 #pragma unroll
-        for (int t = 0; t < S::KS; ++t)
-            asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen offset:%3"
-                         : "=v"(raw[q][t]) : "v"(off + (unsigned)(16 * q) * Q.row_bytes), "s"(rsrc), "i"(64 * t));
+        for (int t = 0; t < S::KS; ++t) {
+            const unsigned at = off + (unsigned)(16 * q) * Q.row_bytes;
+            // (five wait states behind a vector instruction that wrote the descriptor, which the compiler does not see to here)
+            if (q == 0 && t == 0) asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(raw[q][t]) : "v"(at), "s"(rsrc));
+            else asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen offset:%3" : "=v"(raw[q][t]) : "v"(at), "s"(rsrc), "i"(64 * t));
+        }
 }
 template <class S, int D>
 __device__ __forceinline__ void stream_q_arrived(StreamRegs<S, D>& x, u32x4 (&raw)[S::NQ][S::KS])
@@ -2043,13 +2046,16 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         voff[e] = copy_off + (unsigned)more * K.row_bytes + stream_copy_chunk<S, D, true>(copy_row + more, lane);
     }
     const unsigned lds0 = (unsigned)(size_t)LDS_PTR(char, lds);
-    const unsigned dst0 = lds0 + (unsigned)(wave * LC) * 1024u;
-    auto copy = [&](const TileBuffer& b, const unsigned (&off)[LC], int e, unsigned dst) {
+    unsigned dst0 = lds0 + (unsigned)(wave * LC) * 1024u;
+    // (dst0 as it is here: else every stage's address is a register of its own, kept in lanes of a vector register)
+    auto copy = [&](const TileBuffer& b, const unsigned (&off)[LC], int e, unsigned ahead) {
+        asm volatile("" : "+s"(dst0));
+        const unsigned dst = dst0 + ahead;
         if constexpr (P::PER_M0 == 1) copy_1k(b, off[e], dst);
         else if (e % 2 == 0) copy_2k(b, off[e], off[e + 1], dst);
     };
-    auto copy_k = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, koff, e, dst0 + stage + e * 1024); };
-    auto copy_v = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, voff, e, dst0 + VBASE + stage + e * 1024); };
+    auto copy_k = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, koff, e, stage + e * 1024); };
+    auto copy_v = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, voff, e, VBASE + stage + e * 1024); };
     // what the barriers before tile 0 would have issued
 #pragma unroll
     for (int b = -P::KLEAD; b < (P::SPT == 1 ? -1 : 0); ++b) {
