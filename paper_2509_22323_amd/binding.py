@@ -1,4 +1,5 @@
-"""ctypes binding of librapid_attn.so: same names as the C ABI, marshalling only.
+"""Binding of librapid_attn.so: same names as the C ABI, marshalling only.  The calls that launch go through
+native_call.so (csrc/native_call.cpp) where their arguments are what most calls hand over, else through ctypes.
 
 PyTorch is used for device memory and streams, nothing else: tensors are passed as
 raw device pointers, kernels go to torch's current HIP stream.  There is no fallback:
@@ -11,7 +12,9 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "librapid_attn.so")
+_NATIVE_SO = os.path.join(_HERE, "native_call.so")
 _lib = None
+_native = None
 
 STATUS = {
     "RAPID_OK": 0, "RAPID_ERR_NULL": -1, "RAPID_ERR_SHAPE": -2, "RAPID_ERR_UNSUPPORTED": -3,
@@ -112,6 +115,25 @@ def library():
     return lib
 
 
+def _load_native():
+    """native_call.so, bound to the loaded library.  Raises if it has not been built."""
+    global _native
+    import importlib.machinery
+    import importlib.util
+    import torch  # noqa: F401  (its libraries have to be there)
+    lib = library()
+    if not os.path.exists(_NATIVE_SO):
+        raise ImportError(f"{_NATIVE_SO} is missing: build it first (python paper_2509_22323_amd/build.py).")
+    loader = importlib.machinery.ExtensionFileLoader("native_call", _NATIVE_SO)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("native_call", loader))
+    loader.exec_module(module)
+    module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+        "rapid_attn_dense", "rapid_attn_block_sparse", "rapid_attn_joint", "rapid_attn_joint_select", "rapid_mask_select",
+        "rapid_cache_store", "rapid_cache_reuse")))
+    _native = module
+    return module
+
+
 def rapid_attn_status_string(status: int) -> str:
     return library().rapid_attn_status_string(int(status)).decode()
 
@@ -156,6 +178,10 @@ def _stream(t):
 def rapid_attn_dense(q, k, v, o, kv_len=None, scale=0.0):
     """o <- softmax(scale q k^T) v over the first kv_len tokens (all heads, samples).
     Tensors: CUDA bf16 [B,H,N,D], contiguous.  Enqueued on torch's current stream."""
+    status = (_native or _load_native()).dense(q, k, v, o, kv_len, scale)
+    if status is not None:
+        _check(status)
+        return o
     B, H, N, D = _qkvo(q, k, v, o)
     kv_len = N if kv_len is None else int(kv_len)
     _check(library().rapid_attn_dense(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
@@ -167,6 +193,10 @@ def rapid_attn_block_sparse(q, k, v, o, mask, block, kv_len=None, scale=0.0, wor
     """As rapid_attn_dense, restricted to the tiles kept by `mask` (CUDA uint8
     [B,H,N/block,N/block]).  `workspace`: CUDA uint8 tensor of at least
     rapid_attn_workspace_bytes(...) bytes; allocated with torch if None.  Returns o."""
+    status = (_native or _load_native()).block_sparse(q, k, v, o, mask, block, kv_len, scale, workspace)
+    if status is not None:
+        _check(status)
+        return o
     import torch
     B, H, N, D = _qkvo(q, k, v, o)
     kv_len = N if kv_len is None else int(kv_len)
@@ -257,6 +287,10 @@ def rapid_attn_joint(segments, mask=None, block=128, kv_len=None, kv_lens=None, 
     each a CUDA bf16 tensor indexed [B, H, n, D] with a contiguous last dimension and any other
     strides (a permuted view of a [B, n, H, D] or fused [B, n, 3, H, D] tensor is fine); q, k, v
     of a segment share their strides.  mask None = dense.  kv_lens: CUDA int32 [B] or None."""
+    status = (_native or _load_native()).joint(segments, mask, block, kv_len, kv_lens, scale, workspace)
+    if status is not None:
+        _check(status)
+        return [seg[3] for seg in segments]
     import torch
     descr, B, H, N, D = _segments(segments)
     q0 = segments[0][0]
@@ -301,6 +335,10 @@ def _residual_args(a, b, out, sample_flags):
 
 def rapid_cache_store(gen_out, x, delta, sample_flags=None):
     """delta <- gen_out - x (the residual a cache-updating step keeps), per flagged sample."""
+    status = (_native or _load_native()).store(gen_out, x, delta, sample_flags)
+    if status is not None:
+        _check(status)
+        return delta
     B, per_sample, flags = _residual_args(gen_out, x, delta, sample_flags)
     _check(library().rapid_cache_store(gen_out.data_ptr(), x.data_ptr(), delta.data_ptr(), B, per_sample, flags,
                                        _stream(x)))
@@ -309,6 +347,10 @@ def rapid_cache_store(gen_out, x, delta, sample_flags=None):
 
 def rapid_cache_reuse(x, delta, out, sample_flags=None):
     """out <- x + delta (the output of a step that reuses the cache), per flagged sample."""
+    status = (_native or _load_native()).reuse(x, delta, out, sample_flags)
+    if status is not None:
+        _check(status)
+        return out
     B, per_sample, flags = _residual_args(x, delta, out, sample_flags)
     _check(library().rapid_cache_reuse(x.data_ptr(), delta.data_ptr(), out.data_ptr(), B, per_sample, flags,
                                        _stream(x)))
@@ -345,6 +387,10 @@ def rapid_mask_select(q, k, mask, block, kv_len=None, text_start=None, tau=0.95,
     """mask <- block mask [B,H,N/block,N/block] (uint8) keeping, per row, the key-blocks that hold
     `tau` of the pooled attention mass, plus the diagonal and the text rows/columns.  q, k: CUDA
     bf16 [B,H,N,D] contiguous."""
+    status = (_native or _load_native()).select(q, k, mask, block, kv_len, text_start, tau, scale, workspace)
+    if status is not None:
+        _check(status)
+        return mask
     import torch
     for name, t in (("q", q), ("k", k)):
         if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.bfloat16 and t.dim() == 4
@@ -433,6 +479,10 @@ def rapid_attn_joint_select(segments, block=128, kv_len=None, kv_lens=None, text
     """Mask selection at `tau` and block-sparse attention under it in one call, on (q, k, v, o)
     segments as rapid_attn_joint takes them; mask_out: optional CUDA uint8 [B,H,nb,nb] that receives
     the selected mask.  Returns the o tensors."""
+    status = (_native or _load_native()).joint_select(segments, block, kv_len, kv_lens, text_start, tau, scale, mask_out, workspace)
+    if status is not None:
+        _check(status)
+        return [seg[3] for seg in segments]
     import torch
     descr, B, H, N, D = _segments(segments)
     q0 = segments[0][0]

@@ -14,6 +14,10 @@ OUT = os.path.join(HERE, "librapid_attn.so")
 PROBE_SOURCES = [os.path.join(HERE, "csrc", "mfma_probe.hip")]
 PROBE_OUT = os.path.join(HERE, "libmfma_probe.so")
 
+# the launching entry points called with tensors (host code; see its head)
+NATIVE_SOURCE = os.path.join(HERE, "csrc", "native_call.cpp")
+NATIVE_OUT = os.path.join(HERE, "native_call.so")
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -30,18 +34,36 @@ FLAGS = [
 
 def build(verbose: bool = False, extra: list[str] | None = None, out: str = OUT) -> str:
     _compile(PROBE_SOURCES, PROBE_OUT, verbose, extra)
+    build_native(verbose)
     return _compile(SOURCES, out, verbose, extra)
 
 
+def build_native(verbose: bool = False) -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include")]
+    for path in include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    for path in library_paths():
+        cmd += ["-L", path]
+    return _run(cmd + ["-o", NATIVE_OUT, NATIVE_SOURCE, "-ltorch_python", "-ltorch_cpu", "-lc10"], NATIVE_OUT, verbose)
+
+
 def _compile(sources, out, verbose, extra):
-    cmd = [HIPCC] + FLAGS + (extra or []) + ["-o", out] + sources
+    return _run([HIPCC] + FLAGS + (extra or []) + ["-o", out] + sources, out, verbose)
+
+
+def _run(cmd, out, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "packed-fp32-ops"
     err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
+        raise RuntimeError(f"{cmd[0]} failed ({res.returncode}):\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
     return out

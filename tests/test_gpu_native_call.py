@@ -1,0 +1,105 @@
+"""The native form of the launching calls against the Python form: the same results bit for bit, the same refusals."""
+import pytest
+import torch
+
+import paper_2509_22323_amd as ra
+from paper_2509_22323_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+class Nothing:
+    """Stands in for the native module: leaves every call to the Python form."""
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def tensors(*shape, n=3):
+    g = torch.Generator(device="cuda").manual_seed(sum(shape))
+    return [torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(n)]
+
+
+def scratch(n):
+    return torch.empty(n, dtype=torch.uint8, device="cuda")
+
+
+def dense(kv):
+    q, k, v = tensors(2, 3, 200, 64)
+    return [ra.rapid_attn_dense(q, k, v, torch.zeros_like(q), kv, 0.2)]
+
+
+def sparse(kv):
+    q, k, v = tensors(1, 3, 256, 128)
+    mask = torch.eye(4, dtype=torch.uint8, device="cuda").expand(1, 3, 4, 4).contiguous()
+    return [ra.rapid_attn_block_sparse(q, k, v, torch.zeros_like(q), mask, 64, kv, workspace=scratch(1 << 20))]
+
+
+def segments():
+    made = []
+    for n in (256, 100):
+        f = tensors(2, n, 3, 4, 64, n=1)[0]
+        made.append(tuple(f[:, :, i].transpose(1, 2) for i in range(3)) + (torch.zeros((2, n, 4, 64), device="cuda", dtype=torch.bfloat16).transpose(1, 2),))
+    return made
+
+
+def joint(kv):
+    lens = torch.tensor([356, 300], dtype=torch.int32, device="cuda")
+    mask = torch.tril(torch.ones((6, 6), dtype=torch.uint8, device="cuda")).expand(2, 4, 6, 6).contiguous()
+    out = ra.rapid_attn_joint(segments(), kv_lens=lens) + ra.rapid_attn_joint(tuple(segments()), mask=mask, block=64, kv_len=kv, workspace=scratch(1 << 22))
+    return out + ra.rapid_attn_joint(segments()[:1])
+
+
+def select(kv):
+    q, k, _ = tensors(1, 2, 512, 128)
+    mask = torch.zeros((1, 2, 8, 8), dtype=torch.uint8, device="cuda")
+    out = [ra.rapid_mask_select(q, k, mask, 64, kv, 400, 0.8, workspace=scratch(1 << 20))]
+    m2 = torch.zeros((2, 4, 6, 6), dtype=torch.uint8, device="cuda")
+    return out + ra.rapid_attn_joint_select(segments(), 64, text_start=256, tau=0.7, mask_out=m2, workspace=scratch(1 << 23)) + [m2]
+
+
+def cache(kv):
+    a, b, c = tensors(3, 17, 40)
+    flags = torch.tensor([1, 0, 1], dtype=torch.uint8, device="cuda")
+    return [ra.rapid_cache_store(a, b, torch.zeros_like(a), flags), ra.rapid_cache_reuse(a, b, c)]
+
+
+@pytest.mark.parametrize("call", [dense, sparse, joint, select, cache])
+@pytest.mark.parametrize("kv", [None, 150])
+def test_same_results_either_way(call, kv, monkeypatch):
+    made = [x.clone() for x in call(kv)]
+    monkeypatch.setattr(binding, "_native", Nothing())
+    for a, b in zip(made, call(kv)):
+        assert torch.equal(a, b)
+
+
+def test_native_form_is_the_one_that_runs(monkeypatch):
+    native = binding._native or binding._load_native()
+    q, k, v = tensors(1, 2, 64, 64)
+    assert native.dense(q, k, v, torch.zeros_like(q), None, 0.0) == 0
+    with torch.cuda.stream(torch.cuda.Stream()) as _:
+        assert native.dense(q, k, v, torch.zeros_like(q), 3, 1) == 0
+    assert native.dense(q, k, v, torch.zeros_like(q).transpose(2, 3), None, 0.0) is None
+    assert native.dense(torch.nn.Parameter(q), k, v, torch.zeros_like(q), None, 0.0) == 0
+    assert native.dense(q, k, v, torch.zeros_like(q), torch.tensor(3), 0.0) is None
+
+
+@pytest.mark.parametrize("python", [False, True])
+def test_same_refusals_either_way(python, monkeypatch):
+    if python:
+        monkeypatch.setattr(binding, "_native", Nothing())
+    q, k, v = tensors(1, 2, 128, 64)
+    o = torch.zeros_like(q)
+    mask = torch.ones((1, 2, 2, 2), dtype=torch.uint8, device="cuda")
+    for code, call in (("RAPID_ERR_SHAPE", lambda: ra.rapid_attn_dense(q, k, v, o, 129)),
+                       ("RAPID_ERR_ALIAS", lambda: ra.rapid_attn_dense(q, k, v, q)),
+                       ("RAPID_ERR_WORKSPACE", lambda: ra.rapid_attn_block_sparse(q, k, v, o, mask, 64, workspace=scratch(64))),
+                       ("RAPID_ERR_UNSUPPORTED", lambda: ra.rapid_attn_dense(*(x[..., :32].contiguous() for x in (q, k, v, o))))):
+        with pytest.raises(ra.RapidAttnError) as e:
+            call()
+        assert e.value.status == ra.STATUS[code]
+    with pytest.raises(ValueError):
+        ra.rapid_attn_block_sparse(q, k, v, o, mask, 128)
+    with pytest.raises(TypeError):
+        ra.rapid_attn_dense(q, k, v, o.float())
+    with pytest.raises(ValueError):
+        ra.rapid_attn_dense(q, k[:, :1].contiguous(), v, o)
