@@ -816,6 +816,16 @@ __device__ __forceinline__ TileBuffer tile_buffer(const Rows& src, int key0, int
     r.bytes = (unsigned)rows * src.row_bytes;
     return r;
 }
+// The descriptor of a run of tiles moved on by one.
+__device__ __forceinline__ void next_tile_of(TileBuffer& b, unsigned tile_bytes)
+{
+    const unsigned long long at = ((unsigned long long)b.hi << 32 | b.lo) + tile_bytes;
+    b.lo = (unsigned)at;
+    b.hi = (unsigned)(at >> 32);
+    unsigned left = b.bytes - tile_bytes;
+    asm("" : "+s"(left));                                  // (a saturating subtraction would be a vector instruction)
+    b.bytes = b.bytes > tile_bytes ? left : 0u;
+}
 // One copy, or two whose second KB is in the next KB of the stage, behind one write of M0 (see issue_tile).
 __device__ __forceinline__ void copy_1k(const TileBuffer& b, unsigned off, unsigned dst)
 {
@@ -1731,16 +1741,14 @@ struct StreamPlan {
 // 113.9; ANY, dense, D = 128, N = 4608 (7 of 143 steps) 216.3 / 213.3, D = 64, B = 2, N = 4480 226.5 / 224.5.  SHORT for dense calls:
 // 0.4 to 1 % slower there, N = 16896, D = 128 0.5 %.
 enum { ANY = -1, SHORT = -2 };
-// Which tiles: at(t, u, moved, ahead) is the first key of tile t; the caller stands in tile t - ahead, which is tile
-// u - ahead of the unrolled steps, both known when compiling, and has called advance in tile UNROLL / SPT - 1 of them or
-// not; next_tile when it has done with a tile.
+// Which tiles: at(t, ahead) is the first key of tile t; the caller stands in tile t - ahead and calls next_tile when it has
+// done with a tile.  (KeptKeys: the same of whole blocks of four tiles.)
 // Tiles in order: the dense path.
 template <class P>
 struct AllKeys {
     static constexpr int LAST = ANY;
-    __device__ __forceinline__ int at(int t, int, bool, int) const { return t * P::KTS; }
+    __device__ __forceinline__ int at(int t, int) const { return t * P::KTS; }
     __device__ __forceinline__ void next_tile() {}
-    __device__ __forceinline__ void advance() {}
 };
 
 // The kept blocks of a row (or of a piece of one), in order.  Up to 64 blocks per side they are the bits of one scalar:
@@ -1962,32 +1970,25 @@ __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork
     }
 }
 
-// The 32-key steps of kept 128-key blocks (four steps = one block = one run of the unrolled loop).  The first keys of
-// the current and the next two blocks are at hand.
+// The 32-key steps of kept 128-key blocks (four steps = one block = one run of the unrolled loop): first keys of the block
+// under way and of the one after it.
 template <class P>
 struct KeptKeys {
-    static_assert(P::KTS == 32 && P::UNROLL == 4, "");
+    static_assert(P::KTS == 32 && P::UNROLL == 4 && P::KLEAD == 5 && P::VLEAD == 3, "");
     static constexpr int LAST = 3;
     KeptBlocks<128> kept;
-    int b0, b1, b2;
+    int b0, b1;
     __device__ __forceinline__ KeptKeys(const KeptBlocks<128>& kept_) : kept(kept_)
     {
         b0 = kept.next() * 128;
         b1 = kept.next() * 128;
-        b2 = kept.next() * 128;
     }
-    __device__ __forceinline__ int at(int, int u, bool moved, int) const
-    {
-        const int r = moved ? u - 4 : u;
-        return (r < 4 ? b0 : r < 8 ? b1 : b2) + r % 4 * 32;
-    }
-    __device__ __forceinline__ void advance()
+    __device__ __forceinline__ int at(int, int ahead) const { return ahead == 0 ? b0 : b1; }
+    __device__ __forceinline__ void next_tile()
     {
         b0 = b1;
-        b1 = b2;
-        b2 = kept.next() * 128;
+        b1 = kept.next() * 128;
     }
-    __device__ __forceinline__ void next_tile() {}
 };
 
 // Kept 64-key blocks, a block one tile: the first keys of the current tile and the three after it.
@@ -2004,7 +2005,7 @@ struct KeptTiles {
         b2 = kept.next() * 64;
         b3 = kept.next() * 64;
     }
-    __device__ __forceinline__ int at(int, int, bool, int ahead) const { return ahead == 0 ? b0 : ahead == 1 ? b1 : ahead == 2 ? b2 : b3; }
+    __device__ __forceinline__ int at(int, int ahead) const { return ahead == 0 ? b0 : ahead == 1 ? b1 : ahead == 2 ? b2 : b3; }
     __device__ __forceinline__ void next_tile()
     {
         b0 = b1;
@@ -2012,7 +2013,6 @@ struct KeptTiles {
         b2 = b3;
         b3 = kept.next() * 64;
     }
-    __device__ __forceinline__ void advance() {}
 };
 
 // Steps 0 .. last of this workgroup's queries against the tiles of `keys` (tiles at or beyond kv_len are all masked).  The
@@ -2056,15 +2056,36 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     };
     auto copy_k = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, koff, e, stage + e * 1024); };
     auto copy_v = [&](const TileBuffer& b, int e, unsigned stage) { copy(b, voff, e, VBASE + stage + e * 1024); };
+    // Kept blocks: a descriptor is made for a whole block and moves on tile by tile, a third of the scalar instructions of one for
+    // every tile.  us, one for every tile / now: H = 24, D = 128, N = 4608, densities 0.2 0.5 1 91.5 136.4 226.3 / 90.8 135.7 224.0; N = 1536
+    // 33.2 / 32.5; D = 64, H = 256, N = 4096, 24 blocks a row 777 / 770.
+    constexpr bool BLOCKS = Keys::LAST == 3;
+    TileBuffer kb, vb;                            // the tiles being copied
+    const unsigned tile_bytes = (unsigned)P::KTS * K.row_bytes;
     // what the barriers before tile 0 would have issued
+    if constexpr (BLOCKS) {
+        kb = tile_buffer<128>(K, keys.b0, kv_len);
+        vb = tile_buffer<128>(V, keys.b0, kv_len);
+#pragma unroll
+        for (int b = -5; b < -1; ++b) {
+            if (b >= -3) {
+                if (b > -3) next_tile_of(vb, tile_bytes);
+#pragma unroll
+                for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + 3) * P::TILE);
+            }
+            if (b > -5) next_tile_of(kb, tile_bytes);
+#pragma unroll
+            for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + 5) * P::TILE);
+        }
+    } else
 #pragma unroll
     for (int b = -P::KLEAD; b < (P::SPT == 1 ? -1 : 0); ++b) {
         if (b + P::VLEAD >= 0) {
-            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD, b + P::VLEAD, false, b + P::VLEAD), kv_len);
+            const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(b + P::VLEAD, b + P::VLEAD), kv_len);
 #pragma unroll
             for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + P::VLEAD) * P::TILE);
         }
-        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD, b + P::KLEAD, false, b + P::KLEAD), kv_len);
+        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(b + P::KLEAD, b + P::KLEAD), kv_len);
 #pragma unroll
         for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + P::KLEAD) * P::TILE);
     }
@@ -2083,8 +2104,13 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     first_qk<S, D, 0, 0, true>(x, st[0]);
     first_qk<S, D, 0, 0, false>(x, st[0]);
     if constexpr (P::SPT == 1) {                  // the barrier before tile 0: K_1, V_0 may be read
-        const TileBuffer vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1, P::VLEAD - 1, false, P::VLEAD - 1), kv_len);
-        const TileBuffer kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1, P::KLEAD - 1, false, P::KLEAD - 1), kv_len);
+        if constexpr (BLOCKS) {
+            next_tile_of(vb, tile_bytes);
+            kb = tile_buffer<128>(K, keys.b1, kv_len);
+        } else {
+            vb = tile_buffer<P::KTS>(V, keys.at(P::VLEAD - 1, P::VLEAD - 1), kv_len);
+            kb = tile_buffer<P::KTS>(K, keys.at(P::KLEAD - 1, P::KLEAD - 1), kv_len);
+        }
         wait_vmcnt<P::LOOSE>();
         phase_barrier();
 #pragma unroll
@@ -2092,7 +2118,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
 #pragma unroll
         for (int e = 0; e < LC; ++e) copy_k(kb, e, 0);
     }
-    mask_step<S>(st[0], keys.at(0, 0, false, 0) + wk * 32, kv_len, lane);
+    mask_step<S>(st[0], keys.at(0, 0) + wk * 32, kv_len, lane);
 #pragma unroll
     for (int q = 0; q < S::NQ; ++q) {
         x.m[q] = fmaxf(step_max<S>(st[0], q, c) + S::UP, REF_LOWEST);  // (a key group may have no valid key at all)
@@ -2101,7 +2127,6 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     soft_half<S, D, 0>(x, st[0], c, pw);
 
     // Step i.  U = i % UNROLL.
-    TileBuffer kb, vb;                            // the tiles being copied
     auto step = [&](auto u, int i) {
         constexpr int U = decltype(u)::value;
         constexpr bool FIRST_OF_TILE = U % P::SPT == 0;
@@ -2127,13 +2152,21 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         else step_qk<S, D, KC, KN, VC, 0>(x, sc, sn, c, pw, hook);
         soft_close<S, D>(x, sc, c, pw);
         const int t = i / P::SPT;
-        mask_step<S>(sn, P::SPT == 1 ? keys.at(t + 1, U + 1, false, 1) + wk * 32 : keys.at((i + 1) / 2, 0, false, 0) + (i + 1) % 2 * 32, kv_len, lane);
+        mask_step<S>(sn, BLOCKS ? keys.at(0, U == 3 ? 1 : 0) + (U + 1) % 4 * 32
+                         : P::SPT == 1 ? keys.at(t + 1, 1) + wk * 32 : keys.at((i + 1) / 2, 0) + (i + 1) % 2 * 32, kv_len, lane);
         if constexpr (FIRST_OF_TILE) {
-            constexpr bool MOVE = U / P::SPT == P::UNROLL / P::SPT - 1;
-            if constexpr (MOVE) keys.advance();
-            vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, U / P::SPT + P::VLEAD, MOVE, P::VLEAD), kv_len);
-            kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, U / P::SPT + P::KLEAD, MOVE, P::KLEAD), kv_len);
-            keys.next_tile();
+            if constexpr (BLOCKS) {               // V_{t+3} and K_{t+5}
+                if constexpr (U == 1) vb = tile_buffer<128>(V, keys.b1, kv_len);
+                else next_tile_of(vb, tile_bytes);
+                if constexpr (U == 3) {
+                    keys.next_tile();
+                    kb = tile_buffer<128>(K, keys.b1, kv_len);
+                } else next_tile_of(kb, tile_bytes);
+            } else {
+                vb = tile_buffer<P::KTS>(V, keys.at(t + P::VLEAD, P::VLEAD), kv_len);
+                kb = tile_buffer<P::KTS>(K, keys.at(t + P::KLEAD, P::KLEAD), kv_len);
+                keys.next_tile();
+            }
             wait_vmcnt<P::LOOSE>();
             phase_barrier();
         }
