@@ -988,7 +988,7 @@ __device__ __forceinline__ void v_addresses(const char* lds_v, int h, int tr_row
 // key0 + 32 rb + 8 (i/4) + 4 h + i%4  of query n.
 __device__ __forceinline__ void mask_tail(f32x16 (&st)[2], int key0, int kv_len, int h)
 {
-    if (key0 + KT > kv_len) {
+    if (__builtin_expect(key0 + KT > kv_len, 0)) {
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
@@ -1465,7 +1465,7 @@ __device__ __forceinline__ void soft_close(StreamRegs<S, D>& x, const Scores<S>&
 template <class S>
 __device__ __forceinline__ void mask_step(Scores<S>& st, int key0, int kv_len, int lane)
 {
-    if (key0 + 32 > kv_len) {
+    if (__builtin_expect(key0 + 32 > kv_len, 0)) {
         const int left = kv_len - key0 - 4 * (lane >> 4);
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
@@ -1772,7 +1772,7 @@ struct KeptBlocks {
     }
     __device__ __forceinline__ int next()
     {
-        if (list == nullptr) {
+        if (__builtin_expect(list == nullptr, 1)) {
             const int j = bits != 0ull ? __builtin_ctzll(bits) : NOWHERE;
             bits &= bits - 1ull;
             return j;
