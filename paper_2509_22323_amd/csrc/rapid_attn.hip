@@ -1834,71 +1834,90 @@ __device__ __forceinline__ void entry_of(const AttnParams& p, int& seg, int& i)
         }
     }
 }
-// The entry of a plan of whole rows that nobody has made: every workgroup counts all rows of its segment, one per thread
-// (8 <= nb <= 64, at most 256 rows), and looks up the one that comes i-th, longest first (with the second round of 32
-// backwards: see plan_small_kernel).  `at`: LDS that no copy uses yet, for FOUND_BYTES.
+// The entry of a plan of whole rows that nobody has made: every workgroup counts all rows of its segment, one or two per
+// thread (8 <= nb <= 64), and looks up the one that comes i-th, longest first (with the second round of 32 backwards, FOURTH:
+// the fourth too: see plan_small_kernel).  `at`: LDS that no copy uses yet, for FOUND_BYTES.
 // Some 1.5 us of every workgroup in place of a launch: run_sparse holds both sides of the line.
+constexpr int FOUND_ROWS = 256;                  // rows of a segment, at most
 struct FoundRow {
     int hist[SMALL_NB + 2];                        // rows by length, longest first
-    int before[4];                                 // rows of the length looked for, by wavefront
+    int before[FOUND_ROWS / 64];                   // rows of the length looked for, by 64 rows
     int item, n;
     unsigned long long row;
 };
-__device__ __forceinline__ void find_row(const AttnParams& p, int seg, int i, SparseWork<64>& w, FoundRow* at)
+template <int BLOCK, int THREADS, bool FOURTH>
+__device__ __forceinline__ void find_row(const AttnParams& p, int seg, int i, SparseWork<BLOCK>& w, FoundRow* at)
 {
+    constexpr int PER = FOUND_ROWS / THREADS;      // rows of a thread
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nb = p.nb;
     const int items = (p.pairs - seg + XCDS - 1) / XCDS * nb;
     if (i >= items) return;
-    const bool has = tid < items;
-    const int t = has ? tid : 0;
-    const int pair = (int)__umulhi((unsigned)t, p.nq.magic) * XCDS + seg;    // (nq = nb)
-    const int item = pair * nb + t - (pair - seg) / XCDS * nb;
-    unsigned long long row = 0ull;
-    int c;
-    if (p.mask != nullptr) {
-        int kv_len = p.kv_len;
-        if (p.kv_lens != nullptr) kv_len = p.kv_lens[p.H.d == 1 ? pair : (int)__umulhi((unsigned)pair, p.H.magic)];
-        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
-        const unsigned char* src = p.mask + (size_t)item * nb;
-        unsigned long long v[8];
+    int item[PER], c[PER];
+    unsigned long long row[PER];
+    bool has[PER];
 #pragma unroll
-        for (int k = 0; k < 8; ++k)                // all on their way at once; the last eight bytes of a row end with it
-            if (8 * k < nb) __builtin_memcpy(&v[k], src + (8 * k + 8 <= nb ? 8 * k : nb - 8), 8);
+    for (int e = 0; e < PER; ++e) {
+        has[e] = tid + THREADS * e < items;
+        const int t = has[e] ? tid + THREADS * e : 0;
+        const int pair = (int)__umulhi((unsigned)t, p.nq.magic) * XCDS + seg;    // (nq = nb)
+        item[e] = pair * nb + t - (pair - seg) / XCDS * nb;
+        row[e] = 0ull;
+        if (p.mask != nullptr) {
+            int kv_len = p.kv_len;
+            if (p.kv_lens != nullptr) kv_len = p.kv_lens[p.H.d == 1 ? pair : (int)__umulhi((unsigned)pair, p.H.magic)];
+            kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+            const unsigned char* src = p.mask + (size_t)item[e] * nb;
+            unsigned long long v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (8 * k < nb) row |= (unsigned long long)byte_bits((unsigned)v[k], (unsigned)(v[k] >> 32)) << (8 * k + 8 <= nb ? 8 * k : nb - 8);
-        const int live = (kv_len + 63) / 64;
-        row &= live >= 64 ? ~0ull : (1ull << live) - 1ull;
-        c = __popcll(row);
-    } else {
-        c = p.counts[item];
+            for (int k = 0; k < 8; ++k)            // all on their way at once; the last eight bytes of a row end with it
+                if (8 * k < nb) __builtin_memcpy(&v[k], src + (8 * k + 8 <= nb ? 8 * k : nb - 8), 8);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (8 * k < nb) row[e] |= (unsigned long long)byte_bits((unsigned)v[k], (unsigned)(v[k] >> 32)) << (8 * k + 8 <= nb ? 8 * k : nb - 8);
+            const int live = (kv_len + BLOCK - 1) / BLOCK;
+            row[e] &= live >= 64 ? ~0ull : (1ull << live) - 1ull;
+            c[e] = __popcll(row[e]);
+        } else {
+            c[e] = p.counts[item[e]];
+        }
     }
-    for (int k = tid; k <= nb; k += 256) at->hist[k] = 0;
+    for (int k = tid; k <= nb; k += THREADS) at->hist[k] = 0;
     __syncthreads();
-    if (has) atomicAdd(&at->hist[nb - c], 1);
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+        if (has[e]) atomicAdd(&at->hist[nb - c[e]], 1);
     __syncthreads();
-    if (i >= CUS_PER_XCD && i < 2 * CUS_PER_XCD) { // backwards
-        const int left = items - CUS_PER_XCD < CUS_PER_XCD ? items - CUS_PER_XCD : CUS_PER_XCD;
-        i = 2 * CUS_PER_XCD + left - CUS_PER_XCD - 1 - (i - CUS_PER_XCD);
-    }
+    auto backwards = [&](int first) {              // a round of 32
+        const int left = items - first < CUS_PER_XCD ? items - first : CUS_PER_XCD;
+        if (i >= first && i < first + CUS_PER_XCD) i = first + left - 1 - (i - first);
+    };
+    backwards(CUS_PER_XCD);
+    if (FOURTH) backwards(3 * CUS_PER_XCD);
     const int upto = wave_scan_inclusive(lane < nb ? at->hist[lane] : 0);
     const int shorter = __popcll(__builtin_amdgcn_ballot_w64(lane < nb && upto <= i));    // nb - the length of the i-th row
     const int start = shorter > 0 ? __builtin_amdgcn_readlane(upto, shorter - 1) : 0;
-    const unsigned long long same = __builtin_amdgcn_ballot_w64(has && nb - c == shorter);
-    if (lane == 0) at->before[wave] = __popcll(same);
-    __syncthreads();
-    int rank = __popcll(same & ((1ull << lane) - 1ull));
+    unsigned long long same[PER];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) rank += k < wave ? at->before[k] : 0;
-    if (has && nb - c == shorter && rank == i - start) { at->item = item; at->n = c; at->row = row; }
+    for (int e = 0; e < PER; ++e) {
+        same[e] = __builtin_amdgcn_ballot_w64(has[e] && nb - c[e] == shorter);
+        if (lane == 0) at->before[THREADS / 64 * e + wave] = __popcll(same[e]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        int rank = __popcll(same[e] & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int k = 0; k < FOUND_ROWS / 64 - 1; ++k) rank += k < THREADS / 64 * e + wave ? at->before[k] : 0;
+        if (has[e] && nb - c[e] == shorter && rank == i - start) { at->item = item[e]; at->n = c[e]; at->row = row[e]; }
+    }
     __syncthreads();
     w.rec.item = __builtin_amdgcn_readfirstlane(at->item);
     w.rec.nblk = __builtin_amdgcn_readfirstlane(at->n);
-    unsigned long long r = at->row;
+    const unsigned long long r = at->row;
     w.row = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(r >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)r);
 }
 
-template <int BLOCK>
+template <int BLOCK, int THREADS, bool FOURTH>
 __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, char* scratch)
 {
     typedef const __attribute__((address_space(4))) int32_t* cptr_t;
@@ -1911,8 +1930,8 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, ch
     SparseWork<BLOCK> w;
     w.rec = {-1, 0, 0, -1};
     w.row = 0ull;
-    if (BLOCK == 64 && p.planned == PLAN_FOUND) {
-        if constexpr (BLOCK == 64) find_row(p, seg, i, w, (FoundRow*)scratch);
+    if (p.planned == PLAN_FOUND) {
+        find_row<BLOCK, THREADS, FOURTH>(p, seg, i, w, (FoundRow*)scratch);
     } else if (p.planned == PLAN_NONE) {
         // The dispatcher deals the workgroups of an XCD out to its 32 CUs in turn; rows with the same number (text rows,
         // the long ones) would meet on the same CU where 32 is a multiple of nb, so every 32 workgroups start 3/8 of the rows on.
@@ -1934,7 +1953,7 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, ch
     w.kept.bits = w.row;
     w.kept.n = w.rec.nblk;
     w.kept.at = w.kept.first = 0;
-    if (item >= 0 && !(BLOCK == 64 && p.planned == PLAN_FOUND && p.mask != nullptr)) {
+    if (item >= 0 && !(p.planned == PLAN_FOUND && p.mask != nullptr)) {
         if (p.mask != nullptr) {                   // nb <= 64
             int kv_len = p.kv_len;
             if (p.kv_lens != nullptr) kv_len = ((cptr_t)p.kv_lens)[p.H.of(p.nq.of(item))];    // (nq = nb)
@@ -2430,7 +2449,7 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     static_assert(P::QT == 64, "one item = 64 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    const auto work = sparse_work<64>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
+    const auto work = sparse_work<64, P::NW * 64, false>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
     const int item = work.rec.item;
     if (item < 0 || work.rec.nblk <= 0) leave_plan<64>(p, work);
     if (item < 0) return;
@@ -2489,7 +2508,7 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     static_assert(P::QT == 128, "one record = 128 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    const auto work = sparse_work<128>(p, nullptr);
+    const auto work = sparse_work<128, P::NW * 64, D == 64>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
     const PlanRec rec = work.rec;
     const int item = rec.item;
     if (rec.nblk <= 0) leave_plan<128>(p, work);
@@ -2623,8 +2642,10 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
     constexpr int LPT = G::LOADS / NW;            // copy instructions per wavefront per tile (K or V)
 
     __shared__ __attribute__((aligned(1024))) char lds[4 * G::TILE_BYTES];
+    auto k_stage = [&](int t) -> char* { return lds + (t & 1) * G::TILE_BYTES; };
+    auto v_stage = [&](int t) -> char* { return lds + (2 + (t & 1)) * G::TILE_BYTES; };
 
-    auto work = sparse_work<128>(p, nullptr);
+    auto work = sparse_work<128, 256, true>(p, v_stage(1));    // (the last stage to be filled)
     const PlanRec rec = work.rec;
     const int item = rec.item;
     if (rec.nblk <= 0) leave_plan<128>(p, work);
@@ -2662,8 +2683,6 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
         write_output<D>(O, acc, 0.f, qrow, false, p.N, h);
         return;
     }
-    auto k_stage = [&](int t) -> char* { return lds + (t & 1) * G::TILE_BYTES; };
-    auto v_stage = [&](int t) -> char* { return lds + (2 + (t & 1)) * G::TILE_BYTES; };
     // first keys of tiles j+1, j+2, j+3 (not used from tile T on)
     const int key0 = work.kept.next() * 128;
     int kn1 = key0 + KT;
@@ -3010,12 +3029,14 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
                          (xcd_items > CUS_PER_XCD * (D == 128 ? 1 : 2) && !short_rows && segments(B * H, nb, block) == XCDS);
     const long long mask_pieces = nb <= SMALL_NB ? (long long)(xcd_items / nb) * (((nb * nb + 7) / 8 + 3) / 4 * 4) : 0;
     const bool small = nb <= SMALL_NB && xcd_items <= SMALL_ITEMS && mask_pieces <= SMALL_PIECES;
-    // 64-token masks: every workgroup looks its row up by itself, while a place works through few of them.  us, plan launch /
-    // looked up, H = 24 unless said otherwise, rows of an XCD x blocks: D = 128 (64 places) 96 x 32 30.3 / 28.1; 132 x 44 62.4 / 61.9; 192 x 64
+    // Every workgroup looks its row up by itself, while a place works through few of them and (128-token masks) no row is
+    // long enough to be cut.  us, plan launch / looked up, 64-token masks, H = 24 unless said otherwise, rows of an XCD x blocks: D = 128 (64 places) 96 x 32 30.3 / 28.1; 132 x 44 62.4 / 61.9; 192 x 64
     // 92.0 / 93.2; B = 8, 240 x 10 42.0 / 42.6; D = 64 (96 places) 96 x 32 23.0 / 20.7; 132 x 44 38.9 / 36.9; 192 x 64 56.6 / 54.5; B = 4,
     // 192 x 16 25.9 / 24.3; B = 8, 240 x 10 23.0 / 21.5; with 2 or 3 pairs the same within 0.5 %.
-    const bool found = planned && block == 64 && nb >= 8 && nb <= SMALL_NB && xcd_items <= (D == 128 ? 144 : 256) &&
-                       (H == 1 || divisor(H, (long long)B * H).magic != 0u);
+    // 128-token masks, density 0.2: D = 128 96 x 8 27.4 / 24.4; 90 x 15 45.5 / 42.5; 144 x 12 51.5 / 49.9; 192 x 12 68.6 / 68.3; 216 x 9
+    // 65.4 / 63.9 but 228 x 12 76.2 / 77.0; D = 64 96 x 8 19.2 / 15.1; 90 x 15 38.4 / 34.6; 192 x 12 40.7 / 39.2; 228 x 12 44.6 / 42.2.
+    const bool found = planned && nb >= 8 && (block == 64 ? nb <= SMALL_NB : nb < 2 * SPLIT_MIN_BLOCKS) &&
+                       xcd_items <= (D == 64 ? FOUND_ROWS : block == 64 ? 144 : 192) && (H == 1 || divisor(H, (long long)B * H).magic != 0u);
     const bool lists = mask != nullptr && (planned && !found ? !small : nb > SMALL_NB);      // compacted by a kernel of its own
     if (lists)
         hipLaunchKernelGGL(compact_mask_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,

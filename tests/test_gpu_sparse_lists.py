@@ -366,6 +366,44 @@ def test_64_token_rows_of_a_selected_mask_looked_up_without_a_plan(D):
         check(torch.cat([out[0][b:b + 1], pad], 2)[:, :, :22 * block], ref, n, f"D={D} sample {b}")
 
 
+@pytest.mark.parametrize("D,B,H,nb,alike", [(64, 3, 24, 8, False), (64, 2, 56, 15, True), (64, 3, 64, 10, False), (64, 5, 40, 11, False), (64, 3, 62, 11, False),
+                                            (128, 2, 20, 8, False), (128, 4, 24, 12, True), (128, 2, 64, 12, False), (128, 1, 132, 12, False), (128, 1, 38, 15, False)])
+def test_128_token_rows_looked_up_without_a_plan(D, B, H, nb, alike):
+    """As above for rows of 8 to 15 blocks of 128 tokens, in the kernels for few and for many rows, either side of the line;
+    samples of different length; the same lists from a mask that is given and from one that is selected."""
+    block, N = 128, nb * 128
+    g = torch.Generator(device="cuda").manual_seed(H * nb + D)
+    q, k, v = (torch.randn((B, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = (torch.rand((B, H, nb, nb), generator=g, device="cuda") < 0.4).to(torch.uint8) * 3
+    mask[:, :, 4], mask[:, 1, 5], mask[:, :, -2:] = 0, 0, 255
+    if alike:
+        mask[:] = 1
+    host = mask.cpu().numpy().reshape(B * H * nb, nb) != 0
+    lens = [N - 29 - 300 * b for b in range(B)]
+    for kv_lens in (None, torch.tensor(lens, dtype=torch.int32, device="cuda")):
+        ws = torch.full((ra.rapid_attn_workspace_bytes(B, H, N, D, block),), 0xa5, dtype=torch.uint8, device="cuda")
+        o = torch.full_like(q, 7.0)
+        if kv_lens is None:
+            ra.rapid_attn_block_sparse(q, k, v, o, mask, block, N - 29, workspace=ws)
+        else:
+            ra.rapid_attn_joint([(q, k, v, o)], mask=mask, block=block, kv_lens=kv_lens)
+        for b in range(B):
+            n = N - 29 if kv_lens is None else lens[b]
+            ref = reference(*(x[b:b + 1] for x in (q, k, v)), mask[b:b + 1], block, n, D ** -0.5)
+            check(o[b:b + 1], ref, n, f"D={D} H={H} nb={nb} sample {b}")
+        if kv_lens is None:
+            counts, order, index, geo = read_plan(ws.cpu().numpy(), B, H, nb, D, block)
+            assert (counts == host.sum(-1)).all()
+            check_plan(counts, order, geo, B, H, nb, block, D)
+            for r in range(B * H * nb):
+                assert (index[r, :counts[r]] == np.flatnonzero(host[r])).all(), r
+    chosen = torch.empty_like(mask)
+    out = [torch.full_like(q, 7.0) for _ in range(2)]
+    ra.rapid_attn_joint_select([(q, k, v, out[0])], block, kv_lens=kv_lens, text_start=(nb - 2) * block, tau=0.7, mask_out=chosen)
+    ra.rapid_attn_joint([(q, k, v, out[1])], mask=chosen, block=block, kv_lens=kv_lens)
+    assert torch.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("H,nb", [(24, 34), (24, 35), (200, 4), (206, 4), (410, 2), (1, 819), (4, 205)])
 def test_either_side_of_the_kernel_for_many_rows(H, nb):
     """D = 64, 128-token masks, calls of 816 to 824 rows and around: short and long rows, last blocks cut, cut rows merged."""
