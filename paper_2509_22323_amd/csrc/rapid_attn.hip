@@ -31,7 +31,7 @@
 //   attn_sparse_sg_kernel<D>    sparse, 128-token mask tiles: one four-wavefront workgroup per plan
 //                               record (a query-block or a piece of its kept list); pieces are
 //                               merged by the last one to finish.  D = 128 on the 16x16x32 stream
-//   attn_sparse_wide_kernel     the same at D = 64 on the stream, for calls whose rows fill the chip
+//   attn_sparse_wide_kernel     the same at D = 64 on the stream, for calls of many rows
 //   attn_sparse_pp_kernel<D>    sparse, 64-token mask tiles: one query-block per workgroup on the stream, the
 //                               keys of a block split between two groups of wavefronts
 //   plan_small_kernel           launch plan in one launch, from the mask or from counts (up to 64 blocks per side); the
@@ -3075,13 +3075,16 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
     p.nb = nb;
     const dim3 grid((unsigned)w.chunk * XCDS);
     if (block == 128) {
-        // D = 64: 64 queries per wavefront read LDS half as often, but a record takes longer: they win where records fill most
-        // of the chip's places (four per CU).  us, 32 / 64 queries per wavefront, densities 0.15, 0.4 and 1, pairs x rows:
-        //   24 x 24 33.9 45.0 77.8 / 34.8 50.7 91.3; 16 x 40 51 95 123 / 52 99 145; 24 x 32 43.8 67.6 121 / 44.8 62.8 124; 96 x 8 28.4 29.7
-        //     39.9 / 28.6 29.8 38.9; 8 x 96 90 170 338 / 88 164 347; 4 x 132 92 170 348 / 108 212 447
-        //   24 x 35 54.7 78.5 144 / 53.7 75.6 138, of density 0.25 and 0.6 63.0 103 / 60.8 94.1; 16 x 64 82 154 298 / 82 156 279; 8 x 132 145 298
-        //     598 / 144 304 567; 192 x 6 23.0 28.7 47.2 / 21.7 26.7 45.7; 192 x 8, 0.4 40.3 / 36.6; 304 x 7 33.1 47.1 81.8 / 32.3 42.9 78.2
-        if (D == 64 && 5 * rows > 4 * (4 * XCDS * CUS_PER_XCD)) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
+        // D = 64: 64 queries per wavefront read LDS half as often, but a record takes longer; it wins where every place
+        // of the chip (four per CU) gets at least two records.  us, 32 / 64 queries per wavefront, H = 24, densities 0.15 to 1:
+        // 3072 rows (B = 8, N = 2048) 87 / 84 to 218 / 208; 6720 (B = 8, N = 4480) 267 / 267 to 973 / 939; 1536 rows
+        // (B = 8, N = 1024) 41 / 42 to 67 / 74; 840 rows of N = 896 26.4 / 29.7.  Rows of one or two kept blocks are all
+        // fixed cost, of which two wavefronts hide less than four: density 0.1, B = 8, H = 38, N = 896 36.5 / 38.3, 1152
+        // 46.8 / 47.2, 1408 55.4 / 56.2 (0.3: 80.7 / 79.4; 1.0: 184 / 171), so not at 8 blocks per side and fewer; a mask of
+        // the diagonal alone, which the host cannot tell, is 7 % slower on it at any N (B = 4, H = 24, N = 4480 46.1 / 49.5).
+        // Calls of 840 to 2048 rows of more than 8 blocks would be up to 8 % faster on it, at errors against 64 bits 0.1 to 0.9 % larger
+        // (2.320 / 2.326e-3 at 24 x 35, density 0.25): not taken.
+        if (D == 64 && rows > 2 * 4 * XCDS * CUS_PER_XCD && nb > 8) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
         else if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(SparsePlan<128>::P::NW * 64), 0, s, p);
     } else {
