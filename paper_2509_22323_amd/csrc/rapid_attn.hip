@@ -136,7 +136,7 @@ struct AttnParams {
     char* partial;           // sparse, 128-token tiles: partial results of the pieces of split items
     int N, kv_len;
     Divisor H;
-    Divisor B;               // dense
+    int turn;                // dense: see dense_run
     Divisor nq;              // query tiles per (sample, head)
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
@@ -2307,10 +2307,6 @@ template <> struct DensePlan<64> {
     static constexpr int LDS = Whole::LDS;
 };
 
-// Samples of different length: consecutive (sample, head) pairs are those of one head, so that an XCD's run of items holds
-// short samples and long ones.  us, sample by sample / head by head, prompts of 1/B, 2/B, .. of the text tokens, H = 24: B = 2,
-// D = 64, 1024 + 333 tokens 31.2 / 31.3, 2048 + 333 72.4 / 70.4; B = 8, 1024 + 333 93.3 / 83.4; D = 128, B = 2, 1024 + 512 59.1 / 55.0;
-// B = 4, 4096 + 512 782 / 746.
 // One wavefront's part of an item whose first query is q00: the queries from q0 on, stored up to `end`; `stage` bytes into the
 // LDS its output goes through.
 template <class P>
@@ -2319,9 +2315,7 @@ __device__ __forceinline__ void dense_wave(const AttnParams& p, char* lds, int p
     typedef typename P::S S;
     constexpr int D = P::D;
     const int lane = threadIdx.x & 63;
-    int smp, head;
-    if (p.kv_lens != nullptr) { head = p.B.of(pair); smp = pair - head * p.B.d; }
-    else { smp = p.H.of(pair); head = pair - smp * p.H.d; }
+    const int smp = p.H.of(pair), head = pair - smp * p.H.d;
     const int kv_len = valid_tokens(p, smp);
     const Rows Q = rows_of(p.q, p.in, smp, head, p.n0), K = rows_of(p.k, p.in, smp, head, p.n0);
     const Rows V = rows_of(p.v, p.in, smp, head, p.n0), O = rows_of(p.o, p.out, smp, head, p.n0);
@@ -2384,6 +2378,16 @@ constexpr __host__ __device__ Piece192 piece_192(int i, int first, int last, int
     return {-1, 0, 0, n};
 }
 
+// The run of `chunk` items whose place `at` the workgroup's XCD works on.  Query tiles of the same (sample, head) share K and V
+// in an XCD's L2, so runs are contiguous; the dispatcher deals consecutive workgroup ids out to the 8 XCDs in turn.  Samples of
+// different length (turn > 0): the runs of one sample are those of neighbouring XCDs, so with every (sample, head)'s worth of
+// places an XCD goes `turn` runs on, into another sample.  Which items are cut follows from their numbers as ever: how a query is
+// computed does not hang on whether lengths were given.  us, turn = 0 / as it is, prompts of 1/B, 2/B, .. of the text tokens,
+// H = 24: D = 64, B = 2, 1024 + 333 tokens 28.4 / 28.5, 2048 + 333 71.6 / 70.7; B = 8, 1024 + 333 91.2 / 83.9; B = 7, 512 + 500 49.0 /
+// 45.5; D = 128, B = 2, 1024 + 512 57.3 / 54.4; B = 8, 512 + 512 86.8 / 75.2; B = 4, 4096 + 512 764 / 752; pairs that the XCDs do not
+// divide: H = 7, B = 5, D = 64, 2048 + 500 55.0 / 52.9; B = 3, D = 128, 8192 + 512 588.9 / 589.2.
+__device__ __forceinline__ int dense_run(const AttnParams& p, int at) { return (int)((blockIdx.x + (unsigned)(p.turn * p.nq.of(at))) % XCDS); }
+
 // 256 queries of one (sample, head) per workgroup; the items of an XCD that do not fill its CUs evenly are
 // cut into `cut` = 2 or 4 workgroups each, or into pieces of 192 queries (p.whole of an XCD's items stay whole).
 template <int D>
@@ -2391,17 +2395,15 @@ __global__ __launch_bounds__(DensePlan<D>::Whole::NW * 64, 2) void attn_dense_st
 {
     typedef DensePlan<D> DP;
     __shared__ __attribute__((aligned(1024))) char lds[DP::LDS];
-    // XCD-aware work mapping: the dispatcher deals consecutive workgroup ids round-robin
-    // over the 8 XCDs, so give each XCD a contiguous run of items (query tiles of the same
-    // head then share K/V in that XCD's L2).
-    const int i = blockIdx.x / XCDS, first = (blockIdx.x % XCDS) * p.chunk;
+    const int i = blockIdx.x / XCDS;
     if (i < p.whole) {
-        const int item = first + i;
+        const int item = dense_run(p, i) * p.chunk + i;
         if (item < p.items) dense_item<typename DP::Whole>(p, lds, item, DENSE_QT, 0);
         return;
     }
     if constexpr (D == 128) {
         if (p.cut == 3) {
+            const int first = dense_run(p, p.whole) * p.chunk;
             const int last = first + p.chunk < p.items ? first + p.chunk : p.items;
             const Piece192 a = piece_192(i - p.whole, first + p.whole, last, p.nq.d, p.N);
             const int bh = __builtin_amdgcn_readfirstlane(a.bh), q0 = __builtin_amdgcn_readfirstlane(a.q0), end = __builtin_amdgcn_readfirstlane(a.end);
@@ -2409,7 +2411,8 @@ __global__ __launch_bounds__(DensePlan<D>::Whole::NW * 64, 2) void attn_dense_st
             return;
         }
     }
-    const int item = first + p.whole + (p.cut == 2 ? (i - p.whole) / 2 : (i - p.whole) / 4);
+    const int at = p.whole + (p.cut == 2 ? (i - p.whole) / 2 : (i - p.whole) / 4);
+    const int item = dense_run(p, at) * p.chunk + at;
     if (item >= p.items) return;
     if (p.cut == 2) dense_item<typename DP::Half>(p, lds, item, DENSE_QT, (i - p.whole) % 2 * (DENSE_QT / 2));
     else dense_item<typename DP::Quarter>(p, lds, item, DENSE_QT, (i - p.whole) % 4 * (DENSE_QT / 4));
@@ -2421,7 +2424,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void attn_dense_pp_kernel(c
 {
     typedef StreamPlan<D, 1, 2, 2, 1, 2, 3> P;
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
-    const int item = (blockIdx.x % XCDS) * p.chunk + blockIdx.x / XCDS;
+    const int at = blockIdx.x / XCDS, item = dense_run(p, at) * p.chunk + at;
     if (item < p.items) dense_item<P>(p, lds, item, P::QT, 0);
 }
 
@@ -2907,7 +2910,6 @@ void fill_common(AttnParams& p, const Problem& pr)
     p.kv_lens = pr.kv_lens;
     p.n0 = pr.n0;
     p.H = divisor(pr.H, (long long)pr.B * pr.H);
-    p.B = divisor(pr.B, (long long)pr.B * pr.H);
     p.N = pr.N; p.kv_len = pr.kv_len;
     p.c = pr.scale * LOG2E;
 }
@@ -2916,6 +2918,7 @@ int run_dense(const Problem& pr, void* stream)
 {
     AttnParams p{};
     fill_common(p, pr);
+    p.turn = pr.kv_lens == nullptr || pr.B == 1 ? 0 : pr.B < XCDS ? XCDS / pr.B : 1;
     hipStream_t s = (hipStream_t)stream;
     const long long pairs = (long long)pr.B * pr.H, small = pairs * ((pr.N + 31) / 32);
     const long long items = pairs * ((pr.N + DENSE_QT - 1) / DENSE_QT), chunk = (items + XCDS - 1) / XCDS;

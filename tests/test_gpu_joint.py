@@ -174,3 +174,32 @@ def test_per_sample_lengths_outside_the_range_are_clamped():
         np.testing.assert_array_equal(a, b)
     assert (outs["wild"][0][0] == 0).all() and (outs["wild"][3][0] == 0).all()
     assert_close(outs["wild"][0][1:2], oracle_joint(q[1:2], k[1:2], v[1:2], N, None, block), "length above N")
+
+
+@pytest.mark.parametrize("D,B,H,N", [
+    (64, 2, 24, 1357),        # 36 items of an XCD: the last four are cut in quarters
+    (64, 2, 24, 1700),        # 42: the last ten in halves
+    (64, 2, 16, 1000),        # one round, all of it cut
+    (64, 3, 2, 300),          # the kernel for few queries
+    (128, 2, 16, 2305),       # 40: the last eight in quarters
+    (128, 3, 8, 4100),        # 51: pieces of 192 queries
+    (128, 5, 7, 2600),        # pairs that do not divide by the XCDs
+])
+def test_lengths_per_sample_leave_the_other_samples_bits_alone(D, B, H, N):
+    """Which queries a workgroup takes, and in what order the sums of a query run, follows from the sizes alone: a sample
+    of N valid tokens has the same bits whether lengths are given or not and whatever the other samples' are."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    fused = torch.randn((B, N, 3, H, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    q, k, v = (fused[:, :, i].transpose(1, 2) for i in range(3))
+
+    def run(lens):
+        o = torch.full((B, N, H, D), float("nan"), device="cuda", dtype=torch.bfloat16).transpose(1, 2)
+        kv_lens = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+        ra.rapid_attn_joint([(q, k, v, o)], kv_lens=kv_lens)
+        return o
+
+    plain = run(None)
+    assert torch.equal(run([N] * B), plain)
+    for whole in range(B):
+        lens = [N if b == whole else N - 200 + 37 * b for b in range(B)]
+        assert torch.equal(run(lens)[whole], plain[whole]), lens
