@@ -1,5 +1,5 @@
 """Binding of librapid_attn.so: same names as the C ABI, marshalling only.  The calls that launch go through
-native_call.so (csrc/native_call.cpp) where their arguments are what most calls hand over, else through ctypes.
+native_call.so (csrc/native_call.cpp) where it is there and their arguments are what most calls hand over, else through ctypes.
 
 PyTorch is used for device memory and streams, nothing else: tensors are passed as
 raw device pointers, kernels go to torch's current HIP stream.  There is no fallback:
@@ -9,6 +9,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "librapid_attn.so")
@@ -115,18 +117,35 @@ def library():
     return lib
 
 
+class _NoNative:
+    """In place of native_call.so where it cannot be had: takes no call."""
+    def _takes_nothing(self, *args):
+        return None
+    dense = block_sparse = joint = joint_select = select = store = reuse = _takes_nothing
+
+
 def _load_native():
-    """native_call.so, bound to the loaded library.  Raises if it has not been built."""
+    """native_call.so, bound to the loaded library.  A package without it (librapid_attn.so needs neither g++ nor torch's headers) or
+    with one for another torch or Python calls by way of ctypes."""
     global _native
     import importlib.machinery
     import importlib.util
-    import torch  # noqa: F401  (its libraries have to be there)
+    import torch
     lib = library()
-    if not os.path.exists(_NATIVE_SO):
-        raise ImportError(f"{_NATIVE_SO} is missing: build it first (python paper_2509_22323_amd/build.py).")
-    loader = importlib.machinery.ExtensionFileLoader("native_call", _NATIVE_SO)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("native_call", loader))
-    loader.exec_module(module)
+    try:
+        if not os.path.exists(_NATIVE_SO):
+            _native = _NoNative()
+            return _native
+        loader = importlib.machinery.ExtensionFileLoader("native_call", _NATIVE_SO)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("native_call", loader))
+        loader.exec_module(module)
+        here = f"{torch.__version__} {sys.implementation.cache_tag}"
+        if module.built_for != here:
+            raise ImportError(f"built for {module.built_for}, this is {here}")
+    except ImportError as e:
+        warnings.warn(f"{_NATIVE_SO} is not used, calls go by way of ctypes: {e}", RuntimeWarning, stacklevel=3)
+        _native = _NoNative()
+        return _native
     module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
         "rapid_attn_dense", "rapid_attn_block_sparse", "rapid_attn_joint", "rapid_attn_joint_select", "rapid_mask_select",
         "rapid_cache_store", "rapid_cache_reuse")))

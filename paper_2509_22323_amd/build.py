@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 
@@ -34,16 +35,40 @@ FLAGS = [
 
 def build(verbose: bool = False, extra: list[str] | None = None, out: str = OUT) -> str:
     _compile(PROBE_SOURCES, PROBE_OUT, verbose, extra)
+    _compile(SOURCES, out, verbose, extra)
     build_native(verbose)
-    return _compile(SOURCES, out, verbose, extra)
+    return out
 
 
-def build_native(verbose: bool = False) -> str:
+def native_lacks() -> str | None:
+    """What a compilation of native_call.so would need and is not here, or None."""
+    import sysconfig
+    if shutil.which("g++") is None:
+        return "g++"
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return "Python.h"
+    try:
+        from torch.utils.cpp_extension import include_paths
+    except ImportError:
+        return "torch"
+    header = os.path.join("torch", "csrc", "autograd", "python_variable.h")
+    return None if any(os.path.exists(os.path.join(path, header)) for path in include_paths()) else header
+
+
+def build_native(verbose: bool = False) -> str | None:
+    """native_call.so; None where it cannot be compiled: the calls then go by way of ctypes."""
+    lacks = native_lacks()
+    if lacks is not None:
+        print(f"{NATIVE_OUT} is not built ({lacks} is missing): calls go by way of ctypes", file=sys.stderr)
+        if os.path.exists(NATIVE_OUT):
+            os.remove(NATIVE_OUT)                 # of other sources
+        return None
     import sysconfig
 
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f'-DBUILT_FOR="{torch.__version__} {sys.implementation.cache_tag}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include")]
     for path in include_paths() + [sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", path]

@@ -331,4 +331,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "native_call", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_native_call(void) { return PyModule_Create(&module); }
+// built_for: the torch and the Python whose headers this was compiled with (binding.py takes no other)
+PyMODINIT_FUNC PyInit_native_call(void)
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", BUILT_FOR) < 0) { Py_DECREF(m); return nullptr; }
+    return m;
+}

@@ -37,3 +37,40 @@ def test_refusals_stay_those_of_python():
             call()
     with pytest.raises(ValueError):
         ra.rapid_attn_joint([])
+
+
+def _refused():
+    x = torch.zeros((1, 2, 64, 64), dtype=torch.bfloat16)
+    with pytest.raises(TypeError):                                          # (of the Python form: not on a GPU)
+        ra.rapid_attn_dense(x, x, x, x)
+    with pytest.raises(TypeError):
+        ra.rapid_attn_joint_select([(x, x, x, x)])
+
+
+def test_a_package_without_the_native_form_calls_by_way_of_ctypes(monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.setattr(binding, "_NATIVE_SO", str(tmp_path / "native_call.so"))
+    _refused()
+
+
+@pytest.mark.parametrize("other", ["file", "torch"])
+def test_a_native_form_that_does_not_fit_is_not_used(other, monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "_native", None)
+    if other == "file":
+        (tmp_path / "native_call.so").write_bytes(b"not a library")
+        monkeypatch.setattr(binding, "_NATIVE_SO", str(tmp_path / "native_call.so"))
+    else:
+        monkeypatch.setattr(torch, "__version__", "0.0")
+    with pytest.warns(RuntimeWarning, match="by way of ctypes"):
+        _refused()
+
+
+def test_the_library_is_built_where_the_native_form_cannot_be(monkeypatch, tmp_path):
+    from paper_2509_22323_amd import build
+    made, stale = [], tmp_path / "native_call.so"
+    stale.write_bytes(b"of other sources")
+    monkeypatch.setattr(build, "NATIVE_OUT", str(stale))
+    monkeypatch.setattr(build, "_run", lambda cmd, out, verbose: made.append(out) or out)
+    monkeypatch.setattr("shutil.which", lambda name: None)
+    assert build.build() == build.OUT
+    assert build.OUT in made and str(stale) not in made and not stale.exists()
