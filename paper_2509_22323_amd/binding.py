@@ -212,10 +212,11 @@ def rapid_attn_block_sparse(q, k, v, o, mask, block, kv_len=None, scale=0.0, wor
     """As rapid_attn_dense, restricted to the tiles kept by `mask` (CUDA uint8
     [B,H,N/block,N/block]).  `workspace`: CUDA uint8 tensor of at least
     rapid_attn_workspace_bytes(...) bytes; allocated with torch if None.  Returns o."""
-    status = (_native or _load_native()).block_sparse(q, k, v, o, mask, block, kv_len, scale, workspace)
-    if status is not None:
-        _check(status)
-        return o
+    if workspace is not None:                     # (the native form allocates nothing)
+        status = (_native or _load_native()).block_sparse(q, k, v, o, mask, block, kv_len, scale, workspace)
+        if status is not None:
+            _check(status)
+            return o
     import torch
     B, H, N, D = _qkvo(q, k, v, o)
     kv_len = N if kv_len is None else int(kv_len)
@@ -306,10 +307,11 @@ def rapid_attn_joint(segments, mask=None, block=128, kv_len=None, kv_lens=None, 
     each a CUDA bf16 tensor indexed [B, H, n, D] with a contiguous last dimension and any other
     strides (a permuted view of a [B, n, H, D] or fused [B, n, 3, H, D] tensor is fine); q, k, v
     of a segment share their strides.  mask None = dense.  kv_lens: CUDA int32 [B] or None."""
-    status = (_native or _load_native()).joint(segments, mask, block, kv_len, kv_lens, scale, workspace)
-    if status is not None:
-        _check(status)
-        return [seg[3] for seg in segments]
+    if mask is None or workspace is not None:
+        status = (_native or _load_native()).joint(segments, mask, block, kv_len, kv_lens, scale, workspace)
+        if status is not None:
+            _check(status)
+            return [seg[3] for seg in segments]
     import torch
     descr, B, H, N, D = _segments(segments)
     q0 = segments[0][0]
@@ -406,10 +408,11 @@ def rapid_mask_select(q, k, mask, block, kv_len=None, text_start=None, tau=0.95,
     """mask <- block mask [B,H,N/block,N/block] (uint8) keeping, per row, the key-blocks that hold
     `tau` of the pooled attention mass, plus the diagonal and the text rows/columns.  q, k: CUDA
     bf16 [B,H,N,D] contiguous."""
-    status = (_native or _load_native()).select(q, k, mask, block, kv_len, text_start, tau, scale, workspace)
-    if status is not None:
-        _check(status)
-        return mask
+    if workspace is not None:
+        status = (_native or _load_native()).select(q, k, mask, block, kv_len, text_start, tau, scale, workspace)
+        if status is not None:
+            _check(status)
+            return mask
     import torch
     for name, t in (("q", q), ("k", k)):
         if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.bfloat16 and t.dim() == 4
@@ -498,10 +501,11 @@ def rapid_attn_joint_select(segments, block=128, kv_len=None, kv_lens=None, text
     """Mask selection at `tau` and block-sparse attention under it in one call, on (q, k, v, o)
     segments as rapid_attn_joint takes them; mask_out: optional CUDA uint8 [B,H,nb,nb] that receives
     the selected mask.  Returns the o tensors."""
-    status = (_native or _load_native()).joint_select(segments, block, kv_len, kv_lens, text_start, tau, scale, mask_out, workspace)
-    if status is not None:
-        _check(status)
-        return [seg[3] for seg in segments]
+    if workspace is not None:
+        status = (_native or _load_native()).joint_select(segments, block, kv_len, kv_lens, text_start, tau, scale, mask_out, workspace)
+        if status is not None:
+            _check(status)
+            return [seg[3] for seg in segments]
     import torch
     descr, B, H, N, D = _segments(segments)
     q0 = segments[0][0]

@@ -74,3 +74,18 @@ def test_the_library_is_built_where_the_native_form_cannot_be(monkeypatch, tmp_p
     monkeypatch.setattr("shutil.which", lambda name: None)
     assert build.build() == build.OUT
     assert build.OUT in made and str(stale) not in made and not stale.exists()
+
+
+def test_calls_without_a_workspace_are_not_put_to_the_native_form(monkeypatch):
+    """It would look at every tensor and hand them back: 0.1 us of a call."""
+    class Asked:
+        def __getattr__(self, name):
+            raise AssertionError(name)
+
+    x = torch.zeros((1, 2, 64, 64), dtype=torch.bfloat16)
+    m = torch.ones((1, 2, 1, 1), dtype=torch.uint8)
+    monkeypatch.setattr(binding, "_native", Asked())
+    for call in (lambda: ra.rapid_attn_block_sparse(x, x, x, x, m, 64), lambda: ra.rapid_attn_joint([(x, x, x, x)], mask=m, block=64),
+                 lambda: ra.rapid_mask_select(x, x, m, 64), lambda: ra.rapid_attn_joint_select([(x, x, x, x)])):
+        with pytest.raises(TypeError):
+            call()
