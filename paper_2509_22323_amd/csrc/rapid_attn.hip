@@ -1994,7 +1994,8 @@ __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork
         entry_of(p, x, i);
         if (BLOCK == 64) p.order[x * p.chunk + i] = w.rec.item;
         else ((PlanRec*)p.order)[x * p.chunk + i] = w.rec;
-        if (w.rec.item >= 0) p.counts[w.rec.item] = w.rec.nblk;
+        // (counts that are there already are what other workgroups look their rows up by)
+        if (p.mask != nullptr && w.rec.item >= 0) p.counts[w.rec.item] = w.rec.nblk;
         if (BLOCK == 128 && i < p.pmax) p.arrived[x * p.pmax + i] = 0;
     }
 }

@@ -353,9 +353,17 @@ def test_64_token_rows_of_a_selected_mask_looked_up_without_a_plan(D):
     lens = torch.tensor([N, 0, N - 700], dtype=torch.int32, device="cuda")
     mask = torch.empty((B, H, 22, 22), dtype=torch.uint8, device="cuda")
     out = [torch.full_like(q, 7.0) for _ in range(2)]
-    ra.rapid_attn_joint_select([(q, k, v, out[0])], block, kv_lens=lens, text_start=20 * block, tau=0.7, mask_out=mask)
-    ra.rapid_attn_joint([(q, k, v, out[1])], mask=mask, block=block, kv_lens=lens)
+    ws = [torch.full((ra.rapid_attn_joint_select_workspace_bytes(B, H, N, D, block),), 0xa5, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    ra.rapid_attn_joint_select([(q, k, v, out[0])], block, kv_lens=lens, text_start=20 * block, tau=0.7, mask_out=mask, workspace=ws[0])
+    ra.rapid_attn_joint([(q, k, v, out[1])], mask=mask, block=block, kv_lens=lens, workspace=ws[1])
     assert torch.equal(out[0], out[1])
+    plans = [read_plan(x.cpu().numpy(), B, H, 22, D, block) for x in ws]
+    live = [(n + block - 1) // block for n in lens.tolist()]
+    kept = torch.stack([mask[b, :, :, :n].sum(-1) for b, n in enumerate(live)]).flatten().cpu().numpy()
+    for counts, order, index, geo in plans:        # counts of the selection, or the attention's own
+        assert (counts == kept).all()
+        check_plan(counts, order, geo, B, H, 22, block, D)
+    assert (plans[0][1] == plans[1][1]).all()
     for b, n in enumerate(lens.tolist()):
         if n == 0:
             assert (out[0][b] == 0).all()
