@@ -1834,58 +1834,50 @@ __device__ __forceinline__ void entry_of(const AttnParams& p, int& seg, int& i)
         }
     }
 }
-// The entry of a plan of whole rows that nobody has made: every workgroup counts all rows of its segment, one or two per
+// The entry of a plan of whole rows that nobody has made: every workgroup counts all rows of its segment, one per
 // thread (8 <= nb <= 64), and looks up the one that comes i-th, longest first (with the second round of 32 backwards, FOURTH:
-// the fourth too: see plan_small_kernel).  `at`: LDS that no copy uses yet, for FOUND_BYTES.
+// the fourth too: see plan_small_kernel).  `at`: LDS that no copy uses yet.
 // Some 1.5 us of every workgroup in place of a launch: run_sparse holds both sides of the line.
-constexpr int FOUND_ROWS = 256;                  // rows of a segment, at most
+constexpr int FOUND_ROWS = 256;                  // rows of a segment, at most: the threads of a workgroup
 struct FoundRow {
     int hist[SMALL_NB + 2];                        // rows by length, longest first
     int before[FOUND_ROWS / 64];                   // rows of the length looked for, by 64 rows
     int item, n;
     unsigned long long row;
 };
-template <int BLOCK, int THREADS, bool FOURTH>
+template <int BLOCK, bool FOURTH>
 __device__ __forceinline__ void find_row(const AttnParams& p, int seg, int i, SparseWork<BLOCK>& w, FoundRow* at)
 {
-    constexpr int PER = FOUND_ROWS / THREADS;      // rows of a thread
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nb = p.nb;
     const int items = (p.pairs - seg + XCDS - 1) / XCDS * nb;
     if (i >= items) return;
-    int item[PER], c[PER];
-    unsigned long long row[PER];
-    bool has[PER];
+    const bool has = tid < items;
+    const int t = has ? tid : 0;
+    const int pair = (int)__umulhi((unsigned)t, p.nq.magic) * XCDS + seg;    // (nq = nb)
+    const int item = pair * nb + t - (pair - seg) / XCDS * nb;
+    int c;
+    unsigned long long row = 0ull;
+    if (p.mask != nullptr) {
+        int kv_len = p.kv_len;
+        if (p.kv_lens != nullptr) kv_len = p.kv_lens[p.H.d == 1 ? pair : (int)__umulhi((unsigned)pair, p.H.magic)];
+        kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
+        const unsigned char* src = p.mask + (size_t)item * nb;
+        unsigned long long v[8];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        has[e] = tid + THREADS * e < items;
-        const int t = has[e] ? tid + THREADS * e : 0;
-        const int pair = (int)__umulhi((unsigned)t, p.nq.magic) * XCDS + seg;    // (nq = nb)
-        item[e] = pair * nb + t - (pair - seg) / XCDS * nb;
-        row[e] = 0ull;
-        if (p.mask != nullptr) {
-            int kv_len = p.kv_len;
-            if (p.kv_lens != nullptr) kv_len = p.kv_lens[p.H.d == 1 ? pair : (int)__umulhi((unsigned)pair, p.H.magic)];
-            kv_len = kv_len < 0 ? 0 : (kv_len > p.N ? p.N : kv_len);
-            const unsigned char* src = p.mask + (size_t)item[e] * nb;
-            unsigned long long v[8];
+        for (int k = 0; k < 8; ++k)                // all on their way at once; the last eight bytes of a row end with it
+            if (8 * k < nb) __builtin_memcpy(&v[k], src + (8 * k + 8 <= nb ? 8 * k : nb - 8), 8);
 #pragma unroll
-            for (int k = 0; k < 8; ++k)            // all on their way at once; the last eight bytes of a row end with it
-                if (8 * k < nb) __builtin_memcpy(&v[k], src + (8 * k + 8 <= nb ? 8 * k : nb - 8), 8);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (8 * k < nb) row[e] |= (unsigned long long)byte_bits((unsigned)v[k], (unsigned)(v[k] >> 32)) << (8 * k + 8 <= nb ? 8 * k : nb - 8);
-            const int live = (kv_len + BLOCK - 1) / BLOCK;
-            row[e] &= live >= 64 ? ~0ull : (1ull << live) - 1ull;
-            c[e] = __popcll(row[e]);
-        } else {
-            c[e] = p.counts[item[e]];
-        }
+        for (int k = 0; k < 8; ++k)
+            if (8 * k < nb) row |= (unsigned long long)byte_bits((unsigned)v[k], (unsigned)(v[k] >> 32)) << (8 * k + 8 <= nb ? 8 * k : nb - 8);
+        const int live = (kv_len + BLOCK - 1) / BLOCK;
+        row &= live >= 64 ? ~0ull : (1ull << live) - 1ull;
+        c = __popcll(row);
+    } else {
+        c = p.counts[item];
     }
-    for (int k = tid; k <= nb; k += THREADS) at->hist[k] = 0;
+    if (tid <= nb) at->hist[tid] = 0;
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < PER; ++e)
-        if (has[e]) atomicAdd(&at->hist[nb - c[e]], 1);
+    if (has) atomicAdd(&at->hist[nb - c], 1);
     __syncthreads();
     auto backwards = [&](int first) {              // a round of 32
         const int left = items - first < CUS_PER_XCD ? items - first : CUS_PER_XCD;
@@ -1896,20 +1888,14 @@ __device__ __forceinline__ void find_row(const AttnParams& p, int seg, int i, Sp
     const int upto = wave_scan_inclusive(lane < nb ? at->hist[lane] : 0);
     const int shorter = __popcll(__builtin_amdgcn_ballot_w64(lane < nb && upto <= i));    // nb - the length of the i-th row
     const int start = shorter > 0 ? __builtin_amdgcn_readlane(upto, shorter - 1) : 0;
-    unsigned long long same[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        same[e] = __builtin_amdgcn_ballot_w64(has[e] && nb - c[e] == shorter);
-        if (lane == 0) at->before[THREADS / 64 * e + wave] = __popcll(same[e]);
-    }
+    const bool as_long = has && nb - c == shorter;
+    const unsigned long long same = __builtin_amdgcn_ballot_w64(as_long);
+    if (lane == 0) at->before[wave] = __popcll(same);
     __syncthreads();
+    int rank = __popcll(same & ((1ull << lane) - 1ull));
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        int rank = __popcll(same[e] & ((1ull << lane) - 1ull));
-#pragma unroll
-        for (int k = 0; k < FOUND_ROWS / 64 - 1; ++k) rank += k < THREADS / 64 * e + wave ? at->before[k] : 0;
-        if (has[e] && nb - c[e] == shorter && rank == i - start) { at->item = item[e]; at->n = c[e]; at->row = row[e]; }
-    }
+    for (int k = 0; k < FOUND_ROWS / 64 - 1; ++k) rank += k < wave ? at->before[k] : 0;
+    if (as_long && rank == i - start) { at->item = item; at->n = c; at->row = row; }
     __syncthreads();
     w.rec.item = __builtin_amdgcn_readfirstlane(at->item);
     w.rec.nblk = __builtin_amdgcn_readfirstlane(at->n);
@@ -1917,7 +1903,8 @@ __device__ __forceinline__ void find_row(const AttnParams& p, int seg, int i, Sp
     w.row = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(r >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)r);
 }
 
-template <int BLOCK, int THREADS, bool FOURTH>
+// ROUNDS: of rows that are looked up, 2 or 4; 0: a kernel whose calls always have a plan (256 threads where not).
+template <int BLOCK, int ROUNDS>
 __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, char* scratch)
 {
     typedef const __attribute__((address_space(4))) int32_t* cptr_t;
@@ -1930,9 +1917,10 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, ch
     SparseWork<BLOCK> w;
     w.rec = {-1, 0, 0, -1};
     w.row = 0ull;
-    if (p.planned == PLAN_FOUND) {
-        find_row<BLOCK, THREADS, FOURTH>(p, seg, i, w, (FoundRow*)scratch);
-    } else if (p.planned == PLAN_NONE) {
+    const int planned = ROUNDS > 0 ? p.planned : PLAN_READ;
+    if (planned == PLAN_FOUND) {
+        find_row<BLOCK, ROUNDS == 4>(p, seg, i, w, (FoundRow*)scratch);
+    } else if (planned == PLAN_NONE) {
         // The dispatcher deals the workgroups of an XCD out to its 32 CUs in turn; rows with the same number (text rows,
         // the long ones) would meet on the same CU where 32 is a multiple of nb, so every 32 workgroups start 3/8 of the rows on.
         const int g = p.nq.of(i), pair = g * XCDS + seg;    // (nq = nb)
@@ -1953,7 +1941,7 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, ch
     w.kept.bits = w.row;
     w.kept.n = w.rec.nblk;
     w.kept.at = w.kept.first = 0;
-    if (item >= 0 && !(p.planned == PLAN_FOUND && p.mask != nullptr)) {
+    if (item >= 0 && !(planned == PLAN_FOUND && p.mask != nullptr)) {
         if (p.mask != nullptr) {                   // nb <= 64
             int kv_len = p.kv_len;
             if (p.kv_lens != nullptr) kv_len = ((cptr_t)p.kv_lens)[p.H.of(p.nq.of(item))];    // (nq = nb)
@@ -1961,7 +1949,7 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, ch
             const unsigned char byte = p.mask[(size_t)item * p.nb + (lane < p.nb ? lane : 0)];
             const bool keep = byte != 0 && lane < p.nb && lane * BLOCK < kv_len;
             w.kept.bits = w.row = __builtin_amdgcn_ballot_w64(keep);
-            if (p.planned == PLAN_NONE) {
+            if (planned == PLAN_NONE) {
                 w.rec.nblk = __popcll(w.row);
             } else if (BLOCK == 128 && w.rec.w >= 0) {
                 const int rank = __popcll(w.row & ((1ull << lane) - 1ull)) - w.rec.blk0;
@@ -1982,14 +1970,14 @@ __device__ __forceinline__ SparseWork<BLOCK> sparse_work(const AttnParams& p, ch
 
 // The workspace as the planner kernels would have left it: called behind the loop, whose waits for copies would wait for
 // these stores as well.
-template <int BLOCK>
+template <int BLOCK, int ROUNDS>
 __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork<BLOCK>& w)
 {
     if (threadIdx.x >= 64) return;
     const int lane = threadIdx.x;
     if (p.mask != nullptr && (w.row >> lane & 1ull) != 0ull && w.rec.blk0 == 0)
         p.index[(size_t)w.rec.item * p.nb + __popcll(w.row & ((1ull << lane) - 1ull))] = lane;
-    if (p.planned != PLAN_READ && lane == 0) {
+    if (ROUNDS > 0 && p.planned != PLAN_READ && lane == 0) {
         int x, i;
         entry_of(p, x, i);
         if (BLOCK == 64) p.order[x * p.chunk + i] = w.rec.item;
@@ -2453,9 +2441,9 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     static_assert(P::QT == 64, "one item = 64 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    const auto work = sparse_work<64, P::NW * 64, false>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
+    const auto work = sparse_work<64, 2>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
     const int item = work.rec.item;
-    if (item < 0 || work.rec.nblk <= 0) leave_plan<64>(p, work);
+    if (item < 0 || work.rec.nblk <= 0) leave_plan<64, 2>(p, work);
     if (item < 0) return;
     const int bh = p.nq.of(item);
     const int qi = item - bh * p.nq.d;
@@ -2471,7 +2459,7 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
 
     StreamRegs<S, D> x;
     if (n <= 0 || qi * 64 >= kv_len) {            // nothing kept, or padding rows only: the rows are zero
-        if (n > 0) leave_plan<64>(p, work);
+        if (n > 0) leave_plan<64, 2>(p, work);
         if (wave % P::WK != 0) return;
 #pragma unroll
         for (int q = 0; q < P::NQ; ++q) x.ls[q][0] = 0.f;
@@ -2480,7 +2468,7 @@ __global__ __launch_bounds__(Sparse64Plan<D>::P::NW * 64, (D == 64 ? 3 : 2)) voi
     }
     KeptTiles<P> keys(work.kept);
     stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, n - 1, keys, wave, lane);
-    leave_plan<64>(p, work);
+    leave_plan<64, 2>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
     stream_merge_rows<P>(x, lds, O, q0, kv_len, p.N, wave, lane);
 }
@@ -2512,10 +2500,11 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     static_assert(P::QT == 128, "one record = 128 queries");
     __shared__ __attribute__((aligned(1024))) char lds[P::LDS];
 
-    const auto work = sparse_work<128, P::NW * 64, D == 64>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
+    constexpr int ROUNDS = D == 64 ? 0 : 2;       // (more than 2048 rows: run_sparse)
+    const auto work = sparse_work<128, ROUNDS>(p, lds + (P::NSK + P::NSV - 1) * P::TILE);    // (the last stage to be filled)
     const PlanRec rec = work.rec;
     const int item = rec.item;
-    if (rec.nblk <= 0) leave_plan<128>(p, work);
+    if (rec.nblk <= 0) leave_plan<128, ROUNDS>(p, work);
     if (item < 0) return;
     const int bh = p.nq.of(item);
     const int qi = item - bh * p.nq.d;
@@ -2541,7 +2530,7 @@ __device__ __forceinline__ void sparse_stream_record(const AttnParams& p)
     // Whole blocks: what lies at or beyond kv_len in a row's last block is masked, at most three steps.
     KeptKeys<P> keys(work.kept);
     stream_attend<P>(x, lds, Q, K, V, q0, kv_len, p.c, rec.nblk * 4 - 1, keys, wave, lane);
-    leave_plan<128>(p, work);
+    leave_plan<128, ROUNDS>(p, work);
     __syncthreads();                              // every wavefront has read its last tile
     if (rec.w < 0) {                              // the whole item
         stream_output_rows<S, D>(x, O, q0, kv_len, p.N, lane, out_stage);
@@ -2649,10 +2638,10 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
     auto k_stage = [&](int t) -> char* { return lds + (t & 1) * G::TILE_BYTES; };
     auto v_stage = [&](int t) -> char* { return lds + (2 + (t & 1)) * G::TILE_BYTES; };
 
-    auto work = sparse_work<128, 256, true>(p, v_stage(1));    // (the last stage to be filled)
+    auto work = sparse_work<128, 4>(p, v_stage(1));    // (the last stage to be filled)
     const PlanRec rec = work.rec;
     const int item = rec.item;
-    if (rec.nblk <= 0) leave_plan<128>(p, work);
+    if (rec.nblk <= 0) leave_plan<128, 4>(p, work);
     if (item < 0) return;
     const int bh = p.nq.of(item);
     const int qi = item - bh * p.nq.d;
@@ -2749,7 +2738,7 @@ __device__ __forceinline__ void sparse_short_record(const AttnParams& p)
         kn3 = (j & 1) == 0 ? work.kept.next() * 128 : kn3 + KT;
     }
 
-    leave_plan<128>(p, work);
+    leave_plan<128, 4>(p, work);
     // Output straight from registers: with four workgroups on the CU, row-wise through LDS was 2-3 % slower.
     if (rec.w < 0) {                              // the whole item
         write_output<D>(O, acc, sm.l, qrow, qvalid, p.N, h);
@@ -3088,7 +3077,8 @@ int run_sparse(const Problem& pr, int block, const unsigned char* mask, void* wo
         // the diagonal alone, which the host cannot tell, is 7 % slower on it at any N (B = 4, H = 24, N = 4480 46.1 / 49.5).
         // Calls of 840 to 2048 rows of more than 8 blocks would be up to 8 % faster on it, at errors against 64 bits 0.1 to 0.9 % larger
         // (2.320 / 2.326e-3 at 24 x 35, density 0.25): not taken.
-        if (D == 64 && rows > 2 * 4 * XCDS * CUS_PER_XCD && nb > 8) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
+        // (that many rows of more than 8 blocks always have a plan)
+        if (D == 64 && rows > 2 * 4 * XCDS * CUS_PER_XCD && nb > 8 && p.planned == PLAN_READ) hipLaunchKernelGGL(attn_sparse_wide_kernel, grid, dim3(SparsePlan<64>::P::NW * 64), 0, s, p);
         else if (D == 64) hipLaunchKernelGGL((attn_sparse_sg_kernel<64>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((attn_sparse_sg_kernel<128>), grid, dim3(SparsePlan<128>::P::NW * 64), 0, s, p);
     } else {
