@@ -137,6 +137,7 @@ struct AttnParams {
     int N, kv_len;
     Divisor H;
     int turn;                // dense: see dense_run
+    int pairs;               // sparse: (sample, head) pairs (here, where it comes with what rows are looked up by; alone it is a load more)
     Divisor nq;              // query tiles per (sample, head)
     int items;               // B*H*nq
     int chunk;               // ceil(items / XCDS)
@@ -145,7 +146,6 @@ struct AttnParams {
     int segs;                // sparse: plan segments that hold items, min(XCDS, B*H)
     unsigned seg_magic;      // ceil(2^32 / segs)
     int planned;             // sparse: PLAN_NONE, PLAN_FOUND or PLAN_READ
-    int pairs;               // sparse: (sample, head) pairs
     int pmax;                // sparse, 128-token tiles: partial-result slots per segment
     float c;                 // scale * log2(e)
 };
