@@ -14,6 +14,18 @@ class Nothing:
         return lambda *a: None
 
 
+class Noted:
+    """Stands in front of the native module: which entry answered what."""
+    def __init__(self):
+        self.native, self.answers = binding._load_native(), []
+
+    def __getattr__(self, name):
+        def call(*a):
+            self.answers.append((name, getattr(self.native, name)(*a)))
+            return self.answers[-1][1]
+        return call
+
+
 def tensors(*shape, n=3):
     g = torch.Generator(device="cuda").manual_seed(sum(shape))
     return [torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(n)]
@@ -53,8 +65,11 @@ def select(kv):
     q, k, _ = tensors(1, 2, 512, 128)
     mask = torch.zeros((1, 2, 8, 8), dtype=torch.uint8, device="cuda")
     out = [ra.rapid_mask_select(q, k, mask, 64, kv, 400, 0.8, workspace=scratch(1 << 20))]
-    m2 = torch.zeros((2, 4, 6, 6), dtype=torch.uint8, device="cuda")
-    return out + ra.rapid_attn_joint_select(segments(), 64, text_start=256, tau=0.7, mask_out=m2, workspace=scratch(1 << 23)) + [m2]
+    for lens in (None, torch.tensor([356, 190], dtype=torch.int32, device="cuda")):
+        m2 = torch.zeros((2, 4, 6, 6), dtype=torch.uint8, device="cuda")
+        out += ra.rapid_attn_joint_select(segments(), 64, kv_len=kv, kv_lens=lens, text_start=256, tau=0.7, mask_out=m2,
+                                          workspace=scratch(1 << 23)) + [m2]
+    return out
 
 
 def cache(kv):
@@ -63,10 +78,14 @@ def cache(kv):
     return [ra.rapid_cache_store(a, b, torch.zeros_like(a), flags), ra.rapid_cache_reuse(a, b, c)]
 
 
-@pytest.mark.parametrize("call", [dense, sparse, joint, select, cache])
+@pytest.mark.parametrize("call,entries", [(dense, ["dense"]), (sparse, ["block_sparse"]), (joint, ["joint"] * 3),
+                                          (select, ["select", "joint_select", "joint_select"]), (cache, ["store", "reuse"])])
 @pytest.mark.parametrize("kv", [None, 150])
-def test_same_results_either_way(call, kv, monkeypatch):
+def test_same_results_either_way(call, entries, kv, monkeypatch):
+    noted = Noted()
+    monkeypatch.setattr(binding, "_native", noted)
     made = [x.clone() for x in call(kv)]
+    assert noted.answers == [(name, 0) for name in entries]      # (each taken, none left to the Python form)
     monkeypatch.setattr(binding, "_native", Nothing())
     for a, b in zip(made, call(kv)):
         assert torch.equal(a, b)

@@ -1,4 +1,4 @@
-"""Sparse path: kept lists of every short length (the list is read three blocks ahead), last blocks cut at
+"""Sparse path: kept lists of every short length (the list is read ahead), last blocks cut at
 odd lengths and rows long enough to be split, against float32 attention of the same bf16 inputs under the
 expanded mask.  Tolerance: P and O are rounded to bf16 (2^-9 each, relative), 2.3e-3 of the output's norm;
 twice that per 64 rows of a head (a wrong row shows as 1)."""
@@ -377,7 +377,7 @@ def test_64_token_rows_of_a_selected_mask_looked_up_without_a_plan(D):
 @pytest.mark.parametrize("D,B,H,nb,alike", [(64, 3, 24, 8, False), (64, 2, 56, 15, True), (64, 3, 64, 10, False), (64, 5, 40, 11, False), (64, 3, 62, 11, False),
                                             (128, 2, 20, 8, False), (128, 4, 24, 12, True), (128, 2, 64, 12, False), (128, 1, 132, 12, False), (128, 1, 38, 15, False)])
 def test_128_token_rows_looked_up_without_a_plan(D, B, H, nb, alike):
-    """As above for rows of 8 to 15 blocks of 128 tokens, in the kernels for few and for many rows, either side of the line;
+    """As above for rows of 8 to 15 blocks of 128 tokens, up to 2048 rows and beyond, either side of the line;
     samples of different length; the same lists from a mask that is given and from one that is selected."""
     block, N = 128, nb * 128
     g = torch.Generator(device="cuda").manual_seed(H * nb + D)
