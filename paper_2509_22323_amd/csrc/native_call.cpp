@@ -1,6 +1,6 @@
 // The entry points that launch, called with tensors: checks and marshalling of binding.py in native code.  A call of few tokens
-// costs what the host needs to issue it.  us a call by way of ctypes / here / on the GPU in a graph, H = 2, N = 256, D = 64: dense
-// 6.4 / 3.8 / 4.2, block-sparse 7.7 / 3.7 / 5.6, joint 11.8 / 3.9 / 4.6, selection (two launches) 10.3 / 7.0 / 5.0.
+// costs what the host needs to issue it.  us of host time a call by way of ctypes / here, and on the GPU in a graph, H = 2, N = 256,
+// D = 64: dense 5.9 / 3.0, 4.2; block-sparse 7.2 / 3.2, 5.6; joint, two segments 11.0 / 3.2, 4.6; selection (two launches) 9.2 / 5.6, 5.0.
 //
 // Every function returns the library's status, or None for arguments that are not what most calls hand over (subclasses of
 // Tensor, tensors without storage, shapes that do not fit, numbers of other types, no workspace): binding.py then goes its own

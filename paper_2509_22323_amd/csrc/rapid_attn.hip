@@ -1751,11 +1751,12 @@ struct StreamPlan {
 // 0.4 to 1 % slower there, N = 16896, D = 128 0.5 %.
 enum { ANY = -1, SHORT = -2 };
 // Which tiles: at(t, ahead) is the first key of tile t; the caller stands in tile t - ahead and calls next_tile when it has
-// done with a tile.  (KeptKeys: the same of whole blocks of four tiles.)
+// done with a tile.  BLOCKS (KeptKeys): the same of whole blocks of four tiles, of which two, b0 and b1, are known.
 // Tiles in order: the dense path.
 template <class P>
 struct AllKeys {
     static constexpr int LAST = ANY;
+    static constexpr bool BLOCKS = false;
     __device__ __forceinline__ int at(int t, int) const { return t * P::KTS; }
     __device__ __forceinline__ void next_tile() {}
 };
@@ -1800,10 +1801,11 @@ struct KeptBlocks {
     }
 };
 
-// What workgroup wg does: an entry of the plan, or, where every workgroup plans for itself (planned = 0: all rows are
-// on the chip at once and none is long enough to be cut, so their order says little), a row of its segment.
-// In the second case, and for the lists wherever the rows come from the mask, it also leaves in the workspace what the
-// planner kernels would have left there.
+// What workgroup wg does: an entry of the plan (PLAN_READ); the entry that a plan of whole rows would have, which it finds by itself
+// (PLAN_FOUND: find_row); or, where all rows are on the chip at once and none is long enough to be cut, so that their order says
+// little, a row of its segment by its own number (PLAN_NONE).
+// Where there is no plan to read, and for the lists wherever the rows come from the mask, it also leaves in the workspace what
+// the planner kernels would have left there.
 template <int BLOCK>
 struct SparseWork {
     PlanRec rec;
@@ -1996,7 +1998,8 @@ __device__ __forceinline__ void leave_plan(const AttnParams& p, const SparseWork
 template <class P>
 struct KeptKeys {
     static_assert(P::KTS == 32 && P::UNROLL == 4 && P::KLEAD == 5 && P::VLEAD == 3, "");
-    static constexpr int LAST = 3;
+    static constexpr int LAST = P::UNROLL - 1;
+    static constexpr bool BLOCKS = true;
     KeptBlocks<128> kept;
     int b0, b1;
     __device__ __forceinline__ KeptKeys(const KeptBlocks<128>& kept_) : kept(kept_)
@@ -2017,6 +2020,7 @@ template <class P>
 struct KeptTiles {
     static_assert(P::KTS == 64 && P::SPT == 1 && P::KLEAD == 3 && P::VLEAD == 2, "");
     static constexpr int LAST = SHORT;
+    static constexpr bool BLOCKS = false;
     KeptBlocks<64> kept;
     int b0, b1, b2, b3;
     __device__ __forceinline__ KeptTiles(const KeptBlocks<64>& kept_) : kept(kept_)
@@ -2080,7 +2084,7 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
     // Kept blocks: a descriptor is made for a whole block and moves on tile by tile, a third of the scalar instructions of one for
     // every tile.  us, one for every tile / now: H = 24, D = 128, N = 4608, densities 0.2 0.5 1 91.5 136.4 226.3 / 90.8 135.7 224.0; N = 1536
     // 33.2 / 32.5; D = 64, H = 256, N = 4096, 24 blocks a row 777 / 770.
-    constexpr bool BLOCKS = Keys::LAST == 3;
+    constexpr bool BLOCKS = Keys::BLOCKS;
     TileBuffer kb, vb;                            // the tiles being copied
     const unsigned tile_bytes = (unsigned)P::KTS * K.row_bytes;
     // what the barriers before tile 0 would have issued
@@ -2088,15 +2092,15 @@ __device__ __forceinline__ void stream_attend(StreamRegs<typename P::S, P::D>& x
         kb = tile_buffer<128>(K, keys.b0, kv_len);
         vb = tile_buffer<128>(V, keys.b0, kv_len);
 #pragma unroll
-        for (int b = -5; b < -1; ++b) {
-            if (b >= -3) {
-                if (b > -3) next_tile_of(vb, tile_bytes);
+        for (int b = -P::KLEAD; b < -1; ++b) {
+            if (b >= -P::VLEAD) {
+                if (b > -P::VLEAD) next_tile_of(vb, tile_bytes);
 #pragma unroll
-                for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + 3) * P::TILE);
+                for (int e = 0; e < LC; ++e) copy_v(vb, e, (b + P::VLEAD) * P::TILE);
             }
-            if (b > -5) next_tile_of(kb, tile_bytes);
+            if (b > -P::KLEAD) next_tile_of(kb, tile_bytes);
 #pragma unroll
-            for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + 5) * P::TILE);
+            for (int e = 0; e < LC; ++e) copy_k(kb, e, (b + P::KLEAD) * P::TILE);
         }
     } else
 #pragma unroll
@@ -3128,7 +3132,7 @@ int joint_problem(const rapid_attn_segment* segments, int n_segments, int B, int
             if (st[j] < 0 || st[j] > (1LL << 40)) return RAPID_ERR_SHAPE;
             if (st[j] % 8 != 0) return RAPID_ERR_ALIGN;            // every row starts on 16 bytes
         }
-        // rows are D contiguous elements; byte offsets inside a 64-row tile stay below 2^31
+        // rows are D contiguous elements; the bytes of 128 rows, which one copy descriptor spans, come to 2^31 at most (32 bits, unsigned)
         if (g.in_stride_n < D || g.out_stride_n < D || g.in_stride_n > (1LL << 23) || g.out_stride_n > (1LL << 23)) return RAPID_ERR_SHAPE;
         N += g.n;
     }
